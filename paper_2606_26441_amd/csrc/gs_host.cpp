@@ -421,7 +421,7 @@ struct gs_index_s {
 // whole on every update), then the per-term arrays (copied up to the terms in use).
 struct BatchLayout {
     size_t rp = 0, k = 0, fs = 0, delta = 0, scale = 0, err = 0, wide = 0, work = 0, diag = 0, head = 0;
-    size_t gcount = 0, gmember = 0, grow = 0;
+    size_t gcount = 0, gmember = 0, grow = 0, order = 0;
     size_t term = 0, w = 0, w8 = 0, fx = 0, ubcum = 0, gterm = 0, gwfx = 0, gw8 = 0, total = 0;
     BatchLayout(size_t nq, size_t nz) {
         size_t at = 0;
@@ -442,6 +442,7 @@ struct BatchLayout {
         gcount = take(4);
         gmember = take((nq + kGroupMax) * 4);
         grow = take((nq + 2) * 4);
+        order = take(nq * 4);
         head = at;
         term = take(nz * 4);
         w = take(nz * 4);
@@ -461,6 +462,7 @@ struct gs_batch_s {
     int32_t n_queries = 0, k_max = 0;  // capacity in queries (launch shapes use it)
     int64_t q_nnz = 0;                 // capacity in query terms
     int32_t n_active = 0;              // queries set by the last update
+    bool any_wide = false;             // one of them has a wide-range limit (q_wide_lim > 0)
     BatchLayout lay{0, 0};
     uint8_t* dmem = nullptr;    // device: every array of the batch
     uint8_t* stage = nullptr;   // pinned host copy of the same layout (update staging)
@@ -574,7 +576,7 @@ size_t arena_bytes(int64_t n_docs, int64_t rows, int32_t precision) {
     b += align256(R * (kMaxQueryNnz + 1) * 8);
     b += align256(R * kMaxQueryNnz * 4);
     b += align256(R * 4);
-    b += align256(16 * 4);
+    b += align256(kCounterWords * 4);
     b += align256(R * 4);
     return b;
 }
@@ -602,7 +604,7 @@ void carve_rows(void* base, int64_t n_docs, int64_t rows, int32_t precision, int
     ws->work_prefix = (int64_t*)take(R * (kMaxQueryNnz + 1) * 8) + o * (kMaxQueryNnz + 1);
     ws->work_pair_q = (int32_t*)take(R * kMaxQueryNnz * 4) + o * kMaxQueryNnz;
     ws->order = (int32_t*)take(R * 4) + o;
-    ws->counters = (uint32_t*)take(16 * 4);
+    ws->counters = (uint32_t*)take(kCounterWords * 4);
     ws->rescore_list = (int32_t*)take(R * 4) + o;
 }
 
@@ -933,6 +935,7 @@ int32_t gs_batch_reserve(gs_index ix, int32_t max_queries, int64_t max_nnz, int3
     d.g_wq = (const float*)(m + L.gwfx);
     d.g_w8 = (const int32_t*)(m + L.gw8);
     d.q_work = (const int64_t*)(m + L.work);
+    d.q_order = (const int32_t*)(m + L.order);
     b->diag = (int32_t*)(m + L.diag);
     // an empty batch until the first update: every slot is a query with no terms and k = 0
     std::vector<int64_t> zero_rp(nq + 1, 0);
@@ -989,6 +992,7 @@ int32_t batch_update(gs_batch b, const int64_t* q_row_ptr, int32_t n_queries, co
         std::memcpy(h + L.w, r.w, (size_t)q_nnz * 4);
     }
     std::vector<float> tmax, tmin;
+    bool any_wide = false;
     for (int32_t q = 0; q < cap; q++) {
         uint64_t maxs = 0;
         const int64_t m = rp[q + 1] - rp[q];
@@ -1013,6 +1017,7 @@ int32_t batch_update(gs_batch b, const int64_t* q_row_ptr, int32_t n_queries, co
         qscale[q] = fp.scale;
         qerr[q] = fp.abs_err;
         qwide[q] = fp.wide_lim;
+        any_wide = any_wide || (fp.wide_lim > 0.0 && kk[q] > 0);
         for (int64_t j = rp[q]; j < rp[q + 1]; j++) qfx[j] = std::ldexp((double)r.w[j], fp.F);
         // Block-max pruning: each term's upper bound on its product with any doc (fixed-point
         // units: the largest stored weight times w_q 2^F, rounded up, plus one for the product's
@@ -1055,6 +1060,11 @@ int32_t batch_update(gs_batch b, const int64_t* q_row_ptr, int32_t n_queries, co
         for (int32_t q = 0; q < n_queries; q++)
             if (kk[q] > 0) ord.push_back(q);
         std::stable_sort(ord.begin(), ord.end(), [&](int32_t a, int32_t b) { return qwork[a] > qwork[b]; });
+        // the persistent kernel's order: these, then the queries with nothing to do
+        int32_t* order = (int32_t*)(h + L.order);
+        std::copy(ord.begin(), ord.end(), order);
+        for (int32_t q = 0, at = (int32_t)ord.size(); q < cap; q++)
+            if (kk[q] == 0) order[at++] = q;
         const int32_t ng = (int32_t)((ord.size() + G - 1) / G);
         *gcnt = ng;
         grow[0] = 0;
@@ -1108,6 +1118,7 @@ int32_t batch_update(gs_batch b, const int64_t* q_row_ptr, int32_t n_queries, co
     }
     if (e != hipSuccess) return fail(GS_EHIP, std::string("batch upload: ") + hipGetErrorString(e));
     b->n_active = n_queries;
+    b->any_wide = any_wide;
     return GS_OK;
 }
 
@@ -1253,13 +1264,15 @@ int32_t plan_search(gs_index ix, gs_batch b, size_t workspace_bytes_, const gs_s
 // Queries [0, nq) are searched; output rows [nq, capacity) are written as padding
 // (id -1, score 0). A direct search passes the queries of the last update, a
 // graph the whole capacity (it is replayed after updates of any size).
+// any_update: the launches must serve every later update of the batch (a graph), not
+// only the queries it holds now.
 int32_t enqueue_search(gs_index ix, gs_batch b, int32_t nq, const Workspace& ws, int32_t qt, const ScoreOpts& so_in,
-                       int32_t* out_ids, void* out_scores, hipStream_t s, bool timing) {
+                       int32_t* out_ids, void* out_scores, hipStream_t s, bool timing, bool any_update = false) {
     ScoreOpts so = so_in;
     // Fused candidate filtering (doc-tiled kernels): every stride-th tile seeds a lower bound
     // of the k-th composite; the other tiles append their candidates while they are scored.
     // The seed tiles should hold several times k documents: stride 8 up to k = 1024, 4 up to
-    // 2048, else off; it needs at least two seed tiles. It adds five launches to a search,
+    // 2048, else off; it needs at least two seed tiles. It adds four launches to a search,
     // which a few queries' row scans do not repay: searches of fewer than 32 queries scan.
     // the group kernel's groups span the whole batch: with query tiles it gives way to the
     // shared-traversal kernel
@@ -1271,19 +1284,30 @@ int32_t enqueue_search(gs_index ix, gs_batch b, int32_t nq, const Workspace& ws,
         if (!tiled || so.seed_stride == 0 || n_tiles < 2 * (int64_t)stride || nq < 32) stride = 0;
         so.seed_stride = stride;
     }
+    const bool doc_tiled =
+        so.kernel == GS_KERNEL_TILED || so.kernel == GS_KERNEL_SHARED || so.kernel == GS_KERNEL_GROUP;
+    // The fp64 pass over wide-range queries and its check are left out when no query of this
+    // batch has a wide-range limit (with weights within a few orders of magnitude of one
+    // another an fp32 query has none): two launches less.
+    const bool wide = doc_tiled && ix->precision != kU8 && (any_update || b->any_wide);
+    // A collection that fits the candidate buffer needs no threshold: the rows themselves are
+    // the candidates, and the search is two launches (scores, final selection) instead of five.
+    const bool from_row = doc_tiled && ix->precision != kBF16 && !wide && ix->n_docs <= kCandCap;
+    so.whole = qt >= nq;
     (void)hipGetLastError();  // launches below report their own status; drop any earlier, unrelated one
     g_failed_launch = "";
     for (int32_t q0 = 0; q0 < nq; q0 += qt) {
         const int32_t n = std::min(qt, nq - q0);
-        hipError_t e = launch_clear(ws, n, s);
+        // the step counters: the shared-traversal kernels count with them in every form
+        hipError_t e = from_row && so.kernel == GS_KERNEL_TILED ? hipSuccess : launch_clear(ws, n, so.seed_stride > 0, s);
         if (e == hipSuccess && ix->n_docs > 0) {
             const bool group = so.kernel == GS_KERNEL_GROUP;
             if (so.seed_stride == 0 || so.kernel == GS_KERNEL_ATOMIC || so.kernel == GS_KERNEL_DOCPAR) {
                 SpanRecorder rec(timing ? 0 : -1, s);
                 if (so.kernel == GS_KERNEL_ATOMIC) e = launch_score_atomic(ix->dev, b->dev, q0, n, so, ws, s);
                 else if (so.kernel == GS_KERNEL_DOCPAR) e = launch_score_docpar(ix->dev, b->dev, q0, n, so, ws, s);
-                else if (group) e = launch_score_group(ix->dev, b->dev, so, ws, s, 0);
-                else e = launch_score_tiled(ix->dev, b->dev, q0, n, so, ws, s);
+                else if (group) e = launch_score_group(ix->dev, b->dev, so, ws, s, from_row ? kPhaseRows : 0);
+                else e = launch_score_tiled(ix->dev, b->dev, q0, n, so, ws, s, from_row ? kPhaseRows : 0);
                 rec.end(s);
             } else {
                 // fused filtering: seed tiles, their bound (selection work), then the other tiles
@@ -1311,13 +1335,10 @@ int32_t enqueue_search(gs_index ix, gs_batch b, int32_t nq, const Workspace& ws,
             // Between the two first-digit selection passes: the rows of the listed queries.
             // Fused queries that fell back get their non-seed tiles scored (phase 3);
             // fixed-point queries found wide range get every tile scored in fp64 (phase 4).
-            const bool doc_tiled =
-                so.kernel == GS_KERNEL_TILED || so.kernel == GS_KERNEL_SHARED || so.kernel == GS_KERNEL_GROUP;
-            const bool fixed = doc_tiled && ix->precision != kU8;
             const bool phase3 = so.seed_stride > 0;
             const int acc = ix->precision == kU8 ? kAccInteger : (doc_tiled ? kAccFixed : kAccFloat);
             e = launch_select(ix->dev, b->dev, q0, n, ws, out_ids, out_scores, b->diag, s, acc, so.tile_shift,
-                              so.seed_stride, phase3 ? &so : nullptr, fixed);
+                              so.seed_stride, phase3 ? &so : nullptr, wide, from_row);
             rec.end(s);
         }
         if (e != hipSuccess)
@@ -1448,7 +1469,7 @@ int32_t gs_graph_create(gs_index ix, gs_batch b, void* workspace, size_t workspa
     Workspace ws;
     carve_workspace(workspace, ix->n_docs, qt, ix->precision, &ws);
     // one eager run first: one-time kernel attributes and occupancy queries happen outside the capture
-    rc = enqueue_search(ix, b, b->n_queries, ws, qt, so, out_ids, out_scores, s, false);
+    rc = enqueue_search(ix, b, b->n_queries, ws, qt, so, out_ids, out_scores, s, false, true);
     if (rc != GS_OK) return rc;
     GS_HIP(hipStreamSynchronize(s));
     gs_graph gr = new (std::nothrow) gs_graph_s();
@@ -1463,7 +1484,7 @@ int32_t gs_graph_create(gs_index ix, gs_batch b, void* workspace, size_t workspa
         delete gr;
         return fail(GS_EHIP, std::string("hipStreamBeginCapture: ") + hipGetErrorString(e));
     }
-    rc = enqueue_search(ix, b, b->n_queries, ws, qt, so, out_ids, out_scores, cs, false);
+    rc = enqueue_search(ix, b, b->n_queries, ws, qt, so, out_ids, out_scores, cs, false, true);
     e = hipStreamEndCapture(cs, &gr->graph);
     (void)hipStreamDestroy(cs);
     if (rc != GS_OK) {

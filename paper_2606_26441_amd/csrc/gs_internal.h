@@ -28,6 +28,14 @@ constexpr int kCandCap = 32768;       // candidates kept per query by the filter
 constexpr int kFusedCap = 24576;      // of which appended while scoring (fused filtering)
 constexpr int kRefinePasses = 6;      // enough to resolve any 64-bit composite key
 constexpr int kFirstShiftFloat = 52;  // first digit of a float key: bits 30..20
+// LDS words of a scoring workgroup's histogram: the bins, then the count of zero scores (padded to 16 bytes)
+constexpr int kHistLds = kHistBins + 4;
+// Step counters of a search (kCounterWords words, cleared at its start): [8 phase ..] per-XCD work
+// counters of the persistent kernels (the phases that follow one another use sets of their own, so
+// that none needs clearing between), [kCntListed] queries in rescore_list.
+constexpr int kCntListed = 63;
+constexpr int kCounterWords = 64;
+__host__ __device__ constexpr int cnt_base(int phase) { return 8 * phase; }  // phases 0 .. 6
 constexpr int kDiagWords = 8;         // per-query words of gs_batch_diagnostics
 // Group kernel (GS_KERNEL_GROUP): 8192-doc tiles, at most 4 queries per group, so at most
 // 4 x 256 distinct terms per group.
@@ -110,6 +118,7 @@ struct DevBatch {
     // scored again with fp64 accumulation; 0 when the bound holds for every positive score.
     const double* q_wide_lim;
     const int64_t* q_work;     // [n] postings of the query's terms (work estimate)
+    const int32_t* q_order;    // [n] queries by descending work, those with k = 0 last
     // Block-max pruning (opt-in): per query term, the sum of the upper bounds of the query's
     // terms (w_q times the term's largest stored weight, in fixed-point units or as an exact
     // uint8 product) taken in ascending order of bound, up to and including this term.
@@ -128,12 +137,9 @@ struct DevBatch {
 };
 
 // Per-query selection state in the workspace.
-struct SelState {
-    unsigned long long prefix;  // bucket: composites c with (c >> shift) == (prefix >> shift)
+struct alignas(16) SelState {
     unsigned long long lo;      // filter threshold (inclusive) once resolved
-    int32_t shift;
-    int32_t k_rem;              // still needed from the bucket
-    int32_t resolved;           // 0 refine, 1 filter with lo, 2 nothing to select (k == 0)
+    int32_t resolved;           // 0 not yet, 1 filter with lo, 2 nothing to select (k == 0)
     int32_t n_cand;             // candidates appended by the filter
     int32_t passes;             // refinement passes over the score array
     int32_t band;               // bf16: candidates inside the error band
@@ -149,6 +155,8 @@ struct SelState {
     // them again, fixed point); 2: wide range (score every tile again, fp64 accumulation)
     int32_t rescore;
     int32_t pruned;             // 64-posting blocks skipped by block-max pruning
+    int32_t zeros;              // zero-score documents among those counted in hist1
+    int32_t seed_rem;           // k_seed to k_seed_bound: composites still needed from its bin (prefix in lo)
 };
 
 // Workspace carve-up for a tile of qt queries.
@@ -163,8 +171,7 @@ struct Workspace {
     int64_t* work_prefix;         // [qt * kMaxQueryNnz + 1] (atomic kernel)
     int32_t* work_pair_q;         // [qt * kMaxQueryNnz]
     int32_t* order;               // [qt] persistent kernel: query order within the tile
-    uint32_t* counters;           // [16]: [0..7] persistent kernel per-XCD work counters,
-                                  // [8] queries in rescore_list
+    uint32_t* counters;           // [kCounterWords] step counters
     int32_t* rescore_list;        // [qt] queries whose rows are scored again (SelState::rescore)
     int64_t ld;                   // row stride of the score arrays (n_docs rounded up to 64)
 };
@@ -181,6 +188,7 @@ struct ScoreOpts {
     int chunk;        // postings per work item
     int seed_stride = 0;  // fused candidate filtering: every seed_stride-th doc tile seeds the bound (0: off)
     int prune = 0;        // block-max pruning of the non-seed tiles (TILED, fp32 and uint8)
+    bool whole = false;   // the query tile is the whole batch (the host's work order applies)
 };
 
 // Doc tiles of a scoring launch: phase 0 all tiles, phase 1 the seed tiles
@@ -188,14 +196,16 @@ struct ScoreOpts {
 // queries that fell back from fused filtering (their rows), phase 4 all tiles
 // again for the wide-range queries (fp64 accumulation), phase 5 the others again
 // for the bf16 queries whose error band reaches below their fused candidates
-// (their rows, for the band pass). v is the launch's tile index.
+// (their rows, for the band pass), phase 6 all tiles, rows only (no histogram). v is the
+// launch's tile index.
+constexpr int kPhaseRows = 6;
 __host__ __device__ inline int64_t phase_tiles(int phase, int stride, int64_t n_tiles) {
-    if (phase == 0 || phase == 4) return n_tiles;
+    if (phase == 0 || phase == 4 || phase == kPhaseRows) return n_tiles;
     const int64_t seeds = (n_tiles + stride - 1) / stride;
     return phase == 1 ? seeds : n_tiles - seeds;
 }
 __host__ __device__ inline int64_t phase_tile(int phase, int stride, int64_t v) {
-    if (phase == 0 || phase == 4) return v;
+    if (phase == 0 || phase == 4 || phase == kPhaseRows) return v;
     if (phase == 1) return v * stride;
     return (v / (stride - 1)) * stride + v % (stride - 1) + 1;
 }
@@ -208,7 +218,7 @@ int32_t batch_update(struct ::gs_batch_s* b, const int64_t* q_row_ptr, int32_t n
                      void* hip_stream, bool wait);
 
 // Search the queries of the batch's last update on rows [r0, r0 + n) of an arena of `rows`
-// rows, with the caller's step counters (16 words, device); asynchronous on s. (Server steps.)
+// rows, with the caller's step counters (kCounterWords words, device); asynchronous on s. (Server steps.)
 int32_t search_rows(struct ::gs_index_s* ix, struct ::gs_batch_s* b, void* arena, int64_t rows, int64_t r0,
                     uint32_t* counters, const struct gs_search_opts* opts, int32_t* out_ids, void* out_scores,
                     hipStream_t s);
@@ -216,7 +226,8 @@ int32_t search_rows(struct ::gs_index_s* ix, struct ::gs_batch_s* b, void* arena
 const int32_t* batch_diag(const struct ::gs_batch_s* b);
 
 // ---- launchers (gs_score.hip) ----
-hipError_t launch_clear(const Workspace& ws, int32_t qt, hipStream_t s);
+// counters, selection state and first-digit histograms; with seeds, the seed histograms too
+hipError_t launch_clear(const Workspace& ws, int32_t qt, bool seeds, hipStream_t s);
 hipError_t launch_score_tiled(const DevIndex& ix, const DevBatch& qb, int32_t q0, int32_t qt,
                               const ScoreOpts& o, const Workspace& ws, hipStream_t s, int phase = 0);
 // group kernel (GS_KERNEL_GROUP): phases 0, 1 and 2 of a search whose queries form one tile
@@ -247,13 +258,15 @@ hipError_t launch_fill(void* p, int64_t n_words, uint32_t v, hipStream_t s);  //
 // absolute error bound, wide-range check), float (global-atomic and document-parallel
 // kernels: relative error bound) or integer (uint8 impacts: exact).
 enum AccKind { kAccFixed = 0, kAccFloat = 1, kAccInteger = 2 };
-// Between the two k_select_first passes, the rows of the listed queries are scored again:
+// Between the two k_select passes, the rows of the listed queries are scored again:
 // with phase3 (non-null) the fused fp32 / uint8 queries that fell back (phase 3 of
-// launch_score_tiled with these options), with wide the wide-range queries (fp64 pass).
+// launch_score_tiled with these options), with wide the wide-range queries (fp64 pass; the
+// check that finds them runs only then). from_row: the score rows are the candidate sets (no
+// histogram or state; collections of at most kCandCap documents, no wide query, not bf16).
 hipError_t launch_select(const DevIndex& ix, const DevBatch& qb, int32_t q0, int32_t qt,
                          const Workspace& ws, int32_t* out_ids, void* out_scores, int32_t* diag,
                          hipStream_t s, int acc, int tile_shift = 0, int seed_stride = 0,
-                         const ScoreOpts* phase3 = nullptr, bool wide = false);
+                         const ScoreOpts* phase3 = nullptr, bool wide = false, bool from_row = false);
 // fused filtering: the bound of every query of the tile from its seed-tile histogram
 hipError_t launch_seed_bound(const DevIndex& ix, const DevBatch& qb, int32_t q0, int32_t qt,
                              const Workspace& ws, hipStream_t s, int tile_shift, int stride);

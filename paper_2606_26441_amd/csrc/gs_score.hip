@@ -143,7 +143,8 @@ __device__ __forceinline__ void append_candidates(bool take, unsigned long long 
     if (take && slot < kFusedCap) C[slot] = c;
 }
 
-// write: store the scores in the row; count: add the tile to the first-digit histogram.
+// write: store the scores in the row; count: add the tile to the first-digit histogram (hist:
+// kHistLds words, zeroed by the caller) and its zero scores to the query's count of them.
 // Q: 0 for a plain tile (doc d in accumulator d); else a tile in quarters (doc d in
 // accumulator (d % 4) * Q + d / 4, Q = tile size / 4), as the four-postings-per-lane loads of
 // score_tile leave it.
@@ -260,13 +261,17 @@ __device__ __forceinline__ void flush_tile(const void* acc_v, uint32_t* hist, in
             return;
         }
     }
+    int zc = 0;  // counted zero scores of this thread
     // docs 4 i .. 4 i + 3 with their scores v: row store, histogram, candidates
     auto emit = [&](int i, const uint32_t* v) {
         if (write) reinterpret_cast<uint4*>(Sq)[i] = make_uint4(v[0], v[1], v[2], v[3]);
         const uint32_t d0 = (uint32_t)(base + 4 * i);
         if (count) {
 #pragma unroll
-            for (int j = 0; j < 4; j++) atomicAdd(&hist[(comp_key(v[j], d0 + j) >> fs) & (kHistBins - 1)], 1u);
+            for (int j = 0; j < 4; j++) {
+                atomicAdd(&hist[(comp_key(v[j], d0 + j) >> fs) & (kHistBins - 1)], 1u);
+                zc += v[j] == 0u;
+            }
         }
         // a composite reaches the bound only if its score bits reach the bound's: one test
         // of the lane's largest score first, the exact per-document test only then
@@ -353,14 +358,20 @@ __device__ __forceinline__ void flush_tile(const void* acc_v, uint32_t* hist, in
         else v = ((const uint32_t*)acc_v)[ai];
         if (write) Sq[i] = v;
         const unsigned long long c = comp_key(v, (uint32_t)(base + i));
-        if (count) atomicAdd(&hist[(c >> fs) & (kHistBins - 1)], 1u);
+        if (count) {
+            atomicAdd(&hist[(c >> fs) & (kHistBins - 1)], 1u);
+            zc += v == 0u;
+        }
         if (append) put(c >= bound, c);
     }
     drain();
     if (!count) return;
+    zc = wave_sum(zc);
+    if ((tid & (kWave - 1)) == 0 && zc) atomicAdd(&hist[kHistBins], (uint32_t)zc);
     __syncthreads();
     for (int b = tid; b < kHistBins; b += BS)
         if (hist[b]) atomicAdd(&hist_out[b], hist[b]);
+    if (tid == 0 && hist[kHistBins]) atomicAdd(&st->zeros, (int)hist[kHistBins]);
 }
 
 // ------------------------------------------------------------- tiled --
@@ -484,7 +495,7 @@ __device__ __forceinline__ void score_tile(const DevIndex& ix, const DevBatch& q
     constexpr int AW = (AF == kAccFx64 || AF == kAccF64) ? 2 : 1;  // accumulator words per doc
     unsigned long long* acc64 = reinterpret_cast<unsigned long long*>(lds);  // [TILE] (fp32)
     uint32_t* acc32 = lds;                                                   // [TILE] (bf16, uint8)
-    uint32_t* hist = lds + TILE * AW;                                        // [kHistBins]
+    uint32_t* hist = lds + TILE * AW;                                        // [kHistLds]
 
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: chunk bookkeeping stays scalar
@@ -1007,7 +1018,7 @@ __device__ __forceinline__ void score_tile(const DevIndex& ix, const DevBatch& q
         else two_loops(std::false_type());
     }
     __syncthreads();
-    for (int i = tid; i < kHistBins; i += BS) hist[i] = 0u;
+    for (int i = tid; i < kHistLds; i += BS) hist[i] = 0u;
     __syncthreads();
     // Fused filtering (the non-seed tiles of a query whose seed bound is set): append while
     // flushing, no appends once past the cap, and no score row. A query that falls back gets
@@ -1024,7 +1035,7 @@ __device__ __forceinline__ void score_tile(const DevIndex& ix, const DevBatch& q
     // The first-digit histogram of a fused query keeps the seed tiles' counts only: its
     // selection needs no more, and if it falls back, phase 3 scores these tiles again and
     // counts them then.
-    const bool count = !fused_q;
+    const bool count = !fused_q && phase != kPhaseRows;
     flush_tile<BS, AF, (QD ? TILE / 4 : 0), TILE>(lds, hist, tile_n, base, S + (int64_t)ql * ld + base, sh.fl_shift,
                        sh.fl_scale, hist1 + (int64_t)ql * kHistBins, app, app ? sh.fl_bound : 0ull, st,
                        cand + (int64_t)ql * kCandCap, write, count, sh.stg, count ? stage_seg : stage_hist,
@@ -1064,7 +1075,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
     __shared__ TileShared sh;
     const int64_t tile = phase_tile(phase, stride, (int64_t)blockIdx.x);
     constexpr bool DB = P != kU8 && !W;
-    const int nres = (int)counters[8];
+    const int nres = (int)counters[kCntListed];
     for (int r = 0; r < nres; r++) {
         score_tile<P, TS, CH, DB, W>(ix, qb, q0, tile, rescore_list[r], S, ld, hist1, lds, sh, phase, state, cand);
         __syncthreads();
@@ -1092,10 +1103,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
     // phases 3 and 5 cover only the listed queries (fused filtering's fallbacks, bf16 band
     // passes; usually none)
     const bool listed = phase == 3 || phase == 5;
-    const int nq = listed ? (int)counters[8] : qt;
+    const int nq = listed ? (int)counters[kCntListed] : qt;
     const int64_t items = tiles_x * nq;
     for (;;) {
-        if (threadIdx.x == 0) item_sh = (int64_t)atomicAdd(&counters[x], 1u);
+        if (threadIdx.x == 0) item_sh = (int64_t)atomicAdd(&counters[cnt_base(phase) + x], 1u);
         __syncthreads();
         const int64_t item = item_sh;
         if (item >= items) break;
@@ -1110,17 +1121,20 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
 }
 
 // Work order of a query tile for the persistent kernel: local query indices by
-// descending estimated work (postings of the query's terms), ties by index.
+// descending estimated work (postings of the query's terms), ties by index. One wavefront
+// per query counts the queries before it, 64 at a time (one thread per query took 274 us
+// for 4,096 queries).
 __global__ __launch_bounds__(256) void k_work_order(DevBatch qb, int32_t q0, int32_t qt, int32_t* __restrict__ order) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int i = blockIdx.x * (256 / kWave) + (threadIdx.x >> 6), lane = threadIdx.x & (kWave - 1);
     if (i >= qt) return;
     const int64_t wi = qb.q_work[q0 + i];
     int r = 0;
-    for (int j = 0; j < qt; j++) {
+    for (int j = lane; j < qt; j += kWave) {
         const int64_t wj = qb.q_work[q0 + j];
         r += (wj > wi) || (wj == wi && j < i);
     }
-    order[r] = i;
+    r = wave_sum(r);
+    if (lane == 0) order[r] = i;
 }
 
 // ------------------------------------------------------------- group --
@@ -1141,7 +1155,7 @@ struct GroupShared {
             int32_t len[MT];
             int32_t cpre[MT + 1];
         } seg;
-        uint32_t hist[kHistBins];  // the flush histogram, once the segments are no longer read
+        uint32_t hist[kHistLds];  // the flush histogram, once the segments are no longer read
     };
     uint32_t w[MT][G];  // per union term, each member's w_q (fp32 bits) or uint8 impact
     uint16_t tab[kGroupChunkTab];  // chunk -> union term, when the item has at most that many chunks
@@ -1172,7 +1186,7 @@ __global__ __launch_bounds__(group_size<P>() * kMaxQueryNnz) __attribute__((amdg
     const int64_t items = tiles_x * ng;
     using WT = std::conditional_t<P == kU8, uint8_t, std::conditional_t<P == kBF16, uint16_t, uint32_t>>;
     for (;;) {
-        if (tid == 0) sh.item = (int64_t)atomicAdd(&counters[x], 1u);
+        if (tid == 0) sh.item = (int64_t)atomicAdd(&counters[cnt_base(phase) + x], 1u);
         __syncthreads();
         const int64_t item = sh.item;
         if (item >= items) break;
@@ -1332,7 +1346,7 @@ __global__ __launch_bounds__(group_size<P>() * kMaxQueryNnz) __attribute__((amdg
         for (int m = 0; m < G; m++) {
             const int ql = qb.g_member[g * G + m];
             if (ql < 0 || qb.k[ql] == 0) continue;  // uniform: read from global memory
-            for (int i = tid; i < kHistBins; i += BS) hist[i] = 0u;
+            for (int i = tid; i < kHistLds; i += BS) hist[i] = 0u;
             __syncthreads();
             SelState* st = state + ql;
             const bool fused_q = phase == 2 && st->fused == 1;
@@ -1340,7 +1354,7 @@ __global__ __launch_bounds__(group_size<P>() * kMaxQueryNnz) __attribute__((amdg
             // as in score_tile: a fused query writes no row and counts no tile here; its
             // fallback (phase 3) or bf16 band pass (phase 5) scores these tiles again
             const bool write = !fused_q;
-            const bool count = !fused_q;
+            const bool count = !fused_q && phase != kPhaseRows;
             flush_tile<BS, AF>(lds + m * TILE * AW, hist, tile_n, base, S + (int64_t)ql * ld + base,
                                qb.first_shift[ql], FX ? qb.q_scale[ql] : 1.0, hist1 + (int64_t)ql * kHistBins, app,
                                app ? st->bound : 0ull, st, cand + (int64_t)ql * kCandCap, write, count);
@@ -1485,24 +1499,45 @@ __global__ __launch_bounds__(1024) void k_score_docpar(DevIndex ix, DevBatch qb,
 // ------------------------------------------------------ hist / clear --
 
 __global__ __launch_bounds__(512) void k_hist1(DevBatch qb, int32_t q0, int64_t N, const uint32_t* __restrict__ S,
-                                               int64_t ld, int per_block, uint32_t* __restrict__ hist1) {
-    __shared__ uint32_t hist[kHistBins];
+                                               int64_t ld, int per_block, uint32_t* __restrict__ hist1,
+                                               SelState* __restrict__ state) {
+    __shared__ uint32_t hist[kHistLds];
     const int tid = threadIdx.x, ql = blockIdx.y;
-    for (int i = tid; i < kHistBins; i += 512) hist[i] = 0u;
+    for (int i = tid; i < kHistLds; i += 512) hist[i] = 0u;
     __syncthreads();
+    int zc = 0;  // zero scores
     const int fs = qb.first_shift[q0 + ql];
     const int64_t d0 = (int64_t)blockIdx.x * per_block, d1 = min(N, d0 + per_block);
     const uint32_t* Sq = S + (int64_t)ql * ld;
-    for (int64_t d = d0 + tid; d < d1; d += 512)
+    for (int64_t d = d0 + tid; d < d1; d += 512) {
         atomicAdd(&hist[(comp_key(Sq[d], (uint32_t)d) >> fs) & (kHistBins - 1)], 1u);
+        zc += Sq[d] == 0u;
+    }
+    zc = wave_sum(zc);
+    if ((tid & (kWave - 1)) == 0 && zc) atomicAdd(&hist[kHistBins], (uint32_t)zc);
     __syncthreads();
     for (int b = tid; b < kHistBins; b += 512)
         if (hist[b]) atomicAdd(&hist1[(int64_t)ql * kHistBins + b], hist[b]);
+    if (tid == 0 && hist[kHistBins]) atomicAdd(&state[ql].zeros, (int)hist[kHistBins]);
 }
 
 __global__ void k_fill_u32(uint32_t* __restrict__ p, int64_t n, uint32_t v) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         p[i] = v;
+}
+
+// The start of a search: its step counters, selection state and histograms, in one launch.
+static_assert(sizeof(SelState) % 16 == 0, "cleared 16 bytes at a time");
+__global__ __launch_bounds__(256) void k_clear(uint32_t* __restrict__ counters, uint4* __restrict__ state,
+                                               int64_t n_state, uint4* __restrict__ h1, int64_t n1,
+                                               uint4* __restrict__ h2, int64_t n2) {
+    const uint4 z = make_uint4(0u, 0u, 0u, 0u);
+    if (blockIdx.x == 0 && threadIdx.x < kCounterWords) counters[threadIdx.x] = 0u;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n_state + n1 + n2; i += (int64_t)gridDim.x * 256) {
+        if (i < n_state) state[i] = z;
+        else if (i < n_state + n1) h1[i - n_state] = z;
+        else h2[i - n_state - n1] = z;
+    }
 }
 
 hipError_t fill_u32(void* p, int64_t n_words, hipStream_t s) { return launch_fill(p, n_words, 0u, s); }
@@ -1518,11 +1553,11 @@ hipError_t by_precision(int p, F f) {
 }
 
 template <int P, int TS, int CH>
-hipError_t launch_tiled_one(const DevIndex& ix, const DevBatch& qb, int32_t q0, int32_t qt, bool persistent,
+hipError_t launch_tiled_one(const DevIndex& ix, const DevBatch& qb, int32_t q0, int32_t qt, bool persistent, bool whole,
                             const Workspace& ws, int64_t ld, hipStream_t s, int phase, int stride, bool prune) {
     const int64_t n_tiles = phase_tiles(phase, stride, (ix.n_docs + (1 << TS) - 1) >> TS);
     if (n_tiles <= 0) return hipSuccess;
-    const size_t lds = (size_t)((1 << TS) * (acc_form<P>() == kAccFx64 ? 2 : 1) + kHistBins) * 4;
+    const size_t lds = (size_t)((1 << TS) * (acc_form<P>() == kAccFx64 ? 2 : 1) + kHistLds) * 4;
     if (lds > 150 * 1024) return hipErrorInvalidValue;
     if (lds > 65536) {
         static const hipError_t attr = [&] {
@@ -1582,15 +1617,18 @@ hipError_t launch_tiled_one(const DevIndex& ix, const DevBatch& qb, int32_t q0, 
         return std::max(8, (p.multiProcessorCount * std::max(per_cu, 1)) / 8 * 8);
     }();
     if (grid <= 0) return hipErrorInvalidConfiguration;
-    if (phase <= 1) {  // the later launches of a fused search keep the first one's order
-        hipLaunchKernelGGL(k_work_order, dim3((unsigned)((qt + 255) / 256)), dim3(256), 0, s, qb, q0, qt, ws.order);
-        GS_CHECK_LAUNCH("k_work_order");
-    } else {
-        const hipError_t e = launch_fill(ws.counters, 8, 0u, s);  // the first launch used the counters
-        if (e != hipSuccess) return e;
+    // a search in one query tile takes the order the host made; the tiles of a longer batch are
+    // ordered here (the later launches of a fused search keep the first one's order)
+    const int32_t* order = qb.q_order;
+    if (!whole) {
+        order = ws.order;
+        if (phase <= 1 || phase == kPhaseRows) {
+            hipLaunchKernelGGL(k_work_order, dim3((unsigned)((qt + 3) / 4)), dim3(256), 0, s, qb, q0, qt, ws.order);
+            GS_CHECK_LAUNCH("k_work_order");
+        }
     }
     hipLaunchKernelGGL((k_score_persistent<P, TS, CH>), dim3((unsigned)grid), dim3(512), lds, s, ix, qb, q0, qt,
-                       (const int32_t*)ws.order, ws.counters, ws.scores, ld, ws.hist1, phase, stride, ws.state,
+                       order, ws.counters, ws.scores, ld, ws.hist1, phase, stride, ws.state,
                        ws.cand, (const int32_t*)ws.rescore_list);
     GS_CHECK_LAUNCH("k_score_persistent");
     return hipSuccess;
@@ -1598,54 +1636,15 @@ hipError_t launch_tiled_one(const DevIndex& ix, const DevBatch& qb, int32_t q0, 
 
 template <int P, int TS>
 hipError_t tiled_chunk(const DevIndex& ix, const DevBatch& qb, int32_t q0, int32_t qt, int chunk, bool persistent,
-                       const Workspace& ws, int64_t ld, hipStream_t s, int phase, int stride, bool prune) {
+                       bool whole, const Workspace& ws, int64_t ld, hipStream_t s, int phase, int stride, bool prune) {
     switch (chunk) {
-        case 64: return launch_tiled_one<P, TS, 64>(ix, qb, q0, qt, persistent, ws, ld, s, phase, stride, prune);
-        case 128: return launch_tiled_one<P, TS, 128>(ix, qb, q0, qt, persistent, ws, ld, s, phase, stride, prune);
-        case 256: return launch_tiled_one<P, TS, 256>(ix, qb, q0, qt, persistent, ws, ld, s, phase, stride, prune);
-        case 512: return launch_tiled_one<P, TS, 512>(ix, qb, q0, qt, persistent, ws, ld, s, phase, stride, prune);
-        case 1024: return launch_tiled_one<P, TS, 1024>(ix, qb, q0, qt, persistent, ws, ld, s, phase, stride, prune);
+        case 64: return launch_tiled_one<P, TS, 64>(ix, qb, q0, qt, persistent, whole, ws, ld, s, phase, stride, prune);
+        case 128: return launch_tiled_one<P, TS, 128>(ix, qb, q0, qt, persistent, whole, ws, ld, s, phase, stride, prune);
+        case 256: return launch_tiled_one<P, TS, 256>(ix, qb, q0, qt, persistent, whole, ws, ld, s, phase, stride, prune);
+        case 512: return launch_tiled_one<P, TS, 512>(ix, qb, q0, qt, persistent, whole, ws, ld, s, phase, stride, prune);
+        case 1024: return launch_tiled_one<P, TS, 1024>(ix, qb, q0, qt, persistent, whole, ws, ld, s, phase, stride, prune);
     }
     return hipErrorInvalidValue;
-}
-
-}  // namespace
-
-int64_t score_ld(int64_t n_docs) { return (n_docs + 63) / 64 * 64; }
-
-hipError_t launch_fill(void* p, int64_t n_words, uint32_t v, hipStream_t s) {
-    if (n_words <= 0) return hipSuccess;
-    const int64_t blocks = std::min<int64_t>((n_words + 255) / 256, 8192);
-    hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)blocks), dim3(256), 0, s, (uint32_t*)p, n_words, v);
-    GS_CHECK_LAUNCH("k_fill_u32");
-    return hipSuccess;
-}
-
-hipError_t launch_clear(const Workspace& ws, int32_t qt, hipStream_t s) {
-    hipError_t e = fill_u32(ws.counters, 16, s);
-    if (e == hipSuccess) e = fill_u32(ws.hist1, (int64_t)qt * kHistBins, s);
-    if (e == hipSuccess) e = fill_u32(ws.hist_ref, (int64_t)qt * kHistBins, s);
-    if (e == hipSuccess) e = fill_u32(ws.state, (int64_t)qt * sizeof(SelState) / 4, s);
-    return e;
-}
-
-hipError_t launch_score_tiled(const DevIndex& ix, const DevBatch& qb, int32_t q0, int32_t qt, const ScoreOpts& o,
-                              const Workspace& ws, hipStream_t s, int phase) {
-    const int stride = phase == 0 ? 1 : o.seed_stride;
-    const int64_t ld = score_ld(ix.n_docs);
-    return by_precision(ix.precision, [&](auto pc) -> hipError_t {
-        constexpr int P = decltype(pc)::value;
-        const bool persistent = o.kernel == 4;  // GS_KERNEL_SHARED: persistent, tile-major, XCD-aware
-        switch (o.tile_shift) {
-            case 13: return tiled_chunk<P, 13>(ix, qb, q0, qt, o.chunk, persistent, ws, ld, s, phase, stride, o.prune != 0);
-            case 14: return tiled_chunk<P, 14>(ix, qb, q0, qt, o.chunk, persistent, ws, ld, s, phase, stride, o.prune != 0);
-            case 15:
-                if constexpr (acc_form<P>() != kAccFx64)
-                    return tiled_chunk<P, 15>(ix, qb, q0, qt, o.chunk, persistent, ws, ld, s, phase, stride, o.prune != 0);
-                return hipErrorInvalidValue;  // 32768 64-bit accumulators exceed one CU's LDS
-        }
-        return hipErrorInvalidValue;
-    });
 }
 
 template <int P, int CH>
@@ -1673,10 +1672,6 @@ hipError_t launch_group_one(const DevIndex& ix, const DevBatch& qb, const Worksp
         return std::max(8, (p.multiProcessorCount * std::max(per_cu, 1)) / 8 * 8);
     }();
     if (grid <= 0) return hipErrorInvalidConfiguration;
-    if (phase > 1) {  // the seed-tile launch used the counters
-        const hipError_t e = launch_fill(ws.counters, 8, 0u, s);
-        if (e != hipSuccess) return e;
-    }
     hipLaunchKernelGGL((k_score_group<P, CH>), dim3((unsigned)grid), dim3(group_size<P>() * kMaxQueryNnz), lds, s,
                        ix, qb, ws.counters,
                        ws.scores, ld, ws.hist1, phase, stride, ws.state, ws.cand);
@@ -1684,45 +1679,119 @@ hipError_t launch_group_one(const DevIndex& ix, const DevBatch& qb, const Worksp
     return hipSuccess;
 }
 
-hipError_t launch_score_group(const DevIndex& ix, const DevBatch& qb, const ScoreOpts& o, const Workspace& ws,
-                              hipStream_t s, int phase) {
-    const int stride = phase == 0 ? 1 : o.seed_stride;
+}  // namespace
+
+static inline int64_t score_ld(int64_t n_docs) { return (n_docs + 63) / 64 * 64; }
+
+// The launches of one weight form. A build may compile this file in parts (GS_SCORE_PART 0, 1
+// and 2: one form each; 3: the rest): the kernels of the three forms take most of its time.
+template <int P>
+struct ScoreForm {
+    static hipError_t tiled(const DevIndex& ix, const DevBatch& qb, int32_t q0, int32_t qt, const ScoreOpts& o,
+                            const Workspace& ws, hipStream_t s, int phase);
+    static hipError_t group(const DevIndex& ix, const DevBatch& qb, const ScoreOpts& o, const Workspace& ws,
+                            hipStream_t s, int phase);
+    static hipError_t wide(const DevIndex& ix, const DevBatch& qb, int32_t q0, const Workspace& ws, hipStream_t s);
+};
+
+#if !defined(GS_SCORE_PART) || GS_SCORE_PART != 3
+template <int P>
+hipError_t ScoreForm<P>::tiled(const DevIndex& ix, const DevBatch& qb, int32_t q0, int32_t qt, const ScoreOpts& o,
+                               const Workspace& ws, hipStream_t s, int phase) {
+    const int stride = phase == 0 || phase == kPhaseRows ? 1 : o.seed_stride;
     const int64_t ld = score_ld(ix.n_docs);
-    return by_precision(ix.precision, [&](auto pc) -> hipError_t {
-        constexpr int P = decltype(pc)::value;
-        switch (o.chunk) {
-            case 256: return launch_group_one<P, 256>(ix, qb, ws, ld, s, phase, stride);
-            case 512: return launch_group_one<P, 512>(ix, qb, ws, ld, s, phase, stride);
-            case 1024: return launch_group_one<P, 1024>(ix, qb, ws, ld, s, phase, stride);
-        }
-        return hipErrorInvalidValue;
-    });
+    const bool persistent = o.kernel == 4;  // GS_KERNEL_SHARED: persistent, tile-major, XCD-aware
+    switch (o.tile_shift) {
+        case 13: return tiled_chunk<P, 13>(ix, qb, q0, qt, o.chunk, persistent, o.whole, ws, ld, s, phase, stride, o.prune != 0);
+        case 14: return tiled_chunk<P, 14>(ix, qb, q0, qt, o.chunk, persistent, o.whole, ws, ld, s, phase, stride, o.prune != 0);
+        case 15:
+            if constexpr (acc_form<P>() != kAccFx64)
+                return tiled_chunk<P, 15>(ix, qb, q0, qt, o.chunk, persistent, o.whole, ws, ld, s, phase, stride, o.prune != 0);
+            return hipErrorInvalidValue;  // 32768 64-bit accumulators exceed one CU's LDS
+    }
+    return hipErrorInvalidValue;
 }
 
-hipError_t launch_score_wide(const DevIndex& ix, const DevBatch& qb, int32_t q0, const Workspace& ws, hipStream_t s) {
+template <int P>
+hipError_t ScoreForm<P>::group(const DevIndex& ix, const DevBatch& qb, const ScoreOpts& o, const Workspace& ws,
+                               hipStream_t s, int phase) {
+    const int stride = phase == 0 || phase == kPhaseRows ? 1 : o.seed_stride;
+    const int64_t ld = score_ld(ix.n_docs);
+    switch (o.chunk) {
+        case 256: return launch_group_one<P, 256>(ix, qb, ws, ld, s, phase, stride);
+        case 512: return launch_group_one<P, 512>(ix, qb, ws, ld, s, phase, stride);
+        case 1024: return launch_group_one<P, 1024>(ix, qb, ws, ld, s, phase, stride);
+    }
+    return hipErrorInvalidValue;
+}
+
+template <int P>
+hipError_t ScoreForm<P>::wide(const DevIndex& ix, const DevBatch& qb, int32_t q0, const Workspace& ws, hipStream_t s) {
     // 8192 docs of fp64 accumulators (64 KiB of LDS), one workgroup per tile walking the list
     constexpr int TS = 13, CH = 256;
     const int64_t n_tiles = (ix.n_docs + (1 << TS) - 1) >> TS;
     if (n_tiles <= 0) return hipSuccess;
-    const size_t lds = (size_t)((1 << TS) * 2 + kHistBins) * 4;
+    const size_t lds = (size_t)((1 << TS) * 2 + kHistLds) * 4;
     const int64_t ld = score_ld(ix.n_docs);
-    auto go = [&](auto pc) -> hipError_t {
-        constexpr int P = decltype(pc)::value;
-        static const hipError_t attr = hipFuncSetAttribute((const void*)k_score_listed<P, TS, CH, true>,
-                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (attr != hipSuccess) {
-            g_failed_launch = "hipFuncSetAttribute(k_score_listed, wide)";
-            return attr;
-        }
-        hipLaunchKernelGGL((k_score_listed<P, TS, CH, true>), dim3((unsigned)n_tiles, 1u), dim3(512), lds, s, ix, qb,
-                           q0, ws.scores, ld, ws.hist1, 4, 1, ws.state, ws.cand, (const uint32_t*)ws.counters,
-                           (const int32_t*)ws.rescore_list);
-        GS_CHECK_LAUNCH("k_score_listed (wide)");
-        return hipSuccess;
-    };
-    if (ix.precision == kFP32) return go(std::integral_constant<int, kFP32>());
-    if (ix.precision == kBF16) return go(std::integral_constant<int, kBF16>());
+    static const hipError_t attr = hipFuncSetAttribute((const void*)k_score_listed<P, TS, CH, true>,
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (attr != hipSuccess) {
+        g_failed_launch = "hipFuncSetAttribute(k_score_listed, wide)";
+        return attr;
+    }
+    hipLaunchKernelGGL((k_score_listed<P, TS, CH, true>), dim3((unsigned)n_tiles, 1u), dim3(512), lds, s, ix, qb, q0,
+                       ws.scores, ld, ws.hist1, 4, 1, ws.state, ws.cand, (const uint32_t*)ws.counters,
+                       (const int32_t*)ws.rescore_list);
+    GS_CHECK_LAUNCH("k_score_listed (wide)");
+    return hipSuccess;
+}
+
+#if !defined(GS_SCORE_PART) || GS_SCORE_PART == 2
+template <>
+hipError_t ScoreForm<kU8>::wide(const DevIndex&, const DevBatch&, int32_t, const Workspace&, hipStream_t) {
     return hipSuccess;  // uint8 sums are exact
+}
+#endif
+#endif
+
+#if defined(GS_SCORE_PART) && GS_SCORE_PART < 3
+template struct ScoreForm<GS_SCORE_PART>;
+#else
+
+hipError_t launch_fill(void* p, int64_t n_words, uint32_t v, hipStream_t s) {
+    if (n_words <= 0) return hipSuccess;
+    const int64_t blocks = std::min<int64_t>((n_words + 255) / 256, 8192);
+    hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)blocks), dim3(256), 0, s, (uint32_t*)p, n_words, v);
+    GS_CHECK_LAUNCH("k_fill_u32");
+    return hipSuccess;
+}
+
+hipError_t launch_clear(const Workspace& ws, int32_t qt, bool seeds, hipStream_t s) {
+    const int64_t n_state = (int64_t)qt * (sizeof(SelState) / 16), n_hist = (int64_t)qt * (kHistBins / 4);
+    const int64_t blocks = std::min<int64_t>((n_state + n_hist * (seeds ? 2 : 1) + 255) / 256, 2048);
+    hipLaunchKernelGGL(k_clear, dim3((unsigned)blocks), dim3(256), 0, s, ws.counters, (uint4*)ws.state, n_state,
+                       (uint4*)ws.hist1, n_hist, (uint4*)ws.hist_ref, seeds ? n_hist : 0);
+    GS_CHECK_LAUNCH("k_clear");
+    return hipSuccess;
+}
+
+hipError_t launch_score_tiled(const DevIndex& ix, const DevBatch& qb, int32_t q0, int32_t qt, const ScoreOpts& o,
+                              const Workspace& ws, hipStream_t s, int phase) {
+    return by_precision(ix.precision, [&](auto pc) {
+        return ScoreForm<decltype(pc)::value>::tiled(ix, qb, q0, qt, o, ws, s, phase);
+    });
+}
+
+hipError_t launch_score_group(const DevIndex& ix, const DevBatch& qb, const ScoreOpts& o, const Workspace& ws,
+                              hipStream_t s, int phase) {
+    return by_precision(ix.precision, [&](auto pc) {
+        return ScoreForm<decltype(pc)::value>::group(ix, qb, o, ws, s, phase);
+    });
+}
+
+hipError_t launch_score_wide(const DevIndex& ix, const DevBatch& qb, int32_t q0, const Workspace& ws, hipStream_t s) {
+    return by_precision(ix.precision,
+                        [&](auto pc) { return ScoreForm<decltype(pc)::value>::wide(ix, qb, q0, ws, s); });
 }
 
 hipError_t launch_score_atomic(const DevIndex& ix, const DevBatch& qb, int32_t q0, int32_t qt, const ScoreOpts& o,
@@ -1781,9 +1850,11 @@ hipError_t launch_hist1(const DevIndex& ix, const DevBatch& qb, int32_t q0, int3
     const int per = 65536;
     const dim3 grid((unsigned)((ix.n_docs + per - 1) / per), (unsigned)qt);
     hipLaunchKernelGGL(k_hist1, grid, dim3(512), 0, s, qb, q0, ix.n_docs, (const uint32_t*)ws.scores, ld, per,
-                       ws.hist1);
+                       ws.hist1, ws.state);
     GS_CHECK_LAUNCH("k_hist1");
     return hipSuccess;
 }
+
+#endif  // GS_SCORE_PART < 3
 
 }  // namespace gs

@@ -378,7 +378,7 @@ int32_t gs_server_create(gs_index index, const gs_server_opts* opts, gs_server* 
         if (hipStreamCreateWithFlags(&sl.stream, hipStreamNonBlocking) != hipSuccess ||
             hipEventCreateWithFlags(&sl.done, hipEventDisableTiming) != hipSuccess)
             return bail(GS_EHIP, "stream/event creation failed");
-        if (gs::dev_malloc((void**)&sl.counters, 16 * 4) != hipSuccess ||
+        if (gs::dev_malloc((void**)&sl.counters, gs::kCounterWords * 4) != hipSuccess ||
             gs::dev_malloc((void**)&sl.d_ids, out_rows * 4) != hipSuccess ||
             gs::dev_malloc(&sl.d_scores, out_rows * s->score_size) != hipSuccess)
             return bail(GS_ENOMEM, "device allocation for a slot failed");

@@ -10,33 +10,33 @@
 //
 // Pipeline for a tile of queries (all launches fixed, no host round trip):
 //  1. the first 11-bit digit histogram (built by the scoring kernel);
-//  2. k_select_first: find the digit bucket holding the k-th composite; if the
-//     composites at or above that bucket fit the candidate buffer the query is
-//     resolved, otherwise
-//  3. k_refine_hist / k_refine_select (up to six rounds): radix-select refinement
-//     over the full score array, 11 more bits per round, only for unresolved
-//     queries (a degenerate distribution such as a query matching fewer than k
-//     documents, where the answer is decided by doc ids);
-//  4. k_filter: append every composite >= the threshold to the candidate buffer
+//  2. k_select: find the digit bucket holding the k-th composite; if the composites
+//     at or above that bucket fit the candidate buffer the query is resolved,
+//     otherwise its workgroup refines the bucket by radix selection over the full
+//     score array, 11 more bits per pass (massive ties at the k-th score). A query
+//     that fewer than k documents match needs no pass: its answer is every positive
+//     document and documents among the first k (see k_select);
+//  3. k_filter: append every composite >= the threshold to the candidate buffer
 //     (wavefront ballot + popcount for the append slot);
-//  5. k_final: radix select on the candidates (8-bit digits, LDS histograms) for
-//     the exact k-th composite, gather the k winners and place each one by its
-//     rank among them (one pass of comparisons, no sort network needed).
-// bf16 form: k_final also derives the error band of the k-th approximate score
-// and rescores every candidate in the band in fp64 from the fp32 forward rows
-// (ascending term order); k_band_filter / k_band_final handle the rare case in
-// which the band reaches below the candidate threshold (a fused query first gets
-// the rows of its other tiles, scoring phase 5).
+//  4. k_final: histogram selection on the candidates in 2048 bins of their range
+//     (narrowed while the bin of the k-th holds too many), the winners grouped by
+//     bin in LDS and each placed by its rank inside its bin. Collections of at most
+//     kCandCap documents skip 1 to 3: the score row itself is the candidate set.
+// bf16 form: k_final also derives the error band of the k-th approximate score and
+// lists the candidates in the band; k_rescore sums them again in fp64 from the fp32
+// forward rows (ascending term order) on a grid over the listed documents, and
+// k_band_topk ranks them. k_band_filter handles the rare case in which the band
+// reaches below the candidate threshold (a fused query first gets the rows of its
+// other tiles, scoring phase 5).
 //
 // Fused candidate filtering (doc-tiled kernels, searches of 32+ queries): the
-// seed tiles (every 8th doc tile) are scored first; k_seed_bound / k_seed_hist /
-// k_seed_refine derive from them a lower bound of each query's k-th composite
-// (a 22-bit bucket edge); the other tiles append every composite at or above it
-// while they are scored (then writing no score rows for them and not counting
-// them in the histogram), and step 4 scans only the seed tiles.
-// k_select_first falls back to the full row (no bound, too many appended, or a
-// refinement needed); such a query is listed, its other tiles are scored and
-// counted again, and a second k_select_first pass redoes its step 2 from the
+// seed tiles (every 8th doc tile) are scored first; k_seed and k_seed_bound derive from them a
+// lower bound of each query's k-th composite (a 22-bit bucket edge); the other
+// tiles append every composite at or above it while they are scored (then writing
+// no score rows for them and not counting them in the histogram), and step 3 scans
+// only the seed tiles. k_select falls back to the full row (no bound, too many
+// appended, or a refinement needed); such a query is listed, its other tiles are
+// scored and counted again, and a second k_select pass redoes its step 2 from the
 // complete histogram before steps 3 and 4.
 //
 // Wide-range check (fixed-point sums of the doc-tiled kernels, fp32 and bf16
@@ -46,8 +46,11 @@
 // k-th approximate score, also with fused filtering) is compared with the
 // query's limit (E over the budget). Below it, the query is listed as wide
 // range: every tile is scored again with fp64 accumulation of exact fp64
-// products (its histogram counted anew), and the second k_select_first pass
-// selects from those rows.
+// products (its histogram counted anew), and the second k_select pass selects
+// from those rows.
+#include <algorithm>
+#include <type_traits>
+
 #include "gs_internal.h"
 
 namespace gs {
@@ -58,168 +61,78 @@ __device__ __forceinline__ unsigned long long comp_key(uint32_t key, uint32_t id
     return ((unsigned long long)key << 32) | (unsigned long long)(~id);
 }
 
-// One wavefront walks a kHistBins histogram from the top bin down and finds
-// the bin d holding the need-th largest element: above(d) < need <= above(d)+h[d].
-// Returns d; *above receives the count of elements in bins above d.
-__device__ int hist_walk(const uint32_t* h, uint32_t need, uint32_t* above) {
-    const int lane = threadIdx.x & (kWave - 1);
-    constexpr int PER = kHistBins / kWave;
-    const int top = kHistBins - 1 - lane * PER;
-    uint32_t s = 0;
-    for (int j = 0; j < PER; j++) s += h[top - j];
+__device__ __forceinline__ int64_t kq_of(const DevBatch& qb, int q, int64_t N) {
+    return min((int64_t)qb.k[q], N);
+}
+
+// The composite of score 0 and doc id kq - 1. Documents 0 .. kq - 1 are kq composites at or
+// above it, so it never exceeds the kq-th largest composite, whatever the scores.
+__device__ __forceinline__ unsigned long long zero_floor(int64_t kq) { return comp_key(0u, (uint32_t)(kq - 1)); }
+
+constexpr int kSelBS = 512;  // workgroup of the selection kernels: four histogram bins per thread
+static_assert(kHistBins == 4 * kSelBS, "four bins per thread");
+
+// What scan_bins leaves for the workgroup: the bin of the need-th largest element, the number of
+// elements in the bins above it and the number in it.
+struct BinScan {
+    uint32_t wsum[kSelBS / kWave];
+    int d;
+    uint32_t above, count;
+};
+
+// The whole workgroup finds the bin d holding the need-th largest element of a kHistBins
+// histogram, above(d) < need <= above(d) + h[d] (thread t holds bins 2047 - 4 t .. 2044 - 4 t,
+// given top bin first in c; e receives the number of elements above each). 1 <= need; with
+// fewer elements than need, d is bin 0. Ends with a barrier.
+__device__ __forceinline__ void scan_bins(const uint32_t (&c)[4], uint32_t (&e)[4], uint32_t need, BinScan& sh) {
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
+    const uint32_t s = c[0] + c[1] + c[2] + c[3];
     uint32_t incl = s;
 #pragma unroll
     for (int d = 1; d < kWave; d <<= 1) {
         const uint32_t v = __shfl_up(incl, d, kWave);
         if (lane >= d) incl += v;
     }
-    const uint32_t excl = incl - s;
-    const unsigned long long m = __ballot(excl < need && need <= incl);
-    const int owner = m ? __ffsll((long long)m) - 1 : kWave - 1;
-    int dsel = 0;
-    uint32_t ab = 0;
-    if (lane == owner) {
-        uint32_t run = excl;
-        dsel = top - (PER - 1);
-        ab = run;
-        for (int j = 0; j < PER; j++) {
-            const uint32_t c = h[top - j];
-            if (run + c >= need) { dsel = top - j; ab = run; break; }
-            run += c;
-        }
-    }
-    dsel = __shfl(dsel, owner, kWave);
-    *above = __shfl(ab, owner, kWave);
-    return dsel;
-}
-
-__device__ __forceinline__ int64_t kq_of(const DevBatch& qb, int q, int64_t N) {
-    return min((int64_t)qb.k[q], N);
-}
-
-// pass 0 runs once every tile is scored; pass 1 runs after phase 3 for the queries that
-// fell back, whose histograms are complete only then (phase 2 counts the seed tiles of a
-// fused fp32/uint8 query only).
-__global__ __launch_bounds__(64) void k_select_first(DevBatch qb, int32_t q0, int64_t N, int precision,
-                                                     uint32_t* __restrict__ hist1, SelState* __restrict__ state,
-                                                     uint32_t* __restrict__ counters, int32_t* __restrict__ rescore_list,
-                                                     int pass, int wide_check) {
-    const int ql = blockIdx.x, q = q0 + ql;
-    SelState* st = state + ql;
-    if (pass == 1 && st->rescore == 0) return;
-    const int64_t kq = kq_of(qb, q, N);
-    if (kq == 0) {
-        if (threadIdx.x == 0) st->resolved = 2;
-        return;
-    }
-    uint32_t* h = hist1 + (int64_t)ql * kHistBins;
-    uint32_t above;
-    const int d = hist_walk(h, (uint32_t)kq, &above);
-    const int fs = qb.first_shift[q];
-    if (pass == 0 && wide_check) {
-        // lower edge of the k-th composite's bucket: its score bits with the low ones cleared
-        const float s_lo = __uint_as_float((uint32_t)(((unsigned long long)d << fs) >> 32));
-        if ((double)s_lo < qb.q_wide_lim[q]) {
-            __syncthreads();  // every lane is done reading the histogram
-            for (int i = threadIdx.x; i < kHistBins; i += 64) h[i] = 0u;  // the fp64 pass counts anew
-            if (threadIdx.x == 0) {
-                st->fused = 0;
-                st->n_cand = 0;
-                st->resolved = 0;
-                st->rescore = 2;
-                rescore_list[atomicAdd(&counters[8], 1u)] = ql;
-            }
-            return;
-        }
-    }
-    if (threadIdx.x != 0) return;
-    const int64_t ge = (int64_t)above + h[d];
-    int64_t kept;  // composites at or above the filter threshold
-    if (precision == kBF16 && d > 0 && ge + h[d - 1] <= kCandCap) {
-        // one bin lower: the bf16 error band below the k-th score then lies inside the candidates
-        st->resolved = 1;
-        st->lo = (unsigned long long)(d - 1) << fs;
-        kept = ge + h[d - 1];
-    } else if (ge <= kCandCap) {
-        st->resolved = 1;
-        st->lo = (unsigned long long)d << fs;
-        kept = ge;
-    } else {
-        st->resolved = 0;
-        st->prefix = (unsigned long long)d << fs;
-        st->shift = fs;
-        st->k_rem = (int32_t)(kq - above);
-        kept = 0;
-    }
-    // Fused filtering holds the appended candidates (every composite >= the seed bound
-    // of the non-seed tiles; the bound is at most the threshold) and the filter then
-    // scans the seed tiles only. Otherwise the appended ones are dropped and the whole
-    // row is scanned: no bound, too many appended, or a refinement is needed.
-    if (st->fused == 1 && (st->resolved != 1 || st->fused_over || (int64_t)st->n_cand + kept > kCandCap)) {
-        st->fused = 0;
-        st->n_cand = 0;
-        st->rescore = 1;  // its non-seed rows were not written: score them again
-        rescore_list[atomicAdd(&counters[8], 1u)] = ql;
-    }
-}
-
-// Fused filtering, after the seed tiles are scored. The bound of a query is the
-// lower edge of a two-digit bucket (22 bits of the composite key) that holds the
-// k-th largest composite among the seed tiles' documents: k_seed_bound finds the
-// first-digit bin from the histogram the seed tiles built, k_seed_hist counts the
-// next digit within that bin over the seed tiles' scores, and k_seed_refine picks
-// the sub-bin. The k-th largest over all documents is at least as large, so the
-// bound never exceeds it. With fewer than k seed documents there is no bound.
-__global__ __launch_bounds__(64) void k_seed_bound(DevBatch qb, int32_t q0, int64_t N,
-                                                   const uint32_t* __restrict__ hist1, SelState* __restrict__ state) {
-    const int ql = blockIdx.x, q = q0 + ql;
-    SelState* st = state + ql;
-    const int64_t kq = kq_of(qb, q, N);
-    if (kq == 0) {
-        if (threadIdx.x == 0) st->fused = 0;
-        return;
-    }
-    const uint32_t* h = hist1 + (int64_t)ql * kHistBins;
-    uint32_t above;
-    const int d = hist_walk(h, (uint32_t)kq, &above);
-    if (threadIdx.x != 0) return;
-    if ((int64_t)above + h[d] < kq) {
-        st->fused = 0;
-        return;
-    }
-    const int fs = qb.first_shift[q];
-    st->prefix = (unsigned long long)d << fs;
-    st->shift = fs;
-    st->k_rem = (int32_t)(kq - above);
-    st->fused = 2;  // refining
-}
-
-__global__ __launch_bounds__(512) void k_seed_hist(int64_t N, const uint32_t* __restrict__ S, int64_t ld,
-                                                   int tile_shift, int stride, const SelState* __restrict__ state,
-                                                   uint32_t* __restrict__ hist_ref) {
-    __shared__ uint32_t hist[kHistBins];
-    const int ql = blockIdx.y;
-    const SelState st = state[ql];
-    if (st.fused != 2) return;
-    const int tid = threadIdx.x;
-    for (int i = tid; i < kHistBins; i += 512) hist[i] = 0u;
+    if (lane == kWave - 1) sh.wsum[wave] = incl;
     __syncthreads();
-    const int shift = st.shift, nshift = max(shift - kHistBits, 0);
-    const unsigned long long want = st.prefix >> shift;
+    uint32_t run = incl - s;
+#pragma unroll
+    for (int w = 0; w < kSelBS / kWave; w++) run += w < wave ? sh.wsum[w] : 0u;
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        e[j] = run;
+        const bool last = tid == kSelBS - 1 && j == 3;
+        if ((run < need && need <= run + c[j]) || (last && run + c[j] < need)) {
+            sh.d = kHistBins - 1 - 4 * tid - j;
+            sh.above = run;
+            sh.count = c[j];
+        }
+        run += c[j];
+    }
+    __syncthreads();
+}
+
+__device__ __forceinline__ void load_bins(const uint32_t* h, uint32_t (&c)[4]) {
+    const uint4 v = reinterpret_cast<const uint4*>(h)[kSelBS - 1 - (int)threadIdx.x];
+    c[0] = v.w; c[1] = v.z; c[2] = v.y; c[3] = v.x;
+}
+
+// Count the digit at nshift of the composites of docs [d0, d1) whose bits above `shift` are
+// `want` into an LDS histogram. Four rounds of 16-byte loads are issued before the first count
+// (a lane past the range reads its last aligned four scores and counts nothing).
+// d0 is a multiple of 4.
+__device__ __forceinline__ void count_digit(const uint32_t* Sq, int64_t d0, int64_t d1, int shift, int nshift,
+                                            unsigned long long want, uint32_t* hist) {
     const unsigned long long mask = (1ull << (shift - nshift)) - 1ull;
-    const int64_t d0 = ((int64_t)blockIdx.x * stride) << tile_shift, d1 = min(N, d0 + (1ll << tile_shift));
-    const uint32_t* Sq = S + (int64_t)ql * ld;
-    // four rounds of 16-byte loads before the first count (a lane past the tile reads its last
-    // aligned four scores and counts nothing)
     constexpr int R = 4;
     const int64_t last = (d1 - 1) & ~3ll;  // d + 3 < ld: rows are padded to 64
-    for (int64_t d0r = d0 + 4 * tid; d0r < d1; d0r += 4 * 512 * R) {
+    for (int64_t d0r = d0 + 4 * threadIdx.x; d0r < d1; d0r += 4 * kSelBS * R) {
         uint4 v[R];
 #pragma unroll
-        for (int r = 0; r < R; r++) v[r] = *reinterpret_cast<const uint4*>(Sq + min(d0r + r * 2048, last));
+        for (int r = 0; r < R; r++) v[r] = *reinterpret_cast<const uint4*>(Sq + min(d0r + r * 4 * kSelBS, last));
 #pragma unroll
         for (int r = 0; r < R; r++) {
-            const int64_t d = d0r + r * 2048;
+            const int64_t d = d0r + r * 4 * kSelBS;
             const uint32_t vs[4] = {v[r].x, v[r].y, v[r].z, v[r].w};
 #pragma unroll
             for (int j = 0; j < 4; j++) {
@@ -228,78 +141,187 @@ __global__ __launch_bounds__(512) void k_seed_hist(int64_t N, const uint32_t* __
             }
         }
     }
-    __syncthreads();
-    for (int b = tid; b < kHistBins; b += 512)
-        if (hist[b]) atomicAdd(&hist_ref[(int64_t)ql * kHistBins + b], hist[b]);
 }
 
-__global__ __launch_bounds__(64) void k_seed_refine(uint32_t* __restrict__ hist_ref, SelState* __restrict__ state) {
-    const int ql = blockIdx.x;
-    SelState* st = state + ql;
-    if (st->fused != 2) return;
-    uint32_t* h = hist_ref + (int64_t)ql * kHistBins;
-    uint32_t above;
-    const int e = hist_walk(h, (uint32_t)st->k_rem, &above);
-    __syncthreads();
-    for (int i = threadIdx.x; i < kHistBins; i += 64) h[i] = 0u;  // the refinement passes reuse the rows
-    if (threadIdx.x != 0) return;
-    const int nshift = max(st->shift - kHistBits, 0);
-    st->bound = st->prefix | ((unsigned long long)e << nshift);
-    st->prefix = 0;
-    st->shift = 0;
-    st->k_rem = 0;
-    st->fused = 1;
-}
-
-__global__ __launch_bounds__(512) void k_refine_hist(int32_t q0, int64_t N, const uint32_t* __restrict__ S, int64_t ld,
-                                                     const SelState* __restrict__ state, uint32_t* __restrict__ hist_ref) {
+// pass 0 runs once every tile is scored; pass 1 runs after phase 3 for the queries that
+// fell back, whose histograms are complete only then (phase 2 counts the seed tiles of a
+// fused query only). One workgroup per query: the first digit, then, for a query whose
+// threshold bucket is too large for the candidate buffer, the refinement passes over its
+// row (a loop in this launch: as launches of their own, twelve of them, they took 2 to 4.5 us
+// each also when, as usual, no query needs one: 19 of the 57 us of a search of 10,000
+// documents).
+// A query that fewer than kq documents match: its k-th composite has score 0, and the
+// documents that can win are the positive ones and those with id below kq (zero_floor). With
+// the zero-score documents counted beside the histogram, that needs no pass over the row
+// (four of them before, for every short query of a rare term).
+__global__ __launch_bounds__(kSelBS) void k_select(DevBatch qb, int32_t q0, int64_t N, int precision,
+                                                   const uint32_t* __restrict__ S, int64_t ld,
+                                                   uint32_t* __restrict__ hist1, SelState* __restrict__ state,
+                                                   uint32_t* __restrict__ counters, int32_t* __restrict__ rescore_list,
+                                                   int pass, int wide_check, int tile_shift, int stride) {
     __shared__ uint32_t hist[kHistBins];
-    const int ql = blockIdx.y;
-    const SelState st = state[ql];
-    if (st.resolved != 0) return;
+    __shared__ BinScan sh;
+    __shared__ unsigned long long sh_prefix;
+    __shared__ int sh_shift, sh_need, sh_open;
     const int tid = threadIdx.x;
-    for (int i = tid; i < kHistBins; i += 512) hist[i] = 0u;
-    __syncthreads();
-    const int shift = st.shift, nshift = max(shift - kHistBits, 0);
-    const unsigned long long want = st.prefix >> shift;
-    const unsigned long long mask = (1ull << (shift - nshift)) - 1ull;
-    // a few workgroups per query stride over the row: the launch stays cheap when
-    // no query needs a refinement (the usual case)
-    const uint32_t* Sq = S + (int64_t)ql * ld;
-    for (int64_t d = (int64_t)blockIdx.x * 512 + tid; d < N; d += (int64_t)gridDim.x * 512) {
-        const unsigned long long c = comp_key(Sq[d], (uint32_t)d);
-        if ((c >> shift) == want) atomicAdd(&hist[(c >> nshift) & mask], 1u);
-    }
-    __syncthreads();
-    for (int b = tid; b < kHistBins; b += 512)
-        if (hist[b]) atomicAdd(&hist_ref[(int64_t)ql * kHistBins + b], hist[b]);
-}
-
-__global__ __launch_bounds__(64) void k_refine_select(DevBatch qb, int32_t q0, int64_t N,
-                                                      uint32_t* __restrict__ hist_ref, SelState* __restrict__ state) {
     const int ql = blockIdx.x, q = q0 + ql;
     SelState* st = state + ql;
-    if (st->resolved != 0) return;
-    uint32_t* h = hist_ref + (int64_t)ql * kHistBins;
+    if (pass == 1 && st->rescore == 0) return;
     const int64_t kq = kq_of(qb, q, N);
-    uint32_t above;
-    const int d = hist_walk(h, (uint32_t)st->k_rem, &above);
-    const uint32_t hd = h[d];
-    __syncthreads();
-    for (int i = threadIdx.x; i < kHistBins; i += 64) h[i] = 0u;
-    if (threadIdx.x != 0) return;
-    const int nshift = max(st->shift - kHistBits, 0);
-    const unsigned long long prefix = st->prefix | ((unsigned long long)d << nshift);
-    const int32_t k_rem = st->k_rem - (int32_t)above;
-    st->passes += 1;
-    if ((kq - k_rem) + (int64_t)hd <= kCandCap) {
-        st->resolved = 1;
-        st->lo = prefix;
-    } else {
-        st->prefix = prefix;
-        st->shift = nshift;
-        st->k_rem = k_rem;
+    if (kq == 0) {
+        if (tid == 0) st->resolved = 2;
+        return;
     }
+    uint32_t* h = hist1 + (int64_t)ql * kHistBins;
+    uint32_t c[4], e[4];
+    load_bins(h, c);
+    scan_bins(c, e, (uint32_t)kq, sh);
+    const int d = sh.d, fs = qb.first_shift[q];
+    if (pass == 0 && wide_check) {
+        // lower edge of the k-th composite's bucket: its score bits with the low ones cleared
+        const float s_lo = __uint_as_float((uint32_t)(((unsigned long long)d << fs) >> 32));
+        if ((double)s_lo < qb.q_wide_lim[q]) {
+            // every lane has read its bins: the fp64 pass counts anew
+            reinterpret_cast<uint4*>(h)[tid] = make_uint4(0u, 0u, 0u, 0u);
+            if (tid == 0) {
+                st->fused = 0;
+                st->n_cand = 0;
+                st->zeros = 0;
+                st->resolved = 0;
+                st->rescore = 2;
+                rescore_list[atomicAdd(&counters[kCntListed], 1u)] = ql;
+            }
+            return;
+        }
+    }
+    if (tid == 0) {
+        const int64_t ge = (int64_t)sh.above + sh.count;
+        int64_t kept = 0;  // composites at or above the filter threshold
+        int resolved = 1;
+        unsigned long long lo = 0;
+        if (d == 0) {
+            // documents the histogram counts: all, or a fused query's seed tiles
+            int64_t docs = N;
+            if (st->fused == 1) {
+                const int64_t n_tiles = (N + (1ll << tile_shift) - 1) >> tile_shift, seeds = (n_tiles + stride - 1) / stride;
+                const int64_t last = ((seeds - 1) * stride) << tile_shift;
+                docs = ((seeds - 1) << tile_shift) + min(1ll << tile_shift, N - last);
+            }
+            lo = zero_floor(kq);
+            kept = docs - st->zeros + min(kq, (int64_t)st->zeros);
+            if (kept > kCandCap) resolved = 0;
+        } else if (precision == kBF16 && ge + h[d - 1] <= kCandCap) {
+            // one bin lower: the bf16 error band below the k-th score then lies inside the candidates
+            lo = (unsigned long long)(d - 1) << fs;
+            kept = ge + h[d - 1];
+        } else if (ge <= kCandCap) {
+            lo = (unsigned long long)d << fs;
+            kept = ge;
+        } else {
+            resolved = 0;
+        }
+        // Fused filtering holds the appended candidates (every composite >= the seed bound
+        // of the non-seed tiles; the bound is at most the threshold) and the filter then
+        // scans the seed tiles only. Otherwise the appended ones are dropped and the whole
+        // row is scanned: no bound, too many appended, or a refinement is needed.
+        int open = resolved == 0;
+        if (st->fused == 1 && (!resolved || st->fused_over || (int64_t)st->n_cand + kept > kCandCap)) {
+            st->fused = 0;
+            st->n_cand = 0;
+            st->rescore = 1;  // its non-seed rows were not written: score them again
+            rescore_list[atomicAdd(&counters[kCntListed], 1u)] = ql;
+            open = 0;
+        }
+        st->resolved = resolved;
+        st->lo = lo;
+        sh_open = open;
+        sh_prefix = (unsigned long long)d << fs;
+        sh_shift = fs;
+        sh_need = (int)(kq - sh.above);
+    }
+    __syncthreads();
+    // refinement: 11 more bits of the threshold per pass over the row
+    const uint32_t* Sq = S + (int64_t)ql * ld;
+    for (int p = 0; p < kRefinePasses && sh_open; p++) {
+        reinterpret_cast<uint4*>(hist)[tid] = make_uint4(0u, 0u, 0u, 0u);
+        const unsigned long long prefix = sh_prefix;
+        const int shift = sh_shift, need = sh_need, nshift = max(shift - kHistBits, 0);
+        __syncthreads();
+        count_digit(Sq, 0, N, shift, nshift, prefix >> shift, hist);
+        __syncthreads();
+        load_bins(hist, c);
+        scan_bins(c, e, (uint32_t)need, sh);
+        if (tid == 0) {
+            const unsigned long long np = prefix | ((unsigned long long)sh.d << nshift);
+            const int rem = need - (int)sh.above;
+            st->passes += 1;
+            if ((kq - rem) + (int64_t)sh.count <= kCandCap) {
+                st->resolved = 1;
+                st->lo = np;
+                sh_open = 0;
+            }
+            sh_prefix = np;
+            sh_shift = nshift;
+            sh_need = rem;
+        }
+        __syncthreads();
+    }
+}
+
+// Fused filtering, after the seed tiles are scored. The bound of a query is the
+// lower edge of a two-digit bucket (22 bits of the composite key) that holds the
+// k-th largest composite among the seed tiles' documents: every workgroup finds the
+// first-digit bin from the histogram the seed tiles built and counts the next digit
+// within that bin over its seed tile's scores, then k_seed_bound picks the sub-bin.
+// (Leaving that to the query's last workgroup saves its launch, but the device-scope
+// fences write back the L2s: 4.2 ms for 4,096 queries.) The k-th largest over all
+// documents is at least as large, so the bound never exceeds it; neither does
+// zero_floor, which keeps a query matched by few documents from appending every
+// zero-score one. With fewer than k seed documents there is no bound.
+__global__ __launch_bounds__(kSelBS) void k_seed(DevBatch qb, int32_t q0, int64_t N, const uint32_t* __restrict__ S,
+                                                 int64_t ld, int tile_shift, int stride,
+                                                 const uint32_t* __restrict__ hist1, SelState* __restrict__ state,
+                                                 uint32_t* __restrict__ hist_ref) {
+    __shared__ uint32_t hist[kHistBins];
+    __shared__ BinScan sh;
+    const int tid = threadIdx.x, ql = blockIdx.y, q = q0 + ql;
+    const int64_t kq = kq_of(qb, q, N);
+    if (kq == 0) return;  // fused stays 0 (cleared)
+    uint32_t c[4], e[4];
+    load_bins(hist1 + (int64_t)ql * kHistBins, c);
+    reinterpret_cast<uint4*>(hist)[tid] = make_uint4(0u, 0u, 0u, 0u);
+    scan_bins(c, e, (uint32_t)kq, sh);
+    if ((int64_t)sh.above + sh.count < kq) return;
+    const int shift = qb.first_shift[q], nshift = max(shift - kHistBits, 0);
+    const unsigned long long prefix = (unsigned long long)sh.d << shift;
+    if (blockIdx.x == 0 && tid == 0) {
+        SelState* st = state + ql;
+        st->lo = prefix;
+        st->seed_rem = (int)(kq - sh.above);
+        st->fused = 2;  // refining
+    }
+    const int64_t d0 = ((int64_t)blockIdx.x * stride) << tile_shift, d1 = min(N, d0 + (1ll << tile_shift));
+    count_digit(S + (int64_t)ql * ld, d0, d1, shift, nshift, prefix >> shift, hist);
+    __syncthreads();
+    uint32_t* hr = hist_ref + (int64_t)ql * kHistBins;
+    for (int b = tid; b < kHistBins; b += kSelBS)
+        if (hist[b]) atomicAdd(&hr[b], hist[b]);
+}
+
+__global__ __launch_bounds__(kSelBS) void k_seed_bound(DevBatch qb, int32_t q0, int64_t N, SelState* __restrict__ state,
+                                                       const uint32_t* __restrict__ hist_ref) {
+    __shared__ BinScan sh;
+    const int ql = blockIdx.x, q = q0 + ql;
+    SelState* st = state + ql;
+    if (st->fused != 2) return;
+    uint32_t c[4], e[4];
+    load_bins(hist_ref + (int64_t)ql * kHistBins, c);
+    scan_bins(c, e, (uint32_t)st->seed_rem, sh);
+    if (threadIdx.x != 0) return;
+    const int nshift = max(qb.first_shift[q] - kHistBits, 0);
+    const unsigned long long b = st->lo | ((unsigned long long)sh.d << nshift), z = zero_floor(kq_of(qb, q, N));
+    st->bound = b > z ? b : z;
+    st->fused = 1;
 }
 
 // Append every composite >= the query's threshold to its candidate buffer.
@@ -389,50 +411,72 @@ __global__ __launch_bounds__(512) void k_filter(int32_t q0, int64_t N, const uin
     }
 }
 
-// fp64 rescoring of the docs bid[0..nb) against the query held in LDS (terms
-// ascending), by the whole workgroup: a wavefront takes 4 docs, 16 lanes each.
-// Lane `sub` walks entries sub, sub+16, ... of the doc's forward row (sorted by
-// term) and merges them with the query terms; each step's nonzero products are
-// then added in row order (ascending term), one shuffle at a time, so the sum
-// is the same sequence of fp64 additions as a serial walk of the row.
-__device__ void rescore_band(const DevIndex& ix, const int32_t* bid, double* bs, int nb, const int32_t* qt,
-                             const float* qw, int nq) {
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    const int grp = lane >> 4, sub = lane & 15;
-    for (int base = wave * 4; base < nb; base += nw * 4) {
-        const int i = base + grp;
-        int64_t a = 0;
-        int len = 0;
-        if (i < nb) {
-            const int64_t doc = bid[i];
-            a = ix.fwd_row_ptr[doc];
-            len = (int)(ix.fwd_row_ptr[doc + 1] - a);
-        }
-        int maxlen = len;
-        maxlen = max(maxlen, __shfl_xor(maxlen, 16, kWave));
-        maxlen = max(maxlen, __shfl_xor(maxlen, 32, kWave));
-        double s = 0.0;
-        int j = 0;
-        for (int off = 0; off < maxlen; off += 16) {
-            const int e = off + sub;
-            double pr = 0.0;
-            if (e < len) {
-                const int t = ix.fwd_term[a + e];
-                while (j < nq && qt[j] < t) j++;
-                if (j < nq && qt[j] == t) pr = (double)qw[j] * (double)ix.fwd_w[a + e];
-            }
-            uint32_t mm = (uint32_t)(__ballot(pr != 0.0) >> (grp * 16)) & 0xFFFFu;
-            while (__any(mm != 0u)) {
-                const int src = grp * 16 + (mm ? __ffs(mm) - 1 : 0);
-                const double v = __shfl(pr, src, kWave);
-                if (mm) {
-                    s += v;
-                    mm &= mm - 1u;
-                }
-            }
-        }
-        if (sub == 0 && i < nb) bs[i] = s;
+// Candidates and winners held in LDS by k_final, band documents held by k_band_topk.
+constexpr int kFinalCap = kMaxK + 512;
+// Largest bin whose winners are ranked by comparisons among them (64 comparisons cost about as
+// much as the bitonic sort of 1,000 winners that takes over past it).
+constexpr int kFinalBin = 64;
+
+// Smallest shift that maps offsets 0 .. range onto kHistBins bins.
+__device__ __forceinline__ int range_shift(unsigned long long range) {
+    return range == 0 ? 0 : max(0, 64 - __clzll((long long)range) - kHistBits);
+}
+
+__device__ __forceinline__ unsigned long long wave_max(unsigned long long v) {
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        const unsigned long long o = __shfl_xor(v, d, kWave);
+        v = o > v ? o : v;
     }
+    return v;
+}
+
+// Largest of a workgroup's values, in *out (LDS, zero before).
+__device__ __forceinline__ void block_max(uint32_t v, uint32_t* out) {
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, d, kWave));
+    if ((threadIdx.x & (kWave - 1)) == 0) atomicMax(out, v);
+    __syncthreads();
+}
+
+// Bitonic sort of m elements in LDS by the whole workgroup, with every comparator in the same
+// direction (each merge opens with a mirrored step), so that m need not be a power of two:
+// comparators past the end are left out. order(l, r) puts the elements l < r in order. The way
+// out where one bin holds too many winners to rank them by comparisons (many equal scores).
+// In steps of j <= 64 a wavefront's pairs stay inside its own 128 elements, so those steps need
+// no workgroup barrier between them (1,000 elements: 49 of 55 barriers less).
+template <typename F>
+__device__ __forceinline__ void bitonic_sort(int m, F order) {
+    for (int lk = 1; (1 << (lk - 1)) < m; lk++) {
+        for (int lj = lk - 1; lj >= 0; lj--) {
+            const int j = 1 << lj, pairs = ((m + 2 * j - 1) >> (lj + 1)) << lj;
+            for (int t = threadIdx.x; t < pairs; t += kSelBS) {
+                const int block = t >> lj, at = t & (j - 1);
+                const int l = (block << (lj + 1)) + at;
+                const int r = lj == lk - 1 ? (block << (lj + 1)) + 2 * j - 1 - at : l + j;
+                if (r < m) order(l, r);
+            }
+            if (j > kWave || (lj == 0 ? (1 << lk) : j >> 1) > kWave) __syncthreads();
+            else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        }
+    }
+    __syncthreads();
+}
+
+// Smallest and largest of the workgroup's values (given as per-thread extremes) in red[0], red[1].
+__device__ __forceinline__ void block_range(unsigned long long mn, unsigned long long mx, unsigned long long* red) {
+    mn = ~wave_max(~mn);
+    mx = wave_max(mx);
+    if (threadIdx.x == 0) {
+        red[0] = ~0ull;
+        red[1] = 0ull;
+    }
+    __syncthreads();
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+        atomicMin(&red[0], mn);
+        atomicMax(&red[1], mx);
+    }
+    __syncthreads();
 }
 
 // One wavefront walks a 256-bin histogram from the top bin down for the bin
@@ -582,173 +626,333 @@ __device__ __forceinline__ void band_error(const DevBatch& qb, int q, int acc, i
     }
 }
 
-template <int P>
-__global__ __launch_bounds__(1024) void k_final(DevIndex ix, DevBatch qb, int32_t q0, SelState* __restrict__ state,
-                                                const unsigned long long* __restrict__ cand,
-                                                double* __restrict__ band_s, int32_t* __restrict__ band_id,
-                                                int32_t* __restrict__ out_ids, void* __restrict__ out_scores, int acc,
-                                                uint32_t* __restrict__ counters, int32_t* __restrict__ rescore_list) {
-    __shared__ unsigned long long sel[kMaxK];
-    __shared__ uint32_t hist[256];
-    __shared__ int sh_d, sh_cnt;
-    __shared__ uint32_t sh_above;
-    __shared__ int32_t sq_t[kMaxQueryNnz];
-    __shared__ float sq_w[kMaxQueryNnz];
-    __shared__ int32_t band_wid[P == kBF16 ? kMaxK : 1];
+// One row of the per-query diagnostics (gs_batch_diagnostics).
+__device__ __forceinline__ void write_diag(int32_t* diag, int q, const SelState& st) {
+    if (diag == nullptr || threadIdx.x != 0) return;
+    int32_t* o = diag + (int64_t)q * kDiagWords;
+    o[0] = st.n_cand;
+    o[1] = st.passes;
+    o[2] = st.band;
+    o[3] = st.overflow;
+    o[4] = st.rescore;
+    o[5] = st.fused == 1 ? 1 : 0;
+    o[6] = st.pruned;
+    o[7] = 0;
+}
+
+// The k best of a query's candidates, in order. ROW: the candidates are the documents of the
+// score row themselves (collections of at most kCandCap documents; no selection state is read).
+// A histogram of the candidates over 2048 equal bins of their range finds the bin of the k-th
+// in one pass; while that bin is too large to be ranked by comparisons the range is narrowed to
+// it and counted again. The winners are grouped by bin in LDS (the scanned histogram gives each
+// bin's first place), so that each needs comparing only with its own bin. Before: up to eight
+// 8-bit radix passes and a rank by comparison with all k winners (27 us for one query of
+// 4M documents, k = 1000, now 8; 4,096 queries of 250,000 documents 300 us, now 73).
+template <int P, bool ROW>
+__global__ __launch_bounds__(kSelBS) void k_final(DevIndex ix, DevBatch qb, int32_t q0, SelState* __restrict__ state,
+                                                  const unsigned long long* __restrict__ cand,
+                                                  const uint32_t* __restrict__ S, int64_t ld,
+                                                  int32_t* __restrict__ band_id, int32_t* __restrict__ out_ids,
+                                                  void* __restrict__ out_scores, int acc,
+                                                  uint32_t* __restrict__ counters, int32_t* __restrict__ rescore_list,
+                                                  int32_t* __restrict__ diag) {
+    static_assert(P != kBF16 || !ROW, "bf16 needs the selection state (error band)");
+    __shared__ unsigned long long sel[kFinalCap];
+    __shared__ uint32_t hist[kHistBins];
+    __shared__ BinScan sh;
+    __shared__ unsigned long long red[2];
     const int tid = threadIdx.x;
     const int ql = blockIdx.x, q = q0 + ql;
     SelState* st = state + ql;
     const int64_t kq = kq_of(qb, q, ix.n_docs);
     const int kmax = qb.k_max;
     int32_t* ids = out_ids + (int64_t)q * kmax;
-    for (int i = tid; i < kmax; i += 1024) {
-        if (i >= kq) {
-            ids[i] = -1;
-            if (P == kBF16) ((double*)out_scores)[(int64_t)q * kmax + i] = 0.0;
-            else ((uint32_t*)out_scores)[(int64_t)q * kmax + i] = 0u;
+    if (P != kBF16) {
+        for (int i = tid; i < kmax; i += kSelBS) {
+            if (i >= kq) {
+                ids[i] = -1;
+                ((uint32_t*)out_scores)[(int64_t)q * kmax + i] = 0u;
+            }
+        }
+        if constexpr (ROW) {
+            SelState d{};
+            d.n_cand = kq > 0 ? (int32_t)ix.n_docs : 0;
+            write_diag(diag, q, d);
+        } else {
+            write_diag(diag, q, *st);
         }
     }
     if (kq == 0) return;
-    const int n = min(st->n_cand, kCandCap);
+    const int n = ROW ? (int)ix.n_docs : min(st->n_cand, kCandCap);
+    if (n == 0) return;
     const unsigned long long* C = cand + (int64_t)ql * kCandCap;
-
-    // radix select of the kq-th largest composite among the n candidates
-    unsigned long long prefix = 0;
-    int shift = 64;
-    uint32_t need = (uint32_t)kq;
-    if (n > kq) {
-        while (shift > 0) {
-            const int nshift = shift - 8;
-            for (int i = tid; i < 256; i += 1024) hist[i] = 0u;
-            __syncthreads();
-            for (int i = tid; i < n; i += 1024) {
-                const unsigned long long c = C[i];
-                if (shift == 64 || (c >> shift) == (prefix >> shift)) atomicAdd(&hist[(c >> nshift) & 255ull], 1u);
-            }
-            __syncthreads();
-            if (tid < kWave) {
-                // 256 bins, 4 per lane, walked from the top
-                const int lane = tid;
-                uint32_t s = 0;
-                for (int j = 0; j < 4; j++) s += hist[255 - lane * 4 - j];
-                uint32_t incl = s;
-                for (int dd = 1; dd < kWave; dd <<= 1) {
-                    const uint32_t v = __shfl_up(incl, dd, kWave);
-                    if (lane >= dd) incl += v;
-                }
-                const uint32_t excl = incl - s;
-                const unsigned long long m = __ballot(excl < need && need <= incl);
-                const int owner = m ? __ffsll((long long)m) - 1 : kWave - 1;
-                if (lane == owner) {
-                    uint32_t run = excl;
-                    int dsel = 255 - lane * 4 - 3;
-                    uint32_t ab = run;
-                    for (int j = 0; j < 4; j++) {
-                        const uint32_t c = hist[255 - lane * 4 - j];
-                        if (run + c >= need) { dsel = 255 - lane * 4 - j; ab = run; break; }
-                        run += c;
-                    }
-                    sh_d = dsel;
-                    sh_above = ab;
-                }
-            }
-            __syncthreads();
-            const int d = sh_d;
-            need -= sh_above;
-            prefix |= (unsigned long long)d << nshift;
-            shift = nshift;
-            const uint32_t hd = hist[d];
-            __syncthreads();
-            if (hd == need) break;
-        }
+    const uint32_t* Sq = S + (int64_t)ql * ld;
+    auto get = [&](int i) { return ROW ? comp_key(Sq[i], (uint32_t)i) : C[i]; };
+    // the first REG candidates of each thread stay in registers over the passes
+    constexpr int REG = 16;
+    unsigned long long reg[REG];
+    unsigned long long mn = ~0ull, mx = 0ull;
+#pragma unroll
+    for (int r = 0; r < REG; r++) {
+        const int i = tid + r * kSelBS;
+        reg[r] = i < n ? get(i) : 0ull;
     }
-    // gather the kq winners: composites whose bits above `shift` are >= the prefix's
-    if (tid == 0) sh_cnt = 0;
-    __syncthreads();
-    for (int i = tid; i < n; i += 1024) {
-        const unsigned long long c = C[i];
-        const bool win = (shift == 64) || (shift == 0 ? c >= prefix : (c >> shift) >= (prefix >> shift));
-        if (win) {
-            const int pos = atomicAdd(&sh_cnt, 1);
-            if (pos < kMaxK) sel[pos] = c;
-        }
+    auto each = [&](auto f) {
+#pragma unroll
+        for (int r = 0; r < REG; r++)
+            if (tid + r * kSelBS < n) f(reg[r]);
+        for (int i = tid + REG * kSelBS; i < n; i += kSelBS) f(get(i));
+    };
+    each([&](unsigned long long c) {
+        mn = c < mn ? c : mn;
+        mx = c > mx ? c : mx;
+    });
+    block_range(mn, mx, red);
+    mn = red[0];
+    mx = red[1];
+    unsigned long long lo = mn, hi = mx, thr;
+    uint32_t above = 0;  // composites past hi
+    const uint32_t need = (uint32_t)min((int64_t)n, kq);
+    int s, total;
+    uint32_t c4[4], e4[4];
+    auto count = [&]() {  // composites of [lo, hi] per bin, and the bin of the (need - above)-th
+        s = range_shift(hi - lo);
+        reinterpret_cast<uint4*>(hist)[tid] = make_uint4(0u, 0u, 0u, 0u);
+        __syncthreads();
+        each([&](unsigned long long c) {
+            if (c >= lo && c <= hi) atomicAdd(&hist[(c - lo) >> s], 1u);
+        });
+        __syncthreads();
+        load_bins(hist, c4);
+        scan_bins(c4, e4, need - above, sh);
+    };
+    bool whole = true;  // hist spans every winner
+    for (;;) {
+        count();
+        total = (int)(above + sh.above + sh.count);
+        thr = lo + ((unsigned long long)sh.d << s);
+        if (s == 0 || (total <= kFinalCap && sh.count <= (uint32_t)kFinalBin)) break;
+        above += sh.above;
+        hi = min(hi, thr + ((1ull << s) - 1ull));
+        lo = thr;
+        whole = false;
+        __syncthreads();  // sh is read: the next scan may write it
     }
+    if (!whole) {
+        __syncthreads();
+        lo = thr;
+        hi = mx;
+        above = 0;
+        count();
+    }
+    // the largest bin among the winners' decides how they are put in order
+    __syncthreads();  // sh is read
+    if (tid == 0) sh.above = 0;
     __syncthreads();
-    const int m = min(sh_cnt, kMaxK);
-    if (P != kBF16) {
-        for (int i = tid; i < m; i += 1024) {
-            const unsigned long long c = sel[i];
-            int r = 0;
-            for (int j = 0; j < m; j++) r += sel[j] > c;
+    {
+        uint32_t big = 0;
+#pragma unroll
+        for (int j = 0; j < 4; j++)
+            if (lo + ((unsigned long long)(kHistBins - 1 - 4 * tid - j) << s) >= thr) big = max(big, c4[j]);
+        block_max(big, &sh.above);
+    }
+    const bool sorted = sh.above > (uint32_t)kFinalBin;
+    // group the winners by bin: the scanned histogram (elements above each bin) is the cursor
+    reinterpret_cast<uint4*>(hist)[kSelBS - 1 - tid] = make_uint4(e4[3], e4[2], e4[1], e4[0]);
+    __syncthreads();
+    each([&](unsigned long long c) {
+        if (c >= thr) {
+            const uint32_t pos = atomicAdd(&hist[(c - lo) >> s], 1u);
+            if (pos < (uint32_t)kFinalCap) sel[pos] = c;
+        }
+    });
+    __syncthreads();
+    const int m = min(total, kFinalCap);
+    if (sorted)
+        bitonic_sort(m, [&](int l, int r) {
+            const unsigned long long a = sel[l], b = sel[r];
+            if (a < b) {
+                sel[l] = b;
+                sel[r] = a;
+            }
+        });
+    // bin b now ends at hist[b] and starts where the bin above it ends
+    auto ranked = [&](auto f) {
+        for (int p = tid; p < m; p += kSelBS) {
+            const unsigned long long c = sel[p];
+            if (sorted) {
+                f(p, c);
+                continue;
+            }
+            const int b = (int)((c - lo) >> s);
+            const int from = b + 1 < kHistBins ? (int)hist[b + 1] : 0, to = min((int)hist[b], m);
+            int r = from;
+            for (int j = from; j < to; j++) r += sel[j] > c;
+            f(r, c);
+        }
+    };
+    if constexpr (P != kBF16) {
+        ranked([&](int r, unsigned long long c) {
             if (r < kq) {
                 ids[r] = (int32_t)(~(uint32_t)c);
                 ((uint32_t*)out_scores)[(int64_t)q * kmax + r] = (uint32_t)(c >> 32);
             }
+        });
+    } else {
+        // bf16: exact k-th approximate score, then the error band
+        __shared__ unsigned long long sh_kth;
+        __shared__ int sh_cnt;
+        if (tid == 0) {
+            sh_kth = 0ull;
+            sh_cnt = 0;
         }
-        return;
+        __syncthreads();
+        int32_t* bid = band_id + (int64_t)ql * kCandCap;
+        ranked([&](int r, unsigned long long c) {
+            if (r == kq - 1) sh_kth = c;
+        });
+        __syncthreads();
+        const float sk = __uint_as_float((uint32_t)(sh_kth >> 32));
+        const int nq = (int)(qb.q_row_ptr[q + 1] - qb.q_row_ptr[q]);
+        double rel_err, abs_err;
+        band_error(qb, q, acc, st->rescore, nq, &rel_err, &abs_err);
+        int nb;
+        if (sk == 0.0f) {
+            // fewer than k docs share a term with the query: the k winners are every doc with a
+            // positive score plus the lowest-id zero-score docs. A zero approximate score is exact
+            // here: from fp32 or fp64 sums (no product of admissible weights underflows to 0), or
+            // from fixed point only if no positive product can round to 0 units (otherwise the
+            // wide-range check sent the query to the fp64 pass: its k-th bucket starts at 0).
+            ranked([&](int r, unsigned long long c) {
+                if (r < kq) bid[r] = (int32_t)(~(uint32_t)c);
+            });
+            nb = (int)kq;
+        } else {
+            const double tau = band_tau(sk, rel_err, abs_err);
+            // with fused filtering the other tiles' candidates start at the bound, the seed tiles' at lo
+            const unsigned long long flo = st->fused == 1 ? max(st->lo, st->bound) : st->lo;
+            const double lo_val = (double)__uint_as_float((uint32_t)(flo >> 32));
+            const bool inside = tau > 0.0 && (((uint32_t)flo == 0u) ? (lo_val <= tau) : (lo_val < tau));
+            if (!inside) {
+                if (tid == 0) {
+                    st->need_band_pass = 1;
+                    st->tau = tau;
+                    if (st->fused == 1) {  // its other tiles wrote no rows: score them for the band pass
+                        st->rescore = 3;
+                        rescore_list[atomicAdd(&counters[kCntListed], 1u)] = ql;
+                    }
+                }
+                return;
+            }
+            each([&](unsigned long long c) {
+                const double v = (double)__uint_as_float((uint32_t)(c >> 32));
+                if (v > 0.0 && v >= tau) bid[atomicAdd(&sh_cnt, 1)] = (int32_t)(~(uint32_t)c);
+            });
+            __syncthreads();
+            nb = sh_cnt;
+        }
+        if (tid == 0) st->band = nb;
     }
-    // bf16: exact k-th approximate score, then the error band and fp64 rescoring
-    __shared__ unsigned long long sh_min;
-    if (tid == 0) sh_min = ~0ull;
-    __syncthreads();
-    for (int i = tid; i < m; i += 1024) atomicMin(&sh_min, sel[i]);
+}
+
+// fp64 rescoring of the listed band documents against their query, on a grid over the
+// documents (a workgroup per query left 252 of 256 CUs idle for a call of four queries: its
+// selection took 368 us, now 37 us, 18 of them here; 500 queries: 826 us, now 250, 204 of
+// them here, bound by the forward rows' reads). A wavefront takes 4 documents, 16 lanes each. Lane `sub` holds entries
+// sub, sub + 16, ... of the document's forward row (sorted by term), eight in flight, and
+// finds each term in the query by a hash of its low bits (most miss at once). The nonzero
+// products are then put side by side in LDS in row order (ascending term) and added by one
+// lane, so the sum is the same sequence of fp64 additions as a serial walk of the row.
+constexpr int kRescoreBS = 256;
+constexpr int kRescoreHash = 1024;
+__global__ __launch_bounds__(kRescoreBS) void k_rescore(DevIndex ix, DevBatch qb, int32_t q0,
+                                                        const SelState* __restrict__ state,
+                                                        double* __restrict__ band_s,
+                                                        const int32_t* __restrict__ band_id) {
+    __shared__ int32_t head[kRescoreHash];
+    __shared__ int32_t next[kMaxQueryNnz];
+    __shared__ int32_t sq_t[kMaxQueryNnz];
+    __shared__ float sq_w[kMaxQueryNnz];
+    constexpr int U = 8;
+    __shared__ double prod[kRescoreBS / 16][16 * U / 2];  // per document, half a step's products in row order
+    const int ql = blockIdx.y, q = q0 + ql, tid = threadIdx.x;
+    const SelState* st = state + ql;
+    const int nb = st->overflow ? 0 : min(st->band, kCandCap);
+    constexpr int per = kRescoreBS / 16;
+    if ((int)blockIdx.x * per >= nb) return;
+    for (int i = tid; i < kRescoreHash; i += kRescoreBS) head[i] = -1;
     const int64_t qa = qb.q_row_ptr[q];
     const int nq = (int)(qb.q_row_ptr[q + 1] - qa);
-    for (int i = tid; i < nq; i += 1024) {
-        sq_t[i] = qb.q_term[qa + i];
+    __syncthreads();
+    for (int i = tid; i < nq; i += kRescoreBS) {
+        const int32_t t = qb.q_term[qa + i];
+        sq_t[i] = t;
         sq_w[i] = qb.q_w[qa + i];
+        next[i] = atomicExch(&head[t & (kRescoreHash - 1)], i);
     }
     __syncthreads();
-    const float sk = __uint_as_float((uint32_t)(sh_min >> 32));
-    double rel_err, abs_err;
-    band_error(qb, q, acc, st->rescore, nq, &rel_err, &abs_err);
+    const int32_t* bid = band_id + (int64_t)ql * kCandCap;
     double* bs = band_s + (int64_t)ql * kCandCap;
-    int32_t* bid = band_id + (int64_t)ql * kCandCap;
-    int nb = 0;
-    if (sk == 0.0f) {
-        // fewer than k docs share a term with the query: the k winners are every doc with a
-        // positive score plus the lowest-id zero-score docs. A zero approximate score is exact
-        // here: from fp32 or fp64 sums (no product of admissible weights underflows to 0), or
-        // from fixed point only if no positive product can round to 0 units (otherwise the
-        // wide-range check sent the query to the fp64 pass: its k-th bucket starts at 0).
-        for (int i = tid; i < m; i += 1024) bid[i] = (int32_t)(~(uint32_t)sel[i]);
-        nb = m;
-    } else {
-        const double tau = band_tau(sk, rel_err, abs_err);
-        // with fused filtering the other tiles' candidates start at the bound, the seed tiles' at lo
-        const unsigned long long lo = st->fused == 1 ? max(st->lo, st->bound) : st->lo;
-        const double lo_val = (double)__uint_as_float((uint32_t)(lo >> 32));
-        const bool inside = tau > 0.0 && (((uint32_t)lo == 0u) ? (lo_val <= tau) : (lo_val < tau));
-        if (!inside) {
-            if (tid == 0) {
-                st->need_band_pass = 1;
-                st->tau = tau;
-                if (st->fused == 1) {  // its other tiles wrote no rows: score them for the band pass
-                    st->rescore = 3;
-                    rescore_list[atomicAdd(&counters[8], 1u)] = ql;
-                }
+    const int lane = tid & (kWave - 1), wave = tid >> 6;
+    const int grp = lane >> 4, sub = lane & 15;
+    double* mine = prod[wave * 4 + grp];
+    auto row = [&](int i, int64_t& a, int& len) {  // document i's forward row
+        a = 0;
+        len = 0;
+        if (i < nb) {
+            const int64_t doc = bid[i];
+            a = ix.fwd_row_ptr[doc];
+            len = (int)(ix.fwd_row_ptr[doc + 1] - a);
+        }
+    };
+    int64_t a, a_next;
+    int len, len_next;
+    const int step = (int)gridDim.x * per;
+    row((int)blockIdx.x * per + wave * 4 + grp, a_next, len_next);
+    for (int base = (int)blockIdx.x * per + wave * 4; base < nb; base += step) {
+        const int i = base + grp;
+        a = a_next;
+        len = len_next;
+        int maxlen = len;
+        maxlen = max(maxlen, __shfl_xor(maxlen, 16, kWave));
+        maxlen = max(maxlen, __shfl_xor(maxlen, 32, kWave));
+        double s = 0.0;
+        for (int off = 0; off < maxlen; off += 16 * U) {
+            int t[U];
+            float w[U];
+            int j[U];
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                const int e = off + 16 * u + sub;
+                t[u] = e < len ? ix.fwd_term[a + e] : -1;
             }
-            return;
+            if (off == 0) row(i + step, a_next, len_next);  // the next document's row under this one's loads
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                j[u] = t[u] >= 0 ? head[t[u] & (kRescoreHash - 1)] : -1;
+                while (j[u] >= 0 && sq_t[j[u]] != t[u]) j[u] = next[j[u]];
+            }
+#pragma unroll
+            for (int u = 0; u < U; u++) w[u] = j[u] >= 0 ? ix.fwd_w[a + off + 16 * u + sub] : 0.0f;
+#pragma unroll
+            for (int h = 0; h < 2; h++) {
+                int cnt = 0;
+#pragma unroll
+                for (int u = h * U / 2; u < (h + 1) * U / 2; u++) {
+                    const double pr = j[u] >= 0 ? (double)sq_w[j[u]] * (double)w[u] : 0.0;
+                    const uint32_t mm = (uint32_t)(__ballot(pr != 0.0) >> (grp * 16)) & 0xFFFFu;
+                    if (pr != 0.0) mine[cnt + __popc(mm & ((1u << sub) - 1u))] = pr;
+                    cnt += __popc(mm);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");  // LDS of this wavefront only
+                if (sub == 0)
+                    for (int p = 0; p < cnt; p++) s += mine[p];
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+            }
         }
-        if (tid == 0) sh_cnt = 0;
-        __syncthreads();
-        for (int i = tid; i < n; i += 1024) {
-            const unsigned long long c = C[i];
-            const double v = (double)__uint_as_float((uint32_t)(c >> 32));
-            if (v > 0.0 && v >= tau) bid[atomicAdd(&sh_cnt, 1)] = (int32_t)(~(uint32_t)c);
-        }
-        __syncthreads();
-        nb = sh_cnt;
+        if (maxlen == 0) row(i + step, a_next, len_next);
+        if (sub == 0 && i < nb) bs[i] = s;
     }
-    __threadfence_block();
-    __syncthreads();
-    rescore_band(ix, bid, bs, nb, sq_t, sq_w, nq);
-    if (tid == 0) st->band = nb;
-    __threadfence_block();
-    __syncthreads();
-    // sel (the approximate winners) is no longer needed: it holds the exact winners' scores
-    band_topk(bs, bid, nb, kq, ids, (double*)out_scores + (int64_t)q * kmax,
-              BandLds{hist, sel, band_wid, &sh_d, &sh_above, &sh_cnt});
 }
 
 __global__ __launch_bounds__(512) void k_band_filter(int32_t q0, int64_t N, const uint32_t* __restrict__ S,
@@ -778,148 +982,218 @@ __global__ __launch_bounds__(512) void k_band_filter(int32_t q0, int64_t N, cons
     }
 }
 
-__global__ __launch_bounds__(1024) void k_band_final(DevIndex ix, DevBatch qb, int32_t q0, SelState* __restrict__ state,
-                                                     double* __restrict__ band_s, int32_t* __restrict__ band_id,
-                                                     int32_t* __restrict__ out_ids, double* __restrict__ out_scores) {
-    __shared__ int32_t sq_t[kMaxQueryNnz];
-    __shared__ float sq_w[kMaxQueryNnz];
-    __shared__ uint32_t hist[256];
-    __shared__ unsigned long long wsc[kMaxK];
-    __shared__ int32_t wid[kMaxK];
+// The kq best band documents of a query by (fp64 score desc, doc id asc): grouped by bins of
+// the score bits in LDS and ranked inside their bin as in k_final; bands past kFinalCap
+// documents (massive near-ties) go through the radix selection of band_topk.
+__global__ __launch_bounds__(kSelBS) void k_band_topk(DevIndex ix, DevBatch qb, int32_t q0,
+                                                      const SelState* __restrict__ state,
+                                                      const double* __restrict__ band_s,
+                                                      const int32_t* __restrict__ band_id,
+                                                      int32_t* __restrict__ out_ids, double* __restrict__ out_scores,
+                                                      int32_t* __restrict__ diag) {
+    __shared__ uint32_t hist[kHistBins];
+    __shared__ unsigned long long wsc[kFinalCap];
+    __shared__ int32_t wid[kFinalCap];
+    __shared__ BinScan sh;
+    __shared__ unsigned long long red[2];
     __shared__ int sh_d, sh_cnt;
     __shared__ uint32_t sh_above;
-    const int ql = blockIdx.x, q = q0 + ql;
-    SelState* st = state + ql;
-    if (st->need_band_pass != 1) return;
-    const int tid = threadIdx.x;
-    const int64_t qa = qb.q_row_ptr[q];
-    const int nq = (int)(qb.q_row_ptr[q + 1] - qa);
-    for (int i = tid; i < nq; i += 1024) {
-        sq_t[i] = qb.q_term[qa + i];
-        sq_w[i] = qb.q_w[qa + i];
-    }
-    __syncthreads();
+    const int ql = blockIdx.x, q = q0 + ql, tid = threadIdx.x;
+    const SelState* st = state + ql;
     const int64_t kq = kq_of(qb, q, ix.n_docs);
-    if (st->overflow) {
-        // the band does not fit the buffer: the row is left as padding and flagged
-        for (int i = tid; i < kq; i += 1024) {
-            out_ids[(int64_t)q * qb.k_max + i] = -1;
-            out_scores[(int64_t)q * qb.k_max + i] = 0.0;
+    int32_t* ids = out_ids + (int64_t)q * qb.k_max;
+    double* sc = out_scores + (int64_t)q * qb.k_max;
+    // a band that does not fit its buffer: the row is left as padding and flagged
+    const bool lost = st->need_band_pass == 1 && st->overflow;
+    for (int i = tid; i < qb.k_max; i += kSelBS) {
+        if (i >= kq || lost) {
+            ids[i] = -1;
+            sc[i] = 0.0;
         }
+    }
+    write_diag(diag, q, *st);
+    if (kq == 0 || lost) return;
+    const int nb = min(st->band, kCandCap);
+    const double* bs = band_s + (int64_t)ql * kCandCap;
+    const int32_t* bid = band_id + (int64_t)ql * kCandCap;
+    if (nb > kFinalCap) {
+        band_topk(bs, bid, nb, kq, ids, sc, BandLds{hist, wsc, wid, &sh_d, &sh_above, &sh_cnt});
         return;
     }
-    const int nb = min(st->band, kCandCap);
-    double* bs = band_s + (int64_t)ql * kCandCap;
-    int32_t* bid = band_id + (int64_t)ql * kCandCap;
-    rescore_band(ix, bid, bs, nb, sq_t, sq_w, nq);
-    __threadfence_block();
+    if (nb == 0) return;
+    constexpr int R = kFinalCap / kSelBS;
+    unsigned long long key[R];
+    int32_t id[R];
+    unsigned long long mn = ~0ull, mx = 0ull;
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        const int i = tid + r * kSelBS;
+        key[r] = i < nb ? (unsigned long long)__double_as_longlong(bs[i]) : 0ull;
+        id[r] = i < nb ? bid[i] : 0;
+        if (i < nb) {
+            mn = key[r] < mn ? key[r] : mn;
+            mx = key[r] > mx ? key[r] : mx;
+        }
+    }
+    reinterpret_cast<uint4*>(hist)[tid] = make_uint4(0u, 0u, 0u, 0u);
+    block_range(mn, mx, red);
+    mn = red[0];
+    const int s = range_shift(red[1] - mn);
+#pragma unroll
+    for (int r = 0; r < R; r++)
+        if (tid + r * kSelBS < nb) atomicAdd(&hist[(key[r] - mn) >> s], 1u);
     __syncthreads();
-    band_topk(bs, bid, nb, kq, out_ids + (int64_t)q * qb.k_max, out_scores + (int64_t)q * qb.k_max,
-              BandLds{hist, wsc, wid, &sh_d, &sh_above, &sh_cnt});
-}
-
-__global__ void k_diag(int32_t q0, int32_t qt, const SelState* __restrict__ state, int32_t* __restrict__ diag) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= qt) return;
-    const SelState st = state[i];
-    int32_t* o = diag + (int64_t)(q0 + i) * kDiagWords;
-    o[0] = st.n_cand;
-    o[1] = st.passes;
-    o[2] = st.band;
-    o[3] = st.overflow;
-    o[4] = st.rescore;
-    o[5] = st.fused == 1 ? 1 : 0;
-    o[6] = st.pruned;
-    o[7] = 0;
+    uint32_t c4[4], e4[4];
+    load_bins(hist, c4);
+    scan_bins(c4, e4, (uint32_t)min((int64_t)nb, kq), sh);
+    reinterpret_cast<uint4*>(hist)[kSelBS - 1 - tid] = make_uint4(e4[3], e4[2], e4[1], e4[0]);
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        if (tid + r * kSelBS >= nb) continue;
+        const uint32_t pos = atomicAdd(&hist[(key[r] - mn) >> s], 1u);
+        wsc[pos] = key[r];
+        wid[pos] = id[r];
+    }
+    __syncthreads();
+    const int m = min((int)(sh.above + sh.count), nb);  // the winners' bins come first
+    const int d_last = sh.d;
+    __syncthreads();
+    if (tid == 0) sh.above = 0;
+    __syncthreads();
+    {
+        uint32_t big = 0;
+#pragma unroll
+        for (int j = 0; j < 4; j++)
+            if (kHistBins - 1 - 4 * tid - j >= d_last) big = max(big, c4[j]);
+        block_max(big, &sh.above);
+    }
+    const bool sorted = sh.above > (uint32_t)kFinalBin;
+    if (sorted)
+        bitonic_sort(m, [&](int l, int r) {
+            const unsigned long long a = wsc[l], b = wsc[r];
+            const int32_t ia = wid[l], ib = wid[r];
+            if (a < b || (a == b && ia > ib)) {
+                wsc[l] = b;
+                wsc[r] = a;
+                wid[l] = ib;
+                wid[r] = ia;
+            }
+        });
+    for (int p = tid; p < m; p += kSelBS) {
+        const unsigned long long k = wsc[p];
+        const int32_t di = wid[p];
+        if (sorted) {
+            if (p < kq) {
+                ids[p] = di;
+                sc[p] = __longlong_as_double((long long)k);
+            }
+            continue;
+        }
+        const int b = (int)((k - mn) >> s);
+        const int from = b + 1 < kHistBins ? (int)hist[b + 1] : 0, to = (int)hist[b];
+        int r = from;
+        for (int j = from; j < to; j++) r += wsc[j] > k || (wsc[j] == k && wid[j] < di);
+        if (r < kq) {
+            ids[r] = di;
+            sc[r] = __longlong_as_double((long long)k);
+        }
+    }
 }
 
 }  // namespace
 
 hipError_t launch_seed_bound(const DevIndex& ix, const DevBatch& qb, int32_t q0, int32_t qt, const Workspace& ws,
                              hipStream_t s, int tile_shift, int stride) {
-    hipLaunchKernelGGL(k_seed_bound, dim3(qt), dim3(64), 0, s, qb, q0, ix.n_docs, (const uint32_t*)ws.hist1,
-                       ws.state);
-    GS_CHECK_LAUNCH("k_seed_bound");
     const int64_t n_tiles = (ix.n_docs + (1ll << tile_shift) - 1) >> tile_shift;
     const int64_t seeds = (n_tiles + stride - 1) / stride;
-    hipLaunchKernelGGL(k_seed_hist, dim3((unsigned)seeds, (unsigned)qt), dim3(512), 0, s, ix.n_docs,
-                       (const uint32_t*)ws.scores, ws.ld, tile_shift, stride, (const SelState*)ws.state, ws.hist_ref);
-    GS_CHECK_LAUNCH("k_seed_hist");
-    hipLaunchKernelGGL(k_seed_refine, dim3(qt), dim3(64), 0, s, ws.hist_ref, ws.state);
-    GS_CHECK_LAUNCH("k_seed_refine");
+    hipLaunchKernelGGL(k_seed, dim3((unsigned)seeds, (unsigned)qt), dim3(kSelBS), 0, s, qb, q0, ix.n_docs,
+                       (const uint32_t*)ws.scores, ws.ld, tile_shift, stride, (const uint32_t*)ws.hist1, ws.state,
+                       ws.hist_ref);
+    GS_CHECK_LAUNCH("k_seed");
+    hipLaunchKernelGGL(k_seed_bound, dim3(qt), dim3(kSelBS), 0, s, qb, q0, ix.n_docs, ws.state,
+                       (const uint32_t*)ws.hist_ref);
+    GS_CHECK_LAUNCH("k_seed_bound");
     return hipSuccess;
 }
 
 hipError_t launch_select(const DevIndex& ix, const DevBatch& qb, int32_t q0, int32_t qt, const Workspace& ws,
                          int32_t* out_ids, void* out_scores, int32_t* diag, hipStream_t s, int acc, int tile_shift,
-                         int seed_stride, const ScoreOpts* phase3, bool wide) {
+                         int seed_stride, const ScoreOpts* phase3, bool wide, bool from_row) {
     const int64_t N = ix.n_docs;
-    const int per = 65536;
-    const dim3 grid_scan((unsigned)((N + per - 1) / per), (unsigned)qt);
-    const int wide_check = acc == kAccFixed ? 1 : 0;
-    hipLaunchKernelGGL(k_select_first, dim3(qt), dim3(64), 0, s, qb, q0, N, ix.precision, ws.hist1, ws.state,
-                       ws.counters, ws.rescore_list, 0, wide_check);
-    GS_CHECK_LAUNCH("k_select_first");
-    if (phase3 || wide) {  // rows (and counts) of the listed queries: fused fallback, wide range
-        hipError_t e = hipSuccess;
-        if (phase3) e = launch_score_tiled(ix, qb, q0, qt, *phase3, ws, s, 3);
-        if (e == hipSuccess && wide) e = launch_score_wide(ix, qb, q0, ws, s);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_select_first, dim3(qt), dim3(64), 0, s, qb, q0, N, ix.precision, ws.hist1, ws.state,
-                           ws.counters, ws.rescore_list, 1, 0);
-        GS_CHECK_LAUNCH("k_select_first");
-    }
     auto final_pass = [&]() -> hipError_t {
+        auto go = [&](auto pc, auto row) {
+            constexpr int P = decltype(pc)::value;
+            hipLaunchKernelGGL((k_final<P, decltype(row)::value>), dim3(qt), dim3(kSelBS), 0, s, ix, qb, q0, ws.state,
+                               (const unsigned long long*)ws.cand, (const uint32_t*)ws.scores, ws.ld, ws.band_id,
+                               out_ids, out_scores, acc, ws.counters, ws.rescore_list, diag);
+        };
+        using FP32 = std::integral_constant<int, kFP32>;
+        using BF16 = std::integral_constant<int, kBF16>;
+        using U8 = std::integral_constant<int, kU8>;
         switch (ix.precision) {
             case kFP32:
-                hipLaunchKernelGGL(k_final<kFP32>, dim3(qt), dim3(1024), 0, s, ix, qb, q0, ws.state,
-                                   (const unsigned long long*)ws.cand, ws.band_s, ws.band_id, out_ids, out_scores,
-                                   acc, ws.counters, ws.rescore_list);
+                if (from_row) go(FP32(), std::true_type()); else go(FP32(), std::false_type());
                 break;
             case kU8:
-                hipLaunchKernelGGL(k_final<kU8>, dim3(qt), dim3(1024), 0, s, ix, qb, q0, ws.state,
-                                   (const unsigned long long*)ws.cand, ws.band_s, ws.band_id, out_ids, out_scores,
-                                   acc, ws.counters, ws.rescore_list);
+                if (from_row) go(U8(), std::true_type()); else go(U8(), std::false_type());
                 break;
-            default:
-                hipLaunchKernelGGL(k_final<kBF16>, dim3(qt), dim3(1024), 0, s, ix, qb, q0, ws.state,
-                                   (const unsigned long long*)ws.cand, ws.band_s, ws.band_id, out_ids, out_scores,
-                                   acc, ws.counters, ws.rescore_list);
-                break;
+            default: go(BF16(), std::false_type()); break;
         }
         GS_CHECK_LAUNCH("k_final");
         return hipSuccess;
     };
-    if (N == 0) return final_pass();  // empty collection: padding only
-    for (int p = 0; p < kRefinePasses; p++) {
-        hipLaunchKernelGGL(k_refine_hist, dim3(8, (unsigned)qt), dim3(512), 0, s, q0, N, (const uint32_t*)ws.scores,
-                           ws.ld, (const SelState*)ws.state, ws.hist_ref);
-        GS_CHECK_LAUNCH("k_refine_hist");
-        hipLaunchKernelGGL(k_refine_select, dim3(qt), dim3(64), 0, s, qb, q0, N, ws.hist_ref, ws.state);
-        GS_CHECK_LAUNCH("k_refine_select");
+    // bf16: the band's rescoring and ranking (also the padding and the diagnostics)
+    auto band_pass = [&]() -> hipError_t {
+        // Workgroups per query: one document group each for a band of 1.25 k where the queries are
+        // few, more groups each (down to 8,192 workgroups in all) where they are many: a workgroup
+        // sets up its query's hash first (500 queries: 277 us at 64 workgroups each).
+        const int x = std::max(1, std::min({64, (qb.k_max + qb.k_max / 4 + 15) / 16, 8192 / std::max(qt, 1)}));
+        hipLaunchKernelGGL(k_rescore, dim3(x, (unsigned)qt), dim3(kRescoreBS), 0, s, ix, qb, q0,
+                           (const SelState*)ws.state, ws.band_s, (const int32_t*)ws.band_id);
+        GS_CHECK_LAUNCH("k_rescore");
+        hipLaunchKernelGGL(k_band_topk, dim3(qt), dim3(kSelBS), 0, s, ix, qb, q0, (const SelState*)ws.state,
+                           (const double*)ws.band_s, (const int32_t*)ws.band_id, out_ids, (double*)out_scores, diag);
+        GS_CHECK_LAUNCH("k_band_topk");
+        return hipSuccess;
+    };
+    if (N == 0) return ix.precision == kBF16 ? band_pass() : final_pass();  // empty collection: padding only
+    if (from_row) return final_pass();
+    // Rows are scanned by workgroups of 65536 documents, or fewer (down to 8192) where that
+    // leaves the chip idle: below 1024 workgroups (four per CU) the range per workgroup, not
+    // the memory, sets the scan's time (27 us at 200,000 documents x 4 queries).
+    int per = 65536;
+    while (per > 8192 && ((N + per - 1) / per) * qt < 1024) per >>= 1;
+    const dim3 grid_scan((unsigned)((N + per - 1) / per), (unsigned)qt);
+    const int wide_check = wide ? 1 : 0;
+    auto select = [&](int pass) -> hipError_t {
+        hipLaunchKernelGGL(k_select, dim3(qt), dim3(kSelBS), 0, s, qb, q0, N, ix.precision,
+                           (const uint32_t*)ws.scores, ws.ld, ws.hist1, ws.state, ws.counters, ws.rescore_list, pass,
+                           pass == 0 ? wide_check : 0, tile_shift, std::max(seed_stride, 1));
+        GS_CHECK_LAUNCH("k_select");
+        return hipSuccess;
+    };
+    hipError_t e = select(0);
+    if (e != hipSuccess) return e;
+    if (phase3 || wide) {  // rows (and counts) of the listed queries: fused fallback, wide range
+        if (phase3) e = launch_score_tiled(ix, qb, q0, qt, *phase3, ws, s, 3);
+        if (e == hipSuccess && wide) e = launch_score_wide(ix, qb, q0, ws, s);
+        if (e == hipSuccess) e = select(1);
+        if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(k_filter, grid_scan, dim3(512), 0, s, q0, N, (const uint32_t*)ws.scores, ws.ld, per, ws.state,
                        ws.cand, seed_stride > 0 ? tile_shift : 16, seed_stride);
     GS_CHECK_LAUNCH("k_filter");
-    hipError_t e = final_pass();
-    if (e != hipSuccess) return e;
-    if (ix.precision == kBF16) {
-        if (phase3) {  // fused queries whose band reaches below their candidates: the other tiles' rows
-            e = launch_score_tiled(ix, qb, q0, qt, *phase3, ws, s, 5);
-            if (e != hipSuccess) return e;
-        }
-        hipLaunchKernelGGL(k_band_filter, grid_scan, dim3(512), 0, s, q0, N, (const uint32_t*)ws.scores, ws.ld, per,
-                           ws.state, ws.band_id);
-        GS_CHECK_LAUNCH("k_band_filter");
-        hipLaunchKernelGGL(k_band_final, dim3(qt), dim3(1024), 0, s, ix, qb, q0, ws.state, ws.band_s, ws.band_id,
-                           out_ids, (double*)out_scores);
-        GS_CHECK_LAUNCH("k_band_final");
+    e = final_pass();
+    if (e != hipSuccess || ix.precision != kBF16) return e;
+    if (phase3) {  // fused queries whose band reaches below their candidates: the other tiles' rows
+        e = launch_score_tiled(ix, qb, q0, qt, *phase3, ws, s, 5);
+        if (e != hipSuccess) return e;
     }
-    if (diag) {
-        hipLaunchKernelGGL(k_diag, dim3((qt + 255) / 256), dim3(256), 0, s, q0, qt, (const SelState*)ws.state, diag);
-        GS_CHECK_LAUNCH("k_diag");
-    }
-    return hipSuccess;
+    hipLaunchKernelGGL(k_band_filter, grid_scan, dim3(512), 0, s, q0, N, (const uint32_t*)ws.scores, ws.ld, per,
+                       ws.state, ws.band_id);
+    GS_CHECK_LAUNCH("k_band_filter");
+    return band_pass();
 }
 
 }  // namespace gs
