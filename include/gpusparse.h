@@ -81,17 +81,18 @@ enum gs_build_flags {
 /* Scoring kernels (Sec. 5.2 term-parallel scatter-add; Sec. 5.3 document-parallel). */
 enum gs_kernel {
     GS_KERNEL_AUTO = 0,   /* library choice */
-    GS_KERNEL_TILED = 1,  /* term-parallel, per (query, doc tile): posting segments
+    GS_KERNEL_TILED = 1,  /* term-parallel, per (query, doc tile): the commonest terms summed
+                             from their rows, the other terms' posting segments
                              scatter-added into an LDS tile, one coalesced write per doc */
     GS_KERNEL_ATOMIC = 2, /* term-parallel, per (query, term, posting chunk): global
                              atomics into the score array (the paper's Sec. 5.2 form) */
     GS_KERNEL_DOCPAR = 3, /* document-parallel: per (query, doc) gather over the
                              forward rows, no atomics (Sec. 5.3); needs GS_KEEP_FORWARD */
-    GS_KERNEL_SHARED = 4, /* batched shared traversal: the TILED work items on a
-                             persistent grid, taken tile by tile (every query of a
-                             doc tile on one XCD, longest queries first), so a
-                             tile's posting segments are read from HBM once and
-                             from that XCD's L2 for the other queries holding them */
+    GS_KERNEL_SHARED = 4, /* batched shared traversal: the TILED work items taken tile by
+                             tile, an eighth of them on each XCD, so a tile's rows and
+                             posting segments are read from HBM once and from that XCD's
+                             L2 for the other queries holding them. TILED takes its items
+                             in the same order: the two are one kernel */
     GS_KERNEL_GROUP = 5   /* batched shared traversal with explicit sharing: per (doc tile
                              of 8192, group of 2 queries), the segments of
                              the union of the group's terms; each posting chunk is loaded
@@ -112,7 +113,8 @@ typedef struct gs_search_opts {
                             8192, 16384 or 32768 (32768: not for GS_FP32,
                             GS_EUNSUPPORTED) */
     int32_t chunk;       /* postings per work item (TILED/ATOMIC): 0 (default),
-                            64, 128, 256, 512 or 1024 */
+                            64, 128, 256, 512 or 1024 (TILED/SHARED read rows of 256
+                            postings: 64 and 128 run as 256) */
     int32_t no_fused_filter; /* TILED/SHARED, searches of 32+ queries: 0 (default)
                                 appends candidates while scoring (a bound from every
                                 8th doc tile, then only those tiles' scores are
@@ -141,9 +143,8 @@ typedef struct gs_index_info_t {
     uint32_t flags;       /* gs_build_flags in effect */
     int32_t tile_grain;   /* doc-tile granularity of the segment table (docs) */
     int64_t n_tiles;      /* tiles of tile_grain docs covering the collection */
-    int64_t n_dense_terms; /* terms whose every 64-posting block spans at most 256 docs:
-                              the doc-tiled kernels read their doc ids as one byte per
-                              posting (distance to the block's first doc) */
+    int64_t n_dense_terms; /* terms whose every 64-posting block spans at most 256 docs (their
+                              doc ids fit one byte: the distance to the block's first doc) */
 } gs_index_info_t;
 
 /* ------------------------------------------------------------------ misc -- */
@@ -179,10 +180,11 @@ int32_t gs_debug_fail_alloc(int64_t n);
  *  - per 64-posting block: the largest weight and the first doc id;
  *  - per term and per tile of tile_grain docs: the offset of the first
  *    posting at or after the tile start (segment table for doc-tiled kernels);
- *  - doc ids again as 16-bit values (doc id modulo 65536), and, for the lists
- *    whose every 64-posting block spans at most 256 docs ("dense" terms), as
- *    one byte per posting: the distance to the block's first doc. The
- *    doc-tiled kernels read 2 or 1 bytes per posting for the id instead of 4.
+ *  - doc ids again as 16-bit values (doc id modulo 65536): the doc-tiled
+ *    kernels read 2 bytes per posting for the id instead of 4;
+ *  - a row for each term held by at least a quarter of the documents: its
+ *    stored weight for every document, 0 where it lacks the term (at most
+ *    4 times the weight bytes of those terms' lists).
  * Synchronous: returns once the index is on the device.
  * Errors: GS_EINVAL (any check above, vocab_size < 1, n_docs < 0,
  *   n_docs >= 2^31, unknown precision or flag), GS_ENOMEM, GS_EHIP.
@@ -199,9 +201,7 @@ int32_t gs_index_info(gs_index index, gs_index_info_t* out);
 /*
  * Byte-form flags of the index's terms (see n_dense_terms): out [vocab_size]
  * (host, caller-owned) receives 1 for a term whose every 64-posting block spans at
- * most 256 docs, else 0. For measurement: the doc-tiled kernels with fp32 or bf16
- * weights read such a term's doc ids as 1 byte per posting plus one 4-byte block
- * base per 64 postings. Errors: GS_EINVAL (null argument, vocab_size differs from
+ * most 256 docs, else 0. Errors: GS_EINVAL (null argument, vocab_size differs from
  * the index's).
  */
 int32_t gs_index_dense_terms(gs_index index, uint8_t* out, int32_t vocab_size);

@@ -372,10 +372,10 @@ int32_t build_layout(const Rows& r, int32_t vocab, int32_t precision, bool tiles
 }
 
 // Byte form of the doc ids: a term whose every 64-posting block spans at most 256 docs
-// ("dense") also stores each id as its distance to the block's first doc.
-void byte_form(const Layout& L, std::vector<uint8_t>& dense, std::vector<uint8_t>& b8) {
+// ("dense") can store each id as its distance to the block's first doc (b8, optional).
+void byte_form(const Layout& L, std::vector<uint8_t>& dense, std::vector<uint8_t>* b8) {
     dense.assign((size_t)L.vocab, 0);
-    b8.assign((size_t)L.padded, 0);
+    if (b8) b8->assign((size_t)L.padded, 0);
     parallel_for(L.vocab, [&](int, int64_t a, int64_t b) {
         for (int64_t v = a; v < b; v++) {
             const int64_t o = L.term_off[(size_t)v];
@@ -388,8 +388,8 @@ void byte_form(const Layout& L, std::vector<uint8_t>& dense, std::vector<uint8_t
             }
             if (!ok) continue;
             dense[(size_t)v] = 1;
-            for (int64_t i = 0; i < len; i++)
-                b8[(size_t)(o + i)] = (uint8_t)(L.post_doc[(size_t)(o + i)] - L.blk_first[(size_t)((o + i) / kBlock)]);
+            for (int64_t i = 0; b8 && i < len; i++)
+                (*b8)[(size_t)(o + i)] = (uint8_t)(L.post_doc[(size_t)(o + i)] - L.blk_first[(size_t)((o + i) / kBlock)]);
         }
     });
 }
@@ -402,6 +402,8 @@ struct gs_index_s {
     int device = 0;
     int64_t n_docs = 0, nnz = 0, padded = 0, n_grains = 0;
     int64_t n_dense = 0;              // terms whose lists have the byte doc-id form
+    std::vector<int32_t> row_slot;    // [V] row of the term, or -1
+    int32_t n_rows = 0;               // terms with a row
     std::vector<uint8_t> term_dense;  // [V] host copy of the byte-form flags
     int32_t vocab = 0, precision = 0;
     uint32_t flags = 0;
@@ -421,8 +423,8 @@ struct gs_index_s {
 // whole on every update), then the per-term arrays (copied up to the terms in use).
 struct BatchLayout {
     size_t rp = 0, k = 0, fs = 0, delta = 0, scale = 0, err = 0, wide = 0, work = 0, diag = 0, head = 0;
-    size_t gcount = 0, gmember = 0, grow = 0, order = 0;
-    size_t term = 0, w = 0, w8 = 0, fx = 0, ubcum = 0, gterm = 0, gwfx = 0, gw8 = 0, total = 0;
+    size_t gcount = 0, gmember = 0, grow = 0, item = 0, order = 0;
+    size_t term = 0, w = 0, w8 = 0, fx = 0, ubcum = 0, gterm = 0, gwfx = 0, gw8 = 0, sterm = 0, total = 0;
     BatchLayout(size_t nq, size_t nz) {
         size_t at = 0;
         auto take = [&](size_t bytes) {
@@ -442,7 +444,8 @@ struct BatchLayout {
         gcount = take(4);
         gmember = take((nq + kGroupMax) * 4);
         grow = take((nq + 2) * 4);
-        order = take(nq * 4);
+        item = take(nq * sizeof(ScoreItem));
+        order = take(nq * sizeof(ScoreItem));
         head = at;
         term = take(nz * 4);
         w = take(nz * 4);
@@ -452,6 +455,7 @@ struct BatchLayout {
         gterm = take(nz * 4);
         gwfx = take(nz * kGroupMax * 4);
         gw8 = take(nz * kGroupMax * 4);
+        sterm = take(nz * sizeof(ScoreTerm));
         total = at;
     }
 };
@@ -494,6 +498,37 @@ int32_t dev_upload(std::vector<void*>& allocs, size_t& bytes, const T* host, siz
     if (host && copy) GS_HIP(hipMemcpyAsync(p, host, copy * sizeof(T), hipMemcpyHostToDevice, s));
     if (n > copy) GS_HIP(hipMemsetAsync((T*)p + copy, 0, (n - copy) * sizeof(T), s));
     *out = (T*)p;
+    return GS_OK;
+}
+
+// Rows of the commonest terms: chosen by list length, filled on the device from the lists.
+int32_t build_rows(gs_index ix, hipStream_t s) {
+    DevIndex& d = ix->dev;
+    std::vector<int32_t> terms;
+    try {
+        ix->row_slot.assign((size_t)ix->vocab, -1);
+        for (int32_t v = 0; v < ix->vocab; v++)
+            if (ix->term_len[(size_t)v] > 0 && (int64_t)ix->term_len[(size_t)v] * kRowShare >= ix->n_docs) terms.push_back(v);
+        std::stable_sort(terms.begin(), terms.end(), [&](int32_t a, int32_t b) {
+            return ix->term_len[(size_t)a] > ix->term_len[(size_t)b];
+        });
+    } catch (const std::bad_alloc&) {
+        return fail(GS_ENOMEM, "host memory for the row table");
+    }
+    const int64_t w = ix->precision == kFP32 ? 4 : ix->precision == kBF16 ? 2 : 1;
+    for (size_t i = 0; i < terms.size(); i++) ix->row_slot[(size_t)terms[i]] = (int32_t)i;
+    ix->n_rows = (int32_t)terms.size();
+    d.n_rows = ix->n_rows;
+    int32_t* pt = nullptr;
+    uint8_t* rows = nullptr;
+    int32_t rc = dev_upload(ix->allocs, ix->bytes, terms.data(), terms.size(), &pt, s);
+    if (rc == GS_OK)
+        rc = dev_upload(ix->allocs, ix->bytes, (const uint8_t*)nullptr, (size_t)((ix->n_grains * ix->n_rows) << kGrainShift) * (size_t)w, &rows, s);
+    if (rc != GS_OK) return rc;
+    d.rows = rows;
+    hipError_t e = launch_fill_rows(d, pt, rows, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);  // `terms` is read by the copy
+    if (e != hipSuccess) return fail(GS_EHIP, std::string("term rows: ") + hipGetErrorString(e));
     return GS_OK;
 }
 
@@ -575,7 +610,6 @@ size_t arena_bytes(int64_t n_docs, int64_t rows, int32_t precision) {
     }
     b += align256(R * (kMaxQueryNnz + 1) * 8);
     b += align256(R * kMaxQueryNnz * 4);
-    b += align256(R * 4);
     b += align256(kCounterWords * 4);
     b += align256(R * 4);
     return b;
@@ -603,7 +637,6 @@ void carve_rows(void* base, int64_t n_docs, int64_t rows, int32_t precision, int
     }
     ws->work_prefix = (int64_t*)take(R * (kMaxQueryNnz + 1) * 8) + o * (kMaxQueryNnz + 1);
     ws->work_pair_q = (int32_t*)take(R * kMaxQueryNnz * 4) + o * kMaxQueryNnz;
-    ws->order = (int32_t*)take(R * 4) + o;
     ws->counters = (uint32_t*)take(kCounterWords * 4);
     ws->rescore_list = (int32_t*)take(R * 4) + o;
 }
@@ -673,7 +706,7 @@ int32_t gs_layout_host(const int64_t* row_ptr, int64_t n_docs, const int32_t* te
     if (term_dense || post_b8) {
         std::vector<uint8_t> dense, b8;
         try {
-            byte_form(L, dense, b8);
+            byte_form(L, dense, &b8);
         } catch (const std::bad_alloc&) {
             return fail(GS_ENOMEM, "host memory for the byte doc offsets");
         }
@@ -811,30 +844,21 @@ int32_t gs_build_index(const int64_t* row_ptr, int64_t n_docs, const int32_t* te
     d.blk_first = blk_first;
     d.blk_max = blk_max;
     {
-        // Byte form of the doc ids: a term whose every 64-posting block spans at most 256 docs
-        // stores each id as its distance to the block's first doc.
-        std::vector<uint8_t> dense, b8;
+        // terms whose every 64-posting block spans at most 256 docs (reported by gs_index_info)
+        std::vector<uint8_t> dense;
         try {
-            byte_form(L, dense, b8);
+            byte_form(L, dense, nullptr);
         } catch (const std::bad_alloc&) {
-            return done(set_error(GS_ENOMEM, "host memory for the byte doc offsets"));
+            return done(set_error(GS_ENOMEM, "host memory for the byte-form flags"));
         }
-        uint8_t *pd = nullptr, *pb = nullptr;
-        if ((rc = dev_upload(ix->allocs, ix->bytes, dense.data(), dense.size(), &pd, s))) return done(rc);
-        // only the fp32 and bf16 kernels read the byte form; a uint8 index keeps a placeholder
-        const bool keep_b8 = precision != kU8;
-        if ((rc = dev_upload(ix->allocs, ix->bytes, keep_b8 ? b8.data() : nullptr, keep_b8 ? b8.size() : 0, &pb, s,
-                             keep_b8 ? kPostSlack : 0)))
-            return done(rc);
-        d.term_dense = pd;
-        d.post_b8 = pb;
         ix->n_dense = 0;
         for (int32_t v = 0; v < vocab_size; v++) ix->n_dense += dense[(size_t)v];
-        ix->term_dense = dense;
+        ix->term_dense = std::move(dense);
         // the uploads above are asynchronous: keep the host buffers until the stream is done
         hipError_t e = hipStreamSynchronize(s);
         if (e != hipSuccess) return done(fail(GS_EHIP, std::string("upload: ") + hipGetErrorString(e)));
     }
+    if ((rc = build_rows(ix, s))) return done(rc);
     if (flags & GS_KEEP_FORWARD) {
         int64_t* frp = nullptr;
         int32_t* ft = nullptr;
@@ -935,7 +959,9 @@ int32_t gs_batch_reserve(gs_index ix, int32_t max_queries, int64_t max_nnz, int3
     d.g_wq = (const float*)(m + L.gwfx);
     d.g_w8 = (const int32_t*)(m + L.gw8);
     d.q_work = (const int64_t*)(m + L.work);
-    d.q_order = (const int32_t*)(m + L.order);
+    d.s_term = (const ScoreTerm*)(m + L.sterm);
+    d.s_item = (const ScoreItem*)(m + L.item);
+    d.s_order = (const ScoreItem*)(m + L.order);
     b->diag = (int32_t*)(m + L.diag);
     // an empty batch until the first update: every slot is a query with no terms and k = 0
     std::vector<int64_t> zero_rp(nq + 1, 0);
@@ -991,6 +1017,9 @@ int32_t batch_update(gs_batch b, const int64_t* q_row_ptr, int32_t n_queries, co
         std::memcpy(h + L.term, r.term, (size_t)q_nnz * 4);
         std::memcpy(h + L.w, r.w, (size_t)q_nnz * 4);
     }
+    ScoreTerm* sterm = (ScoreTerm*)(h + L.sterm);
+    ScoreItem* item = (ScoreItem*)(h + L.item);
+    int64_t n_sterm = 0;
     std::vector<float> tmax, tmin;
     bool any_wide = false;
     for (int32_t q = 0; q < cap; q++) {
@@ -1019,6 +1048,25 @@ int32_t batch_update(gs_batch b, const int64_t* q_row_ptr, int32_t n_queries, co
         qwide[q] = fp.wide_lim;
         any_wide = any_wide || (fp.wide_lim > 0.0 && kk[q] > 0);
         for (int64_t j = rp[q]; j < rp[q + 1]; j++) qfx[j] = std::ldexp((double)r.w[j], fp.F);
+        // the scoring terms: those with rows first, by row
+        {
+            int32_t n = 0, n_row = 0;
+            for (int64_t j = rp[q]; j < rp[q + 1]; j++) {
+                const bool u8 = ix->precision == kU8;
+                if (!(u8 ? w8[j] > 0 : qfx[j] > 0.0)) continue;  // adds nothing
+                ScoreTerm t{r.term[j], ix->row_slot[(size_t)r.term[j]], 0};
+                if (u8) t.q = (unsigned long long)w8[j];
+                else std::memcpy(&t.q, &qfx[j], 8);
+                sterm[n_sterm + n++] = t;
+                n_row += t.row >= 0;
+            }
+            std::sort(sterm + n_sterm, sterm + n_sterm + n, [](const ScoreTerm& x, const ScoreTerm& y) {
+                if ((x.row >= 0) != (y.row >= 0)) return x.row >= 0;
+                return x.row >= 0 ? x.row < y.row : x.term < y.term;
+            });
+            item[q] = ScoreItem{n_sterm, q, kk[q] > 0 ? n | n_row << 10 : -1};
+            n_sterm += n;
+        }
         // Block-max pruning: each term's upper bound on its product with any doc (fixed-point
         // units: the largest stored weight times w_q 2^F, rounded up, plus one for the product's
         // rounding; uint8: the exact integer product), then per term the sum of the bounds of
@@ -1060,11 +1108,13 @@ int32_t batch_update(gs_batch b, const int64_t* q_row_ptr, int32_t n_queries, co
         for (int32_t q = 0; q < n_queries; q++)
             if (kk[q] > 0) ord.push_back(q);
         std::stable_sort(ord.begin(), ord.end(), [&](int32_t a, int32_t b) { return qwork[a] > qwork[b]; });
-        // the persistent kernel's order: these, then the queries with nothing to do
-        int32_t* order = (int32_t*)(h + L.order);
-        std::copy(ord.begin(), ord.end(), order);
-        for (int32_t q = 0, at = (int32_t)ord.size(); q < cap; q++)
-            if (kk[q] == 0) order[at++] = q;
+        // the doc-tiled kernel's order: these dealt into eight runs, then the queries with nothing to do
+        ScoreItem* order = (ScoreItem*)(h + L.order);
+        size_t at_item = 0;
+        for (size_t c = 0; c < 8; c++)
+            for (size_t i = c; i < ord.size(); i += 8) order[at_item++] = item[ord[i]];
+        for (int32_t q = 0; q < cap; q++)
+            if (kk[q] == 0) order[at_item++] = item[q];
         const int32_t ng = (int32_t)((ord.size() + G - 1) / G);
         *gcnt = ng;
         grow[0] = 0;
@@ -1108,6 +1158,7 @@ int32_t batch_update(gs_batch b, const int64_t* q_row_ptr, int32_t n_queries, co
     if (e == hipSuccess) e = up(L.gterm, (size_t)n_union * 4);
     if (e == hipSuccess) e = up(L.gwfx, (size_t)n_union * G * 4);
     if (e == hipSuccess) e = up(L.gw8, (size_t)n_union * G * 4);
+    if (e == hipSuccess) e = up(L.sterm, (size_t)n_sterm * sizeof(ScoreTerm));
     if (e == hipSuccess) e = hipEventRecord(b->copied, s);
     if (e == hipSuccess) {
         b->copy_pending = true;
@@ -1160,7 +1211,9 @@ static int32_t resolve_opts(gs_index ix, const gs_search_opts* o, ScoreOpts* so)
     so->kernel = GS_KERNEL_TILED;
     // 64 KiB of LDS accumulators: 8192 fixed-point (fp32, bf16) or 16384 int32 (uint8) documents
     so->tile_shift = ix->precision == kFP32 ? 13 : 14;
-    so->chunk = 1024;  // measured fastest for both doc-tiled forms at every tile size
+    // measured: 500 queries of 1M documents (fp32) 1.83 / 1.79 / 1.88 ms at 256 / 512 / 1024, of
+    // 500K (bf16) 1.01 / 0.96 / 0.98; 4,096 of 250K (uint8) 2.23 / 2.08 / 2.06
+    so->chunk = ix->precision == kU8 ? 1024 : 512;
     so->seed_stride = 1;  // fused filtering wanted (the stride itself is chosen per search)
     if (!o) return GS_OK;
     for (int i = 0; i < 2; i++)
@@ -1191,8 +1244,9 @@ static int32_t resolve_opts(gs_index ix, const gs_search_opts* o, ScoreOpts* so)
     }
     if (o->prune) {
         const int def_shift = ix->precision == kFP32 ? 13 : 14;
+        if (o->chunk == 0) so->chunk = kMaxChunk;  // the pruned tiles' form
         if (so->kernel != GS_KERNEL_TILED || ix->precision == kBF16 || so->tile_shift != def_shift ||
-            so->chunk != 1024)
+            so->chunk != kMaxChunk)
             return fail(GS_EUNSUPPORTED,
                         "pruning needs GS_KERNEL_TILED, fp32 or uint8 weights, the default tile and chunk 1024");
         so->prune = 1;
@@ -1298,8 +1352,8 @@ int32_t enqueue_search(gs_index ix, gs_batch b, int32_t nq, const Workspace& ws,
     g_failed_launch = "";
     for (int32_t q0 = 0; q0 < nq; q0 += qt) {
         const int32_t n = std::min(qt, nq - q0);
-        // the step counters: the shared-traversal kernels count with them in every form
-        hipError_t e = from_row && so.kernel == GS_KERNEL_TILED ? hipSuccess : launch_clear(ws, n, so.seed_stride > 0, s);
+        // with from_row only the group kernel needs what is cleared (its step counters)
+        hipError_t e = from_row && so.kernel != GS_KERNEL_GROUP ? hipSuccess : launch_clear(ws, n, so.seed_stride > 0, s);
         if (e == hipSuccess && ix->n_docs > 0) {
             const bool group = so.kernel == GS_KERNEL_GROUP;
             if (so.seed_stride == 0 || so.kernel == GS_KERNEL_ATOMIC || so.kernel == GS_KERNEL_DOCPAR) {

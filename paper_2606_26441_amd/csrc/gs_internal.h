@@ -22,6 +22,7 @@ constexpr int kMaxChunk = 1024;       // largest chunk of the doc-tiled kernels 
 // chunk's full-width loads stay inside the arrays (lanes past its end are masked).
 constexpr size_t kPostSlack = kMaxChunk;
 constexpr int kMaxK = 4096;           // GS_MAX_K
+constexpr int kRowShare = 4;          // a term in at least 1 / kRowShare of the documents has a row
 constexpr int kHistBits = 11;         // selection digit width (first digit fused into scoring)
 constexpr int kHistBins = 1 << kHistBits;
 constexpr int kCandCap = 32768;       // candidates kept per query by the filter pass
@@ -31,8 +32,8 @@ constexpr int kFirstShiftFloat = 52;  // first digit of a float key: bits 30..20
 // LDS words of a scoring workgroup's histogram: the bins, then the count of zero scores (padded to 16 bytes)
 constexpr int kHistLds = kHistBins + 4;
 // Step counters of a search (kCounterWords words, cleared at its start): [8 phase ..] per-XCD work
-// counters of the persistent kernels (the phases that follow one another use sets of their own, so
-// that none needs clearing between), [kCntListed] queries in rescore_list.
+// counters of the group kernel (each phase has a set of its own, so that none needs clearing
+// between), [kCntListed] queries in rescore_list.
 constexpr int kCntListed = 63;
 constexpr int kCounterWords = 64;
 __host__ __device__ constexpr int cnt_base(int phase) { return 8 * phase; }  // phases 0 .. 6
@@ -81,19 +82,33 @@ struct DevIndex {
     // size, lies inside one 65536-aligned range, so the doc-tiled kernels read 2 bytes per
     // posting for the id and recover the offset in the tile from the tile's base.
     const uint16_t* post_lo;
-    // Byte form of the doc ids of dense terms (every 64-posting block of the list spans at
-    // most 256 docs): post_b8[i] = doc(i) - blk_first[i / 64]. The doc-tiled kernels read
-    // these lists in whole blocks, 1 byte per posting for the id instead of 2.
-    const uint8_t* post_b8;    // [padded_nnz] (0 outside dense lists)
     const int32_t* blk_first;  // [padded_nnz / 64] doc of each block's first posting (-1 if empty)
     const float* blk_max;      // [padded_nnz / 64] largest stored weight of each block (as float)
-    const uint8_t* term_dense; // [V] 1 if the term's list has the byte form
     const void* post_w;        // [padded_nnz] float | bf16 bits (uint16) | uint8
     const int32_t* tile_off;   // [V][n_grains+1] posting offset (relative to the list start)
     int64_t n_grains;          // ceil(n_docs / 8192)
+    // Rows of the commonest terms (at least 1 / kRowShare of the documents): the stored weight of
+    // every document (0 where it lacks the term), so that the doc-tiled kernel sums these terms in
+    // registers instead of scatter-adding their postings. Rows by descending term_len.
+    const void* rows;          // [n_grains][n_rows][8192] float | bf16 bits | uint8 (order: k_fill_rows)
+    int32_t n_rows;
     const int64_t* fwd_row_ptr;  // [N+1] forward rows (sorted by term), or null
     const int32_t* fwd_term;
     const float* fwd_w;
+};
+
+// What the doc-tiled kernel reads of a query and of its terms, made at the batch update. A
+// query's scoring terms are those with a positive weight: first the ones with rows (by row, the
+// commonest first), then the others (ascending).
+struct ScoreTerm {
+    int32_t term;
+    int32_t row;           // row of the term, or -1
+    unsigned long long q;  // w_q * 2^F (fp64 bits), or the uint8 impact
+};
+struct ScoreItem {
+    int64_t start;  // the query's first scoring term
+    int32_t q;      // query
+    int32_t n;      // scoring terms | those with rows << 10; -1: k = 0
 };
 
 // A query batch on the device.
@@ -118,7 +133,11 @@ struct DevBatch {
     // scored again with fp64 accumulation; 0 when the bound holds for every positive score.
     const double* q_wide_lim;
     const int64_t* q_work;     // [n] postings of the query's terms (work estimate)
-    const int32_t* q_order;    // [n] queries by descending work, those with k = 0 last
+    const ScoreTerm* s_term;   // scoring terms of all queries
+    const ScoreItem* s_item;   // [n] by query
+    // [n] by descending work, those with k = 0 last, dealt into eight runs (ranks 0, 8, 16, ...,
+    // then 1, 9, ...): any run of consecutive entries holds heavy and light queries alike
+    const ScoreItem* s_order;
     // Block-max pruning (opt-in): per query term, the sum of the upper bounds of the query's
     // terms (w_q times the term's largest stored weight, in fixed-point units or as an exact
     // uint8 product) taken in ascending order of bound, up to and including this term.
@@ -170,7 +189,6 @@ struct Workspace {
     int32_t* band_id;             // [qt][kCandCap] (bf16)
     int64_t* work_prefix;         // [qt * kMaxQueryNnz + 1] (atomic kernel)
     int32_t* work_pair_q;         // [qt * kMaxQueryNnz]
-    int32_t* order;               // [qt] persistent kernel: query order within the tile
     uint32_t* counters;           // [kCounterWords] step counters
     int32_t* rescore_list;        // [qt] queries whose rows are scored again (SelState::rescore)
     int64_t ld;                   // row stride of the score arrays (n_docs rounded up to 64)
@@ -226,6 +244,8 @@ int32_t search_rows(struct ::gs_index_s* ix, struct ::gs_batch_s* b, void* arena
 const int32_t* batch_diag(const struct ::gs_batch_s* b);
 
 // ---- launchers (gs_score.hip) ----
+// Fill the rows (zeroed here) of `terms` [ix.n_rows] (device) from their posting lists.
+hipError_t launch_fill_rows(const DevIndex& ix, const int32_t* terms, void* rows, hipStream_t s);
 // counters, selection state and first-digit histograms; with seeds, the seed histograms too
 hipError_t launch_clear(const Workspace& ws, int32_t qt, bool seeds, hipStream_t s);
 hipError_t launch_score_tiled(const DevIndex& ix, const DevBatch& qb, int32_t q0, int32_t qt,

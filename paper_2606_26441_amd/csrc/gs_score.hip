@@ -3,17 +3,19 @@
 // (paper Sec. 4.1: the score decomposes into one scatter-add per query term).
 //
 // Forms:
-//  * k_score_tiled  - term-parallel, work = (query, doc tile). Each query term's
-//    posting list is doc-sorted, so the postings that fall into a doc tile are
-//    one contiguous segment (found in the per-term segment table). The
-//    workgroup streams every segment of its query through coalesced loads and
-//    scatter-adds w_q * w_d into an LDS copy of the tile with LDS atomics, then
-//    writes the tile once (coalesced) and builds the histogram of the first
-//    selection digit. No global atomics, no zeroing pass. This is the hybrid
-//    of scatter-add and on-chip accumulation listed as future work (1) in Sec. 8.
-//  * k_score_persistent - the same work items on a resident grid, taken tile by
-//    tile (all queries of a tile on one XCD while its postings sit in that L2):
-//    the shared traversal of a batch.
+//  * k_score_tiled  - term-parallel, work = (query, doc tile). The query's commonest
+//    terms are summed from rows that hold their weight for every document, in
+//    registers; each other term's posting list is doc-sorted, so the postings that
+//    fall into a doc tile are one contiguous segment (found in the per-term segment
+//    table), streamed through coalesced loads and scatter-added into an LDS copy of
+//    the tile with LDS atomics. The tile is then written once (coalesced) with the
+//    histogram of the first selection digit, or leaves its candidates. No global
+//    atomics on scores, no zeroing pass. This is the hybrid of scatter-add and
+//    on-chip accumulation listed as future work (1) in Sec. 8. Items run tile by
+//    tile, so that the queries of a batch share a tile's rows and postings in L2.
+//  * k_score_group - pairs of queries per item, each posting chunk loaded once.
+//  * k_score_pruned, k_score_listed - posting-only passes over a tile (score_tile):
+//    block-max pruning; the rows of fused filtering's fallbacks; the fp64 pass.
 //  * k_score_atomic - term-parallel, work = (query, term, chunk of postings);
 //    global atomic adds into a zeroed score array, as in the paper's Sec. 5.2
 //    kernel (one program per query term looping over posting chunks), with
@@ -26,9 +28,7 @@
 // per-query scale and summed exactly in 64-bit fixed point), bf16 (stored as the
 // upper 16 bits of the fp32 pattern; 32-bit fixed point, then fp64 rescoring of
 // the candidates) and uint8 impacts (int32 products and sums, exact). Doc ids are
-// read as 16-bit offsets, or, for dense terms in k_score_tiled with fp32 and bf16
-// weights, as one byte per posting from the 64-block's first doc. With fused
-// candidate filtering a search runs them in phases: the seed tiles, then the
+// read as 16-bit offsets. With fused candidate filtering a search runs them in phases: the seed tiles, then the
 // other tiles appending candidates at or above a bound while they flush, then a
 // pass that writes the rows of the queries that fell back (k_score_listed; see
 // gs_topk.hip).
@@ -38,6 +38,8 @@
 #include "gs_internal.h"
 
 namespace gs {
+
+static inline int64_t score_ld(int64_t n_docs) { return (n_docs + 63) / 64 * 64; }
 
 namespace {
 
@@ -83,6 +85,13 @@ __device__ __forceinline__ double uniform_f64(double v) {
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
+// Lane l's value (l uniform), in scalar registers.
+__device__ __forceinline__ unsigned long long read_lane64(unsigned long long v, int l) {
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), l);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
+    return ((unsigned long long)hi << 32) | lo;
+}
+
 __device__ __forceinline__ unsigned long long comp_key(uint32_t key, uint32_t id) {
     return ((unsigned long long)key << 32) | (unsigned long long)(~id);
 }
@@ -105,17 +114,13 @@ __device__ __forceinline__ T wave_sum(T v) {
 // rounded to the nearest integer (within half a unit of it). A product below half
 // a unit becomes 0; the selection's wide-range check covers the queries where
 // that could matter (their rows are summed again in fp64).
-__device__ __forceinline__ unsigned long long fx_product(double qd, uint32_t wbits) {
+__device__ __forceinline__ unsigned long long fx_bits(double qd, uint32_t wbits) {  // exponent bits 0x433 on top
     constexpr double kTwo52 = 4503599627370496.0;
     const double wd = (double)__uint_as_float(wbits);
-    return (unsigned long long)__double_as_longlong(__builtin_fma(qd, wd, kTwo52)) - 0x4330000000000000ull;
+    return (unsigned long long)__double_as_longlong(__builtin_fma(qd, wd, kTwo52));
 }
-
-__device__ __forceinline__ uint32_t stored_bits(const void* p, int64_t i, std::integral_constant<int, kFP32>) {
-    return ((const uint32_t*)p)[i];
-}
-__device__ __forceinline__ uint32_t stored_bits(const void* p, int64_t i, std::integral_constant<int, kBF16>) {
-    return (uint32_t)((const uint16_t*)p)[i] << 16;
+__device__ __forceinline__ unsigned long long fx_product(double qd, uint32_t wbits) {
+    return fx_bits(qd, wbits) & 0x000fffffffffffffull;
 }
 
 // Write a finished LDS tile to the score array (fp32 bits or int32) and add its
@@ -126,245 +131,69 @@ __device__ __forceinline__ uint32_t stored_bits(const void* p, int64_t i, std::i
 enum AccForm { kAccInt = 0, kAccFx32 = 1, kAccFx64 = 2, kAccF64 = 3 };
 
 // Fused candidate filtering: append the composites c >= bound of the lanes that
-// take one to the query's candidate buffer (one atomic per wavefront; hits are
-// rare once the bound is set). Past kFusedCap the query is flagged instead.
+// take one to the query's candidate buffer (one atomic per wavefront). Past kFusedCap
+// the query is flagged instead.
 __device__ __forceinline__ void append_candidates(bool take, unsigned long long c, SelState* st,
                                                   unsigned long long* C) {
     const unsigned long long m = __ballot(take);
     if (m == 0) return;
     const int lane = threadIdx.x & (kWave - 1);
-    const int leader = __ffsll((long long)__ballot(1)) - 1;
     int slot = 0;
-    if (lane == leader) {
+    if (lane == 0) {
         slot = atomicAdd(&st->n_cand, __popcll(m));
         if (slot + __popcll(m) > kFusedCap) st->fused_over = 1;
     }
-    slot = __shfl(slot, leader, kWave) + __popcll(m & ((1ull << lane) - 1ull));
+    slot = __shfl(slot, 0, kWave) + __popcll(m & ((1ull << lane) - 1ull));
     if (take && slot < kFusedCap) C[slot] = c;
 }
 
-// write: store the scores in the row; count: add the tile to the first-digit histogram (hist:
-// kHistLds words, zeroed by the caller) and its zero scores to the query's count of them.
-// Q: 0 for a plain tile (doc d in accumulator d); else a tile in quarters (doc d in
-// accumulator (d % 4) * Q + d / 4, Q = tile size / 4), as the four-postings-per-lane loads of
-// score_tile leave it.
-// stg (optional): 2 + BS / 64 LDS words (a base, unused, and a count per wavefront) and an LDS
-// stage of stage_cap entries. With it, a flush that appends stages its candidates, each
-// wavefront in its own slice with its count in a scalar register (no LDS round trip per hit),
-// and takes one range of the query's buffer for all of them at the end (one global atomic per
-// tile instead of one per wavefront and hit, whose round trips otherwise hold up the tile's
-// last wavefront); candidates past a wavefront's slice go to the buffer directly.
-// TD: the tile's size in docs (0: not known here). With it, the scan's read-ahead rounds stay
-// inside the tile by construction and are issued without a per-read guard.
-template <int BS, int AF, int Q = 0, int TD = 0>
-__device__ __forceinline__ void flush_tile(const void* acc_v, uint32_t* hist, int tile_n, int64_t base, uint32_t* Sq,
-                                           int fs, double scale, uint32_t* hist_out, bool append,
-                                           unsigned long long bound, SelState* st, unsigned long long* C,
-                                           bool write, bool count, int* stg = nullptr,
-                                           unsigned long long* stage = nullptr, int stage_cap = 0) {
-    const int tid = threadIdx.x;
-    const bool staged = stg != nullptr && append;
-    constexpr int NWF = BS / kWave;
-    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int per_w = stage_cap / NWF;
-    unsigned long long* my_stage = stage + wv * per_w;
-    // The wavefront's staged candidates. Lanes that leave a scan loop early keep an old value,
-    // so the count is always taken from the first active lane: every loop here keeps a prefix
-    // of the lanes active, so that is lane 0, which takes part in every append.
-    int w_cnt = 0;
-    auto put = [&](bool take, unsigned long long c) {
-        if (!staged) {
-            append_candidates(take, c, st, C);
-            return;
-        }
-        const unsigned long long m = __ballot(take);
-        if (m == 0) return;
-        const int wc = __builtin_amdgcn_readfirstlane(w_cnt);
-        const int slot = wc + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                                             __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-        if (take && slot < per_w) my_stage[slot] = c;
-        const int pc = __popcll(m);
-        if (wc + pc > per_w) append_candidates(take && slot >= per_w, c, st, C);  // past the slice
-        w_cnt = min(wc + pc, per_w);
-    };
-    auto drain = [&]() {
-        if (!staged) return;
-        const int wc = __builtin_amdgcn_readfirstlane(w_cnt);
-        if ((tid & (kWave - 1)) == 0) stg[2 + wv] = wc;
-        __syncthreads();
-        int n = 0, off = 0;
-#pragma unroll
-        for (int w = 0; w < NWF; w++) {
-            const int cw = stg[2 + w];
-            off += w < wv ? cw : 0;
-            n += cw;
-        }
-        if (n == 0) return;
-        if (tid == 0) {
-            const int b = atomicAdd(&st->n_cand, n);
-            if (b + n > kFusedCap) st->fused_over = 1;
-            stg[0] = b;
-        }
-        __syncthreads();
-        const int b = stg[0] + off;
-        for (int i = tid & (kWave - 1); i < wc; i += kWave)
-            if (b + i < kFusedCap) C[b + i] = my_stage[i];
-    };
-    const int n4 = tile_n >> 2;
-    auto at4 = [](int i, int j) { return Q ? j * Q + i : 4 * i + j; };   // doc 4 i + j
-    auto at = [](int d) { return Q ? (d & 3) * Q + (d >> 2) : d; };
-    if constexpr (AF == kAccFx64) {
-        if (!write && !count) {
-            // Only candidates matter (no row, no histogram). A doc whose float score
-            // float(acc * scale) reaches the bound's score s_b has acc * scale >= s_b (1 - 2^-24),
-            // and converting the sum to double loses at most 2^-53 more, so a sum below t_lo
-            // (taken with margin) cannot reach the bound: test the raw sums first and convert
-            // only where a wavefront holds a sum at or above t_lo.
-            if (!append) return;
-            const double sb = (double)__uint_as_float((uint32_t)(bound >> 32));
-            const unsigned long long t_lo = (unsigned long long)fmax(0.0, floor(sb * (1.0 - 0x1p-22) / scale));
-            const unsigned long long* acc = (const unsigned long long*)acc_v;
-            // two rounds of reads issued before the first test (one LDS round trip per two); in a
-            // tile of TD docs every round reads inside the tile (TD / 4 is a multiple of 2 BS), so
-            // the reads need no guard (rounds past a short last tile's end are not tested)
-            constexpr bool FULL = TD > 0 && (TD / 4) % (2 * BS) == 0;
-            constexpr int R = 2;
-            for (int i0 = tid; i0 < n4; i0 += R * BS) {
-                unsigned long long a[R][4];
-#pragma unroll
-                for (int h = 0; h < R; h++) {
-                    const int i = i0 + h * BS;
-#pragma unroll
-                    for (int j = 0; j < 4; j++) a[h][j] = (FULL || i < n4) ? acc[at4(i, j)] : 0ull;
-                }
-#pragma unroll
-                for (int h = 0; h < R; h++) {
-                    const int i = i0 + h * BS;
-                    const unsigned long long m01 = a[h][0] > a[h][1] ? a[h][0] : a[h][1];
-                    const unsigned long long m23 = a[h][2] > a[h][3] ? a[h][2] : a[h][3];
-                    if (!__ballot(i < n4 && (m01 > m23 ? m01 : m23) >= t_lo)) continue;
-                    const uint32_t d0 = (uint32_t)(base + 4 * i);
-#pragma unroll
-                    for (int j = 0; j < 4; j++) {
-                        const uint32_t v = __float_as_uint((float)((double)a[h][j] * scale));
-                        const unsigned long long c = comp_key(v, d0 + j);
-                        put(i < n4 && c >= bound, c);
-                    }
-                }
-            }
-            for (int i = (n4 << 2) + tid; i < tile_n; i += BS) {
-                const uint32_t v = __float_as_uint((float)((double)acc[at(i)] * scale));
-                const unsigned long long c = comp_key(v, (uint32_t)(base + i));
-                put(c >= bound, c);
-            }
-            drain();
-            return;
-        }
-    }
+// A document's score bits from its accumulator.
+template <int AF, typename T>
+__device__ __forceinline__ uint32_t score_bits(T acc, double scale) {
+    if constexpr (AF == kAccInt) return acc;
+    else if constexpr (AF == kAccF64) return __float_as_uint((float)acc);
+    else return __float_as_uint((float)((double)acc * scale));
+}
+
+template <int AF>
+using AccOf = std::conditional_t<AF == kAccFx64, unsigned long long, std::conditional_t<AF == kAccF64, double, uint32_t>>;
+
+// Write a finished LDS tile to its score row (write) and, with count, add it to the query's
+// first-digit histogram (hist: kHistLds words, zeroed by the caller) and its zero scores to the
+// query's count of them. The digit at fs (at least 32) lies in the composite key's score bits.
+template <int BS, int AF>
+__device__ __forceinline__ void flush_tile(const void* acc_v, uint32_t* hist, int tile_n, uint32_t* Sq, int fs,
+                                           double scale, uint32_t* hist_out, SelState* st, bool write, bool count) {
+    using T = AccOf<AF>;
+    const T* acc = reinterpret_cast<const T*>(acc_v);
+    const int tid = threadIdx.x, sh = fs - 32, n4 = tile_n >> 2;
     int zc = 0;  // counted zero scores of this thread
-    // docs 4 i .. 4 i + 3 with their scores v: row store, histogram, candidates
-    auto emit = [&](int i, const uint32_t* v) {
-        if (write) reinterpret_cast<uint4*>(Sq)[i] = make_uint4(v[0], v[1], v[2], v[3]);
-        const uint32_t d0 = (uint32_t)(base + 4 * i);
-        if (count) {
-#pragma unroll
-            for (int j = 0; j < 4; j++) {
-                atomicAdd(&hist[(comp_key(v[j], d0 + j) >> fs) & (kHistBins - 1)], 1u);
-                zc += v[j] == 0u;
-            }
-        }
-        // a composite reaches the bound only if its score bits reach the bound's: one test
-        // of the lane's largest score first, the exact per-document test only then
-        if (append && __ballot(max(max(v[0], v[1]), max(v[2], v[3])) >= (uint32_t)(bound >> 32))) {
-#pragma unroll
-            for (int j = 0; j < 4; j++) {
-                const unsigned long long c = comp_key(v[j], d0 + j);
-                put(c >= bound, c);
-            }
-        }
+    auto tally = [&](uint32_t v) {
+        atomicAdd(&hist[(v >> sh) & (kHistBins - 1)], 1u);
+        zc += v == 0u;
     };
-    int i_first = 0;
-    if constexpr (Q != 0 && (AF == kAccInt || AF == kAccFx32)) {
-        // a tile in quarters: 16 docs 16 g .. 16 g + 15 per lane, one 16-byte read from each
-        // quarter (word 4 g + m of quarter j is doc 16 g + 4 m + j); two rounds of reads issued
-        // before the first test where a tile's Q / 4 groups are a multiple of 2 BS, else one.
-        // Every round then reads inside the tile (no guard per read); a round past a short
-        // last tile's end is read but not tested.
-        const uint32_t* acc = (const uint32_t*)acc_v;
-        const int n16 = tile_n >> 4;
-        constexpr int IT = (Q / 4) % (2 * BS) == 0 ? 2 : 1;
-        for (int g0 = tid; g0 < n16; g0 += IT * BS) {
-            uint4 r[IT][4];
-#pragma unroll
-            for (int it = 0; it < IT; it++) {
-                const int g = g0 + it * BS;
-#pragma unroll
-                for (int j = 0; j < 4; j++) r[it][j] = *reinterpret_cast<const uint4*>(acc + j * Q + 4 * g);
-            }
-#pragma unroll
-            for (int it = 0; it < IT; it++) {
-                const int g = g0 + it * BS;
-                if (g >= n16) break;
-#pragma unroll
-                for (int m = 0; m < 4; m++) {
-                    uint32_t v[4];
-#pragma unroll
-                    for (int j = 0; j < 4; j++)
-                        v[j] = m == 0 ? r[it][j].x : m == 1 ? r[it][j].y : m == 2 ? r[it][j].z : r[it][j].w;
-                    if constexpr (AF == kAccFx32) {
-#pragma unroll
-                        for (int j = 0; j < 4; j++) v[j] = __float_as_uint((float)((double)v[j] * scale));
-                    }
-                    emit(4 * g + m, v);
-                }
-            }
-        }
-        i_first = n16 * 4;
-    }
-    for (int i = i_first + tid; i < n4; i += BS) {
-        uint32_t v[4];
-        if constexpr (AF == kAccFx64) {
-            const unsigned long long* acc = (const unsigned long long*)acc_v;
-#pragma unroll
-            for (int j = 0; j < 4; j++) v[j] = __float_as_uint((float)((double)acc[at4(i, j)] * scale));
-        } else if constexpr (AF == kAccF64) {
-            const double* acc = (const double*)acc_v;
-#pragma unroll
-            for (int j = 0; j < 4; j++) v[j] = __float_as_uint((float)acc[at4(i, j)]);
-        } else if constexpr (Q != 0) {
-            const uint32_t* acc = (const uint32_t*)acc_v;
-#pragma unroll
-            for (int j = 0; j < 4; j++) v[j] = acc[at4(i, j)];
-            if constexpr (AF == kAccFx32) {
-#pragma unroll
-                for (int j = 0; j < 4; j++) v[j] = __float_as_uint((float)((double)v[j] * scale));
-            }
+    for (int i = tid; i < n4; i += BS) {
+        T a[4];
+        if constexpr (sizeof(T) == 4) {
+            const uint4 u = reinterpret_cast<const uint4*>(acc)[i];
+            a[0] = u.x; a[1] = u.y; a[2] = u.z; a[3] = u.w;
         } else {
-            const uint4 u = reinterpret_cast<const uint4*>(acc_v)[i];
-            v[0] = u.x; v[1] = u.y; v[2] = u.z; v[3] = u.w;
-            if constexpr (AF == kAccFx32) {
 #pragma unroll
-                for (int j = 0; j < 4; j++) v[j] = __float_as_uint((float)((double)v[j] * scale));
-            }
+            for (int j = 0; j < 4; j++) a[j] = acc[4 * i + j];
         }
-        emit(i, v);
+        uint32_t v[4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) v[j] = score_bits<AF>(a[j], scale);
+        if (write) reinterpret_cast<uint4*>(Sq)[i] = make_uint4(v[0], v[1], v[2], v[3]);
+        if (count)
+#pragma unroll
+            for (int j = 0; j < 4; j++) tally(v[j]);
     }
     for (int i = (n4 << 2) + tid; i < tile_n; i += BS) {
-        uint32_t v;
-        const int ai = at(i);
-        if constexpr (AF == kAccFx64) v = __float_as_uint((float)((double)((const unsigned long long*)acc_v)[ai] * scale));
-        else if constexpr (AF == kAccF64) v = __float_as_uint((float)((const double*)acc_v)[ai]);
-        else if constexpr (AF == kAccFx32) v = __float_as_uint((float)((double)((const uint32_t*)acc_v)[ai] * scale));
-        else v = ((const uint32_t*)acc_v)[ai];
+        const uint32_t v = score_bits<AF>(acc[i], scale);
         if (write) Sq[i] = v;
-        const unsigned long long c = comp_key(v, (uint32_t)(base + i));
-        if (count) {
-            atomicAdd(&hist[(c >> fs) & (kHistBins - 1)], 1u);
-            zc += v == 0u;
-        }
-        if (append) put(c >= bound, c);
+        if (count) tally(v);
     }
-    drain();
     if (!count) return;
     zc = wave_sum(zc);
     if ((tid & (kWave - 1)) == 0 && zc) atomicAdd(&hist[kHistBins], (uint32_t)zc);
@@ -374,16 +203,92 @@ __device__ __forceinline__ void flush_tile(const void* acc_v, uint32_t* hist, in
     if (tid == 0 && hist[kHistBins]) atomicAdd(&st->zeros, (int)hist[kHistBins]);
 }
 
+// Append a finished LDS tile's composites at or above the query's bound to its candidates (no
+// row, no histogram). Few documents reach the bound (about 1 in 100), but nearly every
+// wavefront holds some, so no conversion or compaction is done per document: each thread marks
+// its documents whose raw sum can reach the bound in a bit mask (a compare and an add each),
+// then the wavefront takes one marked document per lane at a time: exact composite, exact test,
+// and a place in the wavefront's slice of an LDS stage (stage_cap entries for the workgroup),
+// which goes to the query's buffer as one range; candidates past the slice go there directly.
+// Converting every document of a wavefront with a hit took half of the kernel's vector
+// instructions (fp32).
+// Raw test: a document whose float score float(sum * scale) reaches the bound's score s_b has
+// sum * scale >= s_b (1 - 2^-24), and converting the sum to double loses at most 2^-53 more, so
+// a sum below t_lo (taken with margin) cannot reach it. A bound of score 0 takes zero-score
+// documents up to the bound's id only, so a tile past that id marks positive sums alone.
+template <int BS, int AF, int TILE>
+__device__ __forceinline__ void flush_candidates(const void* acc_v, int tile_n, int64_t base, double scale,
+                                                 unsigned long long bound, SelState* st, unsigned long long* C,
+                                                 unsigned long long* stage, int stage_cap) {
+    static_assert(AF != kAccF64, "integer sums");
+    using T = AccOf<AF>;
+    const T* acc = reinterpret_cast<const T*>(acc_v);
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), per_w = stage_cap / (BS / kWave);
+    unsigned long long* my_stage = stage + wv * per_w;
+    int w_cnt = 0;  // staged candidates of the wavefront (uniform)
+    T t_lo;
+    if constexpr (AF == kAccInt) {
+        t_lo = (uint32_t)(bound >> 32);
+    } else {
+        const double sb = (double)__uint_as_float((uint32_t)(bound >> 32));
+        const double t = fmax(0.0, floor(sb * (1.0 - 0x1p-22) / scale));
+        t_lo = AF == kAccFx64 ? (T)t : (T)fmin(t, 4294967295.0);
+    }
+    if (t_lo == 0 && base > (int64_t)(~(uint32_t)bound)) t_lo = 1;
+    constexpr int D = TILE / BS, DB = D < 32 ? D : 32;  // documents per thread, per mask
+#pragma unroll
+    for (int d0 = 0; d0 < D; d0 += DB) {
+        uint32_t mask = 0;  // bit DB - 1 - d: document d of this block
+#pragma unroll
+        for (int g = 0; g < DB / 4; g++) {
+            const int i = tid + (d0 / 4 + g) * BS;  // documents 4 i ..
+            T a[4];
+            if constexpr (sizeof(T) == 4) {
+                const uint4 u = reinterpret_cast<const uint4*>(acc)[i];
+                a[0] = u.x; a[1] = u.y; a[2] = u.z; a[3] = u.w;
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; j++) a[j] = acc[4 * i + j];
+            }
+#pragma unroll
+            for (int j = 0; j < 4; j++) mask = mask + mask + (a[j] >= t_lo ? 1u : 0u);
+        }
+        while (__ballot(mask != 0u)) {
+            const int d = DB - 1 - (31 - __clz((int)(mask | 1u)));  // this lane's next document
+            const bool has = mask != 0u;
+            if (has) mask &= ~(1u << (DB - 1 - d));
+            const int doc = 4 * (tid + ((d0 + d) >> 2) * BS) + (d & 3);
+            const unsigned long long c = comp_key(score_bits<AF>(acc[doc], scale), (uint32_t)(base + doc));
+            const bool take = has && doc < tile_n && c >= bound;
+            const unsigned long long m = __ballot(take);
+            if (m == 0) continue;
+            const int slot = w_cnt + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                                   __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+            if (take && slot < per_w) my_stage[slot] = c;
+            const int n = w_cnt + __popcll(m);
+            if (n > per_w) append_candidates(take && slot >= per_w, c, st, C);  // past the slice
+            w_cnt = min(n, per_w);
+        }
+    }
+    if (w_cnt == 0) return;
+    int b = 0;
+    if (lane == 0) {
+        b = atomicAdd(&st->n_cand, w_cnt);
+        if (b + w_cnt > kFusedCap) st->fused_over = 1;
+    }
+    b = __builtin_amdgcn_readfirstlane(b);
+    for (int i = lane; i < w_cnt; i += kWave)
+        if (b + i < kFusedCap) C[b + i] = my_stage[i];
+}
+
 // ------------------------------------------------------------- tiled --
 //
 // One workgroup per (query, doc tile of 2^TS docs). LDS holds the tile's
 // accumulators: unsigned fixed point for fp32 (64-bit) and bf16 (32-bit) weights
 // (LDS integer atomics run far faster than LDS float atomics on this GPU, and
 // integer sums do not depend on the order of the updates), int32 for uint8
-// impacts. Work inside
-// the workgroup: the query's posting segments for this tile are cut into chunks
-// of CH postings; wavefronts take chunks round-robin, each lane loads CH/64
-// postings (coalesced across the wavefront) before issuing its LDS adds.
+// impacts.
 
 // fp32 weights: 64-bit fixed point. Its error is absolute, (m+1) half-units of
 // 2^-F with 2^-F about 2^-51 of the query's largest product: far inside the 1e-5
@@ -412,23 +317,20 @@ constexpr int group_size() {
 // against the record count and returns 0 past it.
 constexpr int kRawBufferWord3 = 0x00020000;
 
-// Segments of a (query, tile) work item, dense terms first: a dense term's segment is
-// widened to whole 64-posting blocks (seg_edge = postings before | after the real
-// segment << 8), the others are exact.
+// Segments of a (query, tile) work item of score_tile.
 struct TileShared {
     int64_t seg_beg[kMaxQueryNnz];
     int32_t seg_len[kMaxQueryNnz];
     int32_t seg_cpre[kMaxQueryNnz + 1];
     double seg_qd[kMaxQueryNnz];   // w_q * 2^F (fixed point)
     uint32_t seg_q8[kMaxQueryNnz]; // uint8 query impact
-    uint16_t seg_edge[kMaxQueryNnz];
-    unsigned long long dmask[kMaxQueryNnz / kWave];  // dense terms per wavefront of the setup
+    uint16_t seg_edge[kMaxQueryNnz];  // whole blocks: postings before | after the real segment << 8
+    unsigned long long dmask[kMaxQueryNnz / kWave];  // (PR) essential terms per wavefront of the setup
     unsigned long long wmax[kMaxQueryNnz / kWave];   // pruning: largest bound sum per wavefront
     // what the flush needs of the query (its selection state and histogram scaling)
     unsigned long long fl_bound;
     double fl_scale;
     int fl_fused, fl_over, fl_shift;
-    int stg[2 + 512 / kWave];  // the flush's candidate stage: base, unused, a count per wavefront
 };
 static_assert(kMaxQueryNnz <= 512 && kMaxQueryNnz % kWave == 0, "segment setup: one thread per query term");
 
@@ -462,13 +364,11 @@ __device__ __forceinline__ void chunk_at(const TileShared& sh, const uint8_t* ta
 
 // Score one (query, doc tile) work item into LDS and flush it. Every thread of
 // the workgroup calls this; it ends after the flush (callers that loop must
-// synchronise before reusing the LDS). DB: read the byte doc ids of dense terms.
-// That saves HBM bytes but adds scalar work and a second chunk loop per item, so
-// it pays only where the kernel waits on HBM (the per-query kernel with fp32 or
-// bf16 weights), not where it is bound by instruction issue (shared traversal,
-// uint8 weights). W: the wide-range pass (fp64 products w_q * w_d, fp64 sums).
+// synchronise before reusing the LDS). This is the form of the passes that score_item does
+// not serve: W: the wide-range pass (fp64 products w_q * w_d, fp64 sums); the listed queries'
+// rows; and
 // PR: block-max pruning (MaxScore over 64-posting blocks) in the non-seed tiles of a query
-// with a seed bound, for fp32 and uint8 weights (no byte doc ids, DB false). The query's
+// with a seed bound, for fp32 and uint8 weights. The query's
 // terms with the smallest bounds w_q * maxw, as long as their bounds sum to less than the
 // bound's raw score t_lo, are non-essential: no doc that holds none of the others can be a
 // candidate. The essential terms are scored first; then each 64-doc group of the tile gets
@@ -476,15 +376,7 @@ __device__ __forceinline__ void chunk_at(const TileShared& sh, const uint8_t* ta
 // when every doc it can hold has partial sum + the non-essential bounds' sum below t_lo. A
 // doc of a skipped block can then not reach the bound, so it is no candidate, and every
 // candidate's sum is complete: the result is exact.
-// QD: the 2-byte-id segments are read four postings per lane: one 8-byte load of ids and
-// one load of four weights (4, 8 or 16 bytes) cover a lane's postings 4l .. 4l + 3 of each
-// 256 postings of the chunk, a quarter of the vector memory instructions of one posting per
-// lane and load (those instructions, not HBM or the LDS, bound the shared traversal). Segment
-// starts are rounded down to a multiple of 4 (the postings before the real start are
-// masked). So that the 64 lanes of an add still touch consecutive LDS words where doc ids run
-// consecutively, the tile is kept in quarters: doc x of the tile is accumulator
-// (x % 4) * TILE / 4 + x / 4 (flush_tile reads it back in doc order).
-template <int P, int TS, int CH, bool DB, bool W = false, bool PR = false, bool QD = false>
+template <int P, int TS, int CH, bool W = false, bool PR = false>
 __device__ __forceinline__ void score_tile(const DevIndex& ix, const DevBatch& qb, int32_t q0, int64_t tile, int ql,
                                            uint32_t* __restrict__ S, int64_t ld, uint32_t* __restrict__ hist1,
                                            uint32_t* lds, TileShared& sh, int phase, SelState* state,
@@ -531,8 +423,6 @@ __device__ __forceinline__ void score_tile(const DevIndex& ix, const DevBatch& q
     const int nq = (int)(qb.q_row_ptr[q + 1] - qa);
     const int64_t g0 = tile << GPT;
     const int64_t g1 = min(g0 + (int64_t)(1 << GPT), ix.n_grains);
-    static_assert(!(PR && DB), "pruning reads 2-byte doc ids");
-    static_assert(!QD || (!PR && !W && CH % 256 == 0), "quad loads: chunks of 256-posting rows");
     static_assert(!PR || (P != kBF16 && !W), "pruning: fp32 and uint8 fixed-point or integer sums");
     // Pruning applies to the non-seed tiles of a query whose seed bound is set; t_lo is the
     // bound's score as a raw sum (no sum below it can give a candidate, see flush_tile).
@@ -547,32 +437,29 @@ __device__ __forceinline__ void score_tile(const DevIndex& ix, const DevBatch& q
             prune_item = t_lo > 0;
         }
     }
-    // One thread per query term. Dense terms take the first segment slots (in query
-    // order), so their chunks come first and run in the byte-offset loop. With pruning the
-    // essential terms come first (exact segments) and the non-essential ones after them
-    // (whole 64-posting blocks, each skipped or read).
+    // One thread per query term. With pruning the essential terms come first (exact segments)
+    // and the non-essential ones after them (whole 64-posting blocks, each skipped or read).
     const int t = tid;
     const bool live = t < nq;
     int term = 0, a = 0, b = 0;
-    bool dense = false;  // first loop: byte doc ids (DB), or the essential terms (PR)
+    bool first = false;  // (PR) an essential term
     unsigned long long ub_cum = 0;
     if (live) {
         term = qb.q_term[qa + t];
         const int32_t* row = ix.tile_off + (int64_t)term * (ix.n_grains + 1);
         a = row[g0];
         b = row[g1];
-        dense = DB && ix.term_dense[term] != 0 && b > a;
         if constexpr (PR) {
             ub_cum = qb.q_ub_cum[qa + t];
-            dense = !prune_item || !(ub_cum < t_lo);
+            first = !prune_item || !(ub_cum < t_lo);
         }
     }
     if (t < kMaxQueryNnz) {
-        const unsigned long long m = __ballot(live && dense);
+        const unsigned long long m = __ballot(live && first);
         if (lane == 0) sh.dmask[wave] = m;
         if constexpr (PR) {
             // the bound sum of the non-essential terms: the largest cumulative bound among them
-            unsigned long long v = (live && !dense) ? ub_cum : 0ull;
+            unsigned long long v = (live && !first) ? ub_cum : 0ull;
 #pragma unroll
             for (int d = 32; d >= 1; d >>= 1) {
                 const unsigned long long o = __shfl_xor(v, d, kWave);
@@ -591,7 +478,7 @@ __device__ __forceinline__ void score_tile(const DevIndex& ix, const DevBatch& q
             if (w < wave) before += pc;
         }
         before += __popcll(sh.dmask[wave] & ((1ull << lane) - 1ull));
-        const int slot = dense ? before : nd + (t - before);
+        const int slot = first ? before : nd + (t - before);
         bool zero_weight;
         if constexpr (FX) {
             const double qd = W ? (double)qb.q_w[qa + t] : qb.q_fx[qa + t];
@@ -603,12 +490,7 @@ __device__ __forceinline__ void score_tile(const DevIndex& ix, const DevBatch& q
             zero_weight = q8 == 0u;
         }
         int beg = a, len = b - a, edge = 0;
-        if constexpr (QD) {  // quads: the segment starts at a multiple of 4, edge postings masked
-            beg = a & ~3;
-            len = b - beg;
-            edge = a - beg;
-        }
-        if (PR ? (!dense && b > a) : dense) {  // whole blocks: lists start 64-aligned and are padded to 64
+        if (PR && !first && b > a) {  // whole blocks: lists start 64-aligned and are padded to 64
             beg = a & ~(kBlock - 1);
             const int end = (b + kBlock - 1) & ~(kBlock - 1);
             len = end - beg;
@@ -669,18 +551,15 @@ __device__ __forceinline__ void score_tile(const DevIndex& ix, const DevBatch& q
     const int total = sh.seg_cpre[nq];
     const uint8_t* tab = total <= kHistBins * 4 ? reinterpret_cast<const uint8_t*>(hist) : nullptr;
     struct Chunk {
-        uint32_t doc[U];  // doc id modulo 65536, or (dense) distance to the block's first doc
+        uint32_t doc[U];  // doc id modulo 65536
         uint32_t w[U];    // stored weight as fp32 bits, or the uint8 impact
-        int32_t blk;      // (dense) lane u < U: first doc of the chunk's block u
         int seg, n, lo;   // postings [lo, n) of the chunk are the segment's (lo > 0: first slot only)
         uint32_t skip;    // (pruned blocks) bit u: block u of the chunk is skipped
-        int32_t bq[CH >= 256 ? CH / 256 : 1];  // (quad loads, dense) the block base of the lane's quad q
     };
-    // Chunk forms: 0 exact segment, 2-byte ids; 1 dense term, whole blocks, 1-byte ids;
-    // 2 non-essential term under pruning, whole blocks, 2-byte ids, skipped blocks not read.
-    using FExact = std::integral_constant<int, 0>;
-    using FDense = std::integral_constant<int, 1>;
-    using FPrune = std::integral_constant<int, 2>;
+    // Chunk forms: exact segment; non-essential term under pruning (whole blocks, skipped ones
+    // not read).
+    using FExact = std::integral_constant<bool, false>;
+    using FPrune = std::integral_constant<bool, true>;
     // pruning: per 64-doc group of the tile, the largest sum of the essential terms (in the
     // histogram area's last 2 KiB, which the chunk table leaves free for pruned items)
     unsigned long long* gmax = reinterpret_cast<unsigned long long*>(hist) + (kHistBins / 2 - 256);
@@ -692,91 +571,14 @@ __device__ __forceinline__ void score_tile(const DevIndex& ix, const DevBatch& q
     // reads nothing (record count 0). The chunk's base is wave-uniform (a buffer
     // descriptor in scalar registers), so no address arithmetic is done per posting.
     // The chunk lookup is branch-free with the chunk table (an invalid slot looks up
-    // chunk 0 and gets length 0). A dense chunk covers whole blocks: it reads 1-byte
-    // distances, plus one block base per 64 postings.
+    // chunk 0 and gets length 0).
     auto load = [&](auto use_tab, auto form, int c, Chunk& k, bool valid) {
-        constexpr bool DENSE = decltype(form)::value == 1;
-        constexpr bool PRUNED = decltype(form)::value == 2;
+        constexpr bool PRUNED = decltype(form)::value;
         int64_t p0 = 0;
         int n = 0, off = 0;
         chunk_at<decltype(use_tab)::value>(sh, tab, nq, valid ? c : 0, CH, &k.seg, &p0, &n, &off);
         k.skip = 0u;
-        if constexpr (QD && DENSE) {
-            // whole 64-posting blocks (p0 and n multiples of 64): four 1-byte ids per lane and load,
-            // the block base of each of the lane's quads (block 4 q + lane / 16 of the chunk), and
-            // the weights as for the 2-byte form below
-            const int edge = __builtin_amdgcn_readfirstlane((int)sh.seg_edge[k.seg]);
-            const int real_end = sh.seg_len[k.seg] - (edge >> 8) - off;
-            k.lo = off == 0 ? (edge & 0xFF) : 0;
-            k.n = valid ? min(n, real_end) : 0;
-            const int nrec = valid ? n : 0;
-            const __amdgpu_buffer_rsrc_t rid = __builtin_amdgcn_make_buffer_rsrc(
-                const_cast<uint8_t*>(ix.post_b8 + p0), (short)0, nrec, kRawBufferWord3);
-            const __amdgpu_buffer_rsrc_t rbk = __builtin_amdgcn_make_buffer_rsrc(
-                const_cast<int32_t*>(ix.blk_first + (p0 >> 6)), (short)0, (nrec >> 6) * 4, kRawBufferWord3);
-            const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
-                const_cast<WT*>(reinterpret_cast<const WT*>(ix.post_w) + p0), (short)0, nrec * (int)sizeof(WT),
-                kRawBufferWord3);
-            const int z = (int)((uint64_t)p0 >> 48);  // 0, keeps one lane offset per chunk
-            const int vid = lane * 4 + z;
-            const int vbk = (lane >> 4) * 4 + z;
-            const int vw = lane * 4 * (int)sizeof(WT) + z;
-#pragma unroll
-            for (int q = 0; q < CH / 256; q++) {
-                k.doc[q] = __builtin_amdgcn_raw_buffer_load_b32(rid, vid + q * 256, 0, 0);
-                k.bq[q] = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rbk, vbk + q * 16, 0, 0);
-                if constexpr (sizeof(WT) == 1) {
-                    k.w[q] = __builtin_amdgcn_raw_buffer_load_b32(rw, vw + q * 256, 0, 0);
-                } else if constexpr (sizeof(WT) == 2) {
-                    const auto w = __builtin_amdgcn_raw_buffer_load_b64(rw, vw + q * 512, 0, 0);
-                    k.w[2 * q] = w[0];
-                    k.w[2 * q + 1] = w[1];
-                } else {
-                    const auto w = __builtin_amdgcn_raw_buffer_load_b128(rw, vw + q * 1024, 0, 0);
-                    k.w[4 * q] = w[0];
-                    k.w[4 * q + 1] = w[1];
-                    k.w[4 * q + 2] = w[2];
-                    k.w[4 * q + 3] = w[3];
-                }
-            }
-            return;
-        }
-        if constexpr (QD && !DENSE && !PRUNED) {
-            // p0 is a multiple of 4: ids as 8-byte loads, weights as 4-, 8- or 16-byte loads, both
-            // covering whole quads (up to 3 postings past the segment, inside the padded list)
-            k.lo = off == 0 ? __builtin_amdgcn_readfirstlane((int)sh.seg_edge[k.seg]) : 0;
-            k.n = valid ? n : 0;
-            const int nrec = valid ? (n + 3) & ~3 : 0;
-            const __amdgpu_buffer_rsrc_t rid = __builtin_amdgcn_make_buffer_rsrc(
-                const_cast<uint16_t*>(ix.post_lo + p0), (short)0, nrec * 2, kRawBufferWord3);
-            const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
-                const_cast<WT*>(reinterpret_cast<const WT*>(ix.post_w) + p0), (short)0, nrec * (int)sizeof(WT),
-                kRawBufferWord3);
-            const int z = (int)((uint64_t)p0 >> 48);  // 0, keeps one lane offset per chunk (as below)
-            const int vid = lane * 8 + z;
-            const int vw = lane * 4 * (int)sizeof(WT) + z;
-#pragma unroll
-            for (int q = 0; q < CH / 256; q++) {
-                const auto d = __builtin_amdgcn_raw_buffer_load_b64(rid, vid + q * 512, 0, 0);
-                k.doc[2 * q] = d[0];
-                k.doc[2 * q + 1] = d[1];
-                if constexpr (sizeof(WT) == 1) {
-                    k.w[q] = __builtin_amdgcn_raw_buffer_load_b32(rw, vw + q * 256, 0, 0);
-                } else if constexpr (sizeof(WT) == 2) {
-                    const auto w = __builtin_amdgcn_raw_buffer_load_b64(rw, vw + q * 512, 0, 0);
-                    k.w[2 * q] = w[0];
-                    k.w[2 * q + 1] = w[1];
-                } else {
-                    const auto w = __builtin_amdgcn_raw_buffer_load_b128(rw, vw + q * 1024, 0, 0);
-                    k.w[4 * q] = w[0];
-                    k.w[4 * q + 1] = w[1];
-                    k.w[4 * q + 2] = w[2];
-                    k.w[4 * q + 3] = w[3];
-                }
-            }
-            return;
-        }
-        if constexpr (DENSE || PRUNED) {
+        if constexpr (PRUNED) {
             const int edge = __builtin_amdgcn_readfirstlane((int)sh.seg_edge[k.seg]);
             const int real_end = sh.seg_len[k.seg] - (edge >> 8) - off;
             k.lo = off == 0 ? (edge & 0xFF) : 0;
@@ -786,11 +588,6 @@ __device__ __forceinline__ void score_tile(const DevIndex& ix, const DevBatch& q
             k.n = valid ? n : 0;
         }
         const int nblk = (n + kBlock - 1) >> 6;
-        if constexpr (DENSE) {
-            // one register for the chunk's block bases (lane u holds block u); a slot takes
-            // its base with a lane read, which keeps scalar registers free
-            k.blk = ix.blk_first[(p0 >> 6) + min(lane, max(nblk - 1, 0))];
-        }
         if constexpr (PRUNED) {
             // lane u < nblk decides block u: the docs it can hold are [its first doc, the next
             // block's first doc) inside the segment, the tile's end for the segment's last
@@ -814,24 +611,23 @@ __device__ __forceinline__ void score_tile(const DevIndex& ix, const DevBatch& q
         // so lanes past its end read 0 without a clamp, and slot u's offset is the
         // instruction's immediate (one lane-offset register per chunk).
         const int nrec = valid ? n : 0;
-        const void* lb = DENSE ? static_cast<const void*>(ix.post_b8 + p0) : static_cast<const void*>(ix.post_lo + p0);
+        const void* lb = static_cast<const void*>(ix.post_lo + p0);
         // a skipped block's lanes get an offset past the record count: the hardware reads nothing
         auto far = [&](int u) { return PRUNED && ((k.skip >> u) & 1u) ? (1 << 30) : 0; };
         const void* wb = static_cast<const void*>(reinterpret_cast<const WT*>(ix.post_w) + p0);
         const __amdgpu_buffer_rsrc_t rid =
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(lb), (short)0, nrec * (DENSE ? 1 : 2), kRawBufferWord3);
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(lb), (short)0, nrec * 2, kRawBufferWord3);
         const __amdgpu_buffer_rsrc_t rw =
             __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(wb), (short)0, nrec * (int)sizeof(WT), kRawBufferWord3);
         // z is 0 (posting offsets stay far below 2^48) but not a loop invariant, so the
         // compiler keeps one lane offset per chunk and each slot's offset in the
         // instruction, instead of holding a register per slot across the loop.
         const int z = (int)((uint64_t)p0 >> 48);
-        const int vid = (lane << (DENSE ? 0 : 1)) + z;
+        const int vid = (lane << 1) + z;
         const int vw = lane * (int)sizeof(WT) + z;
 #pragma unroll
         for (int u = 0; u < U; u++) {
-            if constexpr (DENSE) k.doc[u] = __builtin_amdgcn_raw_buffer_load_b8(rid, vid + u * kWave, 0, 0);
-            else k.doc[u] = __builtin_amdgcn_raw_buffer_load_b16(rid, vid + far(u) + u * kWave * 2, 0, 0);
+            k.doc[u] = __builtin_amdgcn_raw_buffer_load_b16(rid, vid + far(u) + u * kWave * 2, 0, 0);
             uint32_t wv;
             if constexpr (sizeof(WT) == 4) wv = __builtin_amdgcn_raw_buffer_load_b32(rw, vw + far(u) + u * kWave * 4, 0, 0);
             else if constexpr (sizeof(WT) == 2) wv = __builtin_amdgcn_raw_buffer_load_b16(rw, vw + far(u) + u * kWave * 2, 0, 0);
@@ -839,109 +635,42 @@ __device__ __forceinline__ void score_tile(const DevIndex& ix, const DevBatch& q
             k.w[u] = P == kBF16 ? wv << 16 : wv;
         }
     };
-    // Accumulator of slot u: exact segments index by doc id modulo 65536 (the tile's offset
-    // folded into the base); dense ones by the distance plus the block's first doc relative
-    // to the tile (a scalar per slot).
+    // Accumulators indexed by doc id modulo 65536: the tile's offset folded into the base.
     unsigned long long* acc64f = acc64 - lbase;
     uint32_t* acc32f = acc32 - lbase;
     // A full chunk (every lane holds a posting in every slot) adds without the
-    // per-posting predicate; a segment's first (dense) and last chunks are predicated.
+    // per-posting predicate; a segment's first (whole blocks) and last chunks are predicated.
     auto apply = [&](auto form, const Chunk& k) {
-        constexpr bool DENSE = decltype(form)::value == 1;
-        constexpr bool PRUNED = decltype(form)::value == 2;
-        // slot u's accumulator: the uniform part (block base) goes into the pointer, so each
-        // lane adds only its scaled offset
-        auto at = [&](auto* acc, int u) {
-            if constexpr (DENSE) return (acc + (__builtin_amdgcn_readlane(k.blk, u) - tbase)) + k.doc[u];
-            else return acc + k.doc[u];
-        };
+        constexpr bool PRUNED = decltype(form)::value;
         auto add = [&](auto pred) {
             constexpr bool PRED = decltype(pred)::value;
-            if constexpr (QD && !PRUNED) {
-                // posting q * 256 + 4 lane + j of the chunk; its quarter-tile accumulator. 2-byte
-                // ids: relative to acc - lbase / 4 (lbase is a multiple of 4, so d16 % 4 is the tile
-                // doc's). 1-byte ids (dense): the quad's block base minus the tile base, plus the id.
-                auto okq = [&](int q, int j) {
-                    const int idx = q * 256 + lane * 4 + j;
-                    return !PRED || (idx >= k.lo && idx < k.n);
-                };
-                auto slot = [&](int q, int j) -> uint32_t {
-                    if constexpr (DENSE) {
-                        const uint32_t x = (uint32_t)(k.bq[q] - tbase) + ((k.doc[q] >> (8 * j)) & 0xffu);
-                        return ((x & 3u) << (TS - 2)) + (x >> 2);
-                    } else {
-                        const uint32_t dw = k.doc[2 * q + (j >> 1)];
-                        const uint32_t d16 = (j & 1) ? (dw >> 16) : (dw & 0xffffu);
-                        return ((d16 & 3u) << (TS - 2)) + (d16 >> 2);
-                    }
-                };
-                auto wbits = [&](int q, int j) -> uint32_t {  // stored weight (fp32 bits or uint8)
-                    if constexpr (sizeof(WT) == 1) {
-                        return (k.w[q] >> (8 * j)) & 0xffu;
-                    } else if constexpr (sizeof(WT) == 2) {
-                        const uint32_t h = k.w[2 * q + (j >> 1)];
-                        return ((j & 1) ? (h >> 16) : (h & 0xffffu)) << 16;
-                    } else {
-                        return k.w[4 * q + j];
-                    }
-                };
-                if constexpr (AF == kAccFx64) {
-                    unsigned long long* acc = DENSE ? acc64 : acc64 - (lbase >> 2);
-                    const double qd = uniform_f64(sh.seg_qd[k.seg]);
-#pragma unroll
-                    for (int q = 0; q < CH / 256; q++)
-#pragma unroll
-                        for (int j = 0; j < 4; j++)
-                            if (okq(q, j)) atomicAdd(acc + slot(q, j), fx_product(qd, wbits(q, j)));
-                } else if constexpr (AF == kAccFx32) {
-                    uint32_t* acc = DENSE ? acc32 : acc32 - (lbase >> 2);
-                    const double qd = uniform_f64(sh.seg_qd[k.seg]);
-#pragma unroll
-                    for (int q = 0; q < CH / 256; q++)
-#pragma unroll
-                        for (int j = 0; j < 4; j++)
-                            if (okq(q, j)) atomicAdd(acc + slot(q, j), (uint32_t)fx_product(qd, wbits(q, j)));
-                } else if constexpr (AF == kAccInt) {
-                    uint32_t* acc = DENSE ? acc32 : acc32 - (lbase >> 2);
-                    const uint32_t q8v = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.seg_q8[k.seg]);
-#pragma unroll
-                    for (int q = 0; q < CH / 256; q++)
-#pragma unroll
-                        for (int j = 0; j < 4; j++)
-                            if (okq(q, j)) atomicAdd(acc + slot(q, j), __umul24(q8v, wbits(q, j)));
-                }
-                return;
-            }
             auto ok = [&](int u) {
                 return (!PRUNED || !((k.skip >> u) & 1u)) &&
                        (!PRED || ((u > 0 || lane >= k.lo) && lane + u * kWave < k.n));
             };
             if constexpr (AF == kAccFx64) {
-                unsigned long long* acc = DENSE ? acc64 : acc64f;
                 const double qd = uniform_f64(sh.seg_qd[k.seg]);
 #pragma unroll
                 for (int u = 0; u < U; u++)
-                    if (ok(u)) atomicAdd(at(acc, u), fx_product(qd, k.w[u]));
+                    if (ok(u)) atomicAdd(acc64f + k.doc[u], fx_product(qd, k.w[u]));
             } else if constexpr (AF == kAccF64) {
                 // products of two fp32 values (or fp32 and bf16) are exact in fp64
-                double* acc = reinterpret_cast<double*>(DENSE ? acc64 : acc64f);
+                double* acc = reinterpret_cast<double*>(acc64f);
                 const double qd = uniform_f64(sh.seg_qd[k.seg]);
 #pragma unroll
                 for (int u = 0; u < U; u++)
-                    if (ok(u)) atomicAdd(at(acc, u), qd * (double)__uint_as_float(k.w[u]));
+                    if (ok(u)) atomicAdd(acc + k.doc[u], qd * (double)__uint_as_float(k.w[u]));
             } else if constexpr (AF == kAccFx32) {
                 // the query's scale keeps every doc's sum below 2^32 units
-                uint32_t* acc = DENSE ? acc32 : acc32f;
                 const double qd = uniform_f64(sh.seg_qd[k.seg]);
 #pragma unroll
                 for (int u = 0; u < U; u++)
-                    if (ok(u)) atomicAdd(at(acc, u), (uint32_t)fx_product(qd, k.w[u]));
+                    if (ok(u)) atomicAdd(acc32f + k.doc[u], (uint32_t)fx_product(qd, k.w[u]));
             } else {
-                uint32_t* acc = DENSE ? acc32 : acc32f;
                 const uint32_t q8v = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.seg_q8[k.seg]);
 #pragma unroll
                 for (int u = 0; u < U; u++)
-                    if (ok(u)) atomicAdd(at(acc, u), __umul24(q8v, k.w[u]));  // both below 256: full rate
+                    if (ok(u)) atomicAdd(acc32f + k.doc[u], __umul24(q8v, k.w[u]));  // both below 256: full rate
             }
         };
         if (k.n == CH && k.lo == 0) add(std::false_type());
@@ -982,10 +711,7 @@ __device__ __forceinline__ void score_tile(const DevIndex& ix, const DevBatch& q
         const int total_d = __builtin_amdgcn_readfirstlane(sh.seg_cpre[n_dense]);
         auto two_loops = [&](auto use_tab) {
             int c = wave;
-            if constexpr (DB) {
-                c = total_d > 0 ? run(use_tab, FDense(), wave, total_d) : wave;
-                run(use_tab, FExact(), c, total);
-            } else if constexpr (PR) {
+            if constexpr (PR) {
                 // essential terms, then the largest essential sum of every 64-doc group, then
                 // the non-essential terms block by block
                 c = total_d > 0 ? run(use_tab, FExact(), wave, total_d) : wave;
@@ -1025,41 +751,358 @@ __device__ __forceinline__ void score_tile(const DevIndex& ix, const DevBatch& q
     // its rows from phase 3; a bf16 query whose error band reaches below its candidates gets
     // them from phase 5, before the band pass.
     SelState* st = state + ql;
-    // the flush's candidate stage: the histogram's LDS when the flush does not count, else the
-    // segment starts (the segment table is not read once the adds are done)
-    unsigned long long* stage_hist = reinterpret_cast<unsigned long long*>(hist);
-    unsigned long long* stage_seg = reinterpret_cast<unsigned long long*>(sh.seg_beg);
-    const bool fused_q = phase == 2 && sh.fl_fused == 1;
-    const bool app = fused_q && !sh.fl_over;
-    const bool write = !fused_q;
-    // The first-digit histogram of a fused query keeps the seed tiles' counts only: its
-    // selection needs no more, and if it falls back, phase 3 scores these tiles again and
-    // counts them then.
-    const bool count = !fused_q && phase != kPhaseRows;
-    flush_tile<BS, AF, (QD ? TILE / 4 : 0), TILE>(lds, hist, tile_n, base, S + (int64_t)ql * ld + base, sh.fl_shift,
-                       sh.fl_scale, hist1 + (int64_t)ql * kHistBins, app, app ? sh.fl_bound : 0ull, st,
-                       cand + (int64_t)ql * kCandCap, write, count, sh.stg, count ? stage_seg : stage_hist,
-                       count ? kMaxQueryNnz : kHistBins / 2);
+    if (phase == 2 && sh.fl_fused == 1) {
+        if constexpr (AF != kAccF64)
+            if (!sh.fl_over)
+                flush_candidates<BS, AF, TILE>(lds, tile_n, base, sh.fl_scale, sh.fl_bound, st,
+                                               cand + (int64_t)ql * kCandCap,
+                                               reinterpret_cast<unsigned long long*>(hist), kHistBins / 2);
+        return;
+    }
+    flush_tile<BS, AF>(lds, hist, tile_n, S + (int64_t)ql * ld + base, sh.fl_shift, sh.fl_scale,
+                       hist1 + (int64_t)ql * kHistBins, st, true, true);
 }
 
-// Per-query form: grid (tiles, queries), the tiles of one query are consecutive
-// workgroups, so each query streams its own postings from HBM.
-// Both scoring kernels are held to 128 VGPRs (four wavefronts per SIMD): two
-// 512-thread workgroups per CU, which is what their LDS footprint allows.
-// PR: block-max pruning (phase 2).
-template <int P, int TS, int CH, bool PR = false>
+// The tile's accumulators from the rows of the query's commonest terms (the first nr of its
+// scoring terms; `rec` holds the first 64, one per lane): every thread sums a few documents in
+// registers over all the rows and writes them to LDS, which starts the tile (zeros without
+// rows). Two rows are in flight per wavefront (uint8: two steps of four).
+// Why: a posting scatter-added into LDS costs 1/8 (32-bit) or 1/5.6 (64-bit) of a CU's clock,
+// which bounded the batched search; with SPLADE-like term frequencies a few rows hold most of a
+// query's postings (nine terms of thirty, nine postings of ten), and a row's document costs
+// about 1/80 (uint8, four rows per dot4) to 1/20 clock (fp32: convert, FMA, 64-bit add) of
+// vector arithmetic, with coalesced 16-byte loads and no doc ids. The integer sums are the
+// same, whatever the order.
+// The rows are stored grain by grain (8192 documents, all rows of a grain side by side: one or
+// two memory pages per tile instead of one per row), and inside a grain in the order that the
+// threads write them: a thread's 16-byte load holds fours of consecutive documents 2048 apart,
+// so that each of its 16-byte LDS writes is next to its neighbours' and no bank conflicts.
+template <int P, int TS>
+__device__ __forceinline__ void sum_rows(const DevIndex& ix, const ScoreTerm* __restrict__ terms, ScoreTerm rec, int nr,
+                                         int64_t base, uint32_t* lds) {
+    using WT = std::conditional_t<P == kU8, uint8_t, std::conditional_t<P == kBF16, uint16_t, uint32_t>>;
+    constexpr int BS = 512, TILE = 1 << TS;
+    constexpr int DPL = 16 / (int)sizeof(WT);  // documents per 16-byte load
+    constexpr int G = TILE / (BS * DPL);       // loads per thread and row
+    constexpr int GM = (P == kFP32 ? 16 : 32) / DPL, GB = G < GM ? G : GM;  // of them in registers at once
+    constexpr int R = P == kU8 ? 4 : 1;        // rows per step
+    using Acc = std::conditional_t<P == kFP32, unsigned long long, uint32_t>;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    // grain by grain, all rows of one grain together
+    constexpr int PER = (1 << kGrainShift) / (BS * DPL);  // loads per thread, row and grain
+    const int64_t g_first = base >> kGrainShift, left = ix.n_grains - g_first;
+    const int grain = ix.n_rows << kGrainShift;
+    const int nrec = (((int)(left < (TILE >> kGrainShift) ? left : (TILE >> kGrainShift)) - 1) * grain +
+                      (1 << kGrainShift)) * (int)sizeof(WT);
+    const WT* rows = reinterpret_cast<const WT*>(ix.rows) + g_first * grain;
+    struct Step {
+        uint32_t w[R][GB][4];
+        unsigned long long q[R];
+    };
+#pragma unroll
+    for (int g0 = 0; g0 < G; g0 += GB) {
+        ScoreTerm rr = rec;  // the 64 terms that the step's rows are among
+        auto fetch = [&](int i0, Step& b) {
+            if (i0 >= kWave && (i0 & (kWave - 1)) == 0 && i0 < nr) rr = terms[min(i0 + lane, nr - 1)];
+#pragma unroll
+            for (int r = 0; r < R; r++) {
+                const bool have = i0 + r < nr;  // a missing row reads nothing (record count 0) and weighs 0
+                const int l = (i0 + r) & (kWave - 1);
+                const int64_t row = have ? __builtin_amdgcn_readlane(rr.row, l) : 0;
+                b.q[r] = have ? read_lane64(rr.q, l) : 0ull;
+                const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                    const_cast<WT*>(rows + (row << kGrainShift)), (short)0, have ? nrec : 0, kRawBufferWord3);
+#pragma unroll
+                for (int g = 0; g < GB; g++) {
+                    const int at = (g0 + g) / PER * grain * (int)sizeof(WT) + ((g0 + g) % PER * BS + tid) * 16;
+                    const auto v = __builtin_amdgcn_raw_buffer_load_b128(rs, at, 0, 0);
+#pragma unroll
+                    for (int x = 0; x < 4; x++) b.w[r][g][x] = v[x];
+                }
+            }
+        };
+        Acc acc[GB * DPL];
+#pragma unroll
+        for (int i = 0; i < GB * DPL; i++)  // fp32: the exponent bits of the rows' products (see fx_bits) taken off
+            acc[i] = P == kFP32 ? (Acc)(0ull - (unsigned long long)nr * 0x4330000000000000ull) : (Acc)0;
+        auto add = [&](const Step& b) {
+            if constexpr (P == kU8) {
+                uint32_t q4 = 0;
+#pragma unroll
+                for (int r = 0; r < R; r++) q4 |= (uint32_t)b.q[r] << (8 * r);
+#pragma unroll
+                for (int g = 0; g < GB; g++)
+#pragma unroll
+                    for (int x = 0; x < 4; x++) {
+                        // four rows' words of four documents each: transposed to a word per document
+                        const uint32_t t0 = __builtin_amdgcn_perm(b.w[1][g][x], b.w[0][g][x], 0x05010400u);
+                        const uint32_t t1 = __builtin_amdgcn_perm(b.w[3][g][x], b.w[2][g][x], 0x05010400u);
+                        const uint32_t t2 = __builtin_amdgcn_perm(b.w[1][g][x], b.w[0][g][x], 0x07030602u);
+                        const uint32_t t3 = __builtin_amdgcn_perm(b.w[3][g][x], b.w[2][g][x], 0x07030602u);
+                        Acc* a = &acc[g * DPL + 4 * x];
+                        a[0] = __builtin_amdgcn_udot4(__builtin_amdgcn_perm(t1, t0, 0x05040100u), q4, a[0], false);
+                        a[1] = __builtin_amdgcn_udot4(__builtin_amdgcn_perm(t1, t0, 0x07060302u), q4, a[1], false);
+                        a[2] = __builtin_amdgcn_udot4(__builtin_amdgcn_perm(t3, t2, 0x05040100u), q4, a[2], false);
+                        a[3] = __builtin_amdgcn_udot4(__builtin_amdgcn_perm(t3, t2, 0x07060302u), q4, a[3], false);
+                    }
+            } else {
+                const double qd = __longlong_as_double((long long)b.q[0]);
+#pragma unroll
+                for (int g = 0; g < GB; g++)
+#pragma unroll
+                    for (int d = 0; d < DPL; d++) {
+                        if constexpr (P == kFP32) {
+                            acc[g * DPL + d] += fx_bits(qd, b.w[0][g][d]);
+                        } else {
+                            const uint32_t x = b.w[0][g][d >> 1];
+                            acc[g * DPL + d] += (uint32_t)fx_product(qd, (d & 1) ? x & 0xffff0000u : x << 16);
+                        }
+                    }
+            }
+        };
+        if (nr > 0) {
+            Step A, B;
+            fetch(0, A);
+            for (int i0 = 0; i0 < nr; i0 += 2 * R) {
+                fetch(i0 + R, B);
+                add(A);
+                if (i0 + R >= nr) break;
+                fetch(i0 + 2 * R, A);
+                add(B);
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < GB; g++) {
+            const Acc* a = &acc[g * DPL];
+#pragma unroll
+            for (int m = 0; m < DPL / 4; m++) {
+                const int at = (g0 + g) * (BS * DPL / 4) + m * BS + tid;  // documents 4 at ..
+                if constexpr (P == kFP32) {
+                    uint4* o = reinterpret_cast<uint4*>(lds) + 2 * at;
+                    o[0] = make_uint4((uint32_t)a[0], (uint32_t)(a[0] >> 32), (uint32_t)a[1], (uint32_t)(a[1] >> 32));
+                    o[1] = make_uint4((uint32_t)a[2], (uint32_t)(a[2] >> 32), (uint32_t)a[3], (uint32_t)(a[3] >> 32));
+                } else {
+                    reinterpret_cast<uint4*>(lds)[at] = make_uint4(a[4 * m], a[4 * m + 1], a[4 * m + 2], a[4 * m + 3]);
+                }
+            }
+        }
+    }
+}
+
+// The doc-tiled kernel: one workgroup per (query, doc tile) work item.
+//  1. Rows: the sums of the query's commonest terms start the tile (sum_rows).
+//  2. Postings: the segments of its other terms in this tile are scatter-added into LDS. Each
+//     wavefront holds the segments of 64 terms in its lanes (no LDS table, no barrier) and takes
+//     every eighth chunk of CH postings; the loads of its next chunk are issued before the LDS
+//     adds of the current one. Ids and weights are read four postings per lane: one 8-byte load
+//     of ids and one load of four weights (4, 8 or 16 bytes) cover a lane's postings 4 l ..
+//     4 l + 3 of each 256 postings of the chunk, a quarter of the vector memory instructions of
+//     one posting per lane. Segment starts are rounded down to a multiple of 4 (the postings
+//     before the real start are masked).
+//  3. Flush: candidates (flush_candidates), or row and histogram (flush_tile).
+// A work item is a chain of dependent loads (item, terms, segments, postings) with little work
+// behind each, and two workgroups share a CU, so the chain is kept short: the item and term
+// records hold what the batch update knows (16 bytes each), the segment bounds are loaded under
+// the rows, and only two barriers order the tile.
+// Items run tile by tile, an eighth of them on each XCD (workgroups are dealt to the XCDs round
+// robin), so that a tile's rows and postings are read from that XCD's L2 by most of the queries
+// that need them; the items of a batch are ordered by descending work, dealt into eight runs
+// (ScoreItem), so that equal eighths are equal work. One mapping for the TILED and SHARED forms.
+template <int P, int TS, int CH>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_score_tiled(
+    DevIndex ix, const ScoreItem* __restrict__ items, const ScoreTerm* __restrict__ all_terms,
+    const int32_t* __restrict__ first_shift, const double* __restrict__ q_scale, int32_t q0, int32_t qt,
+    uint32_t* __restrict__ S, int64_t ld, uint32_t* __restrict__ hist1, int phase, int stride,
+    SelState* __restrict__ state, unsigned long long* __restrict__ cand) {
+    constexpr int BS = 512, NW = BS / kWave, TILE = 1 << TS, GPT = TS - kGrainShift;
+    constexpr bool FX = P != kU8;
+    constexpr int AF = acc_form<P>();
+    constexpr int AW = AF == kAccFx64 ? 2 : 1;  // accumulator words per doc
+    static_assert(CH % 256 == 0, "chunks of 256-posting rows");
+    using WT = std::conditional_t<P == kU8, uint8_t, std::conditional_t<P == kBF16, uint16_t, uint32_t>>;
+    extern __shared__ __align__(16) uint32_t lds[];
+    uint32_t* hist = lds + TILE * AW;  // [kHistLds]; the candidates' stage of a flush that does not count
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: chunk bookkeeping stays scalar
+
+    const uint32_t n_tiles = (uint32_t)phase_tiles(phase, stride, (ix.n_docs + TILE - 1) >> TS);
+    const uint32_t total_items = n_tiles * (uint32_t)qt, per = (total_items + 7) / 8;
+    const uint32_t in_xcd = blockIdx.y * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    const uint32_t item = (blockIdx.x & 7) * per + in_xcd;
+    if (in_xcd >= per || item >= total_items) return;
+    // the division runs in vector registers: back to a scalar, so that all below it stays scalar
+    const uint32_t v = (uint32_t)__builtin_amdgcn_readfirstlane((int)(item / (uint32_t)qt));
+    const ScoreItem it = items[item - v * (uint32_t)qt];
+    if (it.n < 0) return;  // nothing is selected for the query (also every padding slot of a batch)
+    const int64_t tile = phase_tile(phase, stride, (int64_t)v);
+    const int ql = it.q - q0, nt = it.n & 1023, nr = it.n >> 10;
+    const int64_t base = tile << TS;
+    const int tile_n = (int)min((int64_t)TILE, ix.n_docs - base);
+    static_assert(TS <= 16, "a doc tile must lie inside one 65536-doc range");
+    const int lbase = (int)(base & 0xFFFF);  // the tile's offset inside its 65536-doc range
+    const int64_t g0 = tile << GPT;
+    const int64_t g1 = min(g0 + (int64_t)(1 << GPT), ix.n_grains);
+
+    // What the flush needs of the query. The state is set before this launch; the cap flag may be
+    // set during it by other workgroups, and a stale 0 only costs appends that the cap check drops.
+    SelState* st = state + ql;
+    const int fl_fused = st->fused, fl_over = st->fused_over;
+    const unsigned long long fl_bound = st->bound;
+    const bool fused_q = phase == 2 && fl_fused == 1;
+    // Fused filtering (the non-seed tiles of a query whose seed bound is set): append while
+    // flushing, no appends once past the cap, and no score row or counts. A query that falls back
+    // gets its rows and counts from phase 3; a bf16 query whose error band reaches below its
+    // candidates gets its rows from phase 5, before the band pass.
+    const bool count = !fused_q && phase != kPhaseRows;
+
+    // the first 64 terms, one per lane, and the segments of those among them without a row here
+    const ScoreTerm* terms = all_terms + it.start;
+    ScoreTerm rec{0, 0, 0ull};
+    if (lane < nt) rec = terms[lane];
+    struct Seg {
+        int a, b;
+        int64_t off;
+    };
+    auto segment = [&](const ScoreTerm& t, bool live) {
+        Seg s{0, 0, 0};
+        if (live) {
+            const int32_t* row = ix.tile_off + (int64_t)t.term * (ix.n_grains + 1);
+            s.a = row[g0];
+            s.b = row[g1];
+            s.off = ix.term_off[t.term];
+        }
+        return s;
+    };
+    Seg seg = segment(rec, lane >= nr && lane < nt);
+    if (count)
+        for (int i = tid; i < kHistLds; i += BS) hist[i] = 0u;
+    sum_rows<P, TS>(ix, terms, rec, nr, base, lds);
+    __syncthreads();
+
+    struct Chunk {
+        uint32_t doc[CH / 128];                     // four 16-bit ids per 256 postings: doc modulo 65536
+        uint32_t w[CH / 256 * (int)sizeof(WT)];     // their weights
+        int n, lo;                                  // postings [lo, n) of the chunk are the segment's
+        unsigned long long q;                       // w_q * 2^F as fp64 bits, or the uint8 impact
+    };
+    for (int grp = nr >> 6; grp * kWave < nt; grp++) {
+        const int idx = grp * kWave + lane;
+        if (grp > 0) {
+            rec = ScoreTerm{0, 0, 0ull};
+            if (idx < nt) rec = terms[idx];
+            seg = segment(rec, idx >= nr && idx < nt);
+        }
+        // each lane's chunks, and the number before them: an exclusive prefix over the lanes one
+        // bit plane at a time (a ballot and the count of the lower lanes that hold the bit)
+        const int64_t beg = seg.off + (seg.a & ~3);
+        const int len = seg.b > seg.a ? seg.b - (seg.a & ~3) : 0, cnt = (len + CH - 1) / CH, edge = seg.a & 3;
+        int pre = 0, total = 0;
+        for (int b = 0; __ballot((cnt >> b) != 0) != 0ull; b++) {
+            const unsigned long long m = __ballot((cnt >> b) & 1);
+            pre += (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u)) << b;
+            total += __popcll(m) << b;
+        }
+        // Straight-line loads (no branch around them): an empty slot reads nothing (record count
+        // 0), and lanes past the end of a chunk read 0. The chunk's base is wave-uniform (a buffer
+        // descriptor in scalar registers), so no address arithmetic is done per posting.
+        auto fetch = [&](int c, Chunk& k) {
+            const bool valid = c < total;
+            const unsigned long long m = __ballot(c >= pre && c < pre + cnt);
+            const int l = valid ? __ffsll((long long)m) - 1 : 0;
+            const int off = valid ? (c - __builtin_amdgcn_readlane(pre, l)) * CH : 0;
+            k.n = valid ? min(CH, __builtin_amdgcn_readlane(len, l) - off) : 0;
+            k.lo = off == 0 ? __builtin_amdgcn_readlane(edge, l) : 0;
+            k.q = read_lane64(rec.q, l);
+            const int64_t p0 = (int64_t)read_lane64((unsigned long long)beg, l) + off;
+            const int nrec = (k.n + 3) & ~3;  // up to 3 postings past the segment, inside the padded list
+            const __amdgpu_buffer_rsrc_t rid = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<uint16_t*>(ix.post_lo + p0), (short)0, nrec * 2, kRawBufferWord3);
+            const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<WT*>(reinterpret_cast<const WT*>(ix.post_w) + p0), (short)0, nrec * (int)sizeof(WT),
+                kRawBufferWord3);
+            // z is 0 (posting offsets stay far below 2^48) but not a loop invariant, so the compiler
+            // keeps one lane offset per chunk and each row's offset in the instruction
+            const int z = (int)((uint64_t)p0 >> 48);
+            const int vid = lane * 8 + z;
+            const int vw = lane * 4 * (int)sizeof(WT) + z;
+#pragma unroll
+            for (int r = 0; r < CH / 256; r++) {
+                const auto d = __builtin_amdgcn_raw_buffer_load_b64(rid, vid + r * 512, 0, 0);
+                k.doc[2 * r] = d[0];
+                k.doc[2 * r + 1] = d[1];
+                if constexpr (sizeof(WT) == 1) {
+                    k.w[r] = __builtin_amdgcn_raw_buffer_load_b32(rw, vw + r * 256, 0, 0);
+                } else if constexpr (sizeof(WT) == 2) {
+                    const auto w = __builtin_amdgcn_raw_buffer_load_b64(rw, vw + r * 512, 0, 0);
+                    k.w[2 * r] = w[0];
+                    k.w[2 * r + 1] = w[1];
+                } else {
+                    const auto w = __builtin_amdgcn_raw_buffer_load_b128(rw, vw + r * 1024, 0, 0);
+#pragma unroll
+                    for (int x = 0; x < 4; x++) k.w[4 * r + x] = w[x];
+                }
+            }
+        };
+        auto apply = [&](const Chunk& k) {
+            const double qd = __longlong_as_double((long long)k.q);
+            auto add = [&](auto pred, int r) {
+                constexpr bool PRED = decltype(pred)::value;
+                // accumulators indexed by doc id modulo 65536: the tile's offset folded into the base
+                unsigned long long* acc64 = reinterpret_cast<unsigned long long*>(lds) - lbase;
+                uint32_t* acc32 = lds - lbase;
+                const int i0 = lane * 4 - k.lo;  // a posting is the segment's if its index less lo is below n - lo
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    if (PRED && (uint32_t)(i0 + r * 256 + j) >= (uint32_t)(k.n - k.lo)) continue;
+                    const uint32_t dw = k.doc[2 * r + (j >> 1)];
+                    const uint32_t at = (j & 1) ? (dw >> 16) : (dw & 0xffffu);
+                    if constexpr (P == kFP32) {
+                        atomicAdd(acc64 + at, fx_product(qd, k.w[4 * r + j]));
+                    } else if constexpr (P == kBF16) {
+                        const uint32_t h = k.w[2 * r + (j >> 1)];
+                        atomicAdd(acc32 + at, (uint32_t)fx_product(qd, (j & 1) ? h & 0xffff0000u : h << 16));
+                    } else {
+                        atomicAdd(acc32 + at, __umul24((uint32_t)k.q, (k.w[r] >> (8 * j)) & 0xffu));
+                    }
+                }
+            };
+            // a full row of 256 adds without the per-posting predicate
+#pragma unroll
+            for (int r = 0; r < CH / 256; r++) {
+                if (r * 256 >= k.n) break;
+                if (r * 256 + 256 <= k.n && (r > 0 || k.lo == 0)) add(std::false_type(), r);
+                else add(std::true_type(), r);
+            }
+        };
+        Chunk A, B;
+        fetch(wave, A);
+        for (int c = wave; c < total; c += 2 * NW) {
+            fetch(c + NW, B);
+            apply(A);
+            if (c + NW >= total) break;
+            fetch(c + 2 * NW, A);
+            apply(B);
+        }
+    }
+    __syncthreads();
+    const double scale = FX ? q_scale[it.q] : 1.0;
+    if (!fused_q)
+        flush_tile<BS, AF>(lds, hist, tile_n, S + (int64_t)ql * ld + base, first_shift[it.q], scale,
+                           hist1 + (int64_t)ql * kHistBins, st, true, count);
+    else if (!fl_over)
+        flush_candidates<BS, AF, TILE>(lds, tile_n, base, scale, fl_bound, st, cand + (int64_t)ql * kCandCap,
+                                       reinterpret_cast<unsigned long long*>(hist), kHistBins / 2);
+}
+
+// The non-seed tiles with block-max pruning: grid (tiles, queries).
+template <int P, int TS, int CH>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_score_pruned(
     DevIndex ix, DevBatch qb, int32_t q0, uint32_t* __restrict__ S, int64_t ld, uint32_t* __restrict__ hist1,
     int phase, int stride, SelState* __restrict__ state, unsigned long long* __restrict__ cand) {
     extern __shared__ __align__(16) uint32_t lds[];
     __shared__ TileShared sh;
     const int64_t tile = phase_tile(phase, stride, (int64_t)blockIdx.x);
-    constexpr bool DB = P != kU8 && !PR;
-    // four postings per lane and load: uint8 +5 %, bf16 +4 %; fp32 (16-byte weight loads, the
-    // HBM-bound form) measured 0.7 % slower and keeps one posting per lane
-    constexpr bool QD = !PR && CH % 256 == 0 && P != kFP32;
-    score_tile<P, TS, CH, DB, false, PR, QD>(ix, qb, q0, tile, (int)blockIdx.y, S, ld, hist1, lds, sh, phase, state,
-                                             cand);
+    score_tile<P, TS, CH, false, true>(ix, qb, q0, tile, (int)blockIdx.y, S, ld, hist1, lds, sh, phase, state, cand);
 }
 
 // The rows of the listed queries scored again, one workgroup per tile walking the list
@@ -1074,67 +1117,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
     extern __shared__ __align__(16) uint32_t lds[];
     __shared__ TileShared sh;
     const int64_t tile = phase_tile(phase, stride, (int64_t)blockIdx.x);
-    constexpr bool DB = P != kU8 && !W;
     const int nres = (int)counters[kCntListed];
     for (int r = 0; r < nres; r++) {
-        score_tile<P, TS, CH, DB, W>(ix, qb, q0, tile, rescore_list[r], S, ld, hist1, lds, sh, phase, state, cand);
+        score_tile<P, TS, CH, W>(ix, qb, q0, tile, rescore_list[r], S, ld, hist1, lds, sh, phase, state, cand);
         __syncthreads();
     }
-}
-
-// Persistent form of the shared traversal: a grid of (resident workgroups,
-// rounded to a multiple of 8) in which workgroup b stays on XCD b % 8 and pulls
-// work items from that XCD's counter. XCD x owns the tiles x, x+8, ...; the items
-// of a tile are its queries in the order given by `order` (heaviest first), so
-// every query of a tile runs on one XCD while the tile's postings are in its L2.
-// Every workgroup leaves the loop once its XCD's counter passes the item count.
-template <int P, int TS, int CH>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_score_persistent(
-    DevIndex ix, DevBatch qb, int32_t q0, int32_t qt, const int32_t* __restrict__ order,
-    uint32_t* __restrict__ counters, uint32_t* __restrict__ S, int64_t ld, uint32_t* __restrict__ hist1, int phase,
-    int stride, SelState* __restrict__ state, unsigned long long* __restrict__ cand,
-    const int32_t* __restrict__ rescore_list) {
-    extern __shared__ __align__(16) uint32_t lds[];
-    __shared__ TileShared sh;
-    __shared__ int64_t item_sh;
-    const int x = (int)(blockIdx.x & 7);
-    const int64_t n_tiles = phase_tiles(phase, stride, (ix.n_docs + (1 << TS) - 1) >> TS);
-    const int64_t tiles_x = n_tiles > x ? (n_tiles - x + 7) / 8 : 0;
-    // phases 3 and 5 cover only the listed queries (fused filtering's fallbacks, bf16 band
-    // passes; usually none)
-    const bool listed = phase == 3 || phase == 5;
-    const int nq = listed ? (int)counters[kCntListed] : qt;
-    const int64_t items = tiles_x * nq;
-    for (;;) {
-        if (threadIdx.x == 0) item_sh = (int64_t)atomicAdd(&counters[cnt_base(phase) + x], 1u);
-        __syncthreads();
-        const int64_t item = item_sh;
-        if (item >= items) break;
-        const int64_t tile = phase_tile(phase, stride, x + 8 * (item / nq));
-        const int ql = listed ? rescore_list[item % nq] : order[item % nq];
-        // uint8 weights: four postings per lane and load (measured +10 %; the fixed-point forms,
-        // with more arithmetic per posting, ran 4-6 % slower that way)
-        score_tile<P, TS, CH, false, false, false, (P == kU8 && CH % 256 == 0)>(ix, qb, q0, tile, ql, S, ld, hist1,
-                                                                                lds, sh, phase, state, cand);
-        __syncthreads();
-    }
-}
-
-// Work order of a query tile for the persistent kernel: local query indices by
-// descending estimated work (postings of the query's terms), ties by index. One wavefront
-// per query counts the queries before it, 64 at a time (one thread per query took 274 us
-// for 4,096 queries).
-__global__ __launch_bounds__(256) void k_work_order(DevBatch qb, int32_t q0, int32_t qt, int32_t* __restrict__ order) {
-    const int i = blockIdx.x * (256 / kWave) + (threadIdx.x >> 6), lane = threadIdx.x & (kWave - 1);
-    if (i >= qt) return;
-    const int64_t wi = qb.q_work[q0 + i];
-    int r = 0;
-    for (int j = lane; j < qt; j += kWave) {
-        const int64_t wj = qb.q_work[q0 + j];
-        r += (wj > wi) || (wj == wi && j < i);
-    }
-    r = wave_sum(r);
-    if (lane == 0) order[r] = i;
 }
 
 // ------------------------------------------------------------- group --
@@ -1350,14 +1337,16 @@ __global__ __launch_bounds__(group_size<P>() * kMaxQueryNnz) __attribute__((amdg
             __syncthreads();
             SelState* st = state + ql;
             const bool fused_q = phase == 2 && st->fused == 1;
-            const bool app = fused_q && !st->fused_over;
             // as in score_tile: a fused query writes no row and counts no tile here; its
             // fallback (phase 3) or bf16 band pass (phase 5) scores these tiles again
-            const bool write = !fused_q;
-            const bool count = !fused_q && phase != kPhaseRows;
-            flush_tile<BS, AF>(lds + m * TILE * AW, hist, tile_n, base, S + (int64_t)ql * ld + base,
-                               qb.first_shift[ql], FX ? qb.q_scale[ql] : 1.0, hist1 + (int64_t)ql * kHistBins, app,
-                               app ? st->bound : 0ull, st, cand + (int64_t)ql * kCandCap, write, count);
+            const uint32_t* tile_acc = lds + m * TILE * AW;
+            const double scale = FX ? qb.q_scale[ql] : 1.0;
+            if (!fused_q)
+                flush_tile<BS, AF>(tile_acc, hist, tile_n, S + (int64_t)ql * ld + base, qb.first_shift[ql], scale,
+                                   hist1 + (int64_t)ql * kHistBins, st, true, phase != kPhaseRows);
+            else if (!st->fused_over)
+                flush_candidates<BS, AF, TILE>(tile_acc, tile_n, base, scale, st->bound, st, cand + (int64_t)ql * kCandCap,
+                                               reinterpret_cast<unsigned long long*>(hist), kHistBins / 2);
             __syncthreads();
         }
     }
@@ -1526,6 +1515,26 @@ __global__ void k_fill_u32(uint32_t* __restrict__ p, int64_t n, uint32_t v) {
         p[i] = v;
 }
 
+// Row blockIdx.y of the commonest terms: the stored weights of its posting list by document
+// (the rows are zero before). A grain's postings lie in one 65536-document range. A grain's
+// documents are stored so that the 16 bytes a thread of sum_rows loads (4, 8 or 16 weights) are
+// fours of documents 2048 apart.
+template <typename WT>
+__global__ __launch_bounds__(256) void k_fill_rows(DevIndex ix, const int32_t* __restrict__ terms, int r0,
+                                                   WT* __restrict__ rows) {
+    constexpr int DPL = 16 / (int)sizeof(WT), B = 512 * DPL, G = 1 << kGrainShift;
+    const int row = r0 + (int)blockIdx.y, term = terms[row];
+    const int32_t* off = ix.tile_off + (int64_t)term * (ix.n_grains + 1);
+    const int64_t p0 = ix.term_off[term];
+    for (int64_t g = blockIdx.x; g < ix.n_grains; g += gridDim.x) {
+        WT* to = rows + ((g * ix.n_rows + row) << kGrainShift);
+        for (int i = off[g] + (int)threadIdx.x; i < off[g + 1]; i += 256) {
+            const int d = ix.post_lo[p0 + i] & (G - 1), r = d & (B - 1);
+            to[d - r + ((r & 2047) >> 2) * DPL + (r >> 11) * 4 + (r & 3)] = reinterpret_cast<const WT*>(ix.post_w)[p0 + i];
+        }
+    }
+}
+
 // The start of a search: its step counters, selection state and histograms, in one launch.
 static_assert(sizeof(SelState) % 16 == 0, "cleared 16 bytes at a time");
 __global__ __launch_bounds__(256) void k_clear(uint32_t* __restrict__ counters, uint4* __restrict__ state,
@@ -1552,97 +1561,71 @@ hipError_t by_precision(int p, F f) {
     return hipErrorInvalidValue;
 }
 
+// Dynamic LDS past the default limit, once per kernel.
+hipError_t allow_lds(const void* kernel, size_t lds, const char* name) {
+    const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) g_failed_launch = name;
+    return e;
+}
+
+template <int P, int TS>
+constexpr size_t tile_lds() {
+    return (size_t)((1 << TS) * (acc_form<P>() == kAccFx64 ? 2 : 1) + kHistLds) * 4;
+}
+
 template <int P, int TS, int CH>
-hipError_t launch_tiled_one(const DevIndex& ix, const DevBatch& qb, int32_t q0, int32_t qt, bool persistent, bool whole,
-                            const Workspace& ws, int64_t ld, hipStream_t s, int phase, int stride, bool prune) {
-    const int64_t n_tiles = phase_tiles(phase, stride, (ix.n_docs + (1 << TS) - 1) >> TS);
-    if (n_tiles <= 0) return hipSuccess;
-    const size_t lds = (size_t)((1 << TS) * (acc_form<P>() == kAccFx64 ? 2 : 1) + kHistLds) * 4;
-    if (lds > 150 * 1024) return hipErrorInvalidValue;
-    if (lds > 65536) {
-        static const hipError_t attr = [&] {
-            hipError_t e = hipFuncSetAttribute((const void*)k_score_tiled<P, TS, CH>,
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e == hipSuccess)
-                e = hipFuncSetAttribute((const void*)k_score_listed<P, TS, CH>,
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e == hipSuccess)
-                e = hipFuncSetAttribute((const void*)k_score_persistent<P, TS, CH>,
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            return e;
-        }();
-        if (attr != hipSuccess) {
-            g_failed_launch = "hipFuncSetAttribute(k_score_tiled)";
-            return attr;
-        }
-    }
-    if (!persistent) {
-        // block-max pruning (non-seed tiles): the default tile and chunk of fp32 and uint8 only
-        constexpr bool kPrunable = ((P == kFP32 && TS == 13) || (P == kU8 && TS == 14)) && CH == 1024;
-        if constexpr (kPrunable) {
-            if (prune && phase == 2) {
-                static const hipError_t pattr = hipFuncSetAttribute(
-                    (const void*)k_score_tiled<P, TS, CH, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-                if (pattr != hipSuccess) {
-                    g_failed_launch = "hipFuncSetAttribute(k_score_tiled, pruning)";
-                    return pattr;
-                }
-                hipLaunchKernelGGL((k_score_tiled<P, TS, CH, true>), dim3((unsigned)n_tiles, (unsigned)qt),
-                                   dim3(512), lds, s, ix, qb, q0, ws.scores, ld, ws.hist1, phase, stride, ws.state,
-                                   ws.cand);
-                GS_CHECK_LAUNCH("k_score_tiled (pruning)");
-                return hipSuccess;
-            }
-        }
-        if (phase == 3 || phase == 5) {
-            hipLaunchKernelGGL((k_score_listed<P, TS, CH>), dim3((unsigned)n_tiles, 1u), dim3(512), lds, s, ix, qb, q0,
-                               ws.scores, ld, ws.hist1, phase, stride, ws.state, ws.cand, (const uint32_t*)ws.counters,
-                               (const int32_t*)ws.rescore_list);
-            GS_CHECK_LAUNCH("k_score_listed");
-            return hipSuccess;
-        }
-        hipLaunchKernelGGL((k_score_tiled<P, TS, CH>), dim3((unsigned)n_tiles, (unsigned)qt), dim3(512), lds, s, ix,
-                           qb, q0, ws.scores, ld, ws.hist1, phase, stride, ws.state, ws.cand);
-        GS_CHECK_LAUNCH("k_score_tiled");
-        return hipSuccess;
-    }
-    // resident workgroups: as many as fit on every CU at once, a multiple of the 8 XCDs
-    static const int grid = [&] {
-        int dev = 0, per_cu = 0;
-        hipDeviceProp_t p{};
-        if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&p, dev) != hipSuccess) return 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)k_score_persistent<P, TS, CH>, 512,
-                                                         lds) != hipSuccess)
-            return 0;
-        return std::max(8, (p.multiProcessorCount * std::max(per_cu, 1)) / 8 * 8);
-    }();
-    if (grid <= 0) return hipErrorInvalidConfiguration;
-    // a search in one query tile takes the order the host made; the tiles of a longer batch are
-    // ordered here (the later launches of a fused search keep the first one's order)
-    const int32_t* order = qb.q_order;
-    if (!whole) {
-        order = ws.order;
-        if (phase <= 1 || phase == kPhaseRows) {
-            hipLaunchKernelGGL(k_work_order, dim3((unsigned)((qt + 3) / 4)), dim3(256), 0, s, qb, q0, qt, ws.order);
-            GS_CHECK_LAUNCH("k_work_order");
-        }
-    }
-    hipLaunchKernelGGL((k_score_persistent<P, TS, CH>), dim3((unsigned)grid), dim3(512), lds, s, ix, qb, q0, qt,
-                       order, ws.counters, ws.scores, ld, ws.hist1, phase, stride, ws.state,
-                       ws.cand, (const int32_t*)ws.rescore_list);
-    GS_CHECK_LAUNCH("k_score_persistent");
+hipError_t launch_tiled_one(const DevIndex& ix, const DevBatch& qb, int32_t q0, int32_t qt, const ScoreOpts& o,
+                            const Workspace& ws, int64_t ld, hipStream_t s, int phase, int stride, int64_t n_tiles) {
+    constexpr size_t lds = tile_lds<P, TS>();
+    static const hipError_t attr =
+        allow_lds((const void*)k_score_tiled<P, TS, CH>, lds, "hipFuncSetAttribute(k_score_tiled)");
+    if (attr != hipSuccess) return attr;
+    // an eighth of the items per XCD, padded to a rectangle of workgroups
+    const int64_t per = (n_tiles * qt + 7) / 8, gx = std::min<int64_t>(per, 65536), gy = (per + gx - 1) / gx;
+    const ScoreItem* items = o.whole ? qb.s_order : qb.s_item + q0;
+    hipLaunchKernelGGL((k_score_tiled<P, TS, CH>), dim3((unsigned)(8 * gx), (unsigned)gy), dim3(512), lds, s, ix, items,
+                       qb.s_term, qb.first_shift, qb.q_scale, q0, qt, ws.scores, ld, ws.hist1,
+                       phase, stride, ws.state, ws.cand);
+    GS_CHECK_LAUNCH("k_score_tiled");
     return hipSuccess;
 }
 
 template <int P, int TS>
-hipError_t tiled_chunk(const DevIndex& ix, const DevBatch& qb, int32_t q0, int32_t qt, int chunk, bool persistent,
-                       bool whole, const Workspace& ws, int64_t ld, hipStream_t s, int phase, int stride, bool prune) {
-    switch (chunk) {
-        case 64: return launch_tiled_one<P, TS, 64>(ix, qb, q0, qt, persistent, whole, ws, ld, s, phase, stride, prune);
-        case 128: return launch_tiled_one<P, TS, 128>(ix, qb, q0, qt, persistent, whole, ws, ld, s, phase, stride, prune);
-        case 256: return launch_tiled_one<P, TS, 256>(ix, qb, q0, qt, persistent, whole, ws, ld, s, phase, stride, prune);
-        case 512: return launch_tiled_one<P, TS, 512>(ix, qb, q0, qt, persistent, whole, ws, ld, s, phase, stride, prune);
-        case 1024: return launch_tiled_one<P, TS, 1024>(ix, qb, q0, qt, persistent, whole, ws, ld, s, phase, stride, prune);
+hipError_t launch_tiled(const DevIndex& ix, const DevBatch& qb, int32_t q0, int32_t qt, const ScoreOpts& o,
+                        const Workspace& ws, hipStream_t s, int phase) {
+    const int stride = phase == 0 || phase == kPhaseRows ? 1 : o.seed_stride;
+    const int64_t ld = score_ld(ix.n_docs);
+    const int64_t n_tiles = phase_tiles(phase, stride, (ix.n_docs + (1 << TS) - 1) >> TS);
+    if (n_tiles <= 0) return hipSuccess;
+    constexpr size_t lds = tile_lds<P, TS>();
+    if (phase == 3 || phase == 5) {
+        static const hipError_t attr =
+            allow_lds((const void*)k_score_listed<P, TS, kMaxChunk>, lds, "hipFuncSetAttribute(k_score_listed)");
+        if (attr != hipSuccess) return attr;
+        hipLaunchKernelGGL((k_score_listed<P, TS, kMaxChunk>), dim3((unsigned)n_tiles, 1u), dim3(512), lds, s, ix, qb, q0,
+                           ws.scores, ld, ws.hist1, phase, stride, ws.state, ws.cand, (const uint32_t*)ws.counters,
+                           (const int32_t*)ws.rescore_list);
+        GS_CHECK_LAUNCH("k_score_listed");
+        return hipSuccess;
+    }
+    // block-max pruning (non-seed tiles): the default tile and chunk of fp32 and uint8 only
+    if constexpr ((P == kFP32 && TS == 13) || (P == kU8 && TS == 14)) {
+        if (o.prune && phase == 2) {
+            static const hipError_t attr =
+                allow_lds((const void*)k_score_pruned<P, TS, kMaxChunk>, lds, "hipFuncSetAttribute(k_score_pruned)");
+            if (attr != hipSuccess) return attr;
+            hipLaunchKernelGGL((k_score_pruned<P, TS, kMaxChunk>), dim3((unsigned)n_tiles, (unsigned)qt), dim3(512), lds,
+                               s, ix, qb, q0, ws.scores, ld, ws.hist1, phase, stride, ws.state, ws.cand);
+            GS_CHECK_LAUNCH("k_score_pruned");
+            return hipSuccess;
+        }
+    }
+    switch (o.chunk) {  // the kernel reads rows of 256 postings: smaller chunks run as 256
+        case 64:
+        case 128:
+        case 256: return launch_tiled_one<P, TS, 256>(ix, qb, q0, qt, o, ws, ld, s, phase, stride, n_tiles);
+        case 512: return launch_tiled_one<P, TS, 512>(ix, qb, q0, qt, o, ws, ld, s, phase, stride, n_tiles);
+        case 1024: return launch_tiled_one<P, TS, 1024>(ix, qb, q0, qt, o, ws, ld, s, phase, stride, n_tiles);
     }
     return hipErrorInvalidValue;
 }
@@ -1681,8 +1664,6 @@ hipError_t launch_group_one(const DevIndex& ix, const DevBatch& qb, const Worksp
 
 }  // namespace
 
-static inline int64_t score_ld(int64_t n_docs) { return (n_docs + 63) / 64 * 64; }
-
 // The launches of one weight form. A build may compile this file in parts (GS_SCORE_PART 0, 1
 // and 2: one form each; 3: the rest): the kernels of the three forms take most of its time.
 template <int P>
@@ -1698,15 +1679,11 @@ struct ScoreForm {
 template <int P>
 hipError_t ScoreForm<P>::tiled(const DevIndex& ix, const DevBatch& qb, int32_t q0, int32_t qt, const ScoreOpts& o,
                                const Workspace& ws, hipStream_t s, int phase) {
-    const int stride = phase == 0 || phase == kPhaseRows ? 1 : o.seed_stride;
-    const int64_t ld = score_ld(ix.n_docs);
-    const bool persistent = o.kernel == 4;  // GS_KERNEL_SHARED: persistent, tile-major, XCD-aware
     switch (o.tile_shift) {
-        case 13: return tiled_chunk<P, 13>(ix, qb, q0, qt, o.chunk, persistent, o.whole, ws, ld, s, phase, stride, o.prune != 0);
-        case 14: return tiled_chunk<P, 14>(ix, qb, q0, qt, o.chunk, persistent, o.whole, ws, ld, s, phase, stride, o.prune != 0);
+        case 13: return launch_tiled<P, 13>(ix, qb, q0, qt, o, ws, s, phase);
+        case 14: return launch_tiled<P, 14>(ix, qb, q0, qt, o, ws, s, phase);
         case 15:
-            if constexpr (acc_form<P>() != kAccFx64)
-                return tiled_chunk<P, 15>(ix, qb, q0, qt, o.chunk, persistent, o.whole, ws, ld, s, phase, stride, o.prune != 0);
+            if constexpr (acc_form<P>() != kAccFx64) return launch_tiled<P, 15>(ix, qb, q0, qt, o, ws, s, phase);
             return hipErrorInvalidValue;  // 32768 64-bit accumulators exceed one CU's LDS
     }
     return hipErrorInvalidValue;
@@ -1763,6 +1740,21 @@ hipError_t launch_fill(void* p, int64_t n_words, uint32_t v, hipStream_t s) {
     const int64_t blocks = std::min<int64_t>((n_words + 255) / 256, 8192);
     hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)blocks), dim3(256), 0, s, (uint32_t*)p, n_words, v);
     GS_CHECK_LAUNCH("k_fill_u32");
+    return hipSuccess;
+}
+
+hipError_t launch_fill_rows(const DevIndex& ix, const int32_t* terms, void* rows, hipStream_t s) {
+    if (ix.n_rows <= 0 || ix.n_docs <= 0) return hipSuccess;
+    const int w = ix.precision == kFP32 ? 4 : ix.precision == kBF16 ? 2 : 1;
+    const hipError_t e = fill_u32(rows, ((ix.n_grains * ix.n_rows) << kGrainShift) * w / 4, s);
+    if (e != hipSuccess) return e;
+    for (int32_t r0 = 0; r0 < ix.n_rows; r0 += 32768) {  // grid rows
+        const dim3 grid((unsigned)std::min<int64_t>(ix.n_grains, 1024), (unsigned)std::min(ix.n_rows - r0, 32768));
+        if (w == 4) hipLaunchKernelGGL(k_fill_rows<uint32_t>, grid, dim3(256), 0, s, ix, terms, r0, (uint32_t*)rows);
+        else if (w == 2) hipLaunchKernelGGL(k_fill_rows<uint16_t>, grid, dim3(256), 0, s, ix, terms, r0, (uint16_t*)rows);
+        else hipLaunchKernelGGL(k_fill_rows<uint8_t>, grid, dim3(256), 0, s, ix, terms, r0, (uint8_t*)rows);
+        GS_CHECK_LAUNCH("k_fill_rows");
+    }
     return hipSuccess;
 }
 
