@@ -173,6 +173,25 @@ FixedPlan fixed_point_plan(int precision, int64_t m, const float* w, const float
     return p;
 }
 
+// First selection digit (FirstDigit) of a query: uint8 impacts, whose sums are at most maxs, and
+// float scores, at most the query weights times their terms' largest stored weights (and the
+// sums' error, with a margin that covers every accumulation's rounding).
+FirstDigit impact_digit(uint64_t maxs) {
+    int hb = 0;
+    while (hb < 64 && (maxs >> hb) != 0) hb++;
+    return FirstDigit{std::max(hb, kHistBits) - kHistBits, 0};
+}
+
+FirstDigit float_digit(int64_t m, const float* w, const float* tmax, double abs_err) {
+    double u = abs_err;
+    for (int64_t j = 0; j < m; j++) u += (double)w[j] * (double)tmax[j];
+    const float top = (float)(u * (1.0 + std::ldexp(1.0, -12)));
+    uint32_t bits;
+    std::memcpy(&bits, &top, 4);
+    const uint32_t t = bits >> kFirstShiftFloat;
+    return FirstDigit{kFirstShiftFloat, t > (uint32_t)kHistBins - 1 ? t - (uint32_t)(kHistBins - 1) : 0u};
+}
+
 // ----------------------------------------------------------- CSR checks --
 
 struct Rows {
@@ -434,7 +453,7 @@ struct BatchLayout {
         };
         rp = take((nq + 1) * 8);
         k = take(nq * 4);
-        fs = take(nq * 4);
+        fs = take(nq * sizeof(FirstDigit));
         delta = take(nq * 4);
         scale = take(nq * 8);
         err = take(nq * 8);
@@ -601,7 +620,7 @@ size_t arena_bytes(int64_t n_docs, int64_t rows, int32_t precision) {
     const size_t ld = (size_t)((n_docs + 63) / 64 * 64), R = (size_t)rows;
     size_t b = 0;
     b += align256(R * ld * 4);
-    b += 2 * align256(R * kHistBins * 4);
+    b += align256(R * kHistBins * 4);
     b += align256(R * sizeof(SelState));
     b += align256(R * kCandCap * 8);
     if (precision == kBF16) {
@@ -626,7 +645,6 @@ void carve_rows(void* base, int64_t n_docs, int64_t rows, int32_t precision, int
     ws->ld = (int64_t)ld;
     ws->scores = (uint32_t*)take(R * ld * 4) + o * ld;
     ws->hist1 = (uint32_t*)take(R * kHistBins * 4) + o * kHistBins;
-    ws->hist_ref = (uint32_t*)take(R * kHistBins * 4) + o * kHistBins;
     ws->state = (SelState*)take(R * sizeof(SelState)) + o;
     ws->cand = (unsigned long long*)take(R * kCandCap * 8) + o * kCandCap;
     ws->band_s = nullptr;
@@ -947,7 +965,7 @@ int32_t gs_batch_reserve(gs_index ix, int32_t max_queries, int64_t max_nnz, int3
     d.q_fx = (const double*)(m + L.fx);
     d.q_ub_cum = (const unsigned long long*)(m + L.ubcum);
     d.k = (const int32_t*)(m + L.k);
-    d.first_shift = (const int32_t*)(m + L.fs);
+    d.first = (const FirstDigit*)(m + L.fs);
     d.delta = (const float*)(m + L.delta);
     d.q_scale = (const double*)(m + L.scale);
     d.q_abs_err = (const double*)(m + L.err);
@@ -1000,7 +1018,7 @@ int32_t batch_update(gs_batch b, const int64_t* q_row_ptr, int32_t n_queries, co
     uint8_t* h = b->stage;
     int64_t* rp = (int64_t*)(h + L.rp);
     int32_t* kk = (int32_t*)(h + L.k);
-    int32_t* fshift = (int32_t*)(h + L.fs);
+    FirstDigit* first = (FirstDigit*)(h + L.fs);
     float* delta = (float*)(h + L.delta);
     double* qscale = (double*)(h + L.scale);
     double* qerr = (double*)(h + L.err);
@@ -1035,14 +1053,8 @@ int32_t batch_update(gs_batch b, const int64_t* q_row_ptr, int32_t n_queries, co
             tmax[(size_t)(j - rp[q])] = ix->term_max[(size_t)r.term[j]];
             tmin[(size_t)(j - rp[q])] = ix->term_min[(size_t)r.term[j]];
         }
-        if (ix->precision == kU8) {
-            int hb = 0;
-            while (hb < 64 && (maxs >> hb) != 0) hb++;
-            fshift[q] = 32 + std::max(hb, kHistBits) - kHistBits;
-        } else {
-            fshift[q] = kFirstShiftFloat;
-        }
         const FixedPlan fp = fixed_point_plan(ix->precision, m, r.w + rp[q], tmax.data(), tmin.data());
+        first[q] = ix->precision == kU8 ? impact_digit(maxs) : float_digit(m, r.w + rp[q], tmax.data(), fp.abs_err);
         qscale[q] = fp.scale;
         qerr[q] = fp.abs_err;
         qwide[q] = fp.wide_lim;
@@ -1326,7 +1338,7 @@ int32_t enqueue_search(gs_index ix, gs_batch b, int32_t nq, const Workspace& ws,
     // Fused candidate filtering (doc-tiled kernels): every stride-th tile seeds a lower bound
     // of the k-th composite; the other tiles append their candidates while they are scored.
     // The seed tiles should hold several times k documents: stride 8 up to k = 1024, 4 up to
-    // 2048, else off; it needs at least two seed tiles. It adds four launches to a search,
+    // 2048, else off; it needs at least two seed tiles. It adds two launches to a search,
     // which a few queries' row scans do not repay: searches of fewer than 32 queries scan.
     // the group kernel's groups span the whole batch: with query tiles it gives way to the
     // shared-traversal kernel
@@ -1353,7 +1365,7 @@ int32_t enqueue_search(gs_index ix, gs_batch b, int32_t nq, const Workspace& ws,
     for (int32_t q0 = 0; q0 < nq; q0 += qt) {
         const int32_t n = std::min(qt, nq - q0);
         // with from_row only the group kernel needs what is cleared (its step counters)
-        hipError_t e = from_row && so.kernel != GS_KERNEL_GROUP ? hipSuccess : launch_clear(ws, n, so.seed_stride > 0, s);
+        hipError_t e = from_row && so.kernel != GS_KERNEL_GROUP ? hipSuccess : launch_clear(ws, n, s);
         if (e == hipSuccess && ix->n_docs > 0) {
             const bool group = so.kernel == GS_KERNEL_GROUP;
             if (so.seed_stride == 0 || so.kernel == GS_KERNEL_ATOMIC || so.kernel == GS_KERNEL_DOCPAR) {
@@ -1373,7 +1385,7 @@ int32_t enqueue_search(gs_index ix, gs_batch b, int32_t nq, const Workspace& ws,
                 }
                 if (e == hipSuccess) {
                     SpanRecorder rec(timing ? 1 : -1, s, false);
-                    e = launch_seed_bound(ix->dev, b->dev, q0, n, ws, s, so.tile_shift, so.seed_stride);
+                    e = launch_seed_bound(ix->dev, b->dev, q0, n, ws, s);
                     rec.end(s);
                 }
                 if (e == hipSuccess) {

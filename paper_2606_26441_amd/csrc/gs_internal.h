@@ -28,7 +28,7 @@ constexpr int kHistBins = 1 << kHistBits;
 constexpr int kCandCap = 32768;       // candidates kept per query by the filter pass
 constexpr int kFusedCap = 24576;      // of which appended while scoring (fused filtering)
 constexpr int kRefinePasses = 6;      // enough to resolve any 64-bit composite key
-constexpr int kFirstShiftFloat = 52;  // first digit of a float key: bits 30..20
+constexpr int kFirstShiftFloat = 15;  // first digit of a float score: bits 30..15 (256 bins per octave)
 // LDS words of a scoring workgroup's histogram: the bins, then the count of zero scores (padded to 16 bytes)
 constexpr int kHistLds = kHistBins + 4;
 // Step counters of a search (kCounterWords words, cleared at its start): [8 phase ..] per-XCD work
@@ -111,6 +111,26 @@ struct ScoreItem {
     int32_t n;      // scoring terms | those with rows << 10; -1: k = 0
 };
 
+// First selection digit of a query: the score bits shifted right by `shift`, counted from `base`
+// in kHistBins bins (bin 0: all at or below it). Float scores: the eight octaves below the
+// query's largest possible score at 256 bins each, so that the bins near the k-th score are
+// within 0.4 % of each other (one pass bounds it closely) and a tile's documents spread over
+// hundreds of bins (digits of whole octaves had most of a wavefront's LDS adds on the same few
+// words). uint8 impacts: equal parts of the largest possible sum.
+struct FirstDigit {
+    int32_t shift;
+    uint32_t base;
+};
+__host__ __device__ inline uint32_t first_digit(const FirstDigit& f, uint32_t score_bits) {
+    const uint32_t t = score_bits >> f.shift;
+    const uint32_t d = t > f.base ? t - f.base : 0u;
+    return d < (uint32_t)kHistBins - 1 ? d : (uint32_t)kHistBins - 1;
+}
+// Smallest composite key of bin d.
+__host__ __device__ inline unsigned long long first_edge(const FirstDigit& f, uint32_t d) {
+    return d == 0 ? 0ull : (unsigned long long)(d + f.base) << (f.shift + 32);
+}
+
 // A query batch on the device.
 struct DevBatch {
     int32_t n_queries;
@@ -120,7 +140,7 @@ struct DevBatch {
     const float* q_w;          // [q_nnz]
     const int32_t* q_w8;       // [q_nnz] uint8 impacts as int (GS_U8), else null
     const int32_t* k;          // [n]
-    const int32_t* first_shift;  // [n] position of the first selection digit in the composite key
+    const FirstDigit* first;   // [n] first selection digit
     const float* delta;        // [n] bf16 relative error bound per query (GS_BF16), else null
     // fixed-point accumulation (GS_FP32, GS_BF16): each product w_q * w_d is rounded to an
     // integer number of units 2^-F(q) and summed exactly as an unsigned integer (64-bit for
@@ -175,14 +195,12 @@ struct alignas(16) SelState {
     int32_t rescore;
     int32_t pruned;             // 64-posting blocks skipped by block-max pruning
     int32_t zeros;              // zero-score documents among those counted in hist1
-    int32_t seed_rem;           // k_seed to k_seed_bound: composites still needed from its bin (prefix in lo)
 };
 
 // Workspace carve-up for a tile of qt queries.
 struct Workspace {
     uint32_t* scores;             // [qt][N] fp32 bits or int32
     uint32_t* hist1;              // [qt][kHistBins]
-    uint32_t* hist_ref;           // [qt][kHistBins]
     SelState* state;              // [qt]
     unsigned long long* cand;     // [qt][kCandCap]
     double* band_s;               // [qt][kCandCap] (bf16)
@@ -246,8 +264,8 @@ const int32_t* batch_diag(const struct ::gs_batch_s* b);
 // ---- launchers (gs_score.hip) ----
 // Fill the rows (zeroed here) of `terms` [ix.n_rows] (device) from their posting lists.
 hipError_t launch_fill_rows(const DevIndex& ix, const int32_t* terms, void* rows, hipStream_t s);
-// counters, selection state and first-digit histograms; with seeds, the seed histograms too
-hipError_t launch_clear(const Workspace& ws, int32_t qt, bool seeds, hipStream_t s);
+// counters, selection state and first-digit histograms
+hipError_t launch_clear(const Workspace& ws, int32_t qt, hipStream_t s);
 hipError_t launch_score_tiled(const DevIndex& ix, const DevBatch& qb, int32_t q0, int32_t qt,
                               const ScoreOpts& o, const Workspace& ws, hipStream_t s, int phase = 0);
 // group kernel (GS_KERNEL_GROUP): phases 0, 1 and 2 of a search whose queries form one tile
@@ -289,6 +307,6 @@ hipError_t launch_select(const DevIndex& ix, const DevBatch& qb, int32_t q0, int
                          const ScoreOpts* phase3 = nullptr, bool wide = false, bool from_row = false);
 // fused filtering: the bound of every query of the tile from its seed-tile histogram
 hipError_t launch_seed_bound(const DevIndex& ix, const DevBatch& qb, int32_t q0, int32_t qt,
-                             const Workspace& ws, hipStream_t s, int tile_shift, int stride);
+                             const Workspace& ws, hipStream_t s);
 
 }  // namespace gs

@@ -160,16 +160,16 @@ using AccOf = std::conditional_t<AF == kAccFx64, unsigned long long, std::condit
 
 // Write a finished LDS tile to its score row (write) and, with count, add it to the query's
 // first-digit histogram (hist: kHistLds words, zeroed by the caller) and its zero scores to the
-// query's count of them. The digit at fs (at least 32) lies in the composite key's score bits.
+// query's count of them.
 template <int BS, int AF>
-__device__ __forceinline__ void flush_tile(const void* acc_v, uint32_t* hist, int tile_n, uint32_t* Sq, int fs,
-                                           double scale, uint32_t* hist_out, SelState* st, bool write, bool count) {
+__device__ __forceinline__ void flush_tile(const void* acc_v, uint32_t* hist, int tile_n, uint32_t* Sq,
+                                           FirstDigit fd, double scale, uint32_t* hist_out, SelState* st, bool write, bool count) {
     using T = AccOf<AF>;
     const T* acc = reinterpret_cast<const T*>(acc_v);
-    const int tid = threadIdx.x, sh = fs - 32, n4 = tile_n >> 2;
+    const int tid = threadIdx.x, n4 = tile_n >> 2;
     int zc = 0;  // counted zero scores of this thread
     auto tally = [&](uint32_t v) {
-        atomicAdd(&hist[(v >> sh) & (kHistBins - 1)], 1u);
+        atomicAdd(&hist[first_digit(fd, v)], 1u);
         zc += v == 0u;
     };
     for (int i = tid; i < n4; i += BS) {
@@ -330,7 +330,8 @@ struct TileShared {
     // what the flush needs of the query (its selection state and histogram scaling)
     unsigned long long fl_bound;
     double fl_scale;
-    int fl_fused, fl_over, fl_shift;
+    int fl_fused, fl_over;
+    FirstDigit fl_first;
 };
 static_assert(kMaxQueryNnz <= 512 && kMaxQueryNnz % kWave == 0, "segment setup: one thread per query term");
 
@@ -400,7 +401,8 @@ __device__ __forceinline__ void score_tile(const DevIndex& ix, const DevBatch& q
     // under the setup, and leaves it in LDS (registers are what the accumulation runs short
     // of). The state is set before this launch; the cap flag may be set during it by other
     // workgroups, and a stale 0 only costs appends that the cap check drops.
-    int fl_fused = 0, fl_over = 0, fl_shift = 0;
+    int fl_fused = 0, fl_over = 0;
+    FirstDigit fl_first{0, 0};
     unsigned long long fl_bound = 0;
     double fl_scale = 1.0;
     if (threadIdx.x == BS - 1) {
@@ -408,7 +410,7 @@ __device__ __forceinline__ void score_tile(const DevIndex& ix, const DevBatch& q
         fl_fused = stq0->fused;
         fl_over = stq0->fused_over;
         fl_bound = stq0->bound;
-        fl_shift = qb.first_shift[q];
+        fl_first = qb.first[q];
         fl_scale = (FX && !W) ? qb.q_scale[q] : 1.0;
     }
     const int64_t N = ix.n_docs;
@@ -504,7 +506,7 @@ __device__ __forceinline__ void score_tile(const DevIndex& ix, const DevBatch& q
         sh.fl_fused = fl_fused;
         sh.fl_over = fl_over;
         sh.fl_bound = fl_bound;
-        sh.fl_shift = fl_shift;
+        sh.fl_first = fl_first;
         sh.fl_scale = fl_scale;
     }
     __syncthreads();
@@ -759,7 +761,7 @@ __device__ __forceinline__ void score_tile(const DevIndex& ix, const DevBatch& q
                                                reinterpret_cast<unsigned long long*>(hist), kHistBins / 2);
         return;
     }
-    flush_tile<BS, AF>(lds, hist, tile_n, S + (int64_t)ql * ld + base, sh.fl_shift, sh.fl_scale,
+    flush_tile<BS, AF>(lds, hist, tile_n, S + (int64_t)ql * ld + base, sh.fl_first, sh.fl_scale,
                        hist1 + (int64_t)ql * kHistBins, st, true, true);
 }
 
@@ -911,7 +913,7 @@ __device__ __forceinline__ void sum_rows(const DevIndex& ix, const ScoreTerm* __
 template <int P, int TS, int CH>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_score_tiled(
     DevIndex ix, const ScoreItem* __restrict__ items, const ScoreTerm* __restrict__ all_terms,
-    const int32_t* __restrict__ first_shift, const double* __restrict__ q_scale, int32_t q0, int32_t qt,
+    const FirstDigit* __restrict__ first, const double* __restrict__ q_scale, int32_t q0, int32_t qt,
     uint32_t* __restrict__ S, int64_t ld, uint32_t* __restrict__ hist1, int phase, int stride,
     SelState* __restrict__ state, unsigned long long* __restrict__ cand) {
     constexpr int BS = 512, NW = BS / kWave, TILE = 1 << TS, GPT = TS - kGrainShift;
@@ -1087,7 +1089,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
     __syncthreads();
     const double scale = FX ? q_scale[it.q] : 1.0;
     if (!fused_q)
-        flush_tile<BS, AF>(lds, hist, tile_n, S + (int64_t)ql * ld + base, first_shift[it.q], scale,
+        flush_tile<BS, AF>(lds, hist, tile_n, S + (int64_t)ql * ld + base, first[it.q], scale,
                            hist1 + (int64_t)ql * kHistBins, st, true, count);
     else if (!fl_over)
         flush_candidates<BS, AF, TILE>(lds, tile_n, base, scale, fl_bound, st, cand + (int64_t)ql * kCandCap,
@@ -1342,7 +1344,7 @@ __global__ __launch_bounds__(group_size<P>() * kMaxQueryNnz) __attribute__((amdg
             const uint32_t* tile_acc = lds + m * TILE * AW;
             const double scale = FX ? qb.q_scale[ql] : 1.0;
             if (!fused_q)
-                flush_tile<BS, AF>(tile_acc, hist, tile_n, S + (int64_t)ql * ld + base, qb.first_shift[ql], scale,
+                flush_tile<BS, AF>(tile_acc, hist, tile_n, S + (int64_t)ql * ld + base, qb.first[ql], scale,
                                    hist1 + (int64_t)ql * kHistBins, st, true, phase != kPhaseRows);
             else if (!st->fused_over)
                 flush_candidates<BS, AF, TILE>(tile_acc, tile_n, base, scale, st->bound, st, cand + (int64_t)ql * kCandCap,
@@ -1495,11 +1497,11 @@ __global__ __launch_bounds__(512) void k_hist1(DevBatch qb, int32_t q0, int64_t 
     for (int i = tid; i < kHistLds; i += 512) hist[i] = 0u;
     __syncthreads();
     int zc = 0;  // zero scores
-    const int fs = qb.first_shift[q0 + ql];
+    const FirstDigit fd = qb.first[q0 + ql];
     const int64_t d0 = (int64_t)blockIdx.x * per_block, d1 = min(N, d0 + per_block);
     const uint32_t* Sq = S + (int64_t)ql * ld;
     for (int64_t d = d0 + tid; d < d1; d += 512) {
-        atomicAdd(&hist[(comp_key(Sq[d], (uint32_t)d) >> fs) & (kHistBins - 1)], 1u);
+        atomicAdd(&hist[first_digit(fd, Sq[d])], 1u);
         zc += Sq[d] == 0u;
     }
     zc = wave_sum(zc);
@@ -1538,14 +1540,12 @@ __global__ __launch_bounds__(256) void k_fill_rows(DevIndex ix, const int32_t* _
 // The start of a search: its step counters, selection state and histograms, in one launch.
 static_assert(sizeof(SelState) % 16 == 0, "cleared 16 bytes at a time");
 __global__ __launch_bounds__(256) void k_clear(uint32_t* __restrict__ counters, uint4* __restrict__ state,
-                                               int64_t n_state, uint4* __restrict__ h1, int64_t n1,
-                                               uint4* __restrict__ h2, int64_t n2) {
+                                               int64_t n_state, uint4* __restrict__ h1, int64_t n1) {
     const uint4 z = make_uint4(0u, 0u, 0u, 0u);
     if (blockIdx.x == 0 && threadIdx.x < kCounterWords) counters[threadIdx.x] = 0u;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n_state + n1 + n2; i += (int64_t)gridDim.x * 256) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n_state + n1; i += (int64_t)gridDim.x * 256) {
         if (i < n_state) state[i] = z;
-        else if (i < n_state + n1) h1[i - n_state] = z;
-        else h2[i - n_state - n1] = z;
+        else h1[i - n_state] = z;
     }
 }
 
@@ -1584,7 +1584,7 @@ hipError_t launch_tiled_one(const DevIndex& ix, const DevBatch& qb, int32_t q0, 
     const int64_t per = (n_tiles * qt + 7) / 8, gx = std::min<int64_t>(per, 65536), gy = (per + gx - 1) / gx;
     const ScoreItem* items = o.whole ? qb.s_order : qb.s_item + q0;
     hipLaunchKernelGGL((k_score_tiled<P, TS, CH>), dim3((unsigned)(8 * gx), (unsigned)gy), dim3(512), lds, s, ix, items,
-                       qb.s_term, qb.first_shift, qb.q_scale, q0, qt, ws.scores, ld, ws.hist1,
+                       qb.s_term, qb.first, qb.q_scale, q0, qt, ws.scores, ld, ws.hist1,
                        phase, stride, ws.state, ws.cand);
     GS_CHECK_LAUNCH("k_score_tiled");
     return hipSuccess;
@@ -1758,11 +1758,11 @@ hipError_t launch_fill_rows(const DevIndex& ix, const int32_t* terms, void* rows
     return hipSuccess;
 }
 
-hipError_t launch_clear(const Workspace& ws, int32_t qt, bool seeds, hipStream_t s) {
+hipError_t launch_clear(const Workspace& ws, int32_t qt, hipStream_t s) {
     const int64_t n_state = (int64_t)qt * (sizeof(SelState) / 16), n_hist = (int64_t)qt * (kHistBins / 4);
-    const int64_t blocks = std::min<int64_t>((n_state + n_hist * (seeds ? 2 : 1) + 255) / 256, 2048);
+    const int64_t blocks = std::min<int64_t>((n_state + n_hist + 255) / 256, 2048);
     hipLaunchKernelGGL(k_clear, dim3((unsigned)blocks), dim3(256), 0, s, ws.counters, (uint4*)ws.state, n_state,
-                       (uint4*)ws.hist1, n_hist, (uint4*)ws.hist_ref, seeds ? n_hist : 0);
+                       (uint4*)ws.hist1, n_hist);
     GS_CHECK_LAUNCH("k_clear");
     return hipSuccess;
 }

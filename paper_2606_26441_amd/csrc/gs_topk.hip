@@ -30,8 +30,8 @@
 // other tiles, scoring phase 5).
 //
 // Fused candidate filtering (doc-tiled kernels, searches of 32+ queries): the
-// seed tiles (every 8th doc tile) are scored first; k_seed and k_seed_bound derive from them a
-// lower bound of each query's k-th composite (a 22-bit bucket edge); the other
+// seed tiles (every 8th doc tile) are scored first; k_seed_bound derives from their
+// histogram a lower bound of each query's k-th composite (a bin edge); the other
 // tiles append every composite at or above it while they are scored (then writing
 // no score rows for them and not counting them in the histogram), and step 3 scans
 // only the seed tiles. k_select falls back to the full row (no bound, too many
@@ -143,6 +143,10 @@ __device__ __forceinline__ void count_digit(const uint32_t* Sq, int64_t d0, int6
     }
 }
 
+// Bins below the k-th score's that hold the bf16 error band (2^-7 of the score, at most four
+// bins, and the band's absolute part).
+constexpr int kBandBins = 6;
+
 // pass 0 runs once every tile is scored; pass 1 runs after phase 3 for the queries that
 // fell back, whose histograms are complete only then (phase 2 counts the seed tiles of a
 // fused query only). One workgroup per query: the first digit, then, for a query whose
@@ -176,10 +180,11 @@ __global__ __launch_bounds__(kSelBS) void k_select(DevBatch qb, int32_t q0, int6
     uint32_t c[4], e[4];
     load_bins(h, c);
     scan_bins(c, e, (uint32_t)kq, sh);
-    const int d = sh.d, fs = qb.first_shift[q];
+    const int d = sh.d;
+    const FirstDigit fd = qb.first[q];
     if (pass == 0 && wide_check) {
         // lower edge of the k-th composite's bucket: its score bits with the low ones cleared
-        const float s_lo = __uint_as_float((uint32_t)(((unsigned long long)d << fs) >> 32));
+        const float s_lo = __uint_as_float((uint32_t)(first_edge(fd, d) >> 32));
         if ((double)s_lo < qb.q_wide_lim[q]) {
             // every lane has read its bins: the fp64 pass counts anew
             reinterpret_cast<uint4*>(h)[tid] = make_uint4(0u, 0u, 0u, 0u);
@@ -210,13 +215,18 @@ __global__ __launch_bounds__(kSelBS) void k_select(DevBatch qb, int32_t q0, int6
             lo = zero_floor(kq);
             kept = docs - st->zeros + min(kq, (int64_t)st->zeros);
             if (kept > kCandCap) resolved = 0;
-        } else if (precision == kBF16 && ge + h[d - 1] <= kCandCap) {
-            // one bin lower: the bf16 error band below the k-th score then lies inside the candidates
-            lo = (unsigned long long)(d - 1) << fs;
-            kept = ge + h[d - 1];
         } else if (ge <= kCandCap) {
-            lo = (unsigned long long)d << fs;
+            lo = first_edge(fd, d);
             kept = ge;
+            if (precision == kBF16 && d > kBandBins) {
+                // a few bins lower: the bf16 error band below the k-th score then lies inside the candidates
+                int64_t more = 0;
+                for (int j = 1; j <= kBandBins; j++) more += h[d - j];
+                if (ge + more <= kCandCap) {
+                    lo = first_edge(fd, d - kBandBins);
+                    kept = ge + more;
+                }
+            }
         } else {
             resolved = 0;
         }
@@ -235,9 +245,10 @@ __global__ __launch_bounds__(kSelBS) void k_select(DevBatch qb, int32_t q0, int6
         st->resolved = resolved;
         st->lo = lo;
         sh_open = open;
-        sh_prefix = (unsigned long long)d << fs;
-        sh_shift = fs;
-        sh_need = (int)(kq - sh.above);
+        // the refinement starts from the bin, or, for bin 0 (no one prefix), from the whole range
+        sh_prefix = first_edge(fd, d);
+        sh_shift = d == 0 ? 63 : fd.shift + 32;
+        sh_need = (int)(d == 0 ? kq : kq - sh.above);
     }
     __syncthreads();
     // refinement: 11 more bits of the threshold per pass over the row
@@ -268,58 +279,26 @@ __global__ __launch_bounds__(kSelBS) void k_select(DevBatch qb, int32_t q0, int6
     }
 }
 
-// Fused filtering, after the seed tiles are scored. The bound of a query is the
-// lower edge of a two-digit bucket (22 bits of the composite key) that holds the
-// k-th largest composite among the seed tiles' documents: every workgroup finds the
-// first-digit bin from the histogram the seed tiles built and counts the next digit
-// within that bin over its seed tile's scores, then k_seed_bound picks the sub-bin.
-// (Leaving that to the query's last workgroup saves its launch, but the device-scope
-// fences write back the L2s: 4.2 ms for 4,096 queries.) The k-th largest over all
-// documents is at least as large, so the bound never exceeds it; neither does
-// zero_floor, which keeps a query matched by few documents from appending every
-// zero-score one. With fewer than k seed documents there is no bound.
-__global__ __launch_bounds__(kSelBS) void k_seed(DevBatch qb, int32_t q0, int64_t N, const uint32_t* __restrict__ S,
-                                                 int64_t ld, int tile_shift, int stride,
-                                                 const uint32_t* __restrict__ hist1, SelState* __restrict__ state,
-                                                 uint32_t* __restrict__ hist_ref) {
-    __shared__ uint32_t hist[kHistBins];
+// Fused filtering, after the seed tiles are scored: the bound of a query is the lower edge of the
+// first-digit bin that holds the k-th largest composite among the seed tiles' documents (from the
+// histogram they built; a second digit counted over their rows, which made the bound exact to 22
+// bits, cost 54 us for 500 queries of 1M documents and 128 us for 4,096 of 250,000, and saved 3 %
+// of the candidates). The k-th largest over all documents is at least as large, so the bound
+// never exceeds it; neither does zero_floor, which keeps a query matched by few documents from
+// appending every zero-score one. With fewer than k seed documents there is no bound.
+__global__ __launch_bounds__(kSelBS) void k_seed_bound(DevBatch qb, int32_t q0, int64_t N,
+                                                       const uint32_t* __restrict__ hist1,
+                                                       SelState* __restrict__ state) {
     __shared__ BinScan sh;
-    const int tid = threadIdx.x, ql = blockIdx.y, q = q0 + ql;
+    const int ql = blockIdx.x, q = q0 + ql;
+    SelState* st = state + ql;
     const int64_t kq = kq_of(qb, q, N);
     if (kq == 0) return;  // fused stays 0 (cleared)
     uint32_t c[4], e[4];
     load_bins(hist1 + (int64_t)ql * kHistBins, c);
-    reinterpret_cast<uint4*>(hist)[tid] = make_uint4(0u, 0u, 0u, 0u);
     scan_bins(c, e, (uint32_t)kq, sh);
-    if ((int64_t)sh.above + sh.count < kq) return;
-    const int shift = qb.first_shift[q], nshift = max(shift - kHistBits, 0);
-    const unsigned long long prefix = (unsigned long long)sh.d << shift;
-    if (blockIdx.x == 0 && tid == 0) {
-        SelState* st = state + ql;
-        st->lo = prefix;
-        st->seed_rem = (int)(kq - sh.above);
-        st->fused = 2;  // refining
-    }
-    const int64_t d0 = ((int64_t)blockIdx.x * stride) << tile_shift, d1 = min(N, d0 + (1ll << tile_shift));
-    count_digit(S + (int64_t)ql * ld, d0, d1, shift, nshift, prefix >> shift, hist);
-    __syncthreads();
-    uint32_t* hr = hist_ref + (int64_t)ql * kHistBins;
-    for (int b = tid; b < kHistBins; b += kSelBS)
-        if (hist[b]) atomicAdd(&hr[b], hist[b]);
-}
-
-__global__ __launch_bounds__(kSelBS) void k_seed_bound(DevBatch qb, int32_t q0, int64_t N, SelState* __restrict__ state,
-                                                       const uint32_t* __restrict__ hist_ref) {
-    __shared__ BinScan sh;
-    const int ql = blockIdx.x, q = q0 + ql;
-    SelState* st = state + ql;
-    if (st->fused != 2) return;
-    uint32_t c[4], e[4];
-    load_bins(hist_ref + (int64_t)ql * kHistBins, c);
-    scan_bins(c, e, (uint32_t)st->seed_rem, sh);
-    if (threadIdx.x != 0) return;
-    const int nshift = max(qb.first_shift[q] - kHistBits, 0);
-    const unsigned long long b = st->lo | ((unsigned long long)sh.d << nshift), z = zero_floor(kq_of(qb, q, N));
+    if (threadIdx.x != 0 || (int64_t)sh.above + sh.count < kq) return;
+    const unsigned long long b = first_edge(qb.first[q], sh.d), z = zero_floor(kq);
     st->bound = b > z ? b : z;
     st->fused = 1;
 }
@@ -1104,15 +1083,9 @@ __global__ __launch_bounds__(kSelBS) void k_band_topk(DevIndex ix, DevBatch qb, 
 }  // namespace
 
 hipError_t launch_seed_bound(const DevIndex& ix, const DevBatch& qb, int32_t q0, int32_t qt, const Workspace& ws,
-                             hipStream_t s, int tile_shift, int stride) {
-    const int64_t n_tiles = (ix.n_docs + (1ll << tile_shift) - 1) >> tile_shift;
-    const int64_t seeds = (n_tiles + stride - 1) / stride;
-    hipLaunchKernelGGL(k_seed, dim3((unsigned)seeds, (unsigned)qt), dim3(kSelBS), 0, s, qb, q0, ix.n_docs,
-                       (const uint32_t*)ws.scores, ws.ld, tile_shift, stride, (const uint32_t*)ws.hist1, ws.state,
-                       ws.hist_ref);
-    GS_CHECK_LAUNCH("k_seed");
-    hipLaunchKernelGGL(k_seed_bound, dim3(qt), dim3(kSelBS), 0, s, qb, q0, ix.n_docs, ws.state,
-                       (const uint32_t*)ws.hist_ref);
+                             hipStream_t s) {
+    hipLaunchKernelGGL(k_seed_bound, dim3(qt), dim3(kSelBS), 0, s, qb, q0, ix.n_docs, (const uint32_t*)ws.hist1,
+                       ws.state);
     GS_CHECK_LAUNCH("k_seed_bound");
     return hipSuccess;
 }
