@@ -150,8 +150,18 @@ def _check(rc: int, where: str):
         raise GsError(rc, where, lib.gs_last_error().decode())
 
 
+_DTYPES = {t: np.dtype(t) for t in (np.int32, np.int64, np.float32)}
+
+
 def _np(a, dtype):
+    if type(a) is np.ndarray and a.dtype is _DTYPES[dtype] and a.flags.c_contiguous:
+        return a
     return np.ascontiguousarray(np.asarray(a), dtype=dtype)
+
+
+def _ptr(a: np.ndarray) -> int:
+    """Address of an array's data (a.ctypes.data builds an object per call)."""
+    return a.__array_interface__["data"][0]
 
 
 def _stream_ptr(stream=None) -> int:
@@ -209,7 +219,7 @@ class Index:
         self.precision = PRECISIONS[precision] if isinstance(precision, str) else int(precision)
         flags = (GS_KEEP_FORWARD if keep_forward else 0) | (GS_KEEP_DOC_IDS if keep_doc_ids else 0)
         h = ctypes.c_void_p()
-        _check(lib.gs_build_index(rp.ctypes.data, rp.shape[0] - 1, t.ctypes.data, w.ctypes.data, t.shape[0], vocab,
+        _check(lib.gs_build_index(_ptr(rp), rp.shape[0] - 1, _ptr(t), _ptr(w), t.shape[0], vocab,
                                   self.precision, flags, _stream_ptr(stream), ctypes.byref(h)), "gs_build_index")
         self._h = h
         self.vocab = vocab
@@ -233,7 +243,7 @@ class Index:
         """uint8 [vocab]: 1 where the term's doc ids have the byte form (every 64-block spans <= 256 docs)."""
         v = self.info().vocab_size
         out = np.zeros(v, dtype=np.uint8)
-        _check(lib.gs_index_dense_terms(self._h, out.ctypes.data, v), "gs_index_dense_terms")
+        _check(lib.gs_index_dense_terms(self._h, _ptr(out), v), "gs_index_dense_terms")
         return out
 
     @property
@@ -298,7 +308,7 @@ class Index:
             workspace = self.workspace(max(1, min(nq, 64)), opts)
         ids = torch.empty((nq, k_max), dtype=torch.int32, device=workspace.device)
         scores = torch.empty((nq, k_max), dtype=SCORE_DTYPES[self.precision], device=workspace.device)
-        _check(lib.gs_search(self._h, rp.ctypes.data, nq, t.ctypes.data, w.ctypes.data, t.shape[0], kk.ctypes.data,
+        _check(lib.gs_search(self._h, _ptr(rp), nq, _ptr(t), _ptr(w), t.shape[0], _ptr(kk),
                              k_max, workspace.data_ptr(), workspace.numel(), ids.data_ptr(), scores.data_ptr(),
                              ctypes.byref(opts) if opts else None, _stream_ptr(stream)), "gs_search")
         return ids, scores
@@ -355,8 +365,8 @@ class Batch:
         self.k_max = int(kk.max()) if k_max is None and nq else int(k_max or 0)
         self.n_queries = nq
         h = ctypes.c_void_p()
-        _check(lib.gs_batch_create(index.handle, rp.ctypes.data, nq, t.ctypes.data, w.ctypes.data, t.shape[0],
-                                   kk.ctypes.data, self.k_max, _stream_ptr(stream), ctypes.byref(h)),
+        _check(lib.gs_batch_create(index.handle, _ptr(rp), nq, _ptr(t), _ptr(w), t.shape[0],
+                                   _ptr(kk), self.k_max, _stream_ptr(stream), ctypes.byref(h)),
                "gs_batch_create")
         self._h = h
         self._index = index
@@ -377,8 +387,8 @@ class Batch:
         rp, t, w = _np(queries.row_ptr, np.int64), _np(queries.terms, np.int32), _np(queries.weights, np.float32)
         nq = rp.shape[0] - 1
         kk = np.broadcast_to(np.asarray(k, dtype=np.int32), (nq,)).copy()
-        _check(lib.gs_batch_update(self._h, rp.ctypes.data, nq, t.ctypes.data, w.ctypes.data, t.shape[0],
-                                   kk.ctypes.data, _stream_ptr(stream)), "gs_batch_update")
+        _check(lib.gs_batch_update(self._h, _ptr(rp), nq, _ptr(t), _ptr(w), t.shape[0],
+                                   _ptr(kk), _stream_ptr(stream)), "gs_batch_update")
         self.k = np.zeros(self.n_queries, np.int32)
         self.k[:nq] = kk
 
@@ -391,7 +401,7 @@ class Batch:
         again (0 no, 1 fused-filtering fallback, 2 wide range: fp64 pass), fused filtering used,
         64-posting blocks skipped by pruning, 0."""
         out = np.zeros((self.n_queries, 8), dtype=np.int32)
-        _check(lib.gs_batch_diagnostics(self._h, out.ctypes.data), "gs_batch_diagnostics")
+        _check(lib.gs_batch_diagnostics(self._h, _ptr(out)), "gs_batch_diagnostics")
         return out
 
     def close(self):
@@ -451,7 +461,7 @@ class Server:
 
     def submit(self, terms, weights, k: int) -> int:
         t, w = _np(terms, np.int32), _np(weights, np.float32)
-        r = lib.gs_server_submit(self._h, t.ctypes.data, w.ctypes.data, t.shape[0], int(k))
+        r = lib.gs_server_submit(self._h, _ptr(t), _ptr(w), t.shape[0], int(k))
         if r < 0:
             raise GsError(int(r), "gs_server_submit", lib.gs_last_error().decode())
         return int(r)
@@ -461,7 +471,7 @@ class Server:
         ids = np.empty(max(k, 1), np.int32)
         sc = np.empty(max(k, 1), self.score_dtype)
         lat = ctypes.c_double(0)
-        _check(lib.gs_server_wait(self._h, int(ticket), int(timeout_ms), ids.ctypes.data, sc.ctypes.data,
+        _check(lib.gs_server_wait(self._h, int(ticket), int(timeout_ms), _ptr(ids), _ptr(sc),
                                   ctypes.byref(lat)), "gs_server_wait")
         return ids[:k], sc[:k], lat.value
 
@@ -470,7 +480,7 @@ class Server:
         ids = np.empty(max(k, 1), np.int32)
         sc = np.empty(max(k, 1), self.score_dtype)
         lat = ctypes.c_double(0)
-        rc = lib.gs_server_poll(self._h, int(ticket), ids.ctypes.data, sc.ctypes.data, ctypes.byref(lat))
+        rc = lib.gs_server_poll(self._h, int(ticket), _ptr(ids), _ptr(sc), ctypes.byref(lat))
         if rc == GS_ETIMEOUT:
             return None
         _check(rc, "gs_server_poll")

@@ -109,8 +109,11 @@ inline float bf16_widen(uint16_t b) {
 
 // uint8 impact: round(w * 255 / 3) with ties to even, saturated to [0, 255].
 inline uint8_t q8(float w) {
-    const double x = std::nearbyint((double)w * 85.0);
-    return x > 255.0 ? 255 : (x > 0.0 ? (uint8_t)x : 0);
+    const double x = (double)w * 85.0;
+    if (!(x < 255.0)) return 255;
+    if (!(x > 0.0)) return 0;
+    constexpr double kRound = 6755399441055744.0;  // 1.5 * 2^52: adding it rounds to an integer, ties to even
+    return (uint8_t)((x + kRound) - kRound);
 }
 
 }  // namespace
@@ -417,24 +420,35 @@ void byte_form(const Layout& L, std::vector<uint8_t>& dense, std::vector<uint8_t
 
 // ===================================================================== API ==
 
+// What a batch update needs of a term, side by side (it looks up a few thousand terms at random).
+struct TermInfo {
+    float max = 0.0f;                                    // largest stored weight (value of the stored form)
+    float min = std::numeric_limits<float>::infinity();  // smallest positive one (+inf if none)
+    int32_t len = 0;                                     // postings
+    int32_t row = -1;                                    // row of the term, or -1
+};
+
 struct gs_index_s {
     int device = 0;
     int64_t n_docs = 0, nnz = 0, padded = 0, n_grains = 0;
     int64_t n_dense = 0;              // terms whose lists have the byte doc-id form
-    std::vector<int32_t> row_slot;    // [V] row of the term, or -1
     int32_t n_rows = 0;               // terms with a row
     std::vector<uint8_t> term_dense;  // [V] host copy of the byte-form flags
     int32_t vocab = 0, precision = 0;
     uint32_t flags = 0;
     size_t bytes = 0;
-    std::vector<float> term_max;  // largest stored weight of each term (value of the stored form)
-    std::vector<float> term_min;  // smallest positive stored weight of each term (+inf if none)
-    std::vector<int32_t> term_len;  // postings per term (host copy, for work estimates)
+    std::vector<TermInfo> terms;  // [V]
     std::vector<void*> allocs;
     DevIndex dev{};
-    ~gs_index_s() {
-        for (void* p : allocs) (void)hipFree(p);
-    }
+    // batches of finished gs_search calls, kept for the next ones (at most kPoolBatches, each of at
+    // most kPoolBytes; freed with the index). A call takes one out or allocates; calls on other
+    // threads and streams take others.
+    static constexpr int kPoolBatches = 4;
+    static constexpr size_t kPoolBytes = (size_t)1 << 20;
+    std::mutex pool_mu;
+    gs_batch pool[kPoolBatches] = {};
+    int n_pool = 0;
+    ~gs_index_s();
 };
 
 // Byte offsets of a batch's arrays inside its one device allocation (and the
@@ -486,6 +500,7 @@ struct gs_batch_s {
     int64_t q_nnz = 0;                 // capacity in query terms
     int32_t n_active = 0;              // queries set by the last update
     bool any_wide = false;             // one of them has a wide-range limit (q_wide_lim > 0)
+    size_t bytes = 0;  // of dmem and of stage (at least lay.total)
     BatchLayout lay{0, 0};
     uint8_t* dmem = nullptr;    // device: every array of the batch
     uint8_t* stage = nullptr;   // pinned host copy of the same layout (update staging)
@@ -500,6 +515,11 @@ struct gs_batch_s {
         if (stage) (void)hipHostFree(stage);
     }
 };
+
+gs_index_s::~gs_index_s() {
+    for (int i = 0; i < n_pool; i++) delete pool[i];
+    for (void* p : allocs) (void)hipFree(p);
+}
 
 namespace {
 
@@ -525,17 +545,16 @@ int32_t build_rows(gs_index ix, hipStream_t s) {
     DevIndex& d = ix->dev;
     std::vector<int32_t> terms;
     try {
-        ix->row_slot.assign((size_t)ix->vocab, -1);
         for (int32_t v = 0; v < ix->vocab; v++)
-            if (ix->term_len[(size_t)v] > 0 && (int64_t)ix->term_len[(size_t)v] * kRowShare >= ix->n_docs) terms.push_back(v);
+            if (ix->terms[(size_t)v].len > 0 && (int64_t)ix->terms[(size_t)v].len * kRowShare >= ix->n_docs) terms.push_back(v);
         std::stable_sort(terms.begin(), terms.end(), [&](int32_t a, int32_t b) {
-            return ix->term_len[(size_t)a] > ix->term_len[(size_t)b];
+            return ix->terms[(size_t)a].len > ix->terms[(size_t)b].len;
         });
     } catch (const std::bad_alloc&) {
         return fail(GS_ENOMEM, "host memory for the row table");
     }
     const int64_t w = ix->precision == kFP32 ? 4 : ix->precision == kBF16 ? 2 : 1;
-    for (size_t i = 0; i < terms.size(); i++) ix->row_slot[(size_t)terms[i]] = (int32_t)i;
+    for (size_t i = 0; i < terms.size(); i++) ix->terms[(size_t)terms[i]].row = (int32_t)i;
     ix->n_rows = (int32_t)terms.size();
     d.n_rows = ix->n_rows;
     int32_t* pt = nullptr;
@@ -667,6 +686,114 @@ void carve_workspace(void* base, int64_t n_docs, int32_t qt, int32_t precision, 
 
 }  // namespace gs
 
+namespace {
+
+// Device arrays and pinned stage of a batch.
+int32_t batch_alloc(gs_index ix, size_t bytes, gs_batch* out) {
+    gs_batch b = new (std::nothrow) gs_batch_s();
+    if (!b) return fail(GS_ENOMEM, "host allocation failed");
+    b->index = ix;
+    b->device = ix->device;
+    b->bytes = bytes;
+    hipError_t e = dev_malloc((void**)&b->dmem, bytes);
+    if (e == hipSuccess) e = pinned_malloc((void**)&b->stage, bytes);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&b->copied, hipEventDisableTiming);
+    if (e != hipSuccess) {
+        delete b;
+        return fail(e == hipErrorOutOfMemory ? GS_ENOMEM : GS_EHIP,
+                    std::string("batch allocation: ") + hipGetErrorString(e));
+    }
+    *out = b;
+    return GS_OK;
+}
+
+// Capacity of a batch: the layout of its arrays inside its allocation.
+void batch_shape(gs_batch b, int32_t max_queries, int64_t max_nnz, int32_t k_max) {
+    b->n_queries = max_queries;
+    b->k_max = k_max;
+    b->q_nnz = max_nnz;
+    b->lay = BatchLayout((size_t)max_queries, (size_t)max_nnz);
+    const BatchLayout& L = b->lay;
+    uint8_t* m = b->dmem;
+    DevBatch& d = b->dev;
+    d.n_queries = max_queries;
+    d.k_max = k_max;
+    d.q_row_ptr = (const int64_t*)(m + L.rp);
+    d.q_term = (const int32_t*)(m + L.term);
+    d.q_w = (const float*)(m + L.w);
+    d.q_w8 = (const int32_t*)(m + L.w8);
+    d.q_fx = (const double*)(m + L.fx);
+    d.q_ub_cum = (const unsigned long long*)(m + L.ubcum);
+    d.k = (const int32_t*)(m + L.k);
+    d.first = (const FirstDigit*)(m + L.fs);
+    d.delta = (const float*)(m + L.delta);
+    d.q_scale = (const double*)(m + L.scale);
+    d.q_abs_err = (const double*)(m + L.err);
+    d.q_wide_lim = (const double*)(m + L.wide);
+    d.g_count = (const int32_t*)(m + L.gcount);
+    d.g_member = (const int32_t*)(m + L.gmember);
+    d.g_row = (const int32_t*)(m + L.grow);
+    d.g_term = (const int32_t*)(m + L.gterm);
+    d.g_wq = (const float*)(m + L.gwfx);
+    d.g_w8 = (const int32_t*)(m + L.gw8);
+    d.q_work = (const int64_t*)(m + L.work);
+    d.s_term = (const ScoreTerm*)(m + L.sterm);
+    d.s_item = (const ScoreItem*)(m + L.item);
+    d.s_order = (const ScoreItem*)(m + L.order);
+    b->diag = (int32_t*)(m + L.diag);
+}
+
+// The checks of a batch's dimensions, then a batch of that capacity (not yet filled). With pooled,
+// a batch of the index's pool where one is large enough.
+int32_t batch_new(gs_index ix, int32_t max_queries, int64_t max_nnz, int32_t k_max, gs_batch* b, gs_batch* out,
+                  bool pooled = false) {
+    g_err.clear();
+    if (!out) return fail(GS_EINVAL, "out is null");
+    *out = nullptr;
+    if (!ix) return fail(GS_EINVAL, "index is null");
+    if (max_queries < 0 || max_nnz < 0) return fail(GS_EINVAL, "negative capacity");
+    if (k_max < 0 || k_max > GS_MAX_K) return fail(GS_EINVAL, "k_max must be in [0, GS_MAX_K]");
+    DeviceGuard g(ix->device);
+    size_t bytes = BatchLayout((size_t)max_queries, (size_t)max_nnz).total;
+    *b = nullptr;
+    if (pooled && bytes <= gs_index_s::kPoolBytes) {
+        {
+            std::lock_guard<std::mutex> l(ix->pool_mu);
+            for (int i = 0; i < ix->n_pool; i++)
+                if (ix->pool[i]->bytes >= bytes) {
+                    *b = ix->pool[i];
+                    ix->pool[i] = ix->pool[--ix->n_pool];
+                    break;
+                }
+        }
+        size_t up = (size_t)1 << 16;  // sizes that later calls are likely to fit
+        while (up < bytes) up *= 2;
+        bytes = up;
+    }
+    if (!*b) {
+        const int32_t rc = batch_alloc(ix, bytes, b);
+        if (rc != GS_OK) return rc;
+    }
+    batch_shape(*b, max_queries, max_nnz, k_max);
+    return GS_OK;
+}
+
+// Back to the index's pool, or freed. Nothing on any stream may still use the batch.
+void batch_return(gs_batch b) {
+    {
+        gs_index ix = b->index;
+        std::lock_guard<std::mutex> l(ix->pool_mu);
+        if (b->bytes <= gs_index_s::kPoolBytes && ix->n_pool < gs_index_s::kPoolBatches) {
+            ix->pool[ix->n_pool++] = b;
+            return;
+        }
+    }
+    DeviceGuard g(b->device);
+    delete b;
+}
+
+}  // namespace
+
 extern "C" {
 
 const char* gs_version(void) { return "gpusparse-mi355x 0.1 (gfx950)"; }
@@ -780,12 +907,18 @@ int32_t gs_build_index(const int64_t* row_ptr, int64_t n_docs, const int32_t* te
     ix->precision = precision;
     if (precision == kBF16) flags |= GS_KEEP_FORWARD;
     ix->flags = flags;
-    ix->term_len = L.term_len;
-    ix->term_max.assign((size_t)vocab_size, 0.0f);
-    for (int32_t v = 0; v < vocab_size; v++)
+    try {
+        ix->terms.assign((size_t)vocab_size, TermInfo{});
+    } catch (const std::bad_alloc&) {
+        delete ix;
+        return fail(GS_ENOMEM, "host memory for the term table");
+    }
+    for (int32_t v = 0; v < vocab_size; v++) {
+        TermInfo& t = ix->terms[(size_t)v];
+        t.len = L.term_len[(size_t)v];
         for (int64_t k = L.term_off[(size_t)v] / kBlock; k < L.term_off[(size_t)v + 1] / kBlock; k++)
-            ix->term_max[(size_t)v] = std::max(ix->term_max[(size_t)v], L.blk_max[(size_t)k]);
-    ix->term_min.assign((size_t)vocab_size, std::numeric_limits<float>::infinity());
+            t.max = std::max(t.max, L.blk_max[(size_t)k]);
+    }
     parallel_for(vocab_size, [&](int, int64_t a, int64_t b) {
         for (int64_t v = a; v < b; v++) {
             float m = std::numeric_limits<float>::infinity();
@@ -793,7 +926,7 @@ int32_t gs_build_index(const int64_t* row_ptr, int64_t n_docs, const int32_t* te
                 const float w = stored_weight(L, i);
                 if (w > 0.0f) m = std::min(m, w);
             }
-            ix->term_min[(size_t)v] = m;
+            ix->terms[(size_t)v].min = m;
         }
     });
     DevIndex& d = ix->dev;
@@ -925,66 +1058,15 @@ void gs_free_index(gs_index ix) {
 }
 
 int32_t gs_batch_reserve(gs_index ix, int32_t max_queries, int64_t max_nnz, int32_t k_max, gs_batch* out) {
-    g_err.clear();
-    if (!out) return fail(GS_EINVAL, "out is null");
-    *out = nullptr;
-    if (!ix) return fail(GS_EINVAL, "index is null");
-    if (max_queries < 0 || max_nnz < 0) return fail(GS_EINVAL, "negative capacity");
-    if (k_max < 0 || k_max > GS_MAX_K) return fail(GS_EINVAL, "k_max must be in [0, GS_MAX_K]");
-    DeviceGuard g(ix->device);
-    gs_batch b = new (std::nothrow) gs_batch_s();
-    if (!b) return fail(GS_ENOMEM, "host allocation failed");
-    b->index = ix;
-    b->device = ix->device;
-    b->n_queries = max_queries;
-    b->k_max = k_max;
-    b->q_nnz = max_nnz;
-    auto done = [&](int32_t code) {
-        if (code != GS_OK) delete b;
-        return code;
-    };
-    const size_t nq = (size_t)max_queries, nz = (size_t)max_nnz;
-    b->lay = BatchLayout(nq, nz);
-    const BatchLayout& L = b->lay;
-    {
-        hipError_t e = dev_malloc((void**)&b->dmem, L.total);
-        if (e == hipSuccess) e = pinned_malloc((void**)&b->stage, L.total);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&b->copied, hipEventDisableTiming);
-        if (e != hipSuccess)
-            return done(fail(e == hipErrorOutOfMemory ? GS_ENOMEM : GS_EHIP,
-                             std::string("batch allocation: ") + hipGetErrorString(e)));
-    }
-    uint8_t* m = b->dmem;
-    DevBatch& d = b->dev;
-    d.n_queries = max_queries;
-    d.k_max = k_max;
-    d.q_row_ptr = (const int64_t*)(m + L.rp);
-    d.q_term = (const int32_t*)(m + L.term);
-    d.q_w = (const float*)(m + L.w);
-    d.q_w8 = (const int32_t*)(m + L.w8);
-    d.q_fx = (const double*)(m + L.fx);
-    d.q_ub_cum = (const unsigned long long*)(m + L.ubcum);
-    d.k = (const int32_t*)(m + L.k);
-    d.first = (const FirstDigit*)(m + L.fs);
-    d.delta = (const float*)(m + L.delta);
-    d.q_scale = (const double*)(m + L.scale);
-    d.q_abs_err = (const double*)(m + L.err);
-    d.q_wide_lim = (const double*)(m + L.wide);
-    d.g_count = (const int32_t*)(m + L.gcount);
-    d.g_member = (const int32_t*)(m + L.gmember);
-    d.g_row = (const int32_t*)(m + L.grow);
-    d.g_term = (const int32_t*)(m + L.gterm);
-    d.g_wq = (const float*)(m + L.gwfx);
-    d.g_w8 = (const int32_t*)(m + L.gw8);
-    d.q_work = (const int64_t*)(m + L.work);
-    d.s_term = (const ScoreTerm*)(m + L.sterm);
-    d.s_item = (const ScoreItem*)(m + L.item);
-    d.s_order = (const ScoreItem*)(m + L.order);
-    b->diag = (int32_t*)(m + L.diag);
+    gs_batch b = nullptr;
+    int32_t rc = batch_new(ix, max_queries, max_nnz, k_max, &b, out);
+    if (rc != GS_OK) return rc;
     // an empty batch until the first update: every slot is a query with no terms and k = 0
-    std::vector<int64_t> zero_rp(nq + 1, 0);
-    int32_t rc2 = gs_batch_update(b, zero_rp.data(), 0, nullptr, nullptr, 0, nullptr, nullptr);
-    if (rc2 != GS_OK) return done(rc2);
+    rc = gs_batch_update(b, nullptr, 0, nullptr, nullptr, 0, nullptr, nullptr);
+    if (rc != GS_OK) {
+        delete b;
+        return rc;
+    }
     *out = b;
     return GS_OK;
 }
@@ -1038,7 +1120,9 @@ int32_t batch_update(gs_batch b, const int64_t* q_row_ptr, int32_t n_queries, co
     ScoreTerm* sterm = (ScoreTerm*)(h + L.sterm);
     ScoreItem* item = (ScoreItem*)(h + L.item);
     int64_t n_sterm = 0;
+    std::vector<ScoreTerm> rest;
     std::vector<float> tmax, tmin;
+    std::vector<unsigned long long> ub;
     bool any_wide = false;
     for (int32_t q = 0; q < cap; q++) {
         uint64_t maxs = 0;
@@ -1047,11 +1131,12 @@ int32_t batch_update(gs_batch b, const int64_t* q_row_ptr, int32_t n_queries, co
         tmax.resize((size_t)m);
         tmin.resize((size_t)m);
         for (int64_t j = rp[q]; j < rp[q + 1]; j++) {
-            qwork[q] += ix->term_len[(size_t)r.term[j]];
+            const TermInfo& t = ix->terms[(size_t)r.term[j]];
+            qwork[q] += t.len;
             w8[j] = q8(r.w[j]);
             maxs += (uint64_t)w8[j] * 255u;
-            tmax[(size_t)(j - rp[q])] = ix->term_max[(size_t)r.term[j]];
-            tmin[(size_t)(j - rp[q])] = ix->term_min[(size_t)r.term[j]];
+            tmax[(size_t)(j - rp[q])] = t.max;
+            tmin[(size_t)(j - rp[q])] = t.min;
         }
         const FixedPlan fp = fixed_point_plan(ix->precision, m, r.w + rp[q], tmax.data(), tmin.data());
         first[q] = ix->precision == kU8 ? impact_digit(maxs) : float_digit(m, r.w + rp[q], tmax.data(), fp.abs_err);
@@ -1059,23 +1144,25 @@ int32_t batch_update(gs_batch b, const int64_t* q_row_ptr, int32_t n_queries, co
         qerr[q] = fp.abs_err;
         qwide[q] = fp.wide_lim;
         any_wide = any_wide || (fp.wide_lim > 0.0 && kk[q] > 0);
-        for (int64_t j = rp[q]; j < rp[q + 1]; j++) qfx[j] = std::ldexp((double)r.w[j], fp.F);
+        const double two_f = std::ldexp(1.0, fp.F);  // |F| <= 1000
+        for (int64_t j = rp[q]; j < rp[q + 1]; j++) qfx[j] = (double)r.w[j] * two_f;
         // the scoring terms: those with rows first, by row
         {
+            const bool u8 = ix->precision == kU8;
+            rest.clear();
             int32_t n = 0, n_row = 0;
             for (int64_t j = rp[q]; j < rp[q + 1]; j++) {
-                const bool u8 = ix->precision == kU8;
                 if (!(u8 ? w8[j] > 0 : qfx[j] > 0.0)) continue;  // adds nothing
-                ScoreTerm t{r.term[j], ix->row_slot[(size_t)r.term[j]], 0};
+                ScoreTerm t{r.term[j], ix->terms[(size_t)r.term[j]].row, 0};
                 if (u8) t.q = (unsigned long long)w8[j];
                 else std::memcpy(&t.q, &qfx[j], 8);
-                sterm[n_sterm + n++] = t;
-                n_row += t.row >= 0;
+                if (t.row >= 0) sterm[n_sterm + n_row++] = t;
+                else rest.push_back(t);
             }
-            std::sort(sterm + n_sterm, sterm + n_sterm + n, [](const ScoreTerm& x, const ScoreTerm& y) {
-                if ((x.row >= 0) != (y.row >= 0)) return x.row >= 0;
-                return x.row >= 0 ? x.row < y.row : x.term < y.term;
-            });
+            std::sort(sterm + n_sterm, sterm + n_sterm + n_row,
+                      [](const ScoreTerm& x, const ScoreTerm& y) { return x.row < y.row; });
+            std::copy(rest.begin(), rest.end(), sterm + n_sterm + n_row);
+            n = n_row + (int32_t)rest.size();
             item[q] = ScoreItem{n_sterm, q, kk[q] > 0 ? n | n_row << 10 : -1};
             n_sterm += n;
         }
@@ -1084,20 +1171,23 @@ int32_t batch_update(gs_batch b, const int64_t* q_row_ptr, int32_t n_queries, co
         // rounding; uint8: the exact integer product), then per term the sum of the bounds of
         // the terms up to it in ascending order of bound (ties by position).
         {
-            std::vector<std::pair<unsigned long long, int64_t>> ub;
-            ub.reserve((size_t)m);
-            for (int64_t j = rp[q]; j < rp[q + 1]; j++) {
-                const double tm = (double)ix->term_max[(size_t)r.term[j]];
+            // (bounds are at most 2^51 + 2: sorted with the term's position, up to 255, below them;
+            // bf16 searches do not prune)
+            ub.clear();
+            for (int64_t j = rp[q]; j < rp[q + 1] && ix->precision != kBF16; j++) {
+                const double tm = (double)tmax[(size_t)(j - rp[q])];
+                const double v = qfx[j] * tm;  // below 2^51
+                const unsigned long long t = (unsigned long long)v;
                 const unsigned long long u = ix->precision == kU8
                                                  ? (unsigned long long)w8[j] * (unsigned long long)tm
-                                                 : (unsigned long long)std::ceil(qfx[j] * tm) + 1ull;
-                ub.emplace_back(u, j);
+                                                 : t + ((double)t < v) + 1ull;
+                ub.push_back(u << 8 | (unsigned long long)(j - rp[q]));
             }
             std::sort(ub.begin(), ub.end());
             unsigned long long run = 0;
-            for (const auto& e : ub) {
-                run += e.first;
-                qub[e.second] = run;
+            for (const unsigned long long e : ub) {
+                run += e >> 8;
+                qub[rp[q] + (int64_t)(e & 255)] = run;
             }
         }
         // bf16 form: relative error of a stored weight (2^-8) and of the fp32 score (2^-24, with margin)
@@ -1156,21 +1246,35 @@ int32_t batch_update(gs_batch b, const int64_t* q_row_ptr, int32_t n_queries, co
             grow[g + 1] = (int32_t)n_union;
         }
     }
-    // copies on the caller's stream, ordered after the searches already enqueued on it
+    // the upload, on the caller's stream, ordered after the searches already enqueued on it
     hipStream_t s = (hipStream_t)hip_stream;
-    auto up = [&](size_t off, size_t bytes) -> hipError_t {
-        return bytes ? hipMemcpyAsync(b->dmem + off, h + off, bytes, hipMemcpyHostToDevice, s) : hipSuccess;
+    UploadRanges up;
+    size_t up_bytes = 0;
+    auto add = [&](size_t off, size_t bytes) {
+        if (bytes == 0) return;
+        up.at[up.n] = (uint32_t)(off / 16);
+        up.len[up.n++] = (uint32_t)((bytes + 15) / 16);  // array starts are 256 bytes apart at least
+        up_bytes += bytes;
     };
-    hipError_t e = up(0, L.head);
-    if (e == hipSuccess) e = up(L.term, (size_t)q_nnz * 4);
-    if (e == hipSuccess) e = up(L.w, (size_t)q_nnz * 4);
-    if (e == hipSuccess) e = up(L.w8, (size_t)q_nnz * 4);
-    if (e == hipSuccess) e = up(L.fx, (size_t)q_nnz * 8);
-    if (e == hipSuccess) e = up(L.ubcum, (size_t)q_nnz * 8);
-    if (e == hipSuccess) e = up(L.gterm, (size_t)n_union * 4);
-    if (e == hipSuccess) e = up(L.gwfx, (size_t)n_union * G * 4);
-    if (e == hipSuccess) e = up(L.gw8, (size_t)n_union * G * 4);
-    if (e == hipSuccess) e = up(L.sterm, (size_t)n_sterm * sizeof(ScoreTerm));
+    add(0, L.head);
+    add(L.term, (size_t)q_nnz * 4);
+    add(L.w, (size_t)q_nnz * 4);
+    add(L.w8, (size_t)q_nnz * 4);
+    add(L.fx, (size_t)q_nnz * 8);
+    add(L.ubcum, (size_t)q_nnz * 8);
+    add(L.gterm, (size_t)n_union * 4);
+    add(L.gwfx, (size_t)n_union * G * 4);
+    add(L.gw8, (size_t)n_union * G * 4);
+    add(L.sterm, (size_t)n_sterm * sizeof(ScoreTerm));
+    hipError_t e = hipSuccess;
+    if (up_bytes <= kUploadBytes) {
+        (void)hipGetLastError();
+        e = launch_upload(b->dmem, h, up, s);
+    } else {
+        for (int i = 0; i < up.n && e == hipSuccess; i++)
+            e = hipMemcpyAsync(b->dmem + (size_t)up.at[i] * 16, h + (size_t)up.at[i] * 16, (size_t)up.len[i] * 16,
+                               hipMemcpyHostToDevice, s);
+    }
     if (e == hipSuccess) e = hipEventRecord(b->copied, s);
     if (e == hipSuccess) {
         b->copy_pending = true;
@@ -1202,7 +1306,7 @@ int32_t gs_batch_create(gs_index ix, const int64_t* q_row_ptr, int32_t n_queries
     *out = nullptr;
     if (n_queries < 0 || q_nnz < 0) return fail(GS_EINVAL, "negative size");
     gs_batch b = nullptr;
-    int32_t rc = gs_batch_reserve(ix, n_queries, q_nnz, k_max, &b);
+    int32_t rc = batch_new(ix, n_queries, q_nnz, k_max, &b, out);
     if (rc != GS_OK) return rc;
     rc = gs_batch_update(b, q_row_ptr, n_queries, q_term_ids, q_weights, q_nnz, k, hip_stream);
     if (rc != GS_OK) {
@@ -1450,13 +1554,9 @@ const int32_t* batch_diag(const gs_batch_s* b) { return b->diag; }
 
 namespace {
 
-// After a synchronised search: GS_ECAPACITY when the rescored band of some query did not
-// fit its buffer (bf16; that row holds padding), else GS_OK.
-int32_t check_overflow(gs_batch b) {
-    if (b->n_active == 0) return GS_OK;
-    std::vector<int32_t> d((size_t)b->n_active * kDiagWords);
-    const hipError_t e = hipMemcpy(d.data(), b->diag, d.size() * 4, hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return fail(GS_EHIP, std::string("diagnostics: ") + hipGetErrorString(e));
+// GS_ECAPACITY when the rescored band of some query did not fit its buffer (bf16; that row
+// holds padding), else GS_OK. d: the batch's diagnostics on the host.
+int32_t check_overflow(gs_batch b, const int32_t* d) {
     for (int32_t q = 0; q < b->n_active; q++)
         if (d[(size_t)q * kDiagWords + 3])
             return fail(GS_ECAPACITY, "query " + std::to_string(q) + ": more than " + std::to_string(kCandCap) +
@@ -1670,14 +1770,36 @@ int32_t gs_search(gs_index ix, const int64_t* q_row_ptr, int32_t n_queries, cons
                   const float* q_weights, int64_t q_nnz, const int32_t* k, int32_t k_max, void* workspace,
                   size_t workspace_bytes_, int32_t* out_ids, void* out_scores, const gs_search_opts* opts,
                   void* hip_stream) {
-    gs_batch b = nullptr;
-    int32_t rc = gs_batch_create(ix, q_row_ptr, n_queries, q_term_ids, q_weights, q_nnz, k, k_max, hip_stream, &b);
+    g_err.clear();
+    if (n_queries < 0 || q_nnz < 0) return fail(GS_EINVAL, "negative size");
+    gs_batch b = nullptr, unused = nullptr;
+    int32_t rc = batch_new(ix, n_queries, q_nnz, k_max, &b, &unused, true);
     if (rc != GS_OK) return rc;
+    hipStream_t s = (hipStream_t)hip_stream;
+    rc = gs::batch_update(b, q_row_ptr, n_queries, q_term_ids, q_weights, q_nnz, k, hip_stream, false);
+    if (rc != GS_OK) {
+        batch_return(b);
+        return rc;
+    }
     rc = gs_search_batch(ix, b, workspace, workspace_bytes_, out_ids, out_scores, opts, hip_stream);
-    hipError_t e = hipStreamSynchronize((hipStream_t)hip_stream);
+    // bf16: the diagnostics, into the stage's part for them (copied from it before the search)
+    int32_t* diag = (int32_t*)(b->stage + b->lay.diag);
+    const bool check = rc == GS_OK && ix->precision == kBF16 && b->n_active > 0 && b->k_max > 0;
+    hipError_t e = hipSuccess;
+    if (check) {
+        DeviceGuard g(ix->device);
+        e = hipMemcpyAsync(diag, b->diag, (size_t)b->n_active * kDiagWords * 4, hipMemcpyDeviceToHost, s);
+    }
+    const hipError_t es = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = es;
     if (rc == GS_OK && e != hipSuccess) rc = fail(GS_EHIP, std::string("search: ") + hipGetErrorString(e));
-    if (rc == GS_OK) rc = check_overflow(b);
-    gs_batch_free(b);
+    if (rc == GS_OK && check) rc = check_overflow(b, diag);
+    if (es == hipSuccess) {
+        b->copy_pending = false;
+        batch_return(b);
+    } else {
+        gs_batch_free(b);
+    }
     return rc;
 }
 

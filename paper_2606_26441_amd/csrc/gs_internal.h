@@ -286,6 +286,14 @@ hipError_t launch_hist1(const DevIndex& ix, const DevBatch& qb, int32_t q0, int3
 hipError_t scratch_address(int device, void** out);
 
 // ---- launchers (gs_yardstick.hip) ----
+// Ranges of one upload, in 16-byte units from the start of both sides.
+struct UploadRanges {
+    static constexpr int kMax = 16;
+    int32_t n = 0;
+    uint32_t at[kMax], len[kMax];
+};
+constexpr size_t kUploadBytes = (size_t)1 << 20;  // larger updates go through the copy engine, array by array
+hipError_t launch_upload(void* dst, const void* src, const UploadRanges& r, hipStream_t s);
 hipError_t launch_copy16(void* dst, const void* src, int64_t n16, hipStream_t s);
 // LDS atomic-add throughput: op 0 uint32, 1 uint64, 2 float, 3 double; pattern 0 scattered, 1 consecutive
 hipError_t launch_lds_atomic(int op, int pattern, int workgroups, int iters, void* sink, hipStream_t s);
