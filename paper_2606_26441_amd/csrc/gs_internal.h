@@ -225,6 +225,7 @@ struct ScoreOpts {
     int seed_stride = 0;  // fused candidate filtering: every seed_stride-th doc tile seeds the bound (0: off)
     int prune = 0;        // block-max pruning of the non-seed tiles (TILED, fp32 and uint8)
     bool whole = false;   // the query tile is the whole batch (the host's work order applies)
+    bool any_tile = false;  // the caller left the tile size of the doc-tiled kernel to the library
 };
 
 // Doc tiles of a scoring launch: phase 0 all tiles, phase 1 the seed tiles

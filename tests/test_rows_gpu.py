@@ -103,3 +103,24 @@ def test_rows_match_the_group_kernel(precision):
     for ids, sc in got[1:]:
         assert np.array_equal(ids, got[0][0]) and np.array_equal(sc, got[0][1])
     idx.close()
+
+
+@pytest.mark.parametrize("precision", ["u8", "bf16"])
+@pytest.mark.parametrize("n_docs,query_tile", [(114_688, 0), (114_689, 0), (114_689, 31), (114_689, 32)])
+def test_tile_left_to_the_library(precision, n_docs, query_tile):
+    # 36 queries x 7 tiles of 16,384 documents: 252 items; with 8 tiles 288, 248 and 256 (below 256
+    # items the library halves the tile). Either tile gives the same ids and scores.
+    gs, torch = _gs()
+    docs, qs = _docs(n_docs), _queries()
+    idx = gs.Index.from_rows(docs, precision)
+    got = []
+    for tile_docs in (0, 8192, 16384):
+        opts = gs.make_opts("tiled", tile_docs=tile_docs, query_tile=query_tile)
+        b = idx.batch(qs, 100)
+        ids, sc = idx.search(b, idx.workspace(qs.n_rows, opts), opts)
+        torch.cuda.synchronize()
+        got.append((ids.cpu().numpy(), sc.cpu().numpy()))
+        b.close()
+    for ids, sc in got[1:]:
+        assert np.array_equal(ids, got[0][0]) and np.array_equal(sc, got[0][1])
+    idx.close()
