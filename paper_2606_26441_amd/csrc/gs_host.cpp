@@ -540,20 +540,35 @@ int32_t dev_upload(std::vector<void*>& allocs, size_t& bytes, const T* host, siz
     return GS_OK;
 }
 
-// Rows of the commonest terms: chosen by list length, filled on the device from the lists.
+// Rows of the commonest terms: chosen by list length, filled on the device from the lists. A row is
+// whole grains, so in a collection of a few documents rows could take thousands of times their
+// postings' bytes (3 documents of 30,000 terms: 3 GB): beyond 64 MiB they take at most 3 times the
+// bytes of the postings, the longest lists first. In large collections the share of the documents
+// that a row needs keeps them below that by itself. None are built where the device has not four
+// times their room free. A term without a row is summed from its list.
+constexpr int64_t kRowBytesFree = 64ll << 20;
+
 int32_t build_rows(gs_index ix, hipStream_t s) {
     DevIndex& d = ix->dev;
+    const int64_t w = ix->precision == kFP32 ? 4 : ix->precision == kBF16 ? 2 : 1;
+    const int64_t row = (ix->n_grains << kGrainShift) * w;
     std::vector<int32_t> terms;
     try {
         for (int32_t v = 0; v < ix->vocab; v++)
-            if (ix->terms[(size_t)v].len > 0 && (int64_t)ix->terms[(size_t)v].len * kRowShare >= ix->n_docs) terms.push_back(v);
+            if (ix->terms[(size_t)v].len > 0 && (int64_t)ix->terms[(size_t)v].len * kRowShare >= ix->n_docs)
+                terms.push_back(v);
         std::stable_sort(terms.begin(), terms.end(), [&](int32_t a, int32_t b) {
             return ix->terms[(size_t)a].len > ix->terms[(size_t)b].len;
         });
+        const int64_t most = std::max(kRowBytesFree, 3 * (2 + w) * ix->padded) / std::max<int64_t>(row, 1);
+        if ((int64_t)terms.size() > most) terms.resize((size_t)most);
     } catch (const std::bad_alloc&) {
         return fail(GS_ENOMEM, "host memory for the row table");
     }
-    const int64_t w = ix->precision == kFP32 ? 4 : ix->precision == kBF16 ? 2 : 1;
+    size_t room = 0, total = 0;
+    if (row * (int64_t)terms.size() > kRowBytesFree && hipMemGetInfo(&room, &total) == hipSuccess &&
+        (int64_t)(room / 4) < row * (int64_t)terms.size())
+        terms.clear();
     for (size_t i = 0; i < terms.size(); i++) ix->terms[(size_t)terms[i]].row = (int32_t)i;
     ix->n_rows = (int32_t)terms.size();
     d.n_rows = ix->n_rows;
@@ -561,7 +576,7 @@ int32_t build_rows(gs_index ix, hipStream_t s) {
     uint8_t* rows = nullptr;
     int32_t rc = dev_upload(ix->allocs, ix->bytes, terms.data(), terms.size(), &pt, s);
     if (rc == GS_OK)
-        rc = dev_upload(ix->allocs, ix->bytes, (const uint8_t*)nullptr, (size_t)((ix->n_grains * ix->n_rows) << kGrainShift) * (size_t)w, &rows, s);
+        rc = dev_upload(ix->allocs, ix->bytes, (const uint8_t*)nullptr, (size_t)(row * ix->n_rows), &rows, s);
     if (rc != GS_OK) return rc;
     d.rows = rows;
     hipError_t e = launch_fill_rows(d, pt, rows, s);

@@ -124,3 +124,23 @@ def test_tile_left_to_the_library(precision, n_docs, query_tile):
     for ids, sc in got[1:]:
         assert np.array_equal(ids, got[0][0]) and np.array_equal(sc, got[0][1])
     idx.close()
+
+
+@pytest.mark.parametrize("precision", ["fp32", "u8", "bf16"])
+def test_rows_of_a_tiny_collection_stay_small(precision):
+    # 3 documents of 3,000 terms each, none shared: a row of whole grains for each term would take
+    # 74 to 295 MB
+    gs, torch = _gs()
+    rng = np.random.default_rng(5)
+    vocab = 9_000
+    rows = [[(t, float(rng.integers(1, 49)) / 16.0) for t in range(d, vocab, 3)] for d in range(3)]
+    docs = csr(rows, vocab)
+    qs = csr([[(t, 1.0) for t in range(0, vocab, 40)], [(vocab - 1, 2.0)], [(0, 1.0), (8_500, 1.0)]], vocab)
+    idx = gs.Index.from_rows(docs, precision)
+    assert idx.info().device_bytes < (64 << 20) + 16 * idx.info().padded_nnz
+    b = idx.batch(qs, 3)
+    ids, sc = idx.search(b, idx.workspace(qs.n_rows))
+    torch.cuda.synchronize()
+    check_batch(precision, docs, qs, ids.cpu().numpy(), sc.cpu().numpy(), 3, what="3 documents " + precision)
+    b.close()
+    idx.close()
