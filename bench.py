@@ -76,10 +76,9 @@ def algorithmic_bytes(df, queries, n_docs, wbytes, idbytes, written_docs=None):
     """Per-query postings of the query's terms (doc id + weight) and one score-array write / read.
 
     idbytes: bytes per posting for the doc id, a number or one per term. The doc-tiled
-    kernels read a 16-bit doc offset (2), or with fp32/bf16 weights in the per-query
-    kernel, for terms in byte form, 1 byte plus a 4-byte base per 64 postings; the
-    global-atomic kernel reads the 32-bit doc id (4). With fused candidate filtering
-    (fp32, uint8) only the seed tiles' scores are written (written_docs per query).
+    kernels read a 16-bit doc offset (2); for the terms that have a row they read the row
+    (`row_id_bytes`); the global-atomic kernel reads the 32-bit doc id (4). With fused
+    candidate filtering only the seed tiles' scores are written (written_docs per query).
     """
     p_q = np.array([int(df[queries.row(i)[0]].sum()) for i in range(queries.n_rows)], dtype=np.int64)
     per_term = df * (np.broadcast_to(np.asarray(idbytes, dtype=np.float64), df.shape) + wbytes)
@@ -88,6 +87,15 @@ def algorithmic_bytes(df, queries, n_docs, wbytes, idbytes, written_docs=None):
     score_kernel = int(round(post_bytes)) + queries.n_rows * wd * 4
     step = score_kernel + queries.n_rows * wd * 4  # the filter reads what was written
     return p_q, score_kernel, step
+
+
+def row_id_bytes(df, n_docs, wbytes):
+    """Bytes per posting beside the weight, per term, in the doc-tiled kernel: 2 (the doc offset), or for a
+    term held by at least a quarter of the documents what its row (a weight for every document, no ids)
+    has above the postings' weights."""
+    df = np.asarray(df, dtype=np.float64)
+    row = (df > 0) & (4 * df >= n_docs)
+    return np.where(row, n_docs * wbytes / np.maximum(df, 1.0) - wbytes, 2.0)
 
 
 _C_TOKEN = re.compile(r'//[^\n]*|/\*.*?\*/|"(?:\\.|[^"\\\n])*"|\'(?:\\.|[^\'\\\n])*\'', re.S)
@@ -243,8 +251,7 @@ def time_form(gs, torch, idx, queries, k, opts, steps, warmup, host_steps=0):
     total_ms = ev[0].elapsed_time(ev[steps])
     diag = batch.diagnostics()
     res = {"ids": ids.cpu().numpy(), "scores": sc.cpu().numpy(), "total_ms": total_ms, "step_ms": step_ms,
-           "timing": t, "diag": diag, "device_bytes": int(idx.info().device_bytes), "ws_bytes": ws.numel(),
-           "dense_terms": idx.dense_terms()}
+           "timing": t, "diag": diag, "device_bytes": int(idx.info().device_bytes), "ws_bytes": ws.numel()}
     if host_steps:
         # host CSR in (validation, per-query scales, upload), results copied back to host memory
         host_ms = []
@@ -535,16 +542,16 @@ def main():
             and args.k <= 1024 and n_tiles >= 16):
         # fused candidate filtering: score rows of the seed tiles (every 8th) only
         written = sum(min(tile_docs, n_docs - t * tile_docs) for t in range(0, n_tiles, 8))
-    if args.kernel == "tiled" and args.precision != "u8":
-        idbytes = np.where(main_res["dense_terms"] != 0, 1.0 + 4.0 / 64.0, 2.0)
+    if args.kernel in ("tiled", "shared"):
+        idbytes = row_id_bytes(df, n_docs, WEIGHT_BYTES[args.precision])
     else:
-        idbytes = 2 if args.kernel in ("tiled", "shared", "group") else 4
+        idbytes = 2 if args.kernel == "group" else 4
     p_q, layout_bytes, step_bytes = algorithmic_bytes(df, queries, n_docs, WEIGHT_BYTES[args.precision], idbytes,
                                                       written)
     survey_bytes = survey_model_bytes(p_q, n_docs, WEIGHT_BYTES[args.precision])
     if args.kernel == "docpar":
-        # document-parallel: every forward row (term id + fp32 weight) per query, plus one score write
-        layout_bytes = nq * (docs.nnz * 8 + n_docs * 4)
+        # document-parallel: every forward row (2-byte term id, fp32 weight) per query, plus one score write
+        layout_bytes = nq * (docs.nnz * 6 + n_docs * 4)
         survey_bytes = nq * (docs.nnz * 8 + n_docs * 4)
         step_bytes = layout_bytes + nq * n_docs * 4
     ms_per_step = main_res["total_ms"] / args.steps
@@ -557,7 +564,7 @@ def main():
     log("QPS %.1f  ms/step %.2f  score %.2f ms  select %.2f ms  scoring: %.0f GB/s effective (model bytes), "
         "%.0f GB/s on its layout bytes" % (qps, ms_per_step, score_ms, select_ms, achieved, layout_gbs))
 
-    kernel_name = {"tiled": "k_score_tiled", "shared": "k_score_persistent", "atomic": "k_score_atomic",
+    kernel_name = {"tiled": "k_score_tiled", "shared": "k_score_tiled", "atomic": "k_score_atomic",
                    "docpar": "k_score_docpar", "group": "k_score_group"}[args.kernel]
     traffic, traffic_src = (None, None)
     if args.n_docs in (0, w.n_docs) and nq == w.n_queries and args.k == 1000 and not args.no_fused \
@@ -578,7 +585,7 @@ def main():
         "data": "synthetic (seeded Zipf(1.1)/Poisson/lognormal stand-in for MS MARCO + SPLADE)",
         "config": {"workload": w.name, "n_docs": n_docs, "postings": docs.nnz, "batch": nq, "k": args.k,
                    "precision": args.precision, "kernel": args.kernel, "tile_docs": tile_docs,
-                   "chunk": args.chunk or 1024, "query_nnz_mean": round(queries.nnz / max(nq, 1), 2),
+                   "chunk": args.chunk or (1024 if args.precision == "u8" else 512), "query_nnz_mean": round(queries.nnz / max(nq, 1), 2),
                    "postings_per_query_mean": int(p_q.mean())},
         "roofline": {
             "bound": "hbm", "kernel": kernel_name,
@@ -586,7 +593,8 @@ def main():
             "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
             "frac_kind": "effective: the per-query model bytes P_q*(4+s_w) + 8N (postings with 4 B doc ids, one "
                          "score write and read) over the scoring launches' time; above 1 when the kernel moves "
-                         "fewer bytes than the model (2- or 1-byte doc ids, score rows of seed tiles only)",
+                         "fewer bytes than the model (rows without ids, 2-byte ids, score rows of seed tiles only, "
+                         "a tile's postings read from L2 by the queries after the first)",
             "algorithmic_bytes_per_launch": survey_bytes,
             "layout_bytes_per_launch": layout_bytes,
             "layout_frac": round(layout_gbs / HBM_PEAK_GBS, 4),

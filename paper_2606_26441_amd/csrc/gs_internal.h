@@ -93,7 +93,8 @@ struct DevIndex {
     const void* rows;          // [n_grains][n_rows][8192] float | bf16 bits | uint8 (order: k_fill_rows)
     int32_t n_rows;
     const int64_t* fwd_row_ptr;  // [N+1] forward rows (sorted by term), or null
-    const int32_t* fwd_term;
+    const uint16_t* fwd_term16;  // their terms in 2 bytes where the vocabulary has at most 65,536 terms,
+    const int32_t* fwd_term;     // else here
     const float* fwd_w;
 };
 
@@ -265,6 +266,8 @@ const int32_t* batch_diag(const struct ::gs_batch_s* b);
 // ---- launchers (gs_score.hip) ----
 // Fill the rows (zeroed here) of `terms` [ix.n_rows] (device) from their posting lists.
 hipError_t launch_fill_rows(const DevIndex& ix, const int32_t* terms, void* rows, hipStream_t s);
+// dst[i] = src[i] for n terms below 65,536.
+hipError_t launch_narrow(const int32_t* src, uint16_t* dst, int64_t n, hipStream_t s);
 // counters, selection state and first-digit histograms
 hipError_t launch_clear(const Workspace& ws, int32_t qt, hipStream_t s);
 hipError_t launch_score_tiled(const DevIndex& ix, const DevBatch& qb, int32_t q0, int32_t qt,

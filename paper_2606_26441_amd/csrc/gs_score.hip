@@ -1438,7 +1438,8 @@ __global__ __launch_bounds__(256) void k_score_atomic(DevIndex ix, DevBatch qb, 
 // LDS table; a wavefront scores 4 documents at a time, 16 lanes per document,
 // each lane walking its document's forward row with stride 16 and four loads
 // of (term, weight) in flight, then a 16-lane reduction. Rows are contiguous,
-// so the 4 x 16 lanes read 4 short coalesced runs per step.
+// so the 4 x 16 lanes read 4 short coalesced runs per step. The table's size bounds the
+// vocabulary far below 65,536 terms, so the rows' terms are always the 2-byte ones.
 template <int P>
 __global__ __launch_bounds__(1024) void k_score_docpar(DevIndex ix, DevBatch qb, int32_t q0, uint32_t* __restrict__ S,
                                                        int64_t ld, int docs_per_block) {
@@ -1474,7 +1475,7 @@ __global__ __launch_bounds__(1024) void k_score_docpar(DevIndex ix, DevBatch qb,
 #pragma unroll
             for (int u = 0; u < 4; u++) {
                 const int64_t eu = e + 16 * u;
-                t[u] = eu < b ? ix.fwd_term[eu] : 0;
+                t[u] = eu < b ? ix.fwd_term16[eu] : 0;
                 w[u] = eu < b ? ix.fwd_w[eu] : 0.0f;
             }
 #pragma unroll
@@ -1535,6 +1536,12 @@ __global__ __launch_bounds__(256) void k_fill_rows(DevIndex ix, const int32_t* _
             to[d - r + ((r & 2047) >> 2) * DPL + (r >> 11) * 4 + (r & 3)] = reinterpret_cast<const WT*>(ix.post_w)[p0 + i];
         }
     }
+}
+
+__global__ __launch_bounds__(256) void k_narrow(const int32_t* __restrict__ src, uint16_t* __restrict__ dst,
+                                                int64_t n) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
+        dst[i] = (uint16_t)src[i];
 }
 
 // The start of a search: its step counters, selection state and histograms, in one launch.
@@ -1755,6 +1762,14 @@ hipError_t launch_fill_rows(const DevIndex& ix, const int32_t* terms, void* rows
         else hipLaunchKernelGGL(k_fill_rows<uint8_t>, grid, dim3(256), 0, s, ix, terms, r0, (uint8_t*)rows);
         GS_CHECK_LAUNCH("k_fill_rows");
     }
+    return hipSuccess;
+}
+
+hipError_t launch_narrow(const int32_t* src, uint16_t* dst, int64_t n, hipStream_t s) {
+    if (n <= 0) return hipSuccess;
+    const int64_t blocks = std::min<int64_t>((n + 255) / 256, 8192);
+    hipLaunchKernelGGL(k_narrow, dim3((unsigned)blocks), dim3(256), 0, s, src, dst, n);
+    GS_CHECK_LAUNCH("k_narrow");
     return hipSuccess;
 }
 

@@ -836,44 +836,59 @@ __global__ __launch_bounds__(kSelBS) void k_final(DevIndex ix, DevBatch qb, int3
 
 // fp64 rescoring of the listed band documents against their query, on a grid over the
 // documents (a workgroup per query left 252 of 256 CUs idle for a call of four queries: its
-// selection took 368 us, now 37 us, 18 of them here; 500 queries: 826 us, now 250, 204 of
-// them here, bound by the forward rows' reads). A wavefront takes 4 documents, 16 lanes each. Lane `sub` holds entries
-// sub, sub + 16, ... of the document's forward row (sorted by term), eight in flight, and
-// finds each term in the query by a hash of its low bits (most miss at once). The nonzero
-// products are then put side by side in LDS in row order (ascending term) and added by one
-// lane, so the sum is the same sequence of fp64 additions as a serial walk of the row.
-constexpr int kRescoreBS = 256;
-constexpr int kRescoreHash = 1024;
-__global__ __launch_bounds__(kRescoreBS) void k_rescore(DevIndex ix, DevBatch qb, int32_t q0,
-                                                        const SelState* __restrict__ state,
-                                                        double* __restrict__ band_s,
-                                                        const int32_t* __restrict__ band_id) {
-    __shared__ int32_t head[kRescoreHash];
-    __shared__ int32_t next[kMaxQueryNnz];
-    __shared__ int32_t sq_t[kMaxQueryNnz];
-    __shared__ float sq_w[kMaxQueryNnz];
-    constexpr int U = 8;
-    __shared__ double prod[kRescoreBS / 16][16 * U / 2];  // per document, half a step's products in row order
+// selection took 368 us). A wavefront takes 4 documents, 16 lanes each. Lane `sub` holds entries
+// sub, sub + 16, ... of the document's forward row (sorted by term), eight of terms and eight of
+// weights in flight, and finds each term in the query by a hash of its low bits: one LDS read
+// and a compare each, without a branch. The products of the terms found are put side by side in
+// LDS in row order (ascending term) and added by one lane, so the sum is the same sequence of
+// fp64 additions as a serial walk of the row.
+// Bound by the rows' reads, some 1,150 per query at k = 1,000 and in no order, as many
+// wavefronts in flight as there can be: at 8, 6 and 5 a SIMD 159, 201 and 252 us (500 queries of
+// 500,000 documents), so it is held to 64 VGPRs. A chain walk and a wait per lookup took 202 us
+// there, and 18.5 us for 4 queries of 200,000 documents against 10.5.
+constexpr int kRescoreBS = 512;
+constexpr int kRescoreHash = 2048;
+constexpr int kRescoreProds = 96;  // products of a document held at once
+
+template <typename TT>
+__global__ __launch_bounds__(kRescoreBS) __attribute__((amdgpu_waves_per_eu(8))) void k_rescore(
+    DevIndex ix, const TT* __restrict__ fwd_term, DevBatch qb, int32_t q0, const SelState* __restrict__ state,
+    double* __restrict__ band_s, const int32_t* __restrict__ band_id) {
+    // a bucket's last query term: its upper bits << 10 | (512 if the bucket has more) | its place + 1
+    // (at most 256), or 0
+    __shared__ __align__(16) uint32_t head[kRescoreHash];
+    __shared__ int32_t next[kMaxQueryNnz + 1];  // the bucket's other terms, by the same places
+    __shared__ int32_t sq_t[kMaxQueryNnz + 1];
+    __shared__ float sq_w[kMaxQueryNnz + 1];
+    // per document, products in row order, then zeros up to a multiple of 4
+    __shared__ __align__(16) double prod[kRescoreBS / 16][kRescoreProds + 4];
+    constexpr int kBits = 11;
+    static_assert(kRescoreHash == 1 << kBits && kMaxQueryNnz < 512, "bucket entries");
     const int ql = blockIdx.y, q = q0 + ql, tid = threadIdx.x;
     const SelState* st = state + ql;
     const int nb = st->overflow ? 0 : min(st->band, kCandCap);
     constexpr int per = kRescoreBS / 16;
     if ((int)blockIdx.x * per >= nb) return;
-    for (int i = tid; i < kRescoreHash; i += kRescoreBS) head[i] = -1;
+    for (int i = tid; i < kRescoreHash / 4; i += kRescoreBS) ((uint4*)head)[i] = make_uint4(0u, 0u, 0u, 0u);
     const int64_t qa = qb.q_row_ptr[q];
     const int nq = (int)(qb.q_row_ptr[q + 1] - qa);
     __syncthreads();
     for (int i = tid; i < nq; i += kRescoreBS) {
         const int32_t t = qb.q_term[qa + i];
-        sq_t[i] = t;
-        sq_w[i] = qb.q_w[qa + i];
-        next[i] = atomicExch(&head[t & (kRescoreHash - 1)], i);
+        sq_t[i + 1] = t;
+        sq_w[i + 1] = qb.q_w[qa + i];
+        uint32_t* const h = &head[t & (kRescoreHash - 1)];
+        const uint32_t before = atomicExch(h, ((uint32_t)t >> kBits) << 10 | (uint32_t)(i + 1));
+        next[i + 1] = (int32_t)(before & 511u);
+        if (before != 0u) atomicOr(h, 512u);
     }
+    if (tid == 0) sq_w[0] = 0.0f;
     __syncthreads();
     const int32_t* bid = band_id + (int64_t)ql * kCandCap;
     double* bs = band_s + (int64_t)ql * kCandCap;
     const int lane = tid & (kWave - 1), wave = tid >> 6;
-    const int grp = lane >> 4, sub = lane & 15;
+    const int grp = lane >> 4, sub = lane & 15, sh = (grp & 1) * 16;
+    const uint32_t below = (1u << sub) - 1u;
     double* mine = prod[wave * 4 + grp];
     auto row = [&](int i, int64_t& a, int& len) {  // document i's forward row
         a = 0;
@@ -885,7 +900,73 @@ __global__ __launch_bounds__(kRescoreBS) void k_rescore(DevIndex ix, DevBatch qb
         }
     };
     int64_t a, a_next;
-    int len, len_next;
+    int len, len_next, cnt;
+    double s;
+    // the held products into the sum, one lane adding them one by one, four read at once
+    auto add = [&]() {
+        if (sub < 4) mine[cnt + sub] = 0.0;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");  // LDS of this wavefront only
+        if (sub == 0)
+            for (int p = 0; p < cnt; p += 4) {
+                const double2 lo = *(const double2*)&mine[p], hi = *(const double2*)&mine[p + 2];
+                s += lo.x;
+                s += lo.y;
+                s += hi.x;
+                s += hi.y;
+            }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        cnt = 0;
+    };
+    // entries [off, off + 16 U) of the four rows
+    auto entries = [&](auto uc, int off, auto under) {
+        constexpr int U = decltype(uc)::value;
+        int t[U];
+        float w[U];
+        const TT* rt = fwd_term + (a + off + sub);
+        const float* rw = ix.fwd_w + (a + off + sub);
+        const int left = len - off - sub;
+#pragma unroll
+        for (int u = 0; u < U; u++) t[u] = 16 * u < left ? (int)rt[16 * u] : -1;
+        // most of a row's cache lines hold a query term's weight: all are read beside the terms
+#pragma unroll
+        for (int u = 0; u < U; u++) w[u] = 16 * u < left ? rw[16 * u] : 0.0f;
+        under();
+        constexpr int H = U < 4 ? U : 4;
+#pragma unroll
+        for (int u0 = 0; u0 < U; u0 += H) {
+            uint32_t h[H];
+            int j[H];
+            float qw[H];
+#pragma unroll
+            for (int u = 0; u < H; u++) h[u] = head[t[u0 + u] & (kRescoreHash - 1)];
+            bool more = false;
+#pragma unroll
+            for (int u = 0; u < H; u++) {
+                const bool same = h[u] >> 10 == (uint32_t)t[u0 + u] >> kBits;  // never where t is -1
+                j[u] = same ? (int)(h[u] & 511u) : 0;
+                more |= !same && (h[u] & 512u) != 0u;
+            }
+            if (__any(more)) {  // two query terms in one bucket: rare
+#pragma unroll
+                for (int u = 0; u < H; u++)
+                    if (j[u] == 0 && (h[u] & 512u) != 0u) {
+                        j[u] = next[h[u] & 511u];
+                        while (j[u] != 0 && sq_t[j[u]] != t[u0 + u]) j[u] = next[j[u]];
+                    }
+            }
+#pragma unroll
+            for (int u = 0; u < H; u++) qw[u] = sq_w[j[u]];
+            if (__any(cnt > kRescoreProds - 16 * H)) add();
+#pragma unroll
+            for (int u = 0; u < H; u++) {
+                const bool hit = j[u] != 0;
+                const unsigned long long m = __ballot(hit);
+                const uint32_t mm = (lane < 32 ? (uint32_t)m : (uint32_t)(m >> 32)) >> sh & 0xFFFFu;
+                if (hit) mine[cnt + __popc(mm & below)] = (double)qw[u] * (double)w[u0 + u];
+                cnt += __popc(mm);
+            }
+        }
+    };
     const int step = (int)gridDim.x * per;
     row((int)blockIdx.x * per + wave * 4 + grp, a_next, len_next);
     for (int base = (int)blockIdx.x * per + wave * 4; base < nb; base += step) {
@@ -894,42 +975,21 @@ __global__ __launch_bounds__(kRescoreBS) void k_rescore(DevIndex ix, DevBatch qb
         len = len_next;
         int maxlen = len;
         maxlen = max(maxlen, __shfl_xor(maxlen, 16, kWave));
-        maxlen = max(maxlen, __shfl_xor(maxlen, 32, kWave));
-        double s = 0.0;
-        for (int off = 0; off < maxlen; off += 16 * U) {
-            int t[U];
-            float w[U];
-            int j[U];
-#pragma unroll
-            for (int u = 0; u < U; u++) {
-                const int e = off + 16 * u + sub;
-                t[u] = e < len ? ix.fwd_term[a + e] : -1;
-            }
-            if (off == 0) row(i + step, a_next, len_next);  // the next document's row under this one's loads
-#pragma unroll
-            for (int u = 0; u < U; u++) {
-                j[u] = t[u] >= 0 ? head[t[u] & (kRescoreHash - 1)] : -1;
-                while (j[u] >= 0 && sq_t[j[u]] != t[u]) j[u] = next[j[u]];
-            }
-#pragma unroll
-            for (int u = 0; u < U; u++) w[u] = j[u] >= 0 ? ix.fwd_w[a + off + 16 * u + sub] : 0.0f;
-#pragma unroll
-            for (int h = 0; h < 2; h++) {
-                int cnt = 0;
-#pragma unroll
-                for (int u = h * U / 2; u < (h + 1) * U / 2; u++) {
-                    const double pr = j[u] >= 0 ? (double)sq_w[j[u]] * (double)w[u] : 0.0;
-                    const uint32_t mm = (uint32_t)(__ballot(pr != 0.0) >> (grp * 16)) & 0xFFFFu;
-                    if (pr != 0.0) mine[cnt + __popc(mm & ((1u << sub) - 1u))] = pr;
-                    cnt += __popc(mm);
-                }
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");  // LDS of this wavefront only
-                if (sub == 0)
-                    for (int p = 0; p < cnt; p++) s += mine[p];
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        maxlen = __builtin_amdgcn_readfirstlane(max(maxlen, __shfl_xor(maxlen, 32, kWave)));
+        s = 0.0;
+        cnt = 0;
+        auto next_row = [&]() { row(i + step, a_next, len_next); };  // under this one's loads
+        entries(std::integral_constant<int, 8>(), 0, next_row);
+        for (int off = 128; off < maxlen;) {
+            if (maxlen - off > 32) {
+                entries(std::integral_constant<int, 8>(), off, [] {});
+                off += 128;
+            } else {
+                entries(std::integral_constant<int, 2>(), off, [] {});
+                off += 32;
             }
         }
-        if (maxlen == 0) row(i + step, a_next, len_next);
+        add();
         if (sub == 0 && i < nb) bs[i] = s;
     }
 }
@@ -1118,12 +1178,18 @@ hipError_t launch_select(const DevIndex& ix, const DevBatch& qb, int32_t q0, int
     };
     // bf16: the band's rescoring and ranking (also the padding and the diagnostics)
     auto band_pass = [&]() -> hipError_t {
-        // Workgroups per query: one document group each for a band of 1.25 k where the queries are
-        // few, more groups each (down to 8,192 workgroups in all) where they are many: a workgroup
-        // sets up its query's hash first (500 queries: 277 us at 64 workgroups each).
-        const int x = std::max(1, std::min({64, (qb.k_max + qb.k_max / 4 + 15) / 16, 8192 / std::max(qt, 1)}));
-        hipLaunchKernelGGL(k_rescore, dim3(x, (unsigned)qt), dim3(kRescoreBS), 0, s, ix, qb, q0,
-                           (const SelState*)ws.state, ws.band_s, (const int32_t*)ws.band_id);
+        // Workgroups per query: one pass over the documents each for a band of 1.25 k where the
+        // queries are few, more passes each (down to 4,096 workgroups in all) where they are many: a
+        // workgroup sets up its query's hash first (500 queries: 190 us at 8 workgroups each, 221 at
+        // 16, 201 at 4).
+        const int x = std::max(1, std::min({64, (qb.k_max + qb.k_max / 4 + 31) / 32, 4096 / std::max(qt, 1)}));
+        const dim3 grid((unsigned)x, (unsigned)qt);
+        const SelState* st = ws.state;
+        const int32_t* bid = ws.band_id;
+        if (ix.fwd_term16)
+            hipLaunchKernelGGL(k_rescore<uint16_t>, grid, dim3(kRescoreBS), 0, s, ix, ix.fwd_term16, qb, q0, st, ws.band_s, bid);
+        else
+            hipLaunchKernelGGL(k_rescore<int32_t>, grid, dim3(kRescoreBS), 0, s, ix, ix.fwd_term, qb, q0, st, ws.band_s, bid);
         GS_CHECK_LAUNCH("k_rescore");
         hipLaunchKernelGGL(k_band_topk, dim3(qt), dim3(kSelBS), 0, s, ix, qb, q0, (const SelState*)ws.state,
                            (const double*)ws.band_s, (const int32_t*)ws.band_id, out_ids, (double*)out_scores, diag);
