@@ -270,7 +270,7 @@ def time_form(gs, torch, idx, queries, k, opts, steps, warmup, host_steps=0):
 
 def run_batched(gs, torch, docs, args, indexes):
     """Uneven batch: lognormal query lengths (median 25, 5..250), k mixed over {10, 100, 1000}; autotuned
-    options; one persistent-or-grid launch per step; hipGraph replay vs plain launches; oracle-checked sample."""
+    options; one launch per phase and step; hipGraph replay vs plain launches; oracle-checked sample."""
     import workload
     import oracle
     sys.path.insert(0, os.path.join(ROOT, "tests"))

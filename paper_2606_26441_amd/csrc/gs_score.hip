@@ -1134,8 +1134,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
 // segments are those of the union of the group's terms (built on the host, with
 // each member's weight per union term, 0 where the member lacks the term), so a
 // posting chunk is loaded once and scatter-added into the tile of every member
-// that holds its term. The items of a tile run on one XCD (tile-major, as in the
-// persistent kernel), groups in the host's order (heaviest first).
+// that holds its term. The items of a tile run on one XCD (tile-major), groups in
+// the host's order (heaviest first).
 template <int MT, int G>
 struct GroupShared {
     union {
