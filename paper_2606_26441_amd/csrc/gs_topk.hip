@@ -310,6 +310,9 @@ __global__ __launch_bounds__(kSelBS) void k_seed_bound(DevBatch qb, int32_t q0, 
 // the end the workgroup takes one range of the query's buffer and copies the
 // stage out. Hits that find the stage full are appended to the global buffer
 // directly (slot from a global atomic), so any number of hits is handled.
+// Bound by the rows' reads: 5.3 TB/s at 2.2 GB (500 queries of 8.8M documents, seed tiles), 4 TB/s
+// at 250 MB (62 us). Places for all of a wavefront's hits of a round from one atomic on the stage:
+// 70 us there, though 9 -> 7.5 us at 48 queries of 262,147 documents.
 constexpr int kFilterStage = 4096;
 
 __device__ __forceinline__ void append_global(SelState* st, unsigned long long* C, bool take,
