@@ -543,10 +543,20 @@ int32_t dev_upload(std::vector<void*>& allocs, size_t& bytes, const T* host, siz
 // Rows of the commonest terms: chosen by list length, filled on the device from the lists. A row is
 // whole grains, so in a collection of a few documents rows could take thousands of times their
 // postings' bytes (3 documents of 30,000 terms: 3 GB): beyond 64 MiB they take at most 3 times the
-// bytes of the postings, the longest lists first. In large collections the share of the documents
-// that a row needs keeps them below that by itself. None are built where the device has not four
+// bytes of the postings, the longest lists first, and there are never more than max_rows. In large
+// collections the share of the documents that a row needs keeps them below that by itself. None are built where the device has not four
 // times their room free. A term without a row is summed from its list.
 constexpr int64_t kRowBytesFree = 64ll << 20;
+
+}  // namespace
+
+int64_t gs::row_limit(int precision, int64_t n_grains, int64_t padded) {
+    const int64_t w = precision == kFP32 ? 4 : precision == kBF16 ? 2 : 1;
+    const int64_t row = (n_grains << kGrainShift) * w;
+    return std::min(std::max(kRowBytesFree, 3 * (2 + w) * padded) / std::max<int64_t>(row, 1), max_rows(w));
+}
+
+namespace {
 
 int32_t build_rows(gs_index ix, hipStream_t s) {
     DevIndex& d = ix->dev;
@@ -560,7 +570,7 @@ int32_t build_rows(gs_index ix, hipStream_t s) {
         std::stable_sort(terms.begin(), terms.end(), [&](int32_t a, int32_t b) {
             return ix->terms[(size_t)a].len > ix->terms[(size_t)b].len;
         });
-        const int64_t most = std::max(kRowBytesFree, 3 * (2 + w) * ix->padded) / std::max<int64_t>(row, 1);
+        const int64_t most = row_limit(ix->precision, ix->n_grains, ix->padded);
         if ((int64_t)terms.size() > most) terms.resize((size_t)most);
     } catch (const std::bad_alloc&) {
         return fail(GS_ENOMEM, "host memory for the row table");

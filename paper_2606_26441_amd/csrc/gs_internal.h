@@ -23,6 +23,12 @@ constexpr int kMaxChunk = 1024;       // largest chunk of the doc-tiled kernels 
 constexpr size_t kPostSlack = kMaxChunk;
 constexpr int kMaxK = 4096;           // GS_MAX_K
 constexpr int kRowShare = 4;          // a term in at least 1 / kRowShare of the documents has a row
+// Most rows of an index: in a doc tile (at most 16,384 documents of fp32 weights, 32,768 of the others)
+// the scoring kernel's byte offsets from a row's first grain to its last are 32-bit.
+constexpr int64_t max_rows(int64_t weight_bytes) {
+    const int64_t grains = weight_bytes == 4 ? 2 : 4;
+    return ((((int64_t)1 << 31) - 1) / (weight_bytes << kGrainShift) - 1) / (grains - 1);
+}
 constexpr int kHistBits = 11;         // selection digit width (first digit fused into scoring)
 constexpr int kHistBins = 1 << kHistBits;
 constexpr int kCandCap = 32768;       // candidates kept per query by the filter pass
@@ -212,6 +218,9 @@ struct Workspace {
     int32_t* rescore_list;        // [qt] queries whose rows are scored again (SelState::rescore)
     int64_t ld;                   // row stride of the score arrays (n_docs rounded up to 64)
 };
+
+// Most rows of the commonest terms that an index of n_grains grains and `padded` postings gets.
+int64_t row_limit(int precision, int64_t n_grains, int64_t padded);
 
 size_t workspace_bytes(int64_t n_docs, int32_t qt, int32_t precision);
 void carve_workspace(void* base, int64_t n_docs, int32_t qt, int32_t precision, Workspace* ws);

@@ -1,0 +1,240 @@
+// Host side of libgpusparse.so over a stand-in for the device (built and run by
+// tests/test_host_calls_sim.py on the CPU, one case per run). Device memory is host memory,
+// copies are done at once, and kernel launches are only recorded, with the device that was
+// current and the stream they went to. So a case can check what the host code asks of the
+// device - which allocations, on which device it waits, which launches with which
+// arguments - where a GPU could not show it: two devices, memory that runs out, a call that
+// fails, a stream under capture, sizes past any memory.
+#include <cstdint>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <set>
+#include <string>
+#include <utility>
+#include <vector>
+
+#include "../../include/gpusparse.h"
+#include "../../paper_2606_26441_amd/csrc/gs_internal.h"
+
+// ------------------------------------------------------------- the device --
+
+struct Launch {
+    std::string kernel;
+    int device;
+    hipStream_t stream;
+    int tile_shift = 0, chunk = 0;
+    bool wide = false, from_row = false;
+};
+
+static int g_device = 0;
+static std::vector<Launch> g_launches;
+static std::set<std::pair<int, hipStream_t>> g_pending;  // (device, stream) with work not waited for
+static std::map<void*, size_t> g_live;                   // device allocations
+static size_t g_room = (size_t)1 << 40, g_used = 0;
+static int g_fail_event_record = -1;                     // calls left before one fails
+static hipStream_t g_capturing = nullptr;
+static hipError_t g_last = hipSuccess;
+
+static Launch& launch(const char* kernel, hipStream_t s) {
+    g_launches.push_back(Launch{kernel, g_device, s});
+    g_pending.insert({g_device, s});
+    return g_launches.back();
+}
+static void wait_device() {
+    for (auto it = g_pending.begin(); it != g_pending.end();)
+        it = it->first == g_device ? g_pending.erase(it) : std::next(it);
+}
+
+extern "C" {
+hipError_t hipGetDevice(int* d) { *d = g_device; return hipSuccess; }
+hipError_t hipSetDevice(int d) { g_device = d; return hipSuccess; }
+hipError_t hipGetLastError() { const hipError_t e = g_last; g_last = hipSuccess; return e; }
+const char* hipGetErrorString(hipError_t) { return "error"; }
+hipError_t hipMalloc(void** p, size_t n) {
+    if (g_used + n > g_room) { *p = nullptr; return g_last = hipErrorOutOfMemory; }
+    *p = std::malloc(n ? n : 1);
+    g_live[*p] = n;
+    g_used += n;
+    return hipSuccess;
+}
+hipError_t hipFree(void* p) {
+    wait_device();
+    g_used -= g_live[p];
+    g_live.erase(p);
+    std::free(p);
+    return hipSuccess;
+}
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) { *p = std::malloc(n ? n : 1); return hipSuccess; }
+hipError_t hipHostFree(void* p) { std::free(p); return hipSuccess; }
+hipError_t hipMemGetInfo(size_t* f, size_t* t) { *f = g_room - g_used; *t = g_room; return hipSuccess; }
+hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { wait_device(); std::memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t st) {
+    std::memcpy(d, s, n);
+    g_pending.insert({g_device, st});
+    return hipSuccess;
+}
+hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t st) {
+    std::memset(d, v, n);
+    g_pending.insert({g_device, st});
+    return hipSuccess;
+}
+hipError_t hipEventCreate(hipEvent_t* e) { *e = (hipEvent_t)std::malloc(1); return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
+hipError_t hipEventDestroy(hipEvent_t e) { std::free(e); return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) {
+    if (g_fail_event_record == 0) { g_fail_event_record = -1; return hipErrorUnknown; }
+    if (g_fail_event_record > 0) g_fail_event_record--;
+    return hipSuccess;
+}
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 1.0f; return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t s) { g_pending.erase({g_device, s}); return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* st) {
+    *st = s && s == g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = (hipStream_t)std::malloc(1); return hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t s) { std::free(s); return hipSuccess; }
+hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return hipSuccess; }
+hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t* g) { *g = nullptr; return hipSuccess; }
+hipError_t hipGraphInstantiate(hipGraphExec_t* e, hipGraph_t, hipGraphNode_t*, char*, size_t) { *e = nullptr; return hipSuccess; }
+hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
+hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
+hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipSuccess; }
+}
+
+namespace gs {
+hipError_t launch_fill_rows(const DevIndex&, const int32_t*, void*, hipStream_t s) { launch("fill_rows", s); return hipSuccess; }
+hipError_t launch_narrow(const int32_t* src, uint16_t* dst, int64_t n, hipStream_t s) {
+    for (int64_t i = 0; i < n; i++) dst[i] = (uint16_t)src[i];
+    launch("narrow", s);
+    return hipSuccess;
+}
+hipError_t launch_clear(const Workspace&, int32_t, hipStream_t s) { launch("clear", s); return hipSuccess; }
+hipError_t launch_score_tiled(const DevIndex&, const DevBatch&, int32_t, int32_t, const ScoreOpts& o, const Workspace&,
+                              hipStream_t s, int) {
+    Launch& l = launch("score_tiled", s);
+    l.tile_shift = o.tile_shift;
+    l.chunk = o.chunk;
+    return hipSuccess;
+}
+hipError_t launch_score_group(const DevIndex&, const DevBatch&, const ScoreOpts&, const Workspace&, hipStream_t s, int) {
+    launch("score_group", s);
+    return hipSuccess;
+}
+hipError_t launch_score_atomic(const DevIndex&, const DevBatch&, int32_t, int32_t, const ScoreOpts& o, const Workspace&,
+                               hipStream_t s) {
+    launch("score_atomic", s).chunk = o.chunk;
+    return hipSuccess;
+}
+hipError_t launch_score_docpar(const DevIndex&, const DevBatch&, int32_t, int32_t, const ScoreOpts&, const Workspace&,
+                               hipStream_t s) {
+    launch("score_docpar", s);
+    return hipSuccess;
+}
+hipError_t launch_select(const DevIndex&, const DevBatch&, int32_t, int32_t, const Workspace&, int32_t*, void*, int32_t*,
+                         hipStream_t s, int, int, int, const ScoreOpts*, bool wide, bool from_row) {
+    Launch& l = launch("select", s);
+    l.wide = wide;
+    l.from_row = from_row;
+    return hipSuccess;
+}
+hipError_t launch_seed_bound(const DevIndex&, const DevBatch&, int32_t, int32_t, const Workspace&, hipStream_t s) {
+    launch("seed_bound", s);
+    return hipSuccess;
+}
+hipError_t launch_upload(void* d, const void* h, const UploadRanges& r, hipStream_t s) {
+    for (int i = 0; i < r.n; i++)
+        std::memcpy((uint8_t*)d + (size_t)r.at[i] * 16, (const uint8_t*)h + (size_t)r.at[i] * 16, (size_t)r.len[i] * 16);
+    launch("upload", s);
+    return hipSuccess;
+}
+hipError_t launch_copy16(void*, const void*, int64_t, hipStream_t s) { launch("copy16", s); return hipSuccess; }
+hipError_t launch_lds_atomic(int, int, int, int, void*, hipStream_t s) { launch("lds_atomic", s); return hipSuccess; }
+hipError_t launch_fill(void*, int64_t, uint32_t, hipStream_t s) { launch("fill", s); return hipSuccess; }
+hipError_t scratch_address(int, void** out) {
+    static std::vector<uint8_t> scratch(256);  // only its address is used: launches do nothing here
+    *out = scratch.data();
+    return hipSuccess;
+}
+}  // namespace gs
+
+// -------------------------------------------------------------- the cases --
+
+static int failures = 0;
+static void expect(bool ok, const char* what) {
+    if (!ok) {
+        std::fprintf(stderr, "FAILED: %s (%s)\n", what, gs_last_error());
+        failures++;
+    }
+}
+
+// n documents: term 0 in all of them, term 1 in every other one, term 2 + d % 20 in document d.
+static gs_index make_index(int n, int precision, uint32_t flags = 0) {
+    std::vector<int64_t> rp{0};
+    std::vector<int32_t> t;
+    std::vector<float> w;
+    for (int d = 0; d < n; d++) {
+        t.push_back(0);
+        if (d % 2) t.push_back(1);
+        t.push_back(2 + d % 20);
+        while (w.size() < t.size()) w.push_back(0.5f + (float)(w.size() % 7) / 4.0f);
+        rp.push_back((int64_t)t.size());
+    }
+    gs_index ix = nullptr;
+    gs_build_index(rp.data(), n, t.data(), w.data(), (int64_t)t.size(), 22, precision, flags, nullptr, &ix);
+    return ix;
+}
+
+struct Query {
+    std::vector<int64_t> rp{0, 3};
+    std::vector<int32_t> term{0, 1, 5};
+    std::vector<float> w{1.0f, 0.75f, 1.5f};
+    std::vector<int32_t> k{10};
+    std::vector<uint8_t> ws;
+    std::vector<int32_t> ids = std::vector<int32_t>(10);
+    std::vector<double> sc = std::vector<double>(10);
+    explicit Query(gs_index ix) {
+        size_t bytes = 0;
+        gs_workspace_size(ix, 1, nullptr, &bytes);
+        ws.resize(bytes);
+    }
+    int32_t search(gs_index ix, hipStream_t s = nullptr, const gs_search_opts* o = nullptr) {
+        return gs_search(ix, rp.data(), 1, term.data(), w.data(), 3, k.data(), 10, ws.data(), ws.size(), ids.data(),
+                         sc.data(), o, s);
+    }
+};
+
+static int count(const char* kernel) {
+    int n = 0;
+    for (const Launch& l : g_launches) n += l.kernel == kernel;
+    return n;
+}
+
+// The rows of the commonest terms: their number keeps the 32-bit byte offsets that the scoring
+// kernel forms inside its largest tile (2 grains of fp32, 4 of the other forms) below 2^31.
+static void row_limit() {
+    struct { int precision; int64_t w, grains; } form[3] = {{GS_FP32, 4, 2}, {GS_BF16, 2, 4}, {GS_U8, 1, 4}};
+    for (const auto& f : form)
+        for (int64_t n_grains : {1, 2, 3, 4, 100, 262144})
+            for (int64_t padded : {(int64_t)64, (int64_t)1 << 24, (int64_t)1 << 30, (int64_t)1 << 36}) {
+                const int64_t n = gs::row_limit(f.precision, n_grains, padded);
+                expect(n >= 0, "a limit");
+                expect(n << gs::kGrainShift < (int64_t)1 << 31, "a grain's rows");
+                expect((((f.grains - 1) * n + 1) << gs::kGrainShift) * f.w < (int64_t)1 << 31, "a tile's bytes");
+                const int64_t row = (n_grains << gs::kGrainShift) * f.w;
+                expect(n * row <= std::max((int64_t)64 << 20, 3 * (2 + f.w) * padded), "a limit on the rows' bytes");
+            }
+    // 16,384 documents, 262,144 terms in a quarter of them each
+    expect(gs::row_limit(GS_FP32, 2, 262144ll * 4096) > 0, "rows in a large index");
+}
+
+int main(int argc, char** argv) {
+    const std::string name = argc > 1 ? argv[1] : "";
+    if (name == "row_limit") row_limit();
+    else expect(false, "unknown case");
+    std::printf("%s: %d failures\n", name.c_str(), failures);
+    return failures == 0 ? 0 : 1;
+}
