@@ -1836,6 +1836,7 @@ int32_t gs_search(gs_index ix, const int64_t* q_row_ptr, int32_t n_queries, cons
     int32_t rc = batch_new(ix, n_queries, q_nnz, k_max, &b, &unused, true);
     if (rc != GS_OK) return rc;
     hipStream_t s = (hipStream_t)hip_stream;
+    DeviceGuard g(ix->device);  // the default stream that is waited for is the index's device's
     rc = gs::batch_update(b, q_row_ptr, n_queries, q_term_ids, q_weights, q_nnz, k, hip_stream, false);
     if (rc != GS_OK) {
         batch_return(b);
@@ -1846,10 +1847,8 @@ int32_t gs_search(gs_index ix, const int64_t* q_row_ptr, int32_t n_queries, cons
     int32_t* diag = (int32_t*)(b->stage + b->lay.diag);
     const bool check = rc == GS_OK && ix->precision == kBF16 && b->n_active > 0 && b->k_max > 0;
     hipError_t e = hipSuccess;
-    if (check) {
-        DeviceGuard g(ix->device);
+    if (check)
         e = hipMemcpyAsync(diag, b->diag, (size_t)b->n_active * kDiagWords * 4, hipMemcpyDeviceToHost, s);
-    }
     const hipError_t es = hipStreamSynchronize(s);
     if (e == hipSuccess) e = es;
     if (rc == GS_OK && e != hipSuccess) rc = fail(GS_EHIP, std::string("search: ") + hipGetErrorString(e));

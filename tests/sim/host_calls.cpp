@@ -231,9 +231,27 @@ static void row_limit() {
     expect(gs::row_limit(GS_FP32, 2, 262144ll * 4096) > 0, "rows in a large index");
 }
 
+// A synchronous search of an index on another device than the current one, on the default
+// stream: its work, on the index's device, is done when the call returns.
+static void search_waits_on_the_index_device() {
+    for (int precision : {GS_FP32, GS_BF16, GS_U8}) {
+        g_device = 1;
+        gs_index ix = make_index(40000, precision);
+        wait_device();
+        g_device = 0;
+        Query q(ix);
+        expect(q.search(ix) == GS_OK, "search");
+        for (const Launch& l : g_launches) expect(l.device == 1, "launched on the index's device");
+        expect(g_pending.empty(), "waited for");
+        expect(g_device == 0, "the caller's device is current again");
+        gs_free_index(ix);
+    }
+}
+
 int main(int argc, char** argv) {
     const std::string name = argc > 1 ? argv[1] : "";
     if (name == "row_limit") row_limit();
+    else if (name == "search_waits_on_the_index_device") search_waits_on_the_index_device();
     else expect(false, "unknown case");
     std::printf("%s: %d failures\n", name.c_str(), failures);
     return failures == 0 ? 0 : 1;
