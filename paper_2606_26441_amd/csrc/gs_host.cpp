@@ -1839,7 +1839,8 @@ int32_t gs_search(gs_index ix, const int64_t* q_row_ptr, int32_t n_queries, cons
     DeviceGuard g(ix->device);  // the default stream that is waited for is the index's device's
     rc = gs::batch_update(b, q_row_ptr, n_queries, q_term_ids, q_weights, q_nnz, k, hip_stream, false);
     if (rc != GS_OK) {
-        batch_return(b);
+        if (rc == GS_EHIP) gs_batch_free(b);  // its upload may be under way: freeing waits for the device
+        else batch_return(b);
         return rc;
     }
     rc = gs_search_batch(ix, b, workspace, workspace_bytes_, out_ids, out_scores, opts, hip_stream);

@@ -248,10 +248,28 @@ static void search_waits_on_the_index_device() {
     }
 }
 
+// An update that fails after its upload was enqueued: the batch's memory is still being read, so
+// it is freed (which waits for the device) and not kept for the next call.
+static void failed_upload_keeps_no_batch() {
+    gs_index ix = make_index(40000, GS_FP32);
+    wait_device();
+    Query q(ix);
+    const size_t before = g_live.size();
+    g_fail_event_record = 0;
+    expect(q.search(ix) == GS_EHIP, "the update fails");
+    expect(g_pending.empty() && g_live.size() == before, "nothing is kept while work is under way");
+    expect(q.search(ix) == GS_OK && g_live.size() == before + 1, "the next call keeps its batch");
+    q.term[0] = -1;
+    expect(q.search(ix) == GS_EINVAL && g_live.size() == before + 1, "a refused call keeps it too");
+    gs_free_index(ix);
+    expect(g_live.empty(), "all of it is freed with the index");
+}
+
 int main(int argc, char** argv) {
     const std::string name = argc > 1 ? argv[1] : "";
     if (name == "row_limit") row_limit();
     else if (name == "search_waits_on_the_index_device") search_waits_on_the_index_device();
+    else if (name == "failed_upload_keeps_no_batch") failed_upload_keeps_no_batch();
     else expect(false, "unknown case");
     std::printf("%s: %d failures\n", name.c_str(), failures);
     return failures == 0 ? 0 : 1;

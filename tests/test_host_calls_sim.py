@@ -13,7 +13,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2606_26441_amd", "csrc")
 HIP_INCLUDE = "/opt/rocm/include"
 
-CASES = ["row_limit", "search_waits_on_the_index_device"]
+CASES = ["row_limit", "search_waits_on_the_index_device", "failed_upload_keeps_no_batch"]
 
 
 @pytest.fixture(scope="module")
