@@ -323,6 +323,8 @@ int32_t gs_workspace_size(gs_index index, int32_t query_tile, const gs_search_op
  *   GS_BF16, int32 for GS_U8.
  * Asynchronous on hip_stream. The index and batch are only read, so searches
  * with separate workspaces and outputs may run concurrently on different streams.
+ * On a stream under capture the launches are those of every later
+ * gs_batch_update with as many queries as the batch holds at the capture.
  * Errors: GS_EINVAL (NULL arguments, bad opts), GS_ECAPACITY (workspace too
  *   small), GS_EUNSUPPORTED (kernel not available for this index), GS_EHIP.
  */

@@ -1489,8 +1489,8 @@ int32_t plan_search(gs_index ix, gs_batch b, size_t workspace_bytes_, const gs_s
 // Queries [0, nq) are searched; output rows [nq, capacity) are written as padding
 // (id -1, score 0). A direct search passes the queries of the last update, a
 // graph the whole capacity (it is replayed after updates of any size).
-// any_update: the launches must serve every later update of the batch (a graph), not
-// only the queries it holds now.
+// any_update: the launches must serve every later update of the batch (a graph, or a
+// caller's own capture), not only the queries it holds now.
 int32_t enqueue_search(gs_index ix, gs_batch b, int32_t nq, const Workspace& ws, int32_t qt, const ScoreOpts& so_in,
                        int32_t* out_ids, void* out_scores, hipStream_t s, bool timing, bool any_update = false) {
     ScoreOpts so = so_in;
@@ -1586,6 +1586,12 @@ int32_t enqueue_search(gs_index ix, gs_batch b, int32_t nq, const Workspace& ws,
     return GS_OK;
 }
 
+// Whether a caller is capturing stream s (the default stream cannot be captured).
+bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    return s && hipStreamIsCapturing(s, &st) == hipSuccess && st == hipStreamCaptureStatusActive;
+}
+
 }  // namespace
 
 namespace gs {
@@ -1651,7 +1657,8 @@ int32_t gs_search_batch(gs_index ix, gs_batch b, void* workspace, size_t workspa
     DeviceGuard g(ix->device);
     Workspace ws;
     carve_workspace(workspace, ix->n_docs, qt, ix->precision, &ws);
-    return enqueue_search(ix, b, b->n_active, ws, qt, so, out_ids, out_scores, (hipStream_t)hip_stream, true);
+    hipStream_t s = (hipStream_t)hip_stream;
+    return enqueue_search(ix, b, b->n_active, ws, qt, so, out_ids, out_scores, s, true, capturing(s));
 }
 
 int32_t gs_search_batch_noalloc(gs_index ix, gs_batch b, int32_t* out_ids, void* out_scores,
@@ -1676,7 +1683,8 @@ int32_t gs_search_batch_noalloc(gs_index ix, gs_batch b, int32_t* out_ids, void*
     // no timing events: nothing is created or allocated on this path
     Workspace ws;
     carve_workspace(scratch, ix->n_docs, qt, ix->precision, &ws);
-    return enqueue_search(ix, b, b->n_active, ws, qt, so, out_ids, out_scores, (hipStream_t)hip_stream, false);
+    hipStream_t s = (hipStream_t)hip_stream;
+    return enqueue_search(ix, b, b->n_active, ws, qt, so, out_ids, out_scores, s, false, capturing(s));
 }
 
 int32_t gs_graph_create(gs_index ix, gs_batch b, void* workspace, size_t workspace_bytes_, int32_t* out_ids,

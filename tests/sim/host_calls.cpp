@@ -265,11 +265,43 @@ static void failed_upload_keeps_no_batch() {
     expect(g_live.empty(), "all of it is freed with the index");
 }
 
+// A search that its caller captures is replayed after updates with any queries, wide-range ones
+// among them: the launches hold the wide-range pass whatever the batch holds at capture.
+static void captured_search_has_the_wide_pass() {
+    for (int precision : {GS_FP32, GS_BF16, GS_U8})
+        for (int docs : {20000, 40000})
+            for (bool captured : {false, true}) {
+                gs_index ix = make_index(docs, precision);
+                Query q(ix);
+                gs_batch b = nullptr;
+                expect(gs_batch_create(ix, q.rp.data(), 1, q.term.data(), q.w.data(), 3, q.k.data(), 10, nullptr, &b) == GS_OK,
+                       "batch");
+                int mine = 0;
+                const hipStream_t s = (hipStream_t)&mine;
+                g_capturing = captured ? s : nullptr;
+                for (int noalloc = 0; noalloc < 2; noalloc++) {
+                    g_launches.clear();
+                    expect((noalloc ? gs_search_batch_noalloc(ix, b, q.ids.data(), q.sc.data(), nullptr, s)
+                                    : gs_search_batch(ix, b, q.ws.data(), q.ws.size(), q.ids.data(), q.sc.data(), nullptr, s)) == GS_OK,
+                           "search");
+                    expect(count("select") == 1, "one selection");
+                    const Launch& l = g_launches.back();
+                    // these weights give an fp32 query no wide-range limit, a bf16 one neither
+                    expect(l.wide == (captured && precision != GS_U8), "the wide-range pass");
+                    expect(l.from_row == (docs <= gs::kCandCap && precision != GS_BF16 && !l.wide), "rows as candidates");
+                }
+                g_capturing = nullptr;
+                gs_batch_free(b);
+                gs_free_index(ix);
+            }
+}
+
 int main(int argc, char** argv) {
     const std::string name = argc > 1 ? argv[1] : "";
     if (name == "row_limit") row_limit();
     else if (name == "search_waits_on_the_index_device") search_waits_on_the_index_device();
     else if (name == "failed_upload_keeps_no_batch") failed_upload_keeps_no_batch();
+    else if (name == "captured_search_has_the_wide_pass") captured_search_has_the_wide_pass();
     else expect(false, "unknown case");
     std::printf("%s: %d failures\n", name.c_str(), failures);
     return failures == 0 ? 0 : 1;

@@ -13,7 +13,8 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2606_26441_amd", "csrc")
 HIP_INCLUDE = "/opt/rocm/include"
 
-CASES = ["row_limit", "search_waits_on_the_index_device", "failed_upload_keeps_no_batch"]
+CASES = ["row_limit", "search_waits_on_the_index_device", "failed_upload_keeps_no_batch",
+         "captured_search_has_the_wide_pass"]
 
 
 @pytest.fixture(scope="module")
