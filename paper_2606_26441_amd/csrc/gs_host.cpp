@@ -432,7 +432,6 @@ struct gs_index_s {
     int device = 0;
     int64_t n_docs = 0, nnz = 0, padded = 0, n_grains = 0;
     int64_t n_dense = 0;              // terms whose lists have the byte doc-id form
-    int32_t n_rows = 0;               // terms with a row
     std::vector<uint8_t> term_dense;  // [V] host copy of the byte-form flags
     int32_t vocab = 0, precision = 0;
     uint32_t flags = 0;
@@ -544,8 +543,9 @@ int32_t dev_upload(std::vector<void*>& allocs, size_t& bytes, const T* host, siz
 // whole grains, so in a collection of a few documents rows could take thousands of times their
 // postings' bytes (3 documents of 30,000 terms: 3 GB): beyond 64 MiB they take at most 3 times the
 // bytes of the postings, the longest lists first, and there are never more than max_rows. In large
-// collections the share of the documents that a row needs keeps them below that by itself. None are built where the device has not four
-// times their room free. A term without a row is summed from its list.
+// collections the share of the documents that a row needs keeps them below that by itself. None
+// are built where the device has not four times their room free, or their allocation fails: a
+// term without a row is summed from its list.
 constexpr int64_t kRowBytesFree = 64ll << 20;
 
 }  // namespace
@@ -575,22 +575,29 @@ int32_t build_rows(gs_index ix, hipStream_t s) {
     } catch (const std::bad_alloc&) {
         return fail(GS_ENOMEM, "host memory for the row table");
     }
+    const int64_t bytes = row * (int64_t)terms.size();
     size_t room = 0, total = 0;
-    if (row * (int64_t)terms.size() > kRowBytesFree && hipMemGetInfo(&room, &total) == hipSuccess &&
-        (int64_t)(room / 4) < row * (int64_t)terms.size())
-        terms.clear();
-    for (size_t i = 0; i < terms.size(); i++) ix->terms[(size_t)terms[i]].row = (int32_t)i;
-    ix->n_rows = (int32_t)terms.size();
-    d.n_rows = ix->n_rows;
+    if (bytes > kRowBytesFree && hipMemGetInfo(&room, &total) == hipSuccess && (int64_t)(room / 4) < bytes) terms.clear();
+    if (terms.empty()) return GS_OK;
+    // the terms are read by the fill alone
     int32_t* pt = nullptr;
     uint8_t* rows = nullptr;
-    int32_t rc = dev_upload(ix->allocs, ix->bytes, terms.data(), terms.size(), &pt, s);
-    if (rc == GS_OK)
-        rc = dev_upload(ix->allocs, ix->bytes, (const uint8_t*)nullptr, (size_t)(row * ix->n_rows), &rows, s);
-    if (rc != GS_OK) return rc;
+    if (dev_malloc((void**)&rows, (size_t)bytes) != hipSuccess ||
+        dev_malloc((void**)&pt, terms.size() * 4) != hipSuccess) {
+        (void)hipGetLastError();  // the index works without rows
+        if (rows) (void)hipFree(rows);
+        return GS_OK;
+    }
+    ix->allocs.push_back(rows);
+    ix->bytes += (size_t)bytes;
+    for (size_t i = 0; i < terms.size(); i++) ix->terms[(size_t)terms[i]].row = (int32_t)i;
+    d.n_rows = (int32_t)terms.size();
     d.rows = rows;
-    hipError_t e = launch_fill_rows(d, pt, rows, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);  // `terms` is read by the copy
+    hipError_t e = hipMemcpyAsync(pt, terms.data(), terms.size() * 4, hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = launch_fill_rows(d, pt, rows, s);
+    const hipError_t done = hipStreamSynchronize(s);
+    (void)hipFree(pt);
+    if (e == hipSuccess) e = done;
     if (e != hipSuccess) return fail(GS_EHIP, std::string("term rows: ") + hipGetErrorString(e));
     return GS_OK;
 }
@@ -1064,7 +1071,6 @@ int32_t gs_build_index(const int64_t* row_ptr, int64_t n_docs, const int32_t* te
         hipError_t e = hipStreamSynchronize(s);
         if (e != hipSuccess) return done(fail(GS_EHIP, std::string("upload: ") + hipGetErrorString(e)));
     }
-    if ((rc = build_rows(ix, s))) return done(rc);
     if (flags & GS_KEEP_FORWARD) {
         int64_t* frp = nullptr;
         float* fw = nullptr;
@@ -1074,6 +1080,7 @@ int32_t gs_build_index(const int64_t* row_ptr, int64_t n_docs, const int32_t* te
         d.fwd_row_ptr = frp;
         d.fwd_w = fw;
     }
+    if ((rc = build_rows(ix, s))) return done(rc);  // last: rows take no memory that the index needs
     hipError_t e = hipStreamSynchronize(s);
     if (e != hipSuccess) return done(fail(GS_EHIP, std::string("upload: ") + hipGetErrorString(e)));
     *out = ix;

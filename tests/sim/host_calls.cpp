@@ -296,12 +296,62 @@ static void captured_search_has_the_wide_pass() {
             }
 }
 
+// Rows are optional: where their memory cannot be had the index is built without them, and it
+// takes no memory that the rest of the index needs.
+static void index_without_room_for_rows() {
+    for (int precision : {GS_FP32, GS_BF16, GS_U8}) {
+        const int n = 200000;
+        const uint32_t flags = GS_KEEP_FORWARD | GS_KEEP_DOC_IDS;
+        gs_index ix = make_index(n, precision, flags);
+        expect(ix && count("fill_rows") == 1, "rows where there is room");
+        gs_index_info_t with{}, without{};
+        gs_index_info(ix, &with);
+        gs_free_index(ix);
+        expect(g_live.empty(), "freed");
+        // the least memory that the index can be built in, to 1 MiB
+        size_t lo = 0, hi = (size_t)with.device_bytes + (64 << 20);
+        while (hi - lo > (1 << 20)) {
+            g_room = (lo + hi) / 2;
+            g_launches.clear();
+            gs_index t = make_index(n, precision, flags);
+            if (t) {
+                hi = g_room;
+                if (count("fill_rows") == 0) gs_index_info(t, &without);
+                gs_free_index(t);
+            } else {
+                lo = g_room;
+            }
+            expect(g_used == 0, "nothing is left of a failed build");
+        }
+        const int64_t row = ((n + 8191) / 8192) * 8192ll * (precision == GS_FP32 ? 4 : precision == GS_BF16 ? 2 : 1);
+        expect(with.device_bytes - without.device_bytes == 2 * row, "two rows");
+        // the forward terms pass through a stage of four bytes each while the index is built
+        expect((int64_t)hi <= without.device_bytes + 4 * with.nnz + (2 << 20), "no memory of the rows is needed");
+        g_room = (size_t)1 << 40;
+        // their allocation fails, whatever the free memory says: no rows, and a search that works
+        g_launches.clear();
+        int64_t allocs = 0;
+        for (;; allocs++) {
+            gs_debug_fail_alloc(allocs);
+            ix = make_index(n, precision, flags);
+            gs_debug_fail_alloc(-1);
+            if (ix) break;
+        }
+        gs_index_info(ix, &without);
+        expect(count("fill_rows") == 0 && with.device_bytes - without.device_bytes == 2 * row, "built without rows");
+        Query q(ix);
+        expect(q.search(ix) == GS_OK, "searched without rows");
+        gs_free_index(ix);
+    }
+}
+
 int main(int argc, char** argv) {
     const std::string name = argc > 1 ? argv[1] : "";
     if (name == "row_limit") row_limit();
     else if (name == "search_waits_on_the_index_device") search_waits_on_the_index_device();
     else if (name == "failed_upload_keeps_no_batch") failed_upload_keeps_no_batch();
     else if (name == "captured_search_has_the_wide_pass") captured_search_has_the_wide_pass();
+    else if (name == "index_without_room_for_rows") index_without_room_for_rows();
     else expect(false, "unknown case");
     std::printf("%s: %d failures\n", name.c_str(), failures);
     return failures == 0 ? 0 : 1;
