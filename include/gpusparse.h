@@ -386,8 +386,10 @@ void gs_graph_free(gs_graph graph);
 /*
  * Autotuner: runs this batch with every candidate option set - scoring kernel
  * (GS_KERNEL_TILED, GS_KERNEL_SHARED) x tile_docs (8192, 16384; plus 32768 for
- * GS_BF16 and GS_U8) x chunk (128, 256, 512, 1024) - one untimed run then `reps` timed runs
- * each (HIP events on hip_stream), and writes the fastest option set to *best.
+ * GS_BF16 and GS_U8) x chunk (128, 256, 512, 1024), and GS_KERNEL_GROUP x chunk
+ * (256, 512, 1024) - one untimed run then `reps` timed runs each (HIP events on
+ * hip_stream), and writes the fastest option set to *best. Option sets that run
+ * the same launches are timed once and share that time.
  * Optional host outputs: cands[max_candidates] (the option sets tried, in
  * order), times_ms[max_candidates] (mean search time of each), n_candidates.
  * Synchronous; overwrites out_ids / out_scores. Errors: as gs_search_batch.

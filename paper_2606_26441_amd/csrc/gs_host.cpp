@@ -1776,10 +1776,29 @@ int32_t gs_autotune(gs_index ix, gs_batch b, void* workspace, size_t workspace_b
         (void)hipEventDestroy(e0);
         return fail(GS_EHIP, std::string("hipEventCreate: ") + hipGetErrorString(he));
     }
+    // Option sets with the same launches are timed once: TILED and SHARED are one kernel, which
+    // runs chunks below 256 as 256.
+    auto same = [](const gs_search_opts& x, const gs_search_opts& y) {
+        return (x.kernel == GS_KERNEL_GROUP) == (y.kernel == GS_KERNEL_GROUP) && x.tile_docs == y.tile_docs &&
+               std::max(x.chunk, 256) == std::max(y.chunk, 256);
+    };
     float best_ms = 0.0f;
     int best_i = -1;
     int32_t rc = GS_OK;
+    std::vector<float> times(cand.size(), 0.0f);
+    auto report = [&](size_t i) {
+        if ((int32_t)i >= max_candidates) return;
+        if (cands) cands[i] = cand[i];
+        if (times_ms) times_ms[i] = times[i];
+    };
     for (size_t i = 0; i < cand.size() && rc == GS_OK; i++) {
+        size_t first = 0;
+        while (!same(cand[first], cand[i])) first++;
+        if (first < i) {
+            times[i] = times[first];
+            report(i);
+            continue;
+        }
         ScoreOpts so;
         int32_t qt = 1;
         rc = plan_search(ix, b, workspace_bytes_, &cand[i], &so, &qt);
@@ -1798,10 +1817,8 @@ int32_t gs_autotune(gs_index ix, gs_batch b, void* workspace, size_t workspace_b
         if (he != hipSuccess) rc = fail(GS_EHIP, std::string("autotune timing: ") + hipGetErrorString(he));
         if (rc != GS_OK) break;
         ms /= (float)reps;
-        if ((int32_t)i < max_candidates) {
-            if (cands) cands[i] = cand[i];
-            if (times_ms) times_ms[i] = ms;
-        }
+        times[i] = ms;
+        report(i);
         if (best_i < 0 || ms < best_ms) {
             best_ms = ms;
             best_i = (int)i;

@@ -345,6 +345,35 @@ static void index_without_room_for_rows() {
     }
 }
 
+// The autotuner times each different launch once: the per-query and the shared-traversal kernel are
+// one, and chunks below 256 run as 256.
+static void autotune_times_each_launch_once() {
+    for (int precision : {GS_FP32, GS_U8}) {
+        gs_index ix = make_index(40000, precision);
+        Query q(ix);
+        gs_batch b = nullptr;
+        gs_batch_create(ix, q.rp.data(), 1, q.term.data(), q.w.data(), 3, q.k.data(), 10, nullptr, &b);
+        g_launches.clear();
+        gs_search_opts best{}, cands[64];
+        float ms[64] = {};
+        int32_t n = 0;
+        const int reps = 3, tiles = precision == GS_FP32 ? 2 : 3;
+        expect(gs_autotune(ix, b, q.ws.data(), q.ws.size(), q.ids.data(), q.sc.data(), reps, nullptr, &best, cands, ms, 64,
+                           &n) == GS_OK, "autotune");
+        expect(n == 2 * tiles * 4 + 3, "every option set is listed");
+        std::map<std::pair<int, int>, int> runs;
+        for (const Launch& l : g_launches)
+            if (l.kernel == "score_tiled") runs[{l.tile_shift, std::max(l.chunk, 256)}]++;
+        int total = 0;
+        for (const auto& r : runs) total += r.second;
+        expect((int)runs.size() == tiles * 3, "different doc-tiled launches");
+        expect(total == tiles * 3 * (1 + reps) + 1, "each timed once, and the best run at the end");
+        for (int i = 0; i < n; i++) expect(ms[i] > 0.0f, "a time for every option set");
+        gs_batch_free(b);
+        gs_free_index(ix);
+    }
+}
+
 int main(int argc, char** argv) {
     const std::string name = argc > 1 ? argv[1] : "";
     if (name == "row_limit") row_limit();
@@ -352,6 +381,7 @@ int main(int argc, char** argv) {
     else if (name == "failed_upload_keeps_no_batch") failed_upload_keeps_no_batch();
     else if (name == "captured_search_has_the_wide_pass") captured_search_has_the_wide_pass();
     else if (name == "index_without_room_for_rows") index_without_room_for_rows();
+    else if (name == "autotune_times_each_launch_once") autotune_times_each_launch_once();
     else expect(false, "unknown case");
     std::printf("%s: %d failures\n", name.c_str(), failures);
     return failures == 0 ? 0 : 1;

@@ -14,7 +14,8 @@ CSRC = os.path.join(ROOT, "paper_2606_26441_amd", "csrc")
 HIP_INCLUDE = "/opt/rocm/include"
 
 CASES = ["row_limit", "search_waits_on_the_index_device", "failed_upload_keeps_no_batch",
-         "captured_search_has_the_wide_pass", "index_without_room_for_rows"]
+         "captured_search_has_the_wide_pass", "index_without_room_for_rows",
+         "autotune_times_each_launch_once"]
 
 
 @pytest.fixture(scope="module")
