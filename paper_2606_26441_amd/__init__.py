@@ -29,12 +29,138 @@ GS_MAX_QUERY_NNZ = 256
 PRECISIONS = {"fp32": GS_FP32, "bf16": GS_BF16, "u8": GS_U8}
 KERNELS = {"auto": GS_KERNEL_AUTO, "tiled": GS_KERNEL_TILED, "atomic": GS_KERNEL_ATOMIC,
            "docpar": GS_KERNEL_DOCPAR, "shared": GS_KERNEL_SHARED, "group": GS_KERNEL_GROUP}
-SCOREdef _np(a, dtype):
+SCORE_DTYPES = {GS_FP32: torch.float32, GS_BF16: torch.float64, GS_U8: torch.int32}
+
+
+class GsError(RuntimeError):
+    def __init__(self, code: int, where: str, msg: str):
+        super().__init__("%s failed: %s (%d): %s" % (where, _STATUS.get(code, "?"), code, msg))
+        self.code = code
+
+
+_STATUS = {0: "ok", -1: "invalid argument", -2: "out of memory", -3: "HIP error", -4: "capacity exceeded",
+           -5: "unsupported", -6: "timeout"}
+
+
+class SearchOpts(ctypes.Structure):
+    _fields_ = [("kernel", ctypes.c_int32), ("query_tile", ctypes.c_int32), ("tile_docs", ctypes.c_int32),
+                ("chunk", ctypes.c_int32), ("no_fused_filter", ctypes.c_int32), ("prune", ctypes.c_int32),
+                ("reserved", ctypes.c_int32 * 2)]
+
+
+class ServerOpts(ctypes.Structure):
+    _fields_ = [("max_batch", ctypes.c_int32), ("n_slots", ctypes.c_int32), ("k_max", ctypes.c_int32),
+                ("reserved", ctypes.c_int32), ("memory_budget", ctypes.c_int64), ("search", SearchOpts)]
+
+
+class ServerStats(ctypes.Structure):
+    _fields_ = [("n_slots", ctypes.c_int32), ("max_batch", ctypes.c_int32), ("completed", ctypes.c_int64),
+                ("failed", ctypes.c_int64), ("device_steps", ctypes.c_int64), ("mean_batch", ctypes.c_double),
+                ("max_in_flight", ctypes.c_int64), ("pending", ctypes.c_int64), ("arena_rows", ctypes.c_int64),
+                ("arena_bytes", ctypes.c_int64), ("row_bytes", ctypes.c_int64)]
+
+
+class IndexInfo(ctypes.Structure):
+    _fields_ = [("n_docs", ctypes.c_int64), ("nnz", ctypes.c_int64), ("padded_nnz", ctypes.c_int64),
+                ("device_bytes", ctypes.c_int64), ("vocab_size", ctypes.c_int32), ("precision", ctypes.c_int32),
+                ("flags", ctypes.c_uint32), ("tile_grain", ctypes.c_int32), ("n_tiles", ctypes.c_int64),
+                ("n_dense_terms", ctypes.c_int64)]
+
+
+def _load() -> ctypes.CDLL:
+    if not os.path.exists(LIB_PATH):
+        raise ImportError("libgpusparse.so is not built (run: python paper_2606_26441_amd/build.py)")
+    lib = ctypes.CDLL(LIB_PATH)
+    i32, i64, u32, vp, sz = ctypes.c_int32, ctypes.c_int64, ctypes.c_uint32, ctypes.c_void_p, ctypes.c_size_t
+    P = ctypes.POINTER
+    lib.gs_version.restype = ctypes.c_char_p
+    lib.gs_status_string.argtypes = [i32]
+    lib.gs_status_string.restype = ctypes.c_char_p
+    lib.gs_last_error.restype = ctypes.c_char_p
+    lib.gs_debug_fail_alloc.argtypes = [i64]
+    lib.gs_debug_fail_alloc.restype = i32
+    lib.gs_build_index.argtypes = [vp, i64, vp, vp, i64, i32, i32, u32, vp, P(vp)]
+    lib.gs_build_index.restype = i32
+    lib.gs_index_info.argtypes = [vp, P(IndexInfo)]
+    lib.gs_index_info.restype = i32
+    lib.gs_index_dense_terms.argtypes = [vp, vp, i32]
+    lib.gs_index_dense_terms.restype = i32
+    lib.gs_free_index.argtypes = [vp]
+    lib.gs_free_index.restype = None
+    lib.gs_layout_host.argtypes = [vp, i64, vp, vp, i64, i32, i32, vp, vp, vp, vp, vp, vp, vp, vp, vp]
+    lib.gs_layout_host.restype = i32
+    lib.gs_query_plan_host.argtypes = [i32, vp, vp, vp, i32, P(i32), P(ctypes.c_double), P(ctypes.c_double)]
+    lib.gs_query_plan_host.restype = i32
+    lib.gs_batch_create.argtypes = [vp, vp, i32, vp, vp, i64, vp, i32, vp, P(vp)]
+    lib.gs_batch_create.restype = i32
+    lib.gs_batch_free.argtypes = [vp]
+    lib.gs_batch_free.restype = None
+    lib.gs_batch_reserve.argtypes = [vp, i32, i64, i32, P(vp)]
+    lib.gs_batch_reserve.restype = i32
+    lib.gs_batch_update.argtypes = [vp, vp, i32, vp, vp, i64, vp, vp]
+    lib.gs_batch_update.restype = i32
+    lib.gs_graph_create.argtypes = [vp, vp, vp, sz, vp, vp, P(SearchOpts), vp, P(vp)]
+    lib.gs_graph_create.restype = i32
+    lib.gs_graph_launch.argtypes = [vp, vp]
+    lib.gs_graph_launch.restype = i32
+    lib.gs_graph_free.argtypes = [vp]
+    lib.gs_graph_free.restype = None
+    lib.gs_autotune.argtypes = [vp, vp, vp, sz, vp, vp, i32, vp, P(SearchOpts), vp, vp, i32, P(i32)]
+    lib.gs_autotune.restype = i32
+    lib.gs_server_create.argtypes = [vp, P(ServerOpts), P(vp)]
+    lib.gs_server_create.restype = i32
+    lib.gs_server_submit.argtypes = [vp, vp, vp, i32, i32]
+    lib.gs_server_submit.restype = i64
+    lib.gs_server_wait.argtypes = [vp, i64, i32, vp, vp, P(ctypes.c_double)]
+    lib.gs_server_wait.restype = i32
+    lib.gs_server_poll.argtypes = [vp, i64, vp, vp, P(ctypes.c_double)]
+    lib.gs_server_poll.restype = i32
+    lib.gs_server_stats.argtypes = [vp, P(ServerStats)]
+    lib.gs_server_stats.restype = i32
+    lib.gs_server_destroy.argtypes = [vp]
+    lib.gs_server_destroy.restype = None
+    lib.gs_search_workspace_size.argtypes = [vp, i32, i64, i32, P(SearchOpts), P(sz)]
+    lib.gs_search_workspace_size.restype = i32
+    lib.gs_workspace_size.argtypes = [vp, i32, P(SearchOpts), P(sz)]
+    lib.gs_workspace_size.restype = i32
+    lib.gs_search_batch.argtypes = [vp, vp, vp, sz, vp, vp, P(SearchOpts), vp]
+    lib.gs_search_batch.restype = i32
+    lib.gs_search_batch_noalloc.argtypes = [vp, vp, vp, vp, P(SearchOpts), vp]
+    lib.gs_search_batch_noalloc.restype = i32
+    lib.gs_search.argtypes = [vp, vp, i32, vp, vp, i64, vp, i32, vp, sz, vp, vp, P(SearchOpts), vp]
+    lib.gs_search.restype = i32
+    lib.gs_batch_diagnostics.argtypes = [vp, vp]
+    lib.gs_batch_diagnostics.restype = i32
+    lib.gs_device_copy.argtypes = [vp, vp, sz, vp]
+    lib.gs_device_copy.restype = i32
+    lib.gs_lds_atomic_probe.argtypes = [i32, i32, i32, i32, vp, vp, P(i64)]
+    lib.gs_lds_atomic_probe.restype = i32
+    lib.gs_timing_enable.argtypes = [i32]
+    lib.gs_timing_enable.restype = i32
+    lib.gs_timing_read.argtypes = [P(ctypes.c_double), P(i64), P(ctypes.c_double), P(i64)]
+    lib.gs_timing_read.restype = i32
+    return lib
+
+
+lib = _load()
+
+
+def _check(rc: int, where: str):
+    if rc != GS_OK:
+        raise GsError(rc, where, lib.gs_last_error().decode())
+
+
+_DTYPES = {t: np.dtype(t) for t in (np.int32, np.int64, np.float32)}
+
+
+def _np(a, dtype):
+    if type(a) is np.ndarray and a.dtype is _DTYPES[dtype] and a.flags.c_contiguous:
+        return a
     return np.ascontiguousarray(np.asarray(a), dtype=dtype)
 
 
 def _ptr(a: np.ndarray) -> int:
-    """Address of an array's data (0.50 us a call on the GPU's host; a.ctypes.data 0.57)."""
+    """Address of an array's data (a.ctypes.data builds an object per call)."""
     return a.__array_interface__["data"][0]
 
 
