@@ -150,17 +150,12 @@ def _check(rc: int, where: str):
         raise GsError(rc, where, lib.gs_last_error().decode())
 
 
-_DTYPES = {t: np.dtype(t) for t in (np.int32, np.int64, np.float32)}
-
-
 def _np(a, dtype):
-    if type(a) is np.ndarray and a.dtype is _DTYPES[dtype] and a.flags.c_contiguous:
-        return a
     return np.ascontiguousarray(np.asarray(a), dtype=dtype)
 
 
 def _ptr(a: np.ndarray) -> int:
-    """Address of an array's data (a.ctypes.data builds an object per call)."""
+    """Address of an array's data (0.50 us a call on the GPU's host; a.ctypes.data 0.57)."""
     return a.__array_interface__["data"][0]
 
 
