@@ -1107,10 +1107,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
     score_tile<P, TS, CH, false, true>(ix, qb, q0, tile, (int)blockIdx.y, S, ld, hist1, lds, sh, phase, state, cand);
 }
 
-// The rows of the listed queries scored again, one workgroup per tile walking the list
-// (usually empty): those that fell back from fused filtering (phase 3) or were found wide
-// range (phase 4, W: fp64 accumulation). score_tile skips the other kind. A kernel of its
-// own, so that the per-query kernel's registers hold one copy of the scoring loop.
+// The rows of the listed queries scored again, a few workgroups per tile sharing the list (usually
+// empty): those that fell back from fused filtering (phase 3), were found wide range (phase 4, W:
+// fp64 accumulation) or need their band pass's rows (phase 5). score_tile skips the other kinds. A
+// kernel of its own, so that the per-query kernel's registers hold one copy of the scoring loop.
 template <int P, int TS, int CH, bool W = false>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_score_listed(
     DevIndex ix, DevBatch qb, int32_t q0, uint32_t* __restrict__ S, int64_t ld, uint32_t* __restrict__ hist1,
@@ -1120,7 +1120,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
     __shared__ TileShared sh;
     const int64_t tile = phase_tile(phase, stride, (int64_t)blockIdx.x);
     const int nres = (int)counters[kCntListed];
-    for (int r = 0; r < nres; r++) {
+    for (int r = (int)blockIdx.y; r < nres; r += (int)gridDim.y) {
         score_tile<P, TS, CH, W>(ix, qb, q0, tile, rescore_list[r], S, ld, hist1, lds, sh, phase, state, cand);
         __syncthreads();
     }
@@ -1609,7 +1609,8 @@ hipError_t launch_tiled(const DevIndex& ix, const DevBatch& qb, int32_t q0, int3
         static const hipError_t attr =
             allow_lds((const void*)k_score_listed<P, TS, kMaxChunk>, lds, "hipFuncSetAttribute(k_score_listed)");
         if (attr != hipSuccess) return attr;
-        hipLaunchKernelGGL((k_score_listed<P, TS, kMaxChunk>), dim3((unsigned)n_tiles, 1u), dim3(512), lds, s, ix, qb, q0,
+        const dim3 grid((unsigned)n_tiles, (unsigned)listed_ways(n_tiles, qt));
+        hipLaunchKernelGGL((k_score_listed<P, TS, kMaxChunk>), grid, dim3(512), lds, s, ix, qb, q0,
                            ws.scores, ld, ws.hist1, phase, stride, ws.state, ws.cand, (const uint32_t*)ws.counters,
                            (const int32_t*)ws.rescore_list);
         GS_CHECK_LAUNCH("k_score_listed");
@@ -1679,7 +1680,8 @@ struct ScoreForm {
                             const Workspace& ws, hipStream_t s, int phase);
     static hipError_t group(const DevIndex& ix, const DevBatch& qb, const ScoreOpts& o, const Workspace& ws,
                             hipStream_t s, int phase);
-    static hipError_t wide(const DevIndex& ix, const DevBatch& qb, int32_t q0, const Workspace& ws, hipStream_t s);
+    static hipError_t wide(const DevIndex& ix, const DevBatch& qb, int32_t q0, int32_t qt, const Workspace& ws,
+                           hipStream_t s);
 };
 
 #if !defined(GS_SCORE_PART) || GS_SCORE_PART != 3
@@ -1710,8 +1712,9 @@ hipError_t ScoreForm<P>::group(const DevIndex& ix, const DevBatch& qb, const Sco
 }
 
 template <int P>
-hipError_t ScoreForm<P>::wide(const DevIndex& ix, const DevBatch& qb, int32_t q0, const Workspace& ws, hipStream_t s) {
-    // 8192 docs of fp64 accumulators (64 KiB of LDS), one workgroup per tile walking the list
+hipError_t ScoreForm<P>::wide(const DevIndex& ix, const DevBatch& qb, int32_t q0, int32_t qt, const Workspace& ws,
+                              hipStream_t s) {
+    // 8192 docs of fp64 accumulators (64 KiB of LDS)
     constexpr int TS = 13, CH = 256;
     const int64_t n_tiles = (ix.n_docs + (1 << TS) - 1) >> TS;
     if (n_tiles <= 0) return hipSuccess;
@@ -1723,7 +1726,8 @@ hipError_t ScoreForm<P>::wide(const DevIndex& ix, const DevBatch& qb, int32_t q0
         g_failed_launch = "hipFuncSetAttribute(k_score_listed, wide)";
         return attr;
     }
-    hipLaunchKernelGGL((k_score_listed<P, TS, CH, true>), dim3((unsigned)n_tiles, 1u), dim3(512), lds, s, ix, qb, q0,
+    const dim3 grid((unsigned)n_tiles, (unsigned)listed_ways(n_tiles, qt));
+    hipLaunchKernelGGL((k_score_listed<P, TS, CH, true>), grid, dim3(512), lds, s, ix, qb, q0,
                        ws.scores, ld, ws.hist1, 4, 1, ws.state, ws.cand, (const uint32_t*)ws.counters,
                        (const int32_t*)ws.rescore_list);
     GS_CHECK_LAUNCH("k_score_listed (wide)");
@@ -1732,7 +1736,7 @@ hipError_t ScoreForm<P>::wide(const DevIndex& ix, const DevBatch& qb, int32_t q0
 
 #if !defined(GS_SCORE_PART) || GS_SCORE_PART == 2
 template <>
-hipError_t ScoreForm<kU8>::wide(const DevIndex&, const DevBatch&, int32_t, const Workspace&, hipStream_t) {
+hipError_t ScoreForm<kU8>::wide(const DevIndex&, const DevBatch&, int32_t, int32_t, const Workspace&, hipStream_t) {
     return hipSuccess;  // uint8 sums are exact
 }
 #endif
@@ -1796,9 +1800,10 @@ hipError_t launch_score_group(const DevIndex& ix, const DevBatch& qb, const Scor
     });
 }
 
-hipError_t launch_score_wide(const DevIndex& ix, const DevBatch& qb, int32_t q0, const Workspace& ws, hipStream_t s) {
+hipError_t launch_score_wide(const DevIndex& ix, const DevBatch& qb, int32_t q0, int32_t qt, const Workspace& ws,
+                             hipStream_t s) {
     return by_precision(ix.precision,
-                        [&](auto pc) { return ScoreForm<decltype(pc)::value>::wide(ix, qb, q0, ws, s); });
+                        [&](auto pc) { return ScoreForm<decltype(pc)::value>::wide(ix, qb, q0, qt, ws, s); });
 }
 
 hipError_t launch_score_atomic(const DevIndex& ix, const DevBatch& qb, int32_t q0, int32_t qt, const ScoreOpts& o,

@@ -1219,7 +1219,7 @@ hipError_t launch_select(const DevIndex& ix, const DevBatch& qb, int32_t q0, int
     if (e != hipSuccess) return e;
     if (phase3 || wide) {  // rows (and counts) of the listed queries: fused fallback, wide range
         if (phase3) e = launch_score_tiled(ix, qb, q0, qt, *phase3, ws, s, 3);
-        if (e == hipSuccess && wide) e = launch_score_wide(ix, qb, q0, ws, s);
+        if (e == hipSuccess && wide) e = launch_score_wide(ix, qb, q0, qt, ws, s);
         if (e == hipSuccess) e = select(1);
         if (e != hipSuccess) return e;
     }

@@ -374,6 +374,18 @@ static void autotune_times_each_launch_once() {
     }
 }
 
+// Workgroups per tile of a pass over listed queries: the chip is full where the work allows it,
+// and no workgroup is without a query that could be listed.
+static void listed_queries_fill_the_chip() {
+    for (int64_t tiles : {1, 2, 17, 28, 62, 511, 512, 513, 1075, 262144})
+        for (int64_t qt : {1, 2, 32, 500, 4096}) {
+            const int64_t w = gs::listed_ways(tiles, qt);
+            expect(w >= 1 && w <= qt, "at most one workgroup per query and tile");
+            expect(tiles * w >= std::min<int64_t>(512, tiles * qt), "two workgroups per CU");
+            expect(w == 1 || tiles * (w - 1) < 512, "no more than that");
+        }
+}
+
 int main(int argc, char** argv) {
     const std::string name = argc > 1 ? argv[1] : "";
     if (name == "row_limit") row_limit();
@@ -382,6 +394,7 @@ int main(int argc, char** argv) {
     else if (name == "captured_search_has_the_wide_pass") captured_search_has_the_wide_pass();
     else if (name == "index_without_room_for_rows") index_without_room_for_rows();
     else if (name == "autotune_times_each_launch_once") autotune_times_each_launch_once();
+    else if (name == "listed_queries_fill_the_chip") listed_queries_fill_the_chip();
     else expect(false, "unknown case");
     std::printf("%s: %d failures\n", name.c_str(), failures);
     return failures == 0 ? 0 : 1;
