@@ -33,7 +33,6 @@ constexpr int kHistBits = 11;         // selection digit width (first digit fuse
 constexpr int kHistBins = 1 << kHistBits;
 constexpr int kCandCap = 32768;       // candidates kept per query by the filter pass
 constexpr int kFusedCap = 24576;      // of which appended while scoring (fused filtering)
-constexpr int kRefinePasses = 6;      // enough to resolve any 64-bit composite key
 constexpr int kFirstShiftFloat = 15;  // first digit of a float score: bits 30..15 (256 bins per octave)
 // LDS words of a scoring workgroup's histogram: the bins, then the count of zero scores (padded to 16 bytes)
 constexpr int kHistLds = kHistBins + 4;

@@ -12,8 +12,8 @@
 //  1. the first 11-bit digit histogram (built by the scoring kernel);
 //  2. k_select: find the digit bucket holding the k-th composite; if the composites
 //     at or above that bucket fit the candidate buffer the query is resolved,
-//     otherwise its workgroup refines the bucket by radix selection over the full
-//     score array, 11 more bits per pass (massive ties at the k-th score). A query
+//     otherwise its workgroup refines the bucket over the full score array, 11 more
+//     bits of the score per pass, then by id (massive ties at the k-th score). A query
 //     that fewer than k documents match needs no pass: its answer is every positive
 //     document and documents among the first k (see k_select);
 //  3. k_filter: append every composite >= the threshold to the candidate buffer
@@ -117,30 +117,145 @@ __device__ __forceinline__ void load_bins(const uint32_t* h, uint32_t (&c)[4]) {
     c[0] = v.w; c[1] = v.z; c[2] = v.y; c[3] = v.x;
 }
 
-// Count the digit at nshift of the composites of docs [d0, d1) whose bits above `shift` are
-// `want` into an LDS histogram. Four rounds of 16-byte loads are issued before the first count
-// (a lane past the range reads its last aligned four scores and counts nothing).
-// d0 is a multiple of 4.
-__device__ __forceinline__ void count_digit(const uint32_t* Sq, int64_t d0, int64_t d1, int shift, int nshift,
-                                            unsigned long long want, uint32_t* hist) {
-    const unsigned long long mask = (1ull << (shift - nshift)) - 1ull;
-    constexpr int R = 4;
+// Four scores of documents d .. d + 3 of a lane; those at or past d1 are replaced by `none`.
+__device__ __forceinline__ void mask_past(uint4& v, int64_t d, int64_t d1, uint32_t none) {
+    if (d + 3 < d1) return;
+    if (d >= d1) v.x = none;
+    if (d + 1 >= d1) v.y = none;
+    if (d + 2 >= d1) v.z = none;
+    v.w = none;
+}
+
+// Add the scores of docs [d0, d1) that lie in [s_lo, s_lo + s_width) to an LDS histogram of
+// s_width >> nsh bins. Eight rounds of 16-byte loads are issued before the first count (a lane
+// past the range reads its last aligned four scores). A thread counts scores of one bin in a
+// register until one of another comes: where a refinement is needed most scores are often equal,
+// and 64 adds to one LDS word take 64 clocks. d0 is a multiple of 4.
+__device__ __forceinline__ void count_scores(const uint32_t* Sq, int64_t d0, int64_t d1, uint32_t s_lo, uint32_t s_width,
+                                             int nsh, uint32_t* hist) {
+    constexpr int R = 8;
     const int64_t last = (d1 - 1) & ~3ll;  // d + 3 < ld: rows are padded to 64
+    uint32_t bin = 0, n = 0;
     for (int64_t d0r = d0 + 4 * threadIdx.x; d0r < d1; d0r += 4 * kSelBS * R) {
         uint4 v[R];
 #pragma unroll
         for (int r = 0; r < R; r++) v[r] = *reinterpret_cast<const uint4*>(Sq + min(d0r + r * 4 * kSelBS, last));
 #pragma unroll
         for (int r = 0; r < R; r++) {
-            const int64_t d = d0r + r * 4 * kSelBS;
+            mask_past(v[r], d0r + r * 4 * kSelBS, d1, s_lo + s_width);
             const uint32_t vs[4] = {v[r].x, v[r].y, v[r].z, v[r].w};
 #pragma unroll
             for (int j = 0; j < 4; j++) {
-                const unsigned long long c = comp_key(vs[j], (uint32_t)(d + j));
-                if (d + j < d1 && (c >> shift) == want) atomicAdd(&hist[(c >> nshift) & mask], 1u);
+                const uint32_t u = vs[j] - s_lo, b = u >> nsh;
+                const bool in = u < s_width;
+                if (in && b != bin) {
+                    if (n) atomicAdd(&hist[bin], n);
+                    bin = b;
+                    n = 0;
+                }
+                n += in ? 1u : 0u;
             }
         }
     }
+    if (n) atomicAdd(&hist[bin], n);
+}
+
+// The need-th document of score s in docs [d0, d1), in id order: its id if they hold that many,
+// else -1 and need is lowered by their number. The whole workgroup takes part.
+__device__ __forceinline__ int64_t nth_of_score(const uint32_t* Sq, int64_t d0, int64_t d1, uint32_t s, int& need,
+                                                uint32_t* cnt, int64_t* found) {
+    constexpr int R = 4, NW = kSelBS / kWave;
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+    const int64_t last = (d1 - 1) & ~3ll;
+    for (int64_t wb = d0; wb < d1; wb += 4 * kSelBS * R) {
+        const int64_t d0r = wb + 4 * threadIdx.x;
+        uint4 v[R];
+        unsigned long long m[R][4];
+#pragma unroll
+        for (int r = 0; r < R; r++) v[r] = *reinterpret_cast<const uint4*>(Sq + min(d0r + r * 4 * kSelBS, last));
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            mask_past(v[r], d0r + r * 4 * kSelBS, d1, ~s);
+            m[r][0] = __ballot(v[r].x == s);
+            m[r][1] = __ballot(v[r].y == s);
+            m[r][2] = __ballot(v[r].z == s);
+            m[r][3] = __ballot(v[r].w == s);
+            if (lane == 0)
+                cnt[r * NW + wave] = (uint32_t)(__popcll(m[r][0]) + __popcll(m[r][1]) + __popcll(m[r][2]) + __popcll(m[r][3]));
+        }
+        __syncthreads();
+        int run = 0, before[R];
+#pragma unroll
+        for (int r = 0; r < R; r++)
+            for (int w = 0; w < NW; w++) {  // in id order
+                if (w == wave) before[r] = run;
+                run += (int)cnt[r * NW + w];
+            }
+        if (run >= need) {
+            const unsigned long long below = (1ull << lane) - 1ull;
+#pragma unroll
+            for (int r = 0; r < R; r++) {
+                int at = before[r];  // documents of that score before this lane's
+#pragma unroll
+                for (int j = 0; j < 4; j++) at += __popcll(m[r][j] & below);
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    if (!((m[r][j] >> lane) & 1ull)) continue;
+                    if (++at == need) *found = d0r + r * 4 * kSelBS + j;
+                }
+            }
+            __syncthreads();
+            return *found;
+        }
+        need -= run;
+        __syncthreads();  // cnt is read
+    }
+    return -1;
+}
+
+// A composite at or below the need-th largest of the composites of a query's documents whose scores
+// lie in [s_lo, s_lo + s_width), such that fits(number of those at or above it) holds, or the
+// need-th largest itself. ranges(f): f(d0, d1) for the documents, by ascending id, until f returns
+// true. 11 bits of the score per pass; among equal scores the ids decide: the documents are walked
+// from the lowest id until enough hold that score (few are read where many hold it).
+// One workgroup reads the row, so a pass takes one CU's time (4M scores: 0.39 ms). 2M equal scores
+// among 4M, fp32: 0.9 ms a search; with the scores of a tie added one by one and the id's bits as
+// further digits 5.0.
+template <typename Ranges, typename Fits>
+__device__ __forceinline__ unsigned long long refine(const uint32_t* Sq, Ranges ranges, uint32_t s_lo, uint32_t s_width,
+                                                     int need, Fits fits, uint32_t* hist, BinScan& sh, int64_t* found,
+                                                     int* passes, int* kept) {
+    int above = 0;  // composites of the range above [s_lo, s_lo + s_width)
+    while (s_width > 1) {
+        reinterpret_cast<uint4*>(hist)[threadIdx.x] = make_uint4(0u, 0u, 0u, 0u);
+        const int nsh = max(0, 32 - __clz((int)(s_width - 1)) - kHistBits);
+        __syncthreads();
+        ranges([&](int64_t d0, int64_t d1) {
+            count_scores(Sq, d0, d1, s_lo, s_width, nsh, hist);
+            return false;
+        });
+        __syncthreads();
+        uint32_t c[4], e[4];
+        load_bins(hist, c);
+        scan_bins(c, e, (uint32_t)need, sh);
+        const uint32_t off = (uint32_t)sh.d << nsh;
+        s_lo += off;
+        s_width = min(1u << nsh, s_width - off);
+        above += (int)sh.above;
+        need -= (int)sh.above;
+        *passes += 1;
+        *kept = above + (int)sh.count;
+        if (fits(*kept)) return (unsigned long long)s_lo << 32;
+        __syncthreads();  // sh is read
+    }
+    *passes += 1;
+    *kept = above + need;
+    int64_t id = -1;
+    ranges([&](int64_t d0, int64_t d1) {
+        id = nth_of_score(Sq, d0, d1, s_lo, need, hist, found);
+        return id >= 0;
+    });
+    return comp_key(s_lo, (uint32_t)id);
 }
 
 // Bins below the k-th score's that hold the bf16 error band (2^-7 of the score, at most four
@@ -150,8 +265,8 @@ constexpr int kBandBins = 6;
 // pass 0 runs once every tile is scored; pass 1 runs after phase 3 for the queries that
 // fell back, whose histograms are complete only then (phase 2 counts the seed tiles of a
 // fused query only). One workgroup per query: the first digit, then, for a query whose
-// threshold bucket is too large for the candidate buffer, the refinement passes over its
-// row (a loop in this launch: as launches of their own, twelve of them, they took 2 to 4.5 us
+// threshold bucket is too large for the candidate buffer, the refinement over its row (refine; in
+// this launch: as launches of their own, twelve of them, they took 2 to 4.5 us
 // each also when, as usual, no query needs one: 19 of the 57 us of a search of 10,000
 // documents).
 // A query that fewer than kq documents match: its k-th composite has score 0, and the
@@ -165,8 +280,8 @@ __global__ __launch_bounds__(kSelBS) void k_select(DevBatch qb, int32_t q0, int6
                                                    int pass, int wide_check, int tile_shift, int stride) {
     __shared__ uint32_t hist[kHistBins];
     __shared__ BinScan sh;
-    __shared__ unsigned long long sh_prefix;
-    __shared__ int sh_shift, sh_need, sh_open;
+    __shared__ int64_t sh_found;
+    __shared__ int sh_open;
     const int tid = threadIdx.x;
     const int ql = blockIdx.x, q = q0 + ql;
     SelState* st = state + ql;
@@ -245,37 +360,21 @@ __global__ __launch_bounds__(kSelBS) void k_select(DevBatch qb, int32_t q0, int6
         st->resolved = resolved;
         st->lo = lo;
         sh_open = open;
-        // the refinement starts from the bin, or, for bin 0 (no one prefix), from the whole range
-        sh_prefix = first_edge(fd, d);
-        sh_shift = d == 0 ? 63 : fd.shift + 32;
-        sh_need = (int)(d == 0 ? kq : kq - sh.above);
     }
     __syncthreads();
-    // refinement: 11 more bits of the threshold per pass over the row
-    const uint32_t* Sq = S + (int64_t)ql * ld;
-    for (int p = 0; p < kRefinePasses && sh_open; p++) {
-        reinterpret_cast<uint4*>(hist)[tid] = make_uint4(0u, 0u, 0u, 0u);
-        const unsigned long long prefix = sh_prefix;
-        const int shift = sh_shift, need = sh_need, nshift = max(shift - kHistBits, 0);
-        __syncthreads();
-        count_digit(Sq, 0, N, shift, nshift, prefix >> shift, hist);
-        __syncthreads();
-        load_bins(hist, c);
-        scan_bins(c, e, (uint32_t)need, sh);
-        if (tid == 0) {
-            const unsigned long long np = prefix | ((unsigned long long)sh.d << nshift);
-            const int rem = need - (int)sh.above;
-            st->passes += 1;
-            if ((kq - rem) + (int64_t)sh.count <= kCandCap) {
-                st->resolved = 1;
-                st->lo = np;
-                sh_open = 0;
-            }
-            sh_prefix = np;
-            sh_shift = nshift;
-            sh_need = rem;
-        }
-        __syncthreads();
+    if (!sh_open) return;
+    // the threshold inside the bin, from the row (no score reaches the top bin's upper edge: the
+    // digit starts from the query's largest possible one)
+    const uint32_t s_lo = (uint32_t)(first_edge(fd, d) >> 32), s_hi = (uint32_t)(first_edge(fd, d + 1) >> 32);
+    const int above = (int)sh.above;
+    int passes = 0, kept = 0;
+    const unsigned long long lo = refine(
+        S + (int64_t)ql * ld, [&](auto f) { f((int64_t)0, N); }, s_lo, s_hi - s_lo, (int)kq - above,
+        [&](int n) { return above + n <= kCandCap; }, hist, sh, &sh_found, &passes, &kept);
+    if (tid == 0) {
+        st->passes += passes;
+        st->resolved = 1;
+        st->lo = lo;
     }
 }
 
