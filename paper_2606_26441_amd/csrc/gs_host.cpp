@@ -182,18 +182,21 @@ FixedPlan fixed_point_plan(int precision, int64_t m, const float* w, const float
 FirstDigit impact_digit(uint64_t maxs) {
     int hb = 0;
     while (hb < 64 && (maxs >> hb) != 0) hb++;
-    return FirstDigit{std::max(hb, kHistBits) - kHistBits, 0};
+    return FirstDigit{std::max(hb, kHistBits) - kHistBits, 0, 0};
 }
 
-FirstDigit float_digit(int64_t m, const float* w, const float* tmax, double abs_err) {
+}  // namespace
+
+FirstDigit gs::float_digit(int64_t m, const float* w, const float* tmax, double abs_err) {
     double u = abs_err;
     for (int64_t j = 0; j < m; j++) u += (double)w[j] * (double)tmax[j];
     const float top = (float)(u * (1.0 + std::ldexp(1.0, -12)));
     uint32_t bits;
     std::memcpy(&bits, &top, 4);
-    const uint32_t t = bits >> kFirstShiftFloat;
-    return FirstDigit{kFirstShiftFloat, t > (uint32_t)kHistBins - 1 ? t - (uint32_t)(kHistBins - 1) : 0u};
+    return FirstDigit{kFirstShiftFloat, (int32_t)(bits >> kFirstShiftFloat) - (kHistBins - 1 - kLowBins), kLowBins};
 }
+
+namespace {
 
 // ----------------------------------------------------------- CSR checks --
 

@@ -117,25 +117,40 @@ struct ScoreItem {
     int32_t n;      // scoring terms | those with rows << 10; -1: k = 0
 };
 
-// First selection digit of a query: the score bits shifted right by `shift`, counted from `base`
-// in kHistBins bins (bin 0: all at or below it). Float scores: the eight octaves below the
-// query's largest possible score at 256 bins each, so that the bins near the k-th score are
-// within 0.4 % of each other (one pass bounds it closely) and a tile's documents spread over
-// hundreds of bins (digits of whole octaves had most of a wavefront's LDS adds on the same few
-// words). uint8 impacts: equal parts of the largest possible sum.
+// First selection digit of a query: the score bits shifted right by `shift` and counted from
+// `base`, one bin each (from bin `low` up), or below it 1 << kLowBinShift of them to a bin (bin 0:
+// all that is lower still). Float scores: the seven octaves below the query's largest possible
+// score at 256 bins each, so that the bins near the k-th score are within 0.4 % of each other (one
+// pass bounds it closely) and a tile's documents spread over hundreds of bins (digits of whole
+// octaves had most of a wavefront's LDS adds on the same few words), and 32 octaves below those at
+// 8 bins each: where one heavy term sets the largest score and fewer than k documents hold it, the
+// k-th score is far below, and the bin's lower edge decides whether the sums are accurate there
+// (with 8 octaves and nothing below, 256 such queries of 1M documents took 6.4 ms (bf16), most of
+// it in the fp64 pass without need). uint8 impacts: equal parts of the largest possible sum.
 struct FirstDigit {
-    int32_t shift;
-    uint32_t base;
+    int32_t shift, base, low;
 };
+constexpr int kLowBins = 256;    // of a float digit
+constexpr int kLowBinShift = 5;
+template <bool FLOAT>  // whether the digit is a float score's (low == kLowBins) or an impact's (low, base == 0)
 __host__ __device__ inline uint32_t first_digit(const FirstDigit& f, uint32_t score_bits) {
-    const uint32_t t = score_bits >> f.shift;
-    const uint32_t d = t > f.base ? t - f.base : 0u;
-    return d < (uint32_t)kHistBins - 1 ? d : (uint32_t)kHistBins - 1;
+    if constexpr (!FLOAT) {
+        const uint32_t d = score_bits >> f.shift;
+        return d < (uint32_t)kHistBins - 1 ? d : (uint32_t)kHistBins - 1;
+    } else {
+        const int32_t x = (int32_t)(score_bits >> kFirstShiftFloat) - f.base, y = x >> kLowBinShift;
+        const int32_t d = x > y ? x : y;  // x from base up, y below it
+        const int32_t e = d > -kLowBins ? d : -kLowBins;
+        return (uint32_t)((e < kHistBins - 1 - kLowBins ? e : kHistBins - 1 - kLowBins) + kLowBins);
+    }
 }
-// Smallest composite key of bin d.
-__host__ __device__ inline unsigned long long first_edge(const FirstDigit& f, uint32_t d) {
-    return d == 0 ? 0ull : (unsigned long long)(d + f.base) << (f.shift + 32);
+// Smallest composite key of bin d (0 for the bin that holds score 0, whichever it is).
+__host__ __device__ inline unsigned long long first_edge(const FirstDigit& f, int d) {
+    const int32_t x = d - f.low;
+    const int64_t t = (int64_t)f.base + (x >= 0 ? x : (int64_t)x * (1 << kLowBinShift));
+    return d == 0 || t <= 0 ? 0ull : (unsigned long long)t << (f.shift + 32);
 }
+FirstDigit float_digit(int64_t m, const float* w, const float* tmax, double abs_err);
 
 // A query batch on the device.
 struct DevBatch {

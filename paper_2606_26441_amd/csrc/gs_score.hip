@@ -169,7 +169,7 @@ __device__ __forceinline__ void flush_tile(const void* acc_v, uint32_t* hist, in
     const int tid = threadIdx.x, n4 = tile_n >> 2;
     int zc = 0;  // counted zero scores of this thread
     auto tally = [&](uint32_t v) {
-        atomicAdd(&hist[first_digit(fd, v)], 1u);
+        atomicAdd(&hist[first_digit<AF != kAccInt>(fd, v)], 1u);
         zc += v == 0u;
     };
     for (int i = tid; i < n4; i += BS) {
@@ -1502,7 +1502,7 @@ __global__ __launch_bounds__(512) void k_hist1(DevBatch qb, int32_t q0, int64_t 
     const int64_t d0 = (int64_t)blockIdx.x * per_block, d1 = min(N, d0 + per_block);
     const uint32_t* Sq = S + (int64_t)ql * ld;
     for (int64_t d = d0 + tid; d < d1; d += 512) {
-        atomicAdd(&hist[first_digit(fd, Sq[d])], 1u);
+        atomicAdd(&hist[fd.low ? first_digit<true>(fd, Sq[d]) : first_digit<false>(fd, Sq[d])], 1u);
         zc += Sq[d] == 0u;
     }
     zc = wave_sum(zc);

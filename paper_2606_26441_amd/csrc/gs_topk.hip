@@ -259,7 +259,7 @@ __device__ __forceinline__ unsigned long long refine(const uint32_t* Sq, Ranges 
 }
 
 // Bins below the k-th score's that hold the bf16 error band (2^-7 of the score, at most four
-// bins, and the band's absolute part).
+// bins, and the band's absolute part); below the digit's fine range one bin of 12.5 % does.
 constexpr int kBandBins = 6;
 
 // pass 0 runs once every tile is scored; pass 1 runs after phase 3 for the queries that
@@ -297,9 +297,10 @@ __global__ __launch_bounds__(kSelBS) void k_select(DevBatch qb, int32_t q0, int6
     scan_bins(c, e, (uint32_t)kq, sh);
     const int d = sh.d;
     const FirstDigit fd = qb.first[q];
+    const unsigned long long edge = first_edge(fd, d);
     if (pass == 0 && wide_check) {
         // lower edge of the k-th composite's bucket: its score bits with the low ones cleared
-        const float s_lo = __uint_as_float((uint32_t)(first_edge(fd, d) >> 32));
+        const float s_lo = __uint_as_float((uint32_t)(edge >> 32));
         if ((double)s_lo < qb.q_wide_lim[q]) {
             // every lane has read its bins: the fp64 pass counts anew
             reinterpret_cast<uint4*>(h)[tid] = make_uint4(0u, 0u, 0u, 0u);
@@ -319,7 +320,7 @@ __global__ __launch_bounds__(kSelBS) void k_select(DevBatch qb, int32_t q0, int6
         int64_t kept = 0;  // composites at or above the filter threshold
         int resolved = 1;
         unsigned long long lo = 0;
-        if (d == 0) {
+        if (edge == 0ull) {  // the bin that holds score 0
             // documents the histogram counts: all, or a fused query's seed tiles
             int64_t docs = N;
             if (st->fused == 1) {
@@ -331,14 +332,15 @@ __global__ __launch_bounds__(kSelBS) void k_select(DevBatch qb, int32_t q0, int6
             kept = docs - st->zeros + min(kq, (int64_t)st->zeros);
             if (kept > kCandCap) resolved = 0;
         } else if (ge <= kCandCap) {
-            lo = first_edge(fd, d);
+            lo = edge;
             kept = ge;
-            if (precision == kBF16 && d > kBandBins) {
+            const int to = max(d - kBandBins, min(d, fd.low) - 1);
+            if (precision == kBF16 && to > 0) {
                 // a few bins lower: the bf16 error band below the k-th score then lies inside the candidates
                 int64_t more = 0;
-                for (int j = 1; j <= kBandBins; j++) more += h[d - j];
+                for (int j = to; j < d; j++) more += h[j];
                 if (ge + more <= kCandCap) {
-                    lo = first_edge(fd, d - kBandBins);
+                    lo = first_edge(fd, to);
                     kept = ge + more;
                 }
             }
@@ -365,7 +367,7 @@ __global__ __launch_bounds__(kSelBS) void k_select(DevBatch qb, int32_t q0, int6
     if (!sh_open) return;
     // the threshold inside the bin, from the row (no score reaches the top bin's upper edge: the
     // digit starts from the query's largest possible one)
-    const uint32_t s_lo = (uint32_t)(first_edge(fd, d) >> 32), s_hi = (uint32_t)(first_edge(fd, d + 1) >> 32);
+    const uint32_t s_lo = (uint32_t)(edge >> 32), s_hi = (uint32_t)(first_edge(fd, d + 1) >> 32);
     const int above = (int)sh.above;
     int passes = 0, kept = 0;
     const unsigned long long lo = refine(

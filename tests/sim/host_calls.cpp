@@ -5,6 +5,8 @@
 // device - which allocations, on which device it waits, which launches with which
 // arguments - where a GPU could not show it: two devices, memory that runs out, a call that
 // fails, a stream under capture, sizes past any memory.
+#include <algorithm>
+#include <cmath>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -386,6 +388,35 @@ static void listed_queries_fill_the_chip() {
         }
 }
 
+// The first selection digit of float scores: bins in the order of the scores, each score between
+// its bin's edges, and an edge close below it: within 0.4 % in the seven octaves below the query's
+// largest possible score, within 12.5 % in the 32 below those.
+static void first_digit_bounds_the_score() {
+    auto bits = [](float f) { uint32_t b; std::memcpy(&b, &f, 4); return b; };
+    auto value = [](unsigned long long c) { const uint32_t b = (uint32_t)(c >> 32); float f; std::memcpy(&f, &b, 4); return f; };
+    for (float w : {1.0f, 3.0f, 1e-30f, 3e-38f, 1e-44f, 1e30f, 3e38f, 0.0f})
+        for (float t : {1.0f, 2.9f, 1e-6f, 3e38f, 0.0f}) {
+            const gs::FirstDigit f = gs::float_digit(1, &w, &t, 0.0);
+            const double top = (double)w * (double)t;
+            uint32_t last = 0;
+            int zero_bin = (int)gs::first_digit<true>(f, 0u);
+            expect(gs::first_edge(f, zero_bin) == 0ull, "the edge of score 0's bin");
+            for (int e = 400; e >= 0; e--) {  // ascending scores
+                const float s = (float)(top * std::pow(2.0, -e / 8.0) * 0.999);
+                const uint32_t d = gs::first_digit<true>(f, bits(s));
+                expect(d >= last && d < (uint32_t)gs::kHistBins, "ascending bins");
+                last = d;
+                const unsigned long long c = (unsigned long long)bits(s) << 32;
+                expect(gs::first_edge(f, (int)d) <= c && c < gs::first_edge(f, (int)d + 1), "between the bin's edges");
+                if (s >= 1.2e-38f && std::isfinite(s) && e < 38 * 8) {
+                    const double rel = 1.0 - (double)value(gs::first_edge(f, (int)d)) / (double)s;
+                    expect(rel <= (e < 6 * 8 ? 0.004 : 0.125), "an edge close below the score");
+                }
+            }
+            expect(gs::first_digit<true>(f, 0x7f800000u) < (uint32_t)gs::kHistBins, "infinity");
+        }
+}
+
 int main(int argc, char** argv) {
     const std::string name = argc > 1 ? argv[1] : "";
     if (name == "row_limit") row_limit();
@@ -395,6 +426,7 @@ int main(int argc, char** argv) {
     else if (name == "index_without_room_for_rows") index_without_room_for_rows();
     else if (name == "autotune_times_each_launch_once") autotune_times_each_launch_once();
     else if (name == "listed_queries_fill_the_chip") listed_queries_fill_the_chip();
+    else if (name == "first_digit_bounds_the_score") first_digit_bounds_the_score();
     else expect(false, "unknown case");
     std::printf("%s: %d failures\n", name.c_str(), failures);
     return failures == 0 ? 0 : 1;
