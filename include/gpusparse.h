@@ -405,7 +405,8 @@ int32_t gs_autotune(gs_index index, gs_batch batch, void* workspace, size_t work
  * out [n_queries * 8] int32 (host, caller-owned), per query:
  *   [0] candidates kept by the filter (with fused filtering: those appended
  *       while scoring plus the seed tiles');
- *   [1] refinement passes over the score array (the last may end early);
+ *   [1] refinement passes over the score array, or over its seed tiles with fused
+ *       filtering (the last may end early);
  *   [2] bf16 band size (0 for other precisions);
  *   [3] overflow flag: 1 if more than 32768 documents lay inside the bf16 error
  *       band of the k-th score (only when a huge number of documents tie

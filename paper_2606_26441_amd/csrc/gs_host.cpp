@@ -1559,7 +1559,7 @@ int32_t enqueue_search(gs_index ix, gs_batch b, int32_t nq, const Workspace& ws,
                 }
                 if (e == hipSuccess) {
                     SpanRecorder rec(timing ? 1 : -1, s, false);
-                    e = launch_seed_bound(ix->dev, b->dev, q0, n, ws, s);
+                    e = launch_seed_bound(ix->dev, b->dev, q0, n, ws, s, so.tile_shift, so.seed_stride);
                     rec.end(s);
                 }
                 if (e == hipSuccess) {

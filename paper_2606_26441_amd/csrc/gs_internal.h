@@ -201,7 +201,7 @@ struct alignas(16) SelState {
     unsigned long long lo;      // filter threshold (inclusive) once resolved
     int32_t resolved;           // 0 not yet, 1 filter with lo, 2 nothing to select (k == 0)
     int32_t n_cand;             // candidates appended by the filter
-    int32_t passes;             // refinement passes over the score array
+    int32_t passes;             // refinement passes over the score array or its seed tiles
     int32_t band;               // bf16: candidates inside the error band
     int32_t overflow;           // candidate or band buffer overflow
     int32_t need_band_pass;     // bf16: band reaches below the filter threshold
@@ -216,6 +216,7 @@ struct alignas(16) SelState {
     int32_t rescore;
     int32_t pruned;             // 64-posting blocks skipped by block-max pruning
     int32_t zeros;              // zero-score documents among those counted in hist1
+    int32_t seed_kept;          // seed-tile documents at or above bound (at most: zero-score ones counted up to k)
 };
 
 // Workspace carve-up for a tile of qt queries.
@@ -349,8 +350,8 @@ hipError_t launch_select(const DevIndex& ix, const DevBatch& qb, int32_t q0, int
                          const Workspace& ws, int32_t* out_ids, void* out_scores, int32_t* diag,
                          hipStream_t s, int acc, int tile_shift = 0, int seed_stride = 0,
                          const ScoreOpts* phase3 = nullptr, bool wide = false, bool from_row = false);
-// fused filtering: the bound of every query of the tile from its seed-tile histogram
+// fused filtering: the bound of every query of the tile from its seed-tile histogram (and rows)
 hipError_t launch_seed_bound(const DevIndex& ix, const DevBatch& qb, int32_t q0, int32_t qt,
-                             const Workspace& ws, hipStream_t s);
+                             const Workspace& ws, hipStream_t s, int tile_shift, int seed_stride);
 
 }  // namespace gs

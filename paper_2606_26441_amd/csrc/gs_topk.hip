@@ -31,13 +31,13 @@
 //
 // Fused candidate filtering (doc-tiled kernels, searches of 32+ queries): the
 // seed tiles (every 8th doc tile) are scored first; k_seed_bound derives from their
-// histogram a lower bound of each query's k-th composite (a bin edge); the other
-// tiles append every composite at or above it while they are scored (then writing
-// no score rows for them and not counting them in the histogram), and step 3 scans
-// only the seed tiles. k_select falls back to the full row (no bound, too many
-// appended, or a refinement needed); such a query is listed, its other tiles are
-// scored and counted again, and a second k_select pass redoes its step 2 from the
-// complete histogram before steps 3 and 4.
+// histogram a lower bound of each query's k-th composite (a bin edge, refined over
+// the seed rows where too many documents reach it); the other tiles append every
+// composite at or above it while they are scored (then writing no score rows for
+// them and not counting them in the histogram), and step 3 scans only the seed
+// tiles. A query with too many appended falls back to the full row: it is listed,
+// its other tiles are scored and counted again, and a second k_select pass redoes
+// its step 2 from the complete histogram before steps 3 and 4.
 //
 // Wide-range check (fixed-point sums of the doc-tiled kernels, fp32 and bf16
 // weights): a fixed-point sum is within an absolute bound E of the exact score,
@@ -117,32 +117,50 @@ __device__ __forceinline__ void load_bins(const uint32_t* h, uint32_t (&c)[4]) {
     c[0] = v.w; c[1] = v.z; c[2] = v.y; c[3] = v.x;
 }
 
-// Four scores of documents d .. d + 3 of a lane; those at or past d1 are replaced by `none`.
-__device__ __forceinline__ void mask_past(uint4& v, int64_t d, int64_t d1, uint32_t none) {
-    if (d + 3 < d1) return;
-    if (d >= d1) v.x = none;
-    if (d + 1 >= d1) v.y = none;
-    if (d + 2 >= d1) v.z = none;
+// The documents of a refinement, by ascending id: a whole row, or its seed tiles (document i of
+// those is document at(i) of the row). Four from a multiple of 4 on are side by side in the row,
+// which is padded to a multiple of 64.
+struct WholeRow {
+    uint32_t n;  // below 2^31
+    __device__ __forceinline__ uint32_t at(uint32_t i) const { return i; }
+};
+struct SeedTiles {
+    uint32_t n;
+    int tile_shift, stride;
+    __device__ __forceinline__ uint32_t at(uint32_t i) const {
+        return (((i >> tile_shift) * (uint32_t)stride) << tile_shift) + (i & ((1u << tile_shift) - 1u));
+    }
+};
+
+// Four scores of documents i .. i + 3 of a lane (the last aligned four where i is past them); those
+// at or past n are replaced by `none`.
+template <typename Docs>
+__device__ __forceinline__ uint4 load_scores(const uint32_t* Sq, const Docs& docs, uint32_t i) {
+    return *reinterpret_cast<const uint4*>(Sq + docs.at(min(i, (docs.n - 1) & ~3u)));
+}
+__device__ __forceinline__ void mask_past(uint4& v, uint32_t i, uint32_t n, uint32_t none) {
+    if (i + 3 < n) return;
+    if (i >= n) v.x = none;
+    if (i + 1 >= n) v.y = none;
+    if (i + 2 >= n) v.z = none;
     v.w = none;
 }
 
-// Add the scores of docs [d0, d1) that lie in [s_lo, s_lo + s_width) to an LDS histogram of
-// s_width >> nsh bins. Eight rounds of 16-byte loads are issued before the first count (a lane
-// past the range reads its last aligned four scores). A thread counts scores of one bin in a
-// register until one of another comes: where a refinement is needed most scores are often equal,
-// and 64 adds to one LDS word take 64 clocks. d0 is a multiple of 4.
-__device__ __forceinline__ void count_scores(const uint32_t* Sq, int64_t d0, int64_t d1, uint32_t s_lo, uint32_t s_width,
+// Add the scores that lie in [s_lo, s_lo + s_width) to an LDS histogram of s_width >> nsh bins.
+// R rounds of 16-byte loads are issued before the first count. A thread counts scores of one
+// bin in a register until one of another comes: where a refinement is needed most scores are often
+// equal, and 64 adds to one LDS word take 64 clocks.
+template <int R, typename Docs>
+__device__ __forceinline__ void count_scores(const uint32_t* Sq, const Docs& docs, uint32_t s_lo, uint32_t s_width,
                                              int nsh, uint32_t* hist) {
-    constexpr int R = 8;
-    const int64_t last = (d1 - 1) & ~3ll;  // d + 3 < ld: rows are padded to 64
     uint32_t bin = 0, n = 0;
-    for (int64_t d0r = d0 + 4 * threadIdx.x; d0r < d1; d0r += 4 * kSelBS * R) {
+    for (uint32_t i = 4 * threadIdx.x; i < docs.n; i += 4 * kSelBS * R) {
         uint4 v[R];
 #pragma unroll
-        for (int r = 0; r < R; r++) v[r] = *reinterpret_cast<const uint4*>(Sq + min(d0r + r * 4 * kSelBS, last));
+        for (int r = 0; r < R; r++) v[r] = load_scores(Sq, docs, i + r * 4 * kSelBS);
 #pragma unroll
         for (int r = 0; r < R; r++) {
-            mask_past(v[r], d0r + r * 4 * kSelBS, d1, s_lo + s_width);
+            mask_past(v[r], i + r * 4 * kSelBS, docs.n, s_lo + s_width);
             const uint32_t vs[4] = {v[r].x, v[r].y, v[r].z, v[r].w};
 #pragma unroll
             for (int j = 0; j < 4; j++) {
@@ -160,22 +178,21 @@ __device__ __forceinline__ void count_scores(const uint32_t* Sq, int64_t d0, int
     if (n) atomicAdd(&hist[bin], n);
 }
 
-// The need-th document of score s in docs [d0, d1), in id order: its id if they hold that many,
-// else -1 and need is lowered by their number. The whole workgroup takes part.
-__device__ __forceinline__ int64_t nth_of_score(const uint32_t* Sq, int64_t d0, int64_t d1, uint32_t s, int& need,
-                                                uint32_t* cnt, int64_t* found) {
+// The need-th document of score s, in id order (they hold that many).
+template <typename Docs>
+__device__ __forceinline__ uint32_t nth_of_score(const uint32_t* Sq, const Docs& docs, uint32_t s, int need,
+                                                 uint32_t* cnt, uint32_t* found) {
     constexpr int R = 4, NW = kSelBS / kWave;
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
-    const int64_t last = (d1 - 1) & ~3ll;
-    for (int64_t wb = d0; wb < d1; wb += 4 * kSelBS * R) {
-        const int64_t d0r = wb + 4 * threadIdx.x;
+    for (uint32_t wb = 0; wb < docs.n; wb += 4 * kSelBS * R) {
+        const uint32_t i = wb + 4 * threadIdx.x;
         uint4 v[R];
         unsigned long long m[R][4];
 #pragma unroll
-        for (int r = 0; r < R; r++) v[r] = *reinterpret_cast<const uint4*>(Sq + min(d0r + r * 4 * kSelBS, last));
+        for (int r = 0; r < R; r++) v[r] = load_scores(Sq, docs, i + r * 4 * kSelBS);
 #pragma unroll
         for (int r = 0; r < R; r++) {
-            mask_past(v[r], d0r + r * 4 * kSelBS, d1, ~s);
+            mask_past(v[r], i + r * 4 * kSelBS, docs.n, ~s);
             m[r][0] = __ballot(v[r].x == s);
             m[r][1] = __ballot(v[r].y == s);
             m[r][2] = __ballot(v[r].z == s);
@@ -201,7 +218,7 @@ __device__ __forceinline__ int64_t nth_of_score(const uint32_t* Sq, int64_t d0, 
 #pragma unroll
                 for (int j = 0; j < 4; j++) {
                     if (!((m[r][j] >> lane) & 1ull)) continue;
-                    if (++at == need) *found = d0r + r * 4 * kSelBS + j;
+                    if (++at == need) *found = docs.at(i + r * 4 * kSelBS + j);
                 }
             }
             __syncthreads();
@@ -210,30 +227,26 @@ __device__ __forceinline__ int64_t nth_of_score(const uint32_t* Sq, int64_t d0, 
         need -= run;
         __syncthreads();  // cnt is read
     }
-    return -1;
+    return 0xFFFFFFFFu;
 }
 
 // A composite at or below the need-th largest of the composites of a query's documents whose scores
 // lie in [s_lo, s_lo + s_width), such that fits(number of those at or above it) holds, or the
-// need-th largest itself. ranges(f): f(d0, d1) for the documents, by ascending id, until f returns
-// true. 11 bits of the score per pass; among equal scores the ids decide: the documents are walked
+// need-th largest itself. 11 bits of the score per pass; among equal scores the ids decide: the documents are walked
 // from the lowest id until enough hold that score (few are read where many hold it).
-// One workgroup reads the row, so a pass takes one CU's time (4M scores: 0.39 ms). 2M equal scores
-// among 4M, fp32: 0.9 ms a search; with the scores of a tie added one by one and the id's bits as
+// One workgroup reads the row, so a pass takes one CU's time (4M scores: 0.35 ms). 2M equal scores
+// among 4M, fp32: 0.77 ms a search; with the scores of a tie added one by one and the id's bits as
 // further digits 5.0.
-template <typename Ranges, typename Fits>
-__device__ __forceinline__ unsigned long long refine(const uint32_t* Sq, Ranges ranges, uint32_t s_lo, uint32_t s_width,
-                                                     int need, Fits fits, uint32_t* hist, BinScan& sh, int64_t* found,
+template <int R, typename Docs, typename Fits>
+__device__ __forceinline__ unsigned long long refine(const uint32_t* Sq, const Docs& docs, uint32_t s_lo, uint32_t s_width,
+                                                     int need, Fits fits, uint32_t* hist, BinScan& sh, uint32_t* found,
                                                      int* passes, int* kept) {
     int above = 0;  // composites of the range above [s_lo, s_lo + s_width)
     while (s_width > 1) {
         reinterpret_cast<uint4*>(hist)[threadIdx.x] = make_uint4(0u, 0u, 0u, 0u);
         const int nsh = max(0, 32 - __clz((int)(s_width - 1)) - kHistBits);
         __syncthreads();
-        ranges([&](int64_t d0, int64_t d1) {
-            count_scores(Sq, d0, d1, s_lo, s_width, nsh, hist);
-            return false;
-        });
+        count_scores<R>(Sq, docs, s_lo, s_width, nsh, hist);
         __syncthreads();
         uint32_t c[4], e[4];
         load_bins(hist, c);
@@ -250,12 +263,7 @@ __device__ __forceinline__ unsigned long long refine(const uint32_t* Sq, Ranges 
     }
     *passes += 1;
     *kept = above + need;
-    int64_t id = -1;
-    ranges([&](int64_t d0, int64_t d1) {
-        id = nth_of_score(Sq, d0, d1, s_lo, need, hist, found);
-        return id >= 0;
-    });
-    return comp_key(s_lo, (uint32_t)id);
+    return comp_key(s_lo, nth_of_score(Sq, docs, s_lo, need, hist, found));
 }
 
 // Bins below the k-th score's that hold the bf16 error band (2^-7 of the score, at most four
@@ -273,14 +281,19 @@ constexpr int kBandBins = 6;
 // documents that can win are the positive ones and those with id below kq (zero_floor). With
 // the zero-score documents counted beside the histogram, that needs no pass over the row
 // (four of them before, for every short query of a rare term).
-__global__ __launch_bounds__(kSelBS) void k_select(DevBatch qb, int32_t q0, int64_t N, int precision,
+// R: loads in flight per thread of the refinement. Sixteen where there is at most one query per CU (the
+// tied query of refine: 1,026 / 842 / 770 us a search at 4 / 8 / 16); four otherwise, so that the
+// registers let four workgroups share a CU (4,096 queries, none refined: 1,928 us a search at 8, 1,908
+// at 4).
+template <int R>
+__global__ __launch_bounds__(kSelBS) __attribute__((amdgpu_waves_per_eu(R == 4 ? 8 : 2))) void k_select(DevBatch qb, int32_t q0, int64_t N, int precision,
                                                    const uint32_t* __restrict__ S, int64_t ld,
                                                    uint32_t* __restrict__ hist1, SelState* __restrict__ state,
                                                    uint32_t* __restrict__ counters, int32_t* __restrict__ rescore_list,
-                                                   int pass, int wide_check, int tile_shift, int stride) {
+                                                   int pass, int wide_check) {
     __shared__ uint32_t hist[kHistBins];
     __shared__ BinScan sh;
-    __shared__ int64_t sh_found;
+    __shared__ uint32_t sh_found;
     __shared__ int sh_open;
     const int tid = threadIdx.x;
     const int ql = blockIdx.x, q = q0 + ql;
@@ -299,8 +312,8 @@ __global__ __launch_bounds__(kSelBS) void k_select(DevBatch qb, int32_t q0, int6
     const FirstDigit fd = qb.first[q];
     const unsigned long long edge = first_edge(fd, d);
     if (pass == 0 && wide_check) {
-        // lower edge of the k-th composite's bucket: its score bits with the low ones cleared
-        const float s_lo = __uint_as_float((uint32_t)(edge >> 32));
+        // a lower bound of the k-th composite's score: the lower edge of its bucket, or the seed bound
+        const float s_lo = __uint_as_float((uint32_t)((st->fused == 1 ? max(edge, st->bound) : edge) >> 32));
         if ((double)s_lo < qb.q_wide_lim[q]) {
             // every lane has read its bins: the fp64 pass counts anew
             reinterpret_cast<uint4*>(h)[tid] = make_uint4(0u, 0u, 0u, 0u);
@@ -320,37 +333,31 @@ __global__ __launch_bounds__(kSelBS) void k_select(DevBatch qb, int32_t q0, int6
         int64_t kept = 0;  // composites at or above the filter threshold
         int resolved = 1;
         unsigned long long lo = 0;
-        if (edge == 0ull) {  // the bin that holds score 0
-            // documents the histogram counts: all, or a fused query's seed tiles
-            int64_t docs = N;
-            if (st->fused == 1) {
-                const int64_t n_tiles = (N + (1ll << tile_shift) - 1) >> tile_shift, seeds = (n_tiles + stride - 1) / stride;
-                const int64_t last = ((seeds - 1) * stride) << tile_shift;
-                docs = ((seeds - 1) << tile_shift) + min(1ll << tile_shift, N - last);
-            }
+        if (st->fused == 1) {  // the histogram counts the seed tiles alone
+            lo = st->bound;
+            kept = st->seed_kept;
+        } else if (edge == 0ull) {  // the bin that holds score 0
             lo = zero_floor(kq);
-            kept = docs - st->zeros + min(kq, (int64_t)st->zeros);
-            if (kept > kCandCap) resolved = 0;
-        } else if (ge <= kCandCap) {
+            kept = N - st->zeros + min(kq, (int64_t)st->zeros);
+        } else {
             lo = edge;
             kept = ge;
-            const int to = max(d - kBandBins, min(d, fd.low) - 1);
-            if (precision == kBF16 && to > 0) {
-                // a few bins lower: the bf16 error band below the k-th score then lies inside the candidates
-                int64_t more = 0;
-                for (int j = to; j < d; j++) more += h[j];
-                if (ge + more <= kCandCap) {
-                    lo = first_edge(fd, to);
-                    kept = ge + more;
-                }
+        }
+        if (kept > kCandCap) resolved = 0;
+        const int to = max(d - kBandBins, min(d, fd.low) - 1);
+        if (precision == kBF16 && resolved && lo == edge && to > 0) {
+            // a few bins lower: the bf16 error band below the k-th score then lies inside the candidates
+            int64_t more = 0;
+            for (int j = to; j < d; j++) more += h[j];
+            if (st->n_cand + kept + more <= kCandCap) {
+                lo = first_edge(fd, to);
+                kept += more;
             }
-        } else {
-            resolved = 0;
         }
         // Fused filtering holds the appended candidates (every composite >= the seed bound
-        // of the non-seed tiles; the bound is at most the threshold) and the filter then
-        // scans the seed tiles only. Otherwise the appended ones are dropped and the whole
-        // row is scanned: no bound, too many appended, or a refinement is needed.
+        // of the non-seed tiles; the bound is at least the threshold) and the filter then
+        // scans the seed tiles only. With too many appended they are dropped and the whole
+        // row is scanned.
         int open = resolved == 0;
         if (st->fused == 1 && (!resolved || st->fused_over || (int64_t)st->n_cand + kept > kCandCap)) {
             st->fused = 0;
@@ -370,8 +377,8 @@ __global__ __launch_bounds__(kSelBS) void k_select(DevBatch qb, int32_t q0, int6
     const uint32_t s_lo = (uint32_t)(edge >> 32), s_hi = (uint32_t)(first_edge(fd, d + 1) >> 32);
     const int above = (int)sh.above;
     int passes = 0, kept = 0;
-    const unsigned long long lo = refine(
-        S + (int64_t)ql * ld, [&](auto f) { f((int64_t)0, N); }, s_lo, s_hi - s_lo, (int)kq - above,
+    const unsigned long long lo = refine<R>(
+        S + (int64_t)ql * ld, WholeRow{(uint32_t)N}, s_lo, s_hi - s_lo, (int)kq - above,
         [&](int n) { return above + n <= kCandCap; }, hist, sh, &sh_found, &passes, &kept);
     if (tid == 0) {
         st->passes += passes;
@@ -382,15 +389,23 @@ __global__ __launch_bounds__(kSelBS) void k_select(DevBatch qb, int32_t q0, int6
 
 // Fused filtering, after the seed tiles are scored: the bound of a query is the lower edge of the
 // first-digit bin that holds the k-th largest composite among the seed tiles' documents (from the
-// histogram they built; a second digit counted over their rows, which made the bound exact to 22
-// bits, cost 54 us for 500 queries of 1M documents and 128 us for 4,096 of 250,000, and saved 3 %
-// of the candidates). The k-th largest over all documents is at least as large, so the bound
+// histogram they built). The k-th largest over all documents is at least as large, so the bound
 // never exceeds it; neither does zero_floor, which keeps a query matched by few documents from
 // appending every zero-score one. With fewer than k seed documents there is no bound.
-__global__ __launch_bounds__(kSelBS) void k_seed_bound(DevBatch qb, int32_t q0, int64_t N,
-                                                       const uint32_t* __restrict__ hist1,
-                                                       SelState* __restrict__ state) {
+// Where so many seed documents reach the edge that the other tiles would append more than kSeedFit
+// candidates (scores that tie, or in a bin of 12.5 %), the bound is refined over the seed rows until
+// they would not: the appends would pass kFusedCap and the query be scored again from its lists. Only
+// there: a second digit for every query took 54 us for 500 queries of 1M documents and 128 us for
+// 4,096 of 250,000, and saved 3 % of the candidates. (100 queries of 1M documents with equal scores at
+// the bound: 814 -> 298 us, fp32.)
+constexpr int kSeedFit = kFusedCap * 2 / 3;
+
+__global__ __launch_bounds__(kSelBS) __attribute__((amdgpu_waves_per_eu(8))) void k_seed_bound(DevBatch qb, int32_t q0, int64_t N, const uint32_t* __restrict__ S,
+                                                       int64_t ld, const uint32_t* __restrict__ hist1,
+                                                       SelState* __restrict__ state, int tile_shift, int stride) {
+    __shared__ uint32_t hist[kHistBins];
     __shared__ BinScan sh;
+    __shared__ uint32_t sh_found;
     const int ql = blockIdx.x, q = q0 + ql;
     SelState* st = state + ql;
     const int64_t kq = kq_of(qb, q, N);
@@ -398,9 +413,33 @@ __global__ __launch_bounds__(kSelBS) void k_seed_bound(DevBatch qb, int32_t q0, 
     uint32_t c[4], e[4];
     load_bins(hist1 + (int64_t)ql * kHistBins, c);
     scan_bins(c, e, (uint32_t)kq, sh);
-    if (threadIdx.x != 0 || (int64_t)sh.above + sh.count < kq) return;
-    const unsigned long long b = first_edge(qb.first[q], sh.d), z = zero_floor(kq);
+    const int above = (int)sh.above, d = sh.d;
+    int kept = above + (int)sh.count;  // seed composites at or above the bound
+    if (kept < kq) return;
+    const int64_t n_tiles = (N + (1ll << tile_shift) - 1) >> tile_shift, seeds = (n_tiles + stride - 1) / stride;
+    const int64_t docs = ((seeds - 1) << tile_shift) + min(1ll << tile_shift, N - (((seeds - 1) * stride) << tile_shift));
+    auto fits = [&](int64_t n) { return n * (N - docs) <= kSeedFit * docs; };
+    const FirstDigit fd = qb.first[q];
+    unsigned long long b = first_edge(fd, d);
+    const unsigned long long z = zero_floor(kq);
+    int64_t reach = kept;  // of them in every tile alike
+    int passes = 0;
+    if (b == 0ull) {       // every positive document, and the zero-score ones below id kq (in the first tile)
+        reach = docs - st->zeros;
+        kept = (int)(reach + min(kq, (int64_t)st->zeros));
+    }
+    if (!fits(reach)) {
+        int n = 0;
+        const uint32_t s_lo = (uint32_t)(b >> 32), s_hi = (uint32_t)(first_edge(fd, d + 1) >> 32);
+        b = refine<4>(
+            S + (int64_t)ql * ld, SeedTiles{(uint32_t)docs, tile_shift, stride}, s_lo, s_hi - s_lo, (int)kq - above,
+            [&](int m) { return fits(above + m); }, hist, sh, &sh_found, &passes, &n);
+        kept = above + n;
+    }
+    if (threadIdx.x != 0) return;
     st->bound = b > z ? b : z;
+    st->seed_kept = kept;
+    st->passes = passes;
     st->fused = 1;
 }
 
@@ -1247,9 +1286,9 @@ __global__ __launch_bounds__(kSelBS) void k_band_topk(DevIndex ix, DevBatch qb, 
 }  // namespace
 
 hipError_t launch_seed_bound(const DevIndex& ix, const DevBatch& qb, int32_t q0, int32_t qt, const Workspace& ws,
-                             hipStream_t s) {
-    hipLaunchKernelGGL(k_seed_bound, dim3(qt), dim3(kSelBS), 0, s, qb, q0, ix.n_docs, (const uint32_t*)ws.hist1,
-                       ws.state);
+                             hipStream_t s, int tile_shift, int seed_stride) {
+    hipLaunchKernelGGL(k_seed_bound, dim3(qt), dim3(kSelBS), 0, s, qb, q0, ix.n_docs, (const uint32_t*)ws.scores, ws.ld,
+                       (const uint32_t*)ws.hist1, ws.state, tile_shift, seed_stride);
     GS_CHECK_LAUNCH("k_seed_bound");
     return hipSuccess;
 }
@@ -1310,9 +1349,10 @@ hipError_t launch_select(const DevIndex& ix, const DevBatch& qb, int32_t q0, int
     const dim3 grid_scan((unsigned)((N + per - 1) / per), (unsigned)qt);
     const int wide_check = wide ? 1 : 0;
     auto select = [&](int pass) -> hipError_t {
-        hipLaunchKernelGGL(k_select, dim3(qt), dim3(kSelBS), 0, s, qb, q0, N, ix.precision,
+        const auto k = qt <= 256 ? k_select<16> : k_select<4>;
+        hipLaunchKernelGGL(k, dim3(qt), dim3(kSelBS), 0, s, qb, q0, N, ix.precision,
                            (const uint32_t*)ws.scores, ws.ld, ws.hist1, ws.state, ws.counters, ws.rescore_list, pass,
-                           pass == 0 ? wide_check : 0, tile_shift, std::max(seed_stride, 1));
+                           pass == 0 ? wide_check : 0);
         GS_CHECK_LAUNCH("k_select");
         return hipSuccess;
     };

@@ -143,7 +143,7 @@ hipError_t launch_select(const DevIndex&, const DevBatch&, int32_t, int32_t, con
     l.from_row = from_row;
     return hipSuccess;
 }
-hipError_t launch_seed_bound(const DevIndex&, const DevBatch&, int32_t, int32_t, const Workspace&, hipStream_t s) {
+hipError_t launch_seed_bound(const DevIndex&, const DevBatch&, int32_t, int32_t, const Workspace&, hipStream_t s, int, int) {
     launch("seed_bound", s);
     return hipSuccess;
 }
