@@ -457,9 +457,9 @@ struct gs_index_s {
 // pinned host stage of the same layout): the per-query arrays first (copied
 // whole on every update), then the per-term arrays (copied up to the terms in use).
 struct BatchLayout {
-    size_t rp = 0, k = 0, fs = 0, delta = 0, scale = 0, err = 0, wide = 0, work = 0, diag = 0, head = 0;
+    size_t rp = 0, k = 0, fs = 0, delta = 0, scale = 0, err = 0, wide = 0, diag = 0, head = 0;
     size_t gcount = 0, gmember = 0, grow = 0, item = 0, order = 0;
-    size_t term = 0, w = 0, w8 = 0, fx = 0, ubcum = 0, gterm = 0, gwfx = 0, gw8 = 0, sterm = 0, total = 0;
+    size_t term = 0, w = 0, w8 = 0, fx = 0, ubcum = 0, gterm = 0, gwfx = 0, gw8 = 0, sterm = 0, work = 0, total = 0;
     BatchLayout(size_t nq, size_t nz) {
         size_t at = 0;
         auto take = [&](size_t bytes) {
@@ -474,7 +474,6 @@ struct BatchLayout {
         scale = take(nq * 8);
         err = take(nq * 8);
         wide = take(nq * 8);
-        work = take(nq * 8);
         diag = take(nq * kDiagWords * 4);
         gcount = take(4);
         gmember = take((nq + kGroupMax) * 4);
@@ -491,6 +490,7 @@ struct BatchLayout {
         gwfx = take(nz * kGroupMax * 4);
         gw8 = take(nz * kGroupMax * 4);
         sterm = take(nz * sizeof(ScoreTerm));
+        work = take(nq * 8);  // the host's alone (postings of each query's terms)
         total = at;
     }
 };
@@ -801,7 +801,6 @@ void batch_shape(gs_batch b, int32_t max_queries, int64_t max_nnz, int32_t k_max
     d.g_term = (const int32_t*)(m + L.gterm);
     d.g_wq = (const float*)(m + L.gwfx);
     d.g_w8 = (const int32_t*)(m + L.gw8);
-    d.q_work = (const int64_t*)(m + L.work);
     d.s_term = (const ScoreTerm*)(m + L.sterm);
     d.s_item = (const ScoreItem*)(m + L.item);
     d.s_order = (const ScoreItem*)(m + L.order);
@@ -1007,7 +1006,7 @@ int32_t gs_build_index(const int64_t* row_ptr, int64_t n_docs, const int32_t* te
     int32_t *term_len = nullptr, *post_doc = nullptr, *tile_off = nullptr;
     if ((rc = dev_upload(ix->allocs, ix->bytes, L.term_off.data(), L.term_off.size(), &term_off, s))) return done(rc);
     if ((rc = dev_upload(ix->allocs, ix->bytes, L.term_len.data(), L.term_len.size(), &term_len, s))) return done(rc);
-    // 32-bit doc ids only for the global-atomic kernel: the doc-tiled kernels read 16- or 8-bit ones
+    // 32-bit doc ids only for the global-atomic kernel: the doc-tiled kernels read 16-bit ones
     if (flags & GS_KEEP_DOC_IDS)
         if ((rc = dev_upload(ix->allocs, ix->bytes, L.post_doc.data(), L.post_doc.size(), &post_doc, s)))
             return done(rc);
@@ -1481,7 +1480,6 @@ int32_t plan_search(gs_index ix, gs_batch b, size_t workspace_bytes_, const gs_s
     if (b->index != ix) return fail(GS_EINVAL, "batch was created for another index");
     int32_t rc = resolve_opts(ix, opts, so);
     if (rc != GS_OK) return rc;
-    if ((!opts || opts->kernel == GS_KERNEL_AUTO) && b->n_active >= 32) so->kernel = GS_KERNEL_SHARED;
     if (workspace_bytes(ix->n_docs, 1, ix->precision) > workspace_bytes_)
         return fail(GS_ECAPACITY, "workspace smaller than gs_workspace_size(index, 1)");
     const int32_t nq = std::max(b->n_queries, 1);
@@ -1615,7 +1613,6 @@ int32_t search_rows(gs_index ix, gs_batch b, void* arena, int64_t rows, int64_t 
     ScoreOpts so;
     int32_t rc = resolve_opts(ix, opts, &so);
     if (rc != GS_OK) return rc;
-    if ((!opts || opts->kernel == GS_KERNEL_AUTO) && n >= 32) so.kernel = GS_KERNEL_SHARED;
     if (b->n_queries == 0 || b->k_max == 0 || n == 0) return GS_OK;
     DeviceGuard g(ix->device);
     Workspace ws;

@@ -173,7 +173,6 @@ struct DevBatch {
     // lie below this value (its error bound over the relative budget of its precision) is
     // scored again with fp64 accumulation; 0 when the bound holds for every positive score.
     const double* q_wide_lim;
-    const int64_t* q_work;     // [n] postings of the query's terms (work estimate)
     const ScoreTerm* s_term;   // scoring terms of all queries
     const ScoreItem* s_item;   // [n] by query
     // [n] by descending work, those with k = 0 last, dealt into eight runs (ranks 0, 8, 16, ...,
