@@ -89,13 +89,12 @@ def algorithmic_bytes(df, queries, n_docs, wbytes, idbytes, written_docs=None):
     return p_q, score_kernel, step
 
 
-def row_id_bytes(df, n_docs, wbytes):
+def row_id_bytes(df, n_docs, wbytes, row):
     """Bytes per posting beside the weight, per term, in the doc-tiled kernel: 2 (the doc offset), or for a
-    term held by at least a quarter of the documents what its row (a weight for every document, no ids)
-    has above the postings' weights."""
+    term with a row (row: the index's flags) what the row (a weight for every document, no ids) has above the
+    postings' weights."""
     df = np.asarray(df, dtype=np.float64)
-    row = (df > 0) & (4 * df >= n_docs)
-    return np.where(row, n_docs * wbytes / np.maximum(df, 1.0) - wbytes, 2.0)
+    return np.where((df > 0) & (np.asarray(row) != 0), n_docs * wbytes / np.maximum(df, 1.0) - wbytes, 2.0)
 
 
 _C_TOKEN = re.compile(r'//[^\n]*|/\*.*?\*/|"(?:\\.|[^"\\\n])*"|\'(?:\\.|[^\'\\\n])*\'', re.S)
@@ -251,7 +250,8 @@ def time_form(gs, torch, idx, queries, k, opts, steps, warmup, host_steps=0):
     total_ms = ev[0].elapsed_time(ev[steps])
     diag = batch.diagnostics()
     res = {"ids": ids.cpu().numpy(), "scores": sc.cpu().numpy(), "total_ms": total_ms, "step_ms": step_ms,
-           "timing": t, "diag": diag, "device_bytes": int(idx.info().device_bytes), "ws_bytes": ws.numel()}
+           "timing": t, "diag": diag, "device_bytes": int(idx.info().device_bytes), "ws_bytes": ws.numel(),
+           "row_terms": idx.row_terms()}
     if host_steps:
         # host CSR in (validation, per-query scales, upload), results copied back to host memory
         host_ms = []
@@ -543,7 +543,7 @@ def main():
         # fused candidate filtering: score rows of the seed tiles (every 8th) only
         written = sum(min(tile_docs, n_docs - t * tile_docs) for t in range(0, n_tiles, 8))
     if args.kernel in ("tiled", "shared"):
-        idbytes = row_id_bytes(df, n_docs, WEIGHT_BYTES[args.precision])
+        idbytes = row_id_bytes(df, n_docs, WEIGHT_BYTES[args.precision], main_res["row_terms"])
     else:
         idbytes = 2 if args.kernel == "group" else 4
     p_q, layout_bytes, step_bytes = algorithmic_bytes(df, queries, n_docs, WEIGHT_BYTES[args.precision], idbytes,
@@ -595,6 +595,8 @@ def main():
                          "score write and read) over the scoring launches' time; above 1 when the kernel moves "
                          "fewer bytes than the model (rows without ids, 2-byte ids, score rows of seed tiles only, "
                          "a tile's postings read from L2 by the queries after the first)",
+            "bound_kind": "the peak that achieved and frac are priced against; by the counters (hbm_frac_counters) the "
+                          "vector ALUs and L2 bound the batched scoring",
             "algorithmic_bytes_per_launch": survey_bytes,
             "layout_bytes_per_launch": layout_bytes,
             "layout_frac": round(layout_gbs / HBM_PEAK_GBS, 4),

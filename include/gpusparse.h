@@ -75,7 +75,7 @@ enum gs_build_flags {
                             document-parallel kernel; always kept for GS_BF16) */
     GS_KEEP_DOC_IDS = 2  /* keep 32-bit doc ids of every posting on the device (needed by
                             the global-atomic kernel only: the doc-tiled kernels read
-                            16-bit or 8-bit ids, so by default they are not uploaded) */
+                            16-bit ids, so by default they are not uploaded) */
 };
 
 /* Scoring kernels (Sec. 5.2 term-parallel scatter-add; Sec. 5.3 document-parallel). */
@@ -182,9 +182,14 @@ int32_t gs_debug_fail_alloc(int64_t n);
  *    posting at or after the tile start (segment table for doc-tiled kernels);
  *  - doc ids again as 16-bit values (doc id modulo 65536): the doc-tiled
  *    kernels read 2 bytes per posting for the id instead of 4;
- *  - a row for each term held by at least a quarter of the documents: its
- *    stored weight for every document, 0 where it lacks the term (at most
- *    4 times the weight bytes of those terms' lists).
+ *  - rows for terms held by at least a quarter of the documents: a term's
+ *    stored weight for every document, 0 where it lacks the term. A row takes
+ *    its weight bytes for n_docs rounded up to 8192 documents. Rows only make
+ *    searches faster, and are bounded: the longest lists first, in all at most
+ *    64 MiB or 3 times the bytes of the posting lists' ids (2 each) and weights,
+ *    whichever is more, and none where they would take more than a quarter of
+ *    the free device memory (past 64 MiB) or cannot be allocated. A term
+ *    without a row is summed from its list (gs_index_row_terms).
  * Synchronous: returns once the index is on the device.
  * Errors: GS_EINVAL (any check above, vocab_size < 1, n_docs < 0,
  *   n_docs >= 2^31, unknown precision or flag), GS_ENOMEM, GS_EHIP.
@@ -205,6 +210,13 @@ int32_t gs_index_info(gs_index index, gs_index_info_t* out);
  * the index's).
  */
 int32_t gs_index_dense_terms(gs_index index, uint8_t* out, int32_t vocab_size);
+
+/*
+ * Terms that the doc-tiled kernels sum from rows: out [vocab_size] (host,
+ * caller-owned) receives 1 for a term with a row (see gs_build_index), else 0.
+ * Errors: GS_EINVAL (null argument, vocab_size differs from the index's).
+ */
+int32_t gs_index_row_terms(gs_index index, uint8_t* out, int32_t vocab_size);
 /* Releases the index's device memory (the resident index of Sec. 3.2). NULL is a
  * no-op. Batches created for it may still be freed afterwards, not searched. */
 void gs_free_index(gs_index index);

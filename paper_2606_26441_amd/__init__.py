@@ -85,6 +85,8 @@ def _load() -> ctypes.CDLL:
     lib.gs_index_info.restype = i32
     lib.gs_index_dense_terms.argtypes = [vp, vp, i32]
     lib.gs_index_dense_terms.restype = i32
+    lib.gs_index_row_terms.argtypes = [vp, vp, i32]
+    lib.gs_index_row_terms.restype = i32
     lib.gs_free_index.argtypes = [vp]
     lib.gs_free_index.restype = None
     lib.gs_layout_host.argtypes = [vp, i64, vp, vp, i64, i32, i32, vp, vp, vp, vp, vp, vp, vp, vp, vp]
@@ -239,6 +241,13 @@ class Index:
         v = self.info().vocab_size
         out = np.zeros(v, dtype=np.uint8)
         _check(lib.gs_index_dense_terms(self._h, _ptr(out), v), "gs_index_dense_terms")
+        return out
+
+    def row_terms(self) -> np.ndarray:
+        """uint8 [vocab]: 1 where the term has a row (a weight for every document)."""
+        v = self.info().vocab_size
+        out = np.zeros(v, dtype=np.uint8)
+        _check(lib.gs_index_row_terms(self._h, _ptr(out), v), "gs_index_row_terms")
         return out
 
     @property

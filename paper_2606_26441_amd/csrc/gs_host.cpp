@@ -1113,6 +1113,14 @@ int32_t gs_index_dense_terms(gs_index ix, uint8_t* out, int32_t vocab_size) {
     return GS_OK;
 }
 
+int32_t gs_index_row_terms(gs_index ix, uint8_t* out, int32_t vocab_size) {
+    g_err.clear();
+    if (!ix || !out) return fail(GS_EINVAL, "null argument");
+    if (vocab_size != ix->vocab) return fail(GS_EINVAL, "vocab_size differs from the index's");
+    for (int32_t v = 0; v < ix->vocab; v++) out[v] = ix->terms[(size_t)v].row >= 0;
+    return GS_OK;
+}
+
 void gs_free_index(gs_index ix) {
     if (!ix) return;
     DeviceGuard g(ix->device);

@@ -341,6 +341,8 @@ static void index_without_room_for_rows() {
         }
         gs_index_info(ix, &without);
         expect(count("fill_rows") == 0 && with.device_bytes - without.device_bytes == 2 * row, "built without rows");
+        uint8_t has[22];
+        expect(gs_index_row_terms(ix, has, 22) == GS_OK && std::count(has, has + 22, 0) == 22, "no term has a row");
         Query q(ix);
         expect(q.search(ix) == GS_OK, "searched without rows");
         gs_free_index(ix);
@@ -417,6 +419,31 @@ static void first_digit_bounds_the_score() {
         }
 }
 
+// Which terms have rows: held by at least a quarter of the documents.
+static void row_terms_at_the_threshold() {
+    const int n = 10000;
+    std::vector<int64_t> rp{0};
+    std::vector<int32_t> t;
+    for (int d = 0; d < n; d++) {
+        if (d < n / 4) t.push_back(0);      // exactly a quarter
+        if (d < n / 4 - 1) t.push_back(1);  // one less
+        t.push_back(3);                     // every document; none holds terms 2 and 4
+        rp.push_back((int64_t)t.size());
+    }
+    const std::vector<float> w(t.size(), 1.0f);
+    for (int precision : {GS_FP32, GS_BF16, GS_U8}) {
+        gs_index ix = nullptr;
+        expect(gs_build_index(rp.data(), n, t.data(), w.data(), (int64_t)t.size(), 5, precision, 0, nullptr, &ix) == GS_OK,
+               "build");
+        uint8_t row[5] = {9, 9, 9, 9, 9};
+        expect(gs_index_row_terms(ix, row, 5) == GS_OK, "flags");
+        expect(row[0] == 1 && row[1] == 0 && row[2] == 0 && row[3] == 1 && row[4] == 0, "the terms with rows");
+        expect(gs_index_row_terms(ix, row, 4) == GS_EINVAL && gs_index_row_terms(ix, nullptr, 5) == GS_EINVAL &&
+                   gs_index_row_terms(nullptr, row, 5) == GS_EINVAL, "bad arguments");
+        gs_free_index(ix);
+    }
+}
+
 int main(int argc, char** argv) {
     const std::string name = argc > 1 ? argv[1] : "";
     if (name == "row_limit") row_limit();
@@ -427,6 +454,7 @@ int main(int argc, char** argv) {
     else if (name == "autotune_times_each_launch_once") autotune_times_each_launch_once();
     else if (name == "listed_queries_fill_the_chip") listed_queries_fill_the_chip();
     else if (name == "first_digit_bounds_the_score") first_digit_bounds_the_score();
+    else if (name == "row_terms_at_the_threshold") row_terms_at_the_threshold();
     else expect(false, "unknown case");
     std::printf("%s: %d failures\n", name.c_str(), failures);
     return failures == 0 ? 0 : 1;
