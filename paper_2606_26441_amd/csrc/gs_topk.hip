@@ -146,13 +146,22 @@ __device__ __forceinline__ void mask_past(uint4& v, uint32_t i, uint32_t n, uint
     v.w = none;
 }
 
+// Histogram copies of a refinement, one per lane modulo their number, side by side per bin.
+template <int R>
+constexpr int refine_copies() {
+    return R == 16 ? 4 : 1;
+}
+
 // Add the scores that lie in [s_lo, s_lo + s_width) to an LDS histogram of s_width >> nsh bins.
-// R rounds of 16-byte loads are issued before the first count. A thread counts scores of one
-// bin in a register until one of another comes: where a refinement is needed most scores are often
-// equal, and 64 adds to one LDS word take 64 clocks.
+// R rounds of 16-byte loads are issued before the first count. A thread counts scores of one bin in
+// a register until one of another comes: where a refinement is needed most scores are often equal,
+// and 64 adds to one LDS word take 64 clocks. The copies are for a few values among the scores (4M
+// scores of two values: 1.42 -> 0.95 ms a search).
 template <int R, typename Docs>
 __device__ __forceinline__ void count_scores(const uint32_t* Sq, const Docs& docs, uint32_t s_lo, uint32_t s_width,
                                              int nsh, uint32_t* hist) {
+    constexpr int C = refine_copies<R>();
+    uint32_t* const mine = hist + (threadIdx.x & (C - 1));
     uint32_t bin = 0, n = 0;
     for (uint32_t i = 4 * threadIdx.x; i < docs.n; i += 4 * kSelBS * R) {
         uint4 v[R];
@@ -167,7 +176,7 @@ __device__ __forceinline__ void count_scores(const uint32_t* Sq, const Docs& doc
                 const uint32_t u = vs[j] - s_lo, b = u >> nsh;
                 const bool in = u < s_width;
                 if (in && b != bin) {
-                    if (n) atomicAdd(&hist[bin], n);
+                    if (n) atomicAdd(&mine[bin * C], n);
                     bin = b;
                     n = 0;
                 }
@@ -175,7 +184,7 @@ __device__ __forceinline__ void count_scores(const uint32_t* Sq, const Docs& doc
             }
         }
     }
-    if (n) atomicAdd(&hist[bin], n);
+    if (n) atomicAdd(&mine[bin * C], n);
 }
 
 // The need-th document of score s, in id order (they hold that many).
@@ -235,21 +244,31 @@ __device__ __forceinline__ uint32_t nth_of_score(const uint32_t* Sq, const Docs&
 // need-th largest itself. 11 bits of the score per pass; among equal scores the ids decide: the documents are walked
 // from the lowest id until enough hold that score (few are read where many hold it).
 // One workgroup reads the row, so a pass takes one CU's time (4M scores: 0.35 ms). 2M equal scores
-// among 4M, fp32: 0.77 ms a search; with the scores of a tie added one by one and the id's bits as
+// among 4M, fp32: 0.79 ms a search; with the scores of a tie added one by one and the id's bits as
 // further digits 5.0.
 template <int R, typename Docs, typename Fits>
 __device__ __forceinline__ unsigned long long refine(const uint32_t* Sq, const Docs& docs, uint32_t s_lo, uint32_t s_width,
                                                      int need, Fits fits, uint32_t* hist, BinScan& sh, uint32_t* found,
                                                      int* passes, int* kept) {
     int above = 0;  // composites of the range above [s_lo, s_lo + s_width)
+    constexpr int C = refine_copies<R>();
     while (s_width > 1) {
-        reinterpret_cast<uint4*>(hist)[threadIdx.x] = make_uint4(0u, 0u, 0u, 0u);
+        for (int i = threadIdx.x; i < kHistBins * C / 4; i += kSelBS) reinterpret_cast<uint4*>(hist)[i] = make_uint4(0u, 0u, 0u, 0u);
         const int nsh = max(0, 32 - __clz((int)(s_width - 1)) - kHistBits);
         __syncthreads();
         count_scores<R>(Sq, docs, s_lo, s_width, nsh, hist);
         __syncthreads();
         uint32_t c[4], e[4];
-        load_bins(hist, c);
+        if constexpr (C == 1) {
+            load_bins(hist, c);
+        } else {
+            static_assert(C == 4, "a 16-byte load per bin");
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                const uint4 v = reinterpret_cast<const uint4*>(hist)[kHistBins - 1 - 4 * (int)threadIdx.x - j];
+                c[j] = v.x + v.y + v.z + v.w;
+            }
+        }
         scan_bins(c, e, (uint32_t)need, sh);
         const uint32_t off = (uint32_t)sh.d << nsh;
         s_lo += off;
@@ -282,7 +301,7 @@ constexpr int kBandBins = 6;
 // the zero-score documents counted beside the histogram, that needs no pass over the row
 // (four of them before, for every short query of a rare term).
 // R: loads in flight per thread of the refinement. Sixteen where there is at most one query per CU (the
-// tied query of refine: 1,026 / 842 / 770 us a search at 4 / 8 / 16); four otherwise, so that the
+// tied query of refine: 1,026 / 842 / 790 us a search at 4 / 8 / 16); four otherwise, so that the
 // registers let four workgroups share a CU (4,096 queries, none refined: 1,928 us a search at 8, 1,908
 // at 4).
 template <int R>
@@ -291,7 +310,7 @@ __global__ __launch_bounds__(kSelBS) __attribute__((amdgpu_waves_per_eu(R == 4 ?
                                                    uint32_t* __restrict__ hist1, SelState* __restrict__ state,
                                                    uint32_t* __restrict__ counters, int32_t* __restrict__ rescore_list,
                                                    int pass, int wide_check) {
-    __shared__ uint32_t hist[kHistBins];
+    __shared__ __align__(16) uint32_t hist[kHistBins * refine_copies<R>()];
     __shared__ BinScan sh;
     __shared__ uint32_t sh_found;
     __shared__ int sh_open;
