@@ -1190,9 +1190,8 @@ int32_t batch_update(gs_batch b, const int64_t* q_row_ptr, int32_t n_queries, co
     ScoreTerm* sterm = (ScoreTerm*)(h + L.sterm);
     ScoreItem* item = (ScoreItem*)(h + L.item);
     int64_t n_sterm = 0;
-    std::vector<ScoreTerm> rest;
     std::vector<float> tmax, tmin;
-    std::vector<unsigned long long> ub;
+    const bool u8 = ix->precision == kU8;  // impacts in place of weights: each form's arrays alone are made
     bool any_wide = false;
     for (int32_t q = 0; q < cap; q++) {
         uint64_t maxs = 0;
@@ -1203,36 +1202,45 @@ int32_t batch_update(gs_batch b, const int64_t* q_row_ptr, int32_t n_queries, co
         for (int64_t j = rp[q]; j < rp[q + 1]; j++) {
             const TermInfo& t = ix->terms[(size_t)r.term[j]];
             qwork[q] += t.len;
-            w8[j] = q8(r.w[j]);
-            maxs += (uint64_t)w8[j] * 255u;
+            if (u8) {
+                w8[j] = q8(r.w[j]);
+                maxs += (uint64_t)w8[j] * 255u;
+            }
             tmax[(size_t)(j - rp[q])] = t.max;
             tmin[(size_t)(j - rp[q])] = t.min;
         }
         const FixedPlan fp = fixed_point_plan(ix->precision, m, r.w + rp[q], tmax.data(), tmin.data());
-        first[q] = ix->precision == kU8 ? impact_digit(maxs) : float_digit(m, r.w + rp[q], tmax.data(), fp.abs_err);
+        first[q] = u8 ? impact_digit(maxs) : float_digit(m, r.w + rp[q], tmax.data(), fp.abs_err);
         qscale[q] = fp.scale;
         qerr[q] = fp.abs_err;
         qwide[q] = fp.wide_lim;
         any_wide = any_wide || (fp.wide_lim > 0.0 && kk[q] > 0);
         const double two_f = std::ldexp(1.0, fp.F);  // |F| <= 1000
-        for (int64_t j = rp[q]; j < rp[q + 1]; j++) qfx[j] = (double)r.w[j] * two_f;
-        // the scoring terms: those with rows first, by row
+        for (int64_t j = rp[q]; j < rp[q + 1] && !u8; j++) qfx[j] = (double)r.w[j] * two_f;
+        // The scoring terms: those with rows first, by row. (Rows are placed by counting the smaller
+        // ones: a sort mispredicts a branch per comparison or two.)
         {
-            const bool u8 = ix->precision == kU8;
-            rest.clear();
-            int32_t n = 0, n_row = 0;
+            ScoreTerm with_row[kMaxQueryNnz], rest[kMaxQueryNnz];
+            int32_t row[kMaxQueryNnz], n_row = 0, n_rest = 0;
             for (int64_t j = rp[q]; j < rp[q + 1]; j++) {
                 if (!(u8 ? w8[j] > 0 : qfx[j] > 0.0)) continue;  // adds nothing
                 ScoreTerm t{r.term[j], ix->terms[(size_t)r.term[j]].row, 0};
                 if (u8) t.q = (unsigned long long)w8[j];
                 else std::memcpy(&t.q, &qfx[j], 8);
-                if (t.row >= 0) sterm[n_sterm + n_row++] = t;
-                else rest.push_back(t);
+                if (t.row >= 0) {
+                    row[n_row] = t.row;
+                    with_row[n_row++] = t;
+                } else {
+                    rest[n_rest++] = t;
+                }
             }
-            std::sort(sterm + n_sterm, sterm + n_sterm + n_row,
-                      [](const ScoreTerm& x, const ScoreTerm& y) { return x.row < y.row; });
-            std::copy(rest.begin(), rest.end(), sterm + n_sterm + n_row);
-            n = n_row + (int32_t)rest.size();
+            for (int32_t i = 0; i < n_row; i++) {
+                int32_t at = 0;
+                for (int32_t j = 0; j < n_row; j++) at += row[j] < row[i];
+                sterm[n_sterm + at] = with_row[i];
+            }
+            std::copy(rest, rest + n_rest, sterm + n_sterm + n_row);
+            const int32_t n = n_row + n_rest;
             item[q] = ScoreItem{n_sterm, q, kk[q] > 0 ? n | n_row << 10 : -1};
             n_sterm += n;
         }
@@ -1240,24 +1248,26 @@ int32_t batch_update(gs_batch b, const int64_t* q_row_ptr, int32_t n_queries, co
         // units: the largest stored weight times w_q 2^F, rounded up, plus one for the product's
         // rounding; uint8: the exact integer product), then per term the sum of the bounds of
         // the terms up to it in ascending order of bound (ties by position).
-        {
-            // (bounds are at most 2^51 + 2: sorted with the term's position, up to 255, below them;
-            // bf16 searches do not prune)
-            ub.clear();
-            for (int64_t j = rp[q]; j < rp[q + 1] && ix->precision != kBF16; j++) {
-                const double tm = (double)tmax[(size_t)(j - rp[q])];
-                const double v = qfx[j] * tm;  // below 2^51
-                const unsigned long long t = (unsigned long long)v;
-                const unsigned long long u = ix->precision == kU8
-                                                 ? (unsigned long long)w8[j] * (unsigned long long)tm
-                                                 : t + ((double)t < v) + 1ull;
-                ub.push_back(u << 8 | (unsigned long long)(j - rp[q]));
+        // (bounds are at most 2^51 + 2: sorted with the term's position, up to 255, below them; bf16
+        // searches do not prune)
+        if (ix->precision != kBF16) {
+            uint64_t ub[kMaxQueryNnz], run = 0;
+            for (int64_t j = 0; j < m; j++) {
+                const double tm = (double)tmax[(size_t)j];
+                int64_t u;
+                if (u8) {
+                    u = (int64_t)w8[rp[q] + j] * (int64_t)tm;
+                } else {
+                    const double x = qfx[rp[q] + j] * tm;  // below 2^51
+                    u = (int64_t)x;
+                    u += ((double)u < x) + 1;
+                }
+                ub[j] = (uint64_t)u << 8 | (uint64_t)j;
             }
-            std::sort(ub.begin(), ub.end());
-            unsigned long long run = 0;
-            for (const unsigned long long e : ub) {
-                run += e >> 8;
-                qub[rp[q] + (int64_t)(e & 255)] = run;
+            std::sort(ub, ub + m);
+            for (int64_t i = 0; i < m; i++) {
+                run += ub[i] >> 8;
+                qub[rp[q] + (int64_t)(ub[i] & 255)] = run;
             }
         }
         // bf16 form: relative error of a stored weight (2^-8) and of the fp32 score (2^-24, with margin)
@@ -1307,8 +1317,8 @@ int32_t batch_update(gs_batch b, const int64_t* q_row_ptr, int32_t n_queries, co
                 gterm[n_union] = t;
                 for (int m = 0; m < G; m++) {
                     const bool has = at[m] < end[m] && r.term[at[m]] == t;
-                    gwq[n_union * G + m] = has ? r.w[at[m]] : 0.0f;
-                    gw8[n_union * G + m] = has ? w8[at[m]] : 0;
+                    if (u8) gw8[n_union * G + m] = has ? w8[at[m]] : 0;
+                    else gwq[n_union * G + m] = has ? r.w[at[m]] : 0.0f;
                     if (has) at[m]++;
                 }
                 n_union++;
@@ -1329,12 +1339,12 @@ int32_t batch_update(gs_batch b, const int64_t* q_row_ptr, int32_t n_queries, co
     add(0, L.head);
     add(L.term, (size_t)q_nnz * 4);
     add(L.w, (size_t)q_nnz * 4);
-    add(L.w8, (size_t)q_nnz * 4);
-    add(L.fx, (size_t)q_nnz * 8);
-    add(L.ubcum, (size_t)q_nnz * 8);
+    if (u8) add(L.w8, (size_t)q_nnz * 4);
+    else add(L.fx, (size_t)q_nnz * 8);
+    if (ix->precision != kBF16) add(L.ubcum, (size_t)q_nnz * 8);
     add(L.gterm, (size_t)n_union * 4);
-    add(L.gwfx, (size_t)n_union * G * 4);
-    add(L.gw8, (size_t)n_union * G * 4);
+    if (u8) add(L.gw8, (size_t)n_union * G * 4);
+    else add(L.gwfx, (size_t)n_union * G * 4);
     add(L.sterm, (size_t)n_sterm * sizeof(ScoreTerm));
     hipError_t e = hipSuccess;
     if (up_bytes <= kUploadBytes) {
@@ -1398,7 +1408,9 @@ static int32_t resolve_opts(gs_index ix, const gs_search_opts* o, ScoreOpts* so)
     // 64 KiB of LDS accumulators: 8192 fixed-point (fp32, bf16) or 16384 int32 (uint8) documents
     so->tile_shift = ix->precision == kFP32 ? 13 : 14;
     // measured: 500 queries of 1M documents (fp32) 1.83 / 1.79 / 1.88 ms at 256 / 512 / 1024, of
-    // 500K (bf16) 1.01 / 0.96 / 0.98; 4,096 of 250K (uint8) 2.23 / 2.08 / 2.06
+    // 500K (bf16) 1.01 / 0.96 / 0.98; 4,096 of 250K (uint8) 2.23 / 2.08 / 2.06. The global-atomic kernel
+    // takes the same default: 100 queries of 200K documents 1.40 ms at 512, 1.42 at 1024 (fp32), 1.13
+    // and 1.14 (uint8), 1.44 both (bf16)
     so->chunk = ix->precision == kU8 ? 1024 : 512;
     so->seed_stride = 1;  // fused filtering wanted (the stride itself is chosen per search)
     so->any_tile = true;

@@ -12,6 +12,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <random>
 #include <set>
 #include <string>
 #include <utility>
@@ -38,6 +39,8 @@ static size_t g_room = (size_t)1 << 40, g_used = 0;
 static int g_fail_event_record = -1;                     // calls left before one fails
 static hipStream_t g_capturing = nullptr;
 static hipError_t g_last = hipSuccess;
+static gs::DevBatch g_batch{};                           // of the last doc-tiled launch
+static int32_t g_rows = 0;                               // rows of its index
 
 static Launch& launch(const char* kernel, hipStream_t s) {
     g_launches.push_back(Launch{kernel, g_device, s});
@@ -115,9 +118,11 @@ hipError_t launch_narrow(const int32_t* src, uint16_t* dst, int64_t n, hipStream
     return hipSuccess;
 }
 hipError_t launch_clear(const Workspace&, int32_t, hipStream_t s) { launch("clear", s); return hipSuccess; }
-hipError_t launch_score_tiled(const DevIndex&, const DevBatch&, int32_t, int32_t, const ScoreOpts& o, const Workspace&,
-                              hipStream_t s, int) {
+hipError_t launch_score_tiled(const DevIndex& ix, const DevBatch& qb, int32_t, int32_t, const ScoreOpts& o,
+                              const Workspace&, hipStream_t s, int) {
     Launch& l = launch("score_tiled", s);
+    g_batch = qb;
+    g_rows = ix.n_rows;
     l.tile_shift = o.tile_shift;
     l.chunk = o.chunk;
     return hipSuccess;
@@ -444,6 +449,99 @@ static void row_terms_at_the_threshold() {
     }
 }
 
+// What a batch update leaves on the device of a query's terms: the scoring records (terms with rows
+// first, by row, the commonest first; then the others, ascending) and the cumulative bounds of pruning (per
+// term, the sum of the bounds of the terms up to it in ascending order of bound, ties by position).
+static void update_records() {
+    std::mt19937_64 rng(11);
+    const int n = 3000, vocab = 400;
+    std::vector<int64_t> rp{0};
+    std::vector<int32_t> t;
+    std::vector<float> w;
+    for (int d = 0; d < n; d++) {
+        for (int v = 0; v < vocab; v++)
+            if (rng() % 400 < (v < 150 ? 90u + v : 10u)) {  // some of the first 150 terms in a quarter of the documents
+                t.push_back(v);
+                w.push_back((float)(1 + rng() % 255) / 85.0f);
+            }
+        rp.push_back((int64_t)t.size());
+    }
+    std::vector<int64_t> df(vocab, 0);
+    std::vector<float> top(vocab, 0.0f);
+    for (size_t i = 0; i < t.size(); i++) {
+        df[t[i]]++;
+        top[t[i]] = std::max(top[t[i]], w[i]);
+    }
+    for (int precision : {GS_FP32, GS_BF16, GS_U8}) {
+        gs_index ix = nullptr;
+        gs_build_index(rp.data(), n, t.data(), w.data(), (int64_t)t.size(), vocab, precision, 0, nullptr, &ix);
+        std::vector<uint8_t> row(vocab);
+        gs_index_row_terms(ix, row.data(), vocab);
+        std::vector<int64_t> qp{0};
+        std::vector<int32_t> qt, k;
+        std::vector<float> qw;
+        for (int m : {0, 1, 2, 9, 34, 64, 65, 200, 256}) {
+            std::vector<int32_t> all(vocab);
+            for (int v = 0; v < vocab; v++) all[v] = v;
+            std::shuffle(all.begin(), all.end(), rng);
+            std::sort(all.begin(), all.begin() + m);
+            for (int j = 0; j < m; j++) {
+                qt.push_back(all[j]);
+                qw.push_back((float)(rng() % 20) / 10.0f);  // zeros and equal ones among them
+            }
+            qp.push_back((int64_t)qt.size());
+            k.push_back(5);
+        }
+        const int nq = (int)k.size();
+        gs_batch b = nullptr;
+        expect(gs_batch_create(ix, qp.data(), nq, qt.data(), qw.data(), (int64_t)qt.size(), k.data(), 5, nullptr, &b) == GS_OK,
+               "batch");
+        size_t bytes = 0;
+        gs_workspace_size(ix, nq, nullptr, &bytes);
+        std::vector<uint8_t> ws(bytes);
+        std::vector<int32_t> ids(nq * 5);
+        std::vector<double> sc(nq * 5);
+        expect(gs_search_batch(ix, b, ws.data(), bytes, ids.data(), sc.data(), nullptr, nullptr) == GS_OK, "search");
+        expect(g_rows > 10 && g_rows < 150, "some terms have rows");
+        auto impact = [](float x) { return (int64_t)std::nearbyint((double)x * 85.0); };
+        for (int q = 0; q < nq; q++) {
+            std::vector<int32_t> want, rest;
+            for (int64_t j = qp[q]; j < qp[q + 1]; j++)
+                if (qw[j] > 0.0f) (row[qt[j]] ? want : rest).push_back(qt[j]);
+            std::sort(want.begin(), want.end(), [&](int a, int c) { return df[a] > df[c] || (df[a] == df[c] && a < c); });
+            const size_t n_row = want.size();
+            want.insert(want.end(), rest.begin(), rest.end());
+            const gs::ScoreItem it = g_batch.s_item[q];
+            expect(it.q == q && (size_t)(it.n & 1023) == want.size() && (size_t)(it.n >> 10) == n_row, "a query's item");
+            for (size_t i = 0; i < want.size(); i++) {
+                const gs::ScoreTerm& r = g_batch.s_term[it.start + (int64_t)i];
+                expect(r.term == want[i] && (r.row >= 0) == (i < n_row), "the order of the records");
+                expect(i == 0 || i >= n_row || r.row > g_batch.s_term[it.start + (int64_t)i - 1].row, "ascending rows");
+                const int64_t j = std::lower_bound(qt.begin() + qp[q], qt.begin() + qp[q + 1], r.term) - qt.begin();
+                double fx;
+                std::memcpy(&fx, &r.q, 8);
+                expect(precision == GS_U8 ? (int64_t)r.q == impact(qw[j]) : fx == (double)qw[j] / g_batch.q_scale[q], "the weight");
+            }
+            if (precision == GS_BF16) continue;
+            const int64_t m = qp[q + 1] - qp[q];
+            std::vector<std::pair<uint64_t, int64_t>> u;
+            for (int64_t j = 0; j < m; j++) {
+                const float x = qw[qp[q] + j], y = top[qt[qp[q] + j]];
+                u.push_back({precision == GS_U8 ? (uint64_t)(impact(x) * impact(y))
+                                                : (uint64_t)std::ceil((double)x / g_batch.q_scale[q] * (double)y) + 1, j});
+            }
+            std::sort(u.begin(), u.end());
+            uint64_t run = 0;
+            for (const auto& e : u) {
+                run += e.first;
+                expect(g_batch.q_ub_cum[qp[q] + e.second] == run, "a cumulative bound");
+            }
+        }
+        gs_batch_free(b);
+        gs_free_index(ix);
+    }
+}
+
 int main(int argc, char** argv) {
     const std::string name = argc > 1 ? argv[1] : "";
     if (name == "row_limit") row_limit();
@@ -455,6 +553,7 @@ int main(int argc, char** argv) {
     else if (name == "listed_queries_fill_the_chip") listed_queries_fill_the_chip();
     else if (name == "first_digit_bounds_the_score") first_digit_bounds_the_score();
     else if (name == "row_terms_at_the_threshold") row_terms_at_the_threshold();
+    else if (name == "update_records") update_records();
     else expect(false, "unknown case");
     std::printf("%s: %d failures\n", name.c_str(), failures);
     return failures == 0 ? 0 : 1;

@@ -16,7 +16,7 @@ HIP_INCLUDE = "/opt/rocm/include"
 CASES = ["row_limit", "search_waits_on_the_index_device", "failed_upload_keeps_no_batch",
          "captured_search_has_the_wide_pass", "index_without_room_for_rows",
          "autotune_times_each_launch_once", "listed_queries_fill_the_chip",
-         "first_digit_bounds_the_score", "row_terms_at_the_threshold"]
+         "first_digit_bounds_the_score", "row_terms_at_the_threshold", "update_records"]
 
 
 @pytest.fixture(scope="module")
