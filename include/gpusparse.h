@@ -381,10 +381,8 @@ int32_t gs_search(gs_index index, const int64_t* q_row_ptr, int32_t n_queries,
  * holds the pointers given here (the batch included): they must stay valid,
  * and the batch may be refilled with gs_batch_update between launches. No
  * memset or host work is captured (buffers are cleared by kernels). The
- * fixed-point kernels come in two forms, with and without the raise of a
- * positive product that rounds to 0 units; the graph captures the form the
- * batch needs at capture time, and a launch after a refill that needs the
- * other form enqueues the same search directly instead (same results).
+ * captured launches always hold the fp64 pass over wide-range queries, so a
+ * refill may hold any queries.
  * Errors: as gs_search_batch, plus GS_EHIP for capture or instantiation
  * failures.
  */
@@ -416,7 +414,8 @@ int32_t gs_autotune(gs_index index, gs_batch batch, void* workspace, size_t work
  * (host copy; call after the stream has been synchronised).
  * out [n_queries * 8] int32 (host, caller-owned), per query:
  *   [0] candidates kept by the filter (with fused filtering: those appended
- *       while scoring plus the seed tiles');
+ *       while scoring plus the seed tiles'; all documents where the score row
+ *       itself is the candidate set, collections of at most 32768);
  *   [1] refinement passes over the score array, or over its seed tiles with fused
  *       filtering (the last may end early);
  *   [2] bf16 band size (0 for other precisions);

@@ -22,7 +22,7 @@ constexpr int kMaxChunk = 1024;       // largest chunk of the doc-tiled kernels 
 // chunk's full-width loads stay inside the arrays (lanes past its end are masked).
 constexpr size_t kPostSlack = kMaxChunk;
 constexpr int kMaxK = 4096;           // GS_MAX_K
-constexpr int kRowShare = 4;          // a term in at least 1 / kRowShare of the documents has a row
+constexpr int kRowShare = 4;          // a term in at least 1 / kRowShare of the documents may have a row (row_limit)
 // Most rows of an index: in a doc tile (at most 16,384 documents of fp32 weights, 32,768 of the others)
 // the scoring kernel's byte offsets from a row's first grain to its last are 32-bit.
 constexpr int64_t max_rows(int64_t weight_bytes) {
@@ -43,8 +43,8 @@ constexpr int kCntListed = 63;
 constexpr int kCounterWords = 64;
 __host__ __device__ constexpr int cnt_base(int phase) { return 8 * phase; }  // phases 0 .. 6
 constexpr int kDiagWords = 8;         // per-query words of gs_batch_diagnostics
-// Group kernel (GS_KERNEL_GROUP): 8192-doc tiles, at most 4 queries per group, so at most
-// 4 x 256 distinct terms per group.
+// Group kernel (GS_KERNEL_GROUP): 8192-doc tiles; arrays with room for 4 queries per group and
+// 4 x 256 distinct terms (groups of 2 are built).
 constexpr int kGroupTileShift = 13;
 constexpr int kGroupMax = 4;
 constexpr int kGroupMaxTerms = kGroupMax * kMaxQueryNnz;
@@ -92,8 +92,8 @@ struct DevIndex {
     const void* post_w;        // [padded_nnz] float | bf16 bits (uint16) | uint8
     const int32_t* tile_off;   // [V][n_grains+1] posting offset (relative to the list start)
     int64_t n_grains;          // ceil(n_docs / 8192)
-    // Rows of the commonest terms (at least 1 / kRowShare of the documents): the stored weight of
-    // every document (0 where it lacks the term), so that the doc-tiled kernel sums these terms in
+    // Rows of the commonest terms (of those in at least 1 / kRowShare of the documents, as many as
+    // there is room for): the stored weight of every document (0 where it lacks the term), so that the doc-tiled kernel sums these terms in
     // registers instead of scatter-adding their postings. Rows by descending term_len.
     const void* rows;          // [n_grains][n_rows][8192] float | bf16 bits | uint8 (order: k_fill_rows)
     int32_t n_rows;
@@ -183,7 +183,7 @@ struct DevBatch {
     // uint8 product) taken in ascending order of bound, up to and including this term.
     const unsigned long long* q_ub_cum;  // [q_nnz]
     // Groups of the group kernel (built on the host at each update): the queries with k > 0
-    // by descending work, G consecutive per group (G = 2 for fp32, 4 for bf16 and uint8);
+    // by descending work, G = 2 consecutive per group;
     // per group the ascending union of its members' terms with each member's weight
     // (w_q, scaled by the member's 2^F in the kernel, or the uint8 impact; 0 where the member
     // lacks the term).

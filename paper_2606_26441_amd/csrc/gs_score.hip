@@ -1129,8 +1129,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
 // ------------------------------------------------------------- group --
 //
 // Shared traversal with explicit sharing: a work item is (doc tile, group of G
-// queries). The LDS holds G accumulator tiles of 8192 docs (128 KiB: G = 4 with
-// 32-bit sums for bf16 and uint8, G = 2 with 64-bit fixed point for fp32). The
+// queries), G = 2. The LDS holds G accumulator tiles of 8192 docs (64 KiB with
+// 32-bit sums for bf16 and uint8, 128 KiB with 64-bit fixed point for fp32). The
 // segments are those of the union of the group's terms (built on the host, with
 // each member's weight per union term, 0 where the member lacks the term), so a
 // posting chunk is loaded once and scatter-added into the tile of every member
