@@ -241,8 +241,8 @@ __device__ __forceinline__ uint32_t nth_of_score(const uint32_t* Sq, const Docs&
 
 // A composite at or below the need-th largest of the composites of a query's documents whose scores
 // lie in [s_lo, s_lo + s_width), such that fits(number of those at or above it) holds, or the
-// need-th largest itself. 11 bits of the score per pass; among equal scores the ids decide: the documents are walked
-// from the lowest id until enough hold that score (few are read where many hold it).
+// need-th largest itself. 11 bits of the score per pass; among equal scores the ids decide: the
+// documents are walked from the lowest id until enough hold that score (few are read where many do).
 // One workgroup reads the row, so a pass takes one CU's time (4M scores: 0.35 ms). 2M equal scores
 // among 4M, fp32: 0.79 ms a search; with the scores of a tie added one by one and the id's bits as
 // further digits 5.0.
@@ -253,7 +253,8 @@ __device__ __forceinline__ unsigned long long refine(const uint32_t* Sq, const D
     int above = 0;  // composites of the range above [s_lo, s_lo + s_width)
     constexpr int C = refine_copies<R>();
     while (s_width > 1) {
-        for (int i = threadIdx.x; i < kHistBins * C / 4; i += kSelBS) reinterpret_cast<uint4*>(hist)[i] = make_uint4(0u, 0u, 0u, 0u);
+        for (int i = threadIdx.x; i < kHistBins * C / 4; i += kSelBS)
+            reinterpret_cast<uint4*>(hist)[i] = make_uint4(0u, 0u, 0u, 0u);
         const int nsh = max(0, 32 - __clz((int)(s_width - 1)) - kHistBits);
         __syncthreads();
         count_scores<R>(Sq, docs, s_lo, s_width, nsh, hist);
@@ -305,11 +306,10 @@ constexpr int kBandBins = 6;
 // registers let four workgroups share a CU (4,096 queries, none refined: 1,928 us a search at 8, 1,908
 // at 4).
 template <int R>
-__global__ __launch_bounds__(kSelBS) __attribute__((amdgpu_waves_per_eu(R == 4 ? 8 : 2))) void k_select(DevBatch qb, int32_t q0, int64_t N, int precision,
-                                                   const uint32_t* __restrict__ S, int64_t ld,
-                                                   uint32_t* __restrict__ hist1, SelState* __restrict__ state,
-                                                   uint32_t* __restrict__ counters, int32_t* __restrict__ rescore_list,
-                                                   int pass, int wide_check) {
+__global__ __launch_bounds__(kSelBS) __attribute__((amdgpu_waves_per_eu(R == 4 ? 8 : 2))) void k_select(
+    DevBatch qb, int32_t q0, int64_t N, int precision, const uint32_t* __restrict__ S, int64_t ld,
+    uint32_t* __restrict__ hist1, SelState* __restrict__ state, uint32_t* __restrict__ counters,
+    int32_t* __restrict__ rescore_list, int pass, int wide_check) {
     __shared__ __align__(16) uint32_t hist[kHistBins * refine_copies<R>()];
     __shared__ BinScan sh;
     __shared__ uint32_t sh_found;
@@ -324,6 +324,8 @@ __global__ __launch_bounds__(kSelBS) __attribute__((amdgpu_waves_per_eu(R == 4 ?
         return;
     }
     uint32_t* h = hist1 + (int64_t)ql * kHistBins;
+    // read before the barriers below: thread 0 changes it after them
+    const unsigned long long bound = st->fused == 1 ? st->bound : 0ull;
     uint32_t c[4], e[4];
     load_bins(h, c);
     scan_bins(c, e, (uint32_t)kq, sh);
@@ -332,7 +334,7 @@ __global__ __launch_bounds__(kSelBS) __attribute__((amdgpu_waves_per_eu(R == 4 ?
     const unsigned long long edge = first_edge(fd, d);
     if (pass == 0 && wide_check) {
         // a lower bound of the k-th composite's score: the lower edge of its bucket, or the seed bound
-        const float s_lo = __uint_as_float((uint32_t)((st->fused == 1 ? max(edge, st->bound) : edge) >> 32));
+        const float s_lo = __uint_as_float((uint32_t)(max(edge, bound) >> 32));
         if ((double)s_lo < qb.q_wide_lim[q]) {
             // every lane has read its bins: the fp64 pass counts anew
             reinterpret_cast<uint4*>(h)[tid] = make_uint4(0u, 0u, 0u, 0u);
@@ -353,7 +355,7 @@ __global__ __launch_bounds__(kSelBS) __attribute__((amdgpu_waves_per_eu(R == 4 ?
         int resolved = 1;
         unsigned long long lo = 0;
         if (st->fused == 1) {  // the histogram counts the seed tiles alone
-            lo = st->bound;
+            lo = bound;
             kept = st->seed_kept;
         } else if (edge == 0ull) {  // the bin that holds score 0
             lo = zero_floor(kq);
@@ -419,9 +421,9 @@ __global__ __launch_bounds__(kSelBS) __attribute__((amdgpu_waves_per_eu(R == 4 ?
 // the bound: 814 -> 298 us, fp32.)
 constexpr int kSeedFit = kFusedCap * 2 / 3;
 
-__global__ __launch_bounds__(kSelBS) __attribute__((amdgpu_waves_per_eu(8))) void k_seed_bound(DevBatch qb, int32_t q0, int64_t N, const uint32_t* __restrict__ S,
-                                                       int64_t ld, const uint32_t* __restrict__ hist1,
-                                                       SelState* __restrict__ state, int tile_shift, int stride) {
+__global__ __launch_bounds__(kSelBS) __attribute__((amdgpu_waves_per_eu(8))) void k_seed_bound(
+    DevBatch qb, int32_t q0, int64_t N, const uint32_t* __restrict__ S, int64_t ld, const uint32_t* __restrict__ hist1,
+    SelState* __restrict__ state, int tile_shift, int stride) {
     __shared__ uint32_t hist[kHistBins];
     __shared__ BinScan sh;
     __shared__ uint32_t sh_found;
